@@ -669,8 +669,16 @@ int ebsp_gridscan_batch(const int64_t* ts, int64_t B, int32_t P, int32_t R, int3
     if (int rc = check_device()) return rc;
     hipStream_t st = (hipStream_t)stream;
     GridBest* best = (GridBest*)workspace;
-    LAUNCH(K_GRIDSCAN, zl_gridscan_kernel, dim3((unsigned)blocks), dim3(GRID_NT), (const i64*)ts, P, R, full ? 1 : 0, best, status);
-    LAUNCH(K_GRIDSCAN_FINISH, zl_gridscan_finish_kernel, dim3((unsigned)B), dim3(GRID_NT), (const i64*)ts, P, R, full ? 1 : 0,
+    i64 pieces = full ? P : 1;                       // results per instance, in (row, point) order
+    if (R <= GRID_RMAX) {
+        const i64 points = full ? (i64)P * R : R;
+        const i64 per = (i64)grid_point_threads(points, R) * GRID_SCAN_JPT;
+        pieces = (points + per - 1) / per;           // no more than there are designated rows: a piece has R points or more
+        LAUNCH(K_GRIDSCAN, zl_gridscan_kernel, dim3((unsigned)(B * pieces)), dim3(GRID_SCAN_NT), (const i64*)ts, P, R, full ? 1 : 0,
+               (int)pieces, best, status);
+    } else
+        LAUNCH(K_GRIDSCAN, zl_gridscan_long_kernel, dim3((unsigned)blocks), dim3(GRID_NT), (const i64*)ts, P, R, full ? 1 : 0, best, status);
+    LAUNCH(K_GRIDSCAN_FINISH, zl_gridscan_finish_kernel, dim3((unsigned)B), dim3(GRID_NT), (const i64*)ts, P, R, (int)pieces,
            (const GridBest*)best, (i64*)barrier, iters, (i64*)dz);
     if (g_prof.on && g_prof.calls < g_prof.max_calls) ++g_prof.calls;
     return EBSP_OK;

@@ -133,3 +133,12 @@ def test_argument_errors(zl):
     assert lib.ebsp_gridscan_batch(None, 1, 2, 2, 0, ts.data_ptr(), ts.data_ptr(), ts.data_ptr(), None, None, 0, None) == -1
     assert lib.ebsp_gridscan_batch(ts.data_ptr(), 1, 2, 2, 1, ts.data_ptr(), ts.data_ptr(), ts.data_ptr(), None, ts.data_ptr(), 0, None) == -3
     assert zl.ebsp_gridscan_workspace_bytes(4, 100, 15, True) >= 4 * 100 * 16 and zl.ebsp_gridscan_workspace_bytes(4, 0, 15, True) == 0
+
+
+@pytest.mark.parametrize("P,R", [(8, 128), (9, 128), (1, 1023), (3, 1025), (2, 2049), (3, 4096), (41, 100), (60, 257)])
+@pytest.mark.parametrize("scale", [1, 1 << 22])
+def test_pieces_and_batches(zl, oracle, P, R, scale):
+    """Points at the edges of the workgroups' pieces, rows of more than one staging, values of 32 and 64 bits."""
+    rng = np.random.default_rng(77 * P + R)
+    ts = np.stack([workloads.random_small(rng, P, R, 1, 5000, ties=(i == 0)) for i in range(3)]) * scale
+    assert_same(zl, oracle, ts + EPOCH, f"P={P} R={R} scale={scale}")
