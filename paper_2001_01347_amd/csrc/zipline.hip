@@ -82,13 +82,13 @@ int check_device()
 }
 
 enum KernelId { K_INSTANCE = 0, K_INSTANCE_GENERAL, K_BOUNDS, K_PARTITION, K_BINCOUNT, K_PLAN, K_WINDOW,
-                K_WINDOW_GENERAL, K_FINISH, K_COPY, K_RANGE_INSTANCE, K_RANGE_WINDOW, K_PARTITION_PRED, K_RANGE_FAST, K_ADVANCE, K_SWEEP, K_SWEEP_FINISH, K_GRIDSCAN, K_GRIDSCAN_FINISH, K_READ, K_INSTANCE_REG, K_COUNT };
+                K_WINDOW_GENERAL, K_FINISH, K_COPY, K_RANGE_INSTANCE, K_RANGE_WINDOW, K_PARTITION_PRED, K_RANGE_FAST, K_ADVANCE, K_SWEEP, K_SWEEP_FINISH, K_GRIDSCAN, K_GRIDSCAN_FINISH, K_READ, K_INSTANCE_REG, K_RUN, K_COUNT };
 const char* const kKernelNames[K_COUNT] = {
     "zl_instance_kernel", "zl_instance_general_kernel", "zl_bounds_kernel", "zl_partition_kernel",
     "zl_bincount_kernel", "zl_plan_kernel", "zl_window_kernel", "zl_window_general_kernel",
     "zl_finish_kernel", "zl_copy_kernel", "zl_range_instance_kernel", "zl_range_window_kernel",
     "zl_partition_pred_kernel", "zl_range_fast_kernel", "zl_advance_kernel", "zl_sweep_kernel", "zl_sweep_finish_kernel", "zl_gridscan_kernel",
-    "zl_gridscan_finish_kernel", "zl_read_kernel", "zl_instance_reg_kernel"};
+    "zl_gridscan_finish_kernel", "zl_read_kernel", "zl_instance_reg_kernel", "zl_run_kernel"};
 
 size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
@@ -311,6 +311,35 @@ int plan_windows(const Plan& pl, const i64* ts, const i64* le, const i64* iv, i6
     return EBSP_OK;
 }
 
+// Instances of 1024 entries or fewer take both searches in one launch, all supersteps of a run included
+// (zl_run_kernel), where the batch's workgroups are on the chip together; a run's launches weigh more, so twice as
+// many there.  Measured, us per superstep in separate launches / in one: 256 instances of 16 x 60 13.8 / 7.6, 1024
+// 17.6 / 10.8, 2048 24.6 / 20.9, 4096 37.8 / 40.1; 4096 of 16 x 15 21.4 / 16.8.  Single searches: one of 16 x 15
+// 13.5 / 10.6, 2048 of them 16.9 / 14.8, 4096 19.2 / 19.5, 2048 of 16 x 60 21.6 / 22.0.  Larger instances keep the
+// separate kernels: with the general search in the same kernel 100 x 150 predicted took 55.6 us instead of 29.2.
+bool takes_run_kernel(i64 S, i64 B, i64 n)
+{
+    if (n > 1024) return false;
+    const i64 resident = (n <= 256 ? 8ll : 3ll) * GENERAL_GRID;
+    return B <= (S > 1 ? 2 * resident : resident);
+}
+
+int launch_run(const i64* ts, const i64* le, const i64* iv, i64 sync_cost, i64 S, i64 B, int P, int R,
+               i64* barrier, int* iters, i64* wait, int* status, hipStream_t st)
+{
+    const int rshift = (R & (R - 1)) == 0 ? __builtin_ctz((unsigned)R) : -1;
+#define LAUNCH_RUN(NT_, ITEMS_, GITEMS_)                                                                    \
+    do {                                                                                                    \
+        if (ts) LAUNCH(K_RUN, (zl_run_kernel<NT_, ITEMS_, GITEMS_, false>), dim3((unsigned)B), dim3(NT_), ts, le, iv, \
+                       sync_cost, (int)S, B, P, R, rshift, barrier, iters, wait, status);                   \
+        else LAUNCH(K_RUN, (zl_run_kernel<NT_, ITEMS_, GITEMS_, true>), dim3((unsigned)B), dim3(NT_), ts, le, iv, \
+                    sync_cost, (int)S, B, P, R, rshift, barrier, iters, wait, status);                      \
+    } while (0)
+    if (P * R <= 256) LAUNCH_RUN(128, 2, 4); else LAUNCH_RUN(256, 4, 8);
+#undef LAUNCH_RUN
+    return EBSP_OK;
+}
+
 // The rows are either stored (ts != nullptr) or predicted: t[p][i] = le[p] + (i + 1) * iv[p] (ts == nullptr).
 int run_batch(const i64* ts, const i64* le, const i64* iv, i64 B, int P, int R,
               i64* barrier, int* iters, i64* wait, int* status,
@@ -350,6 +379,7 @@ int run_batch(const i64* ts, const i64* le, const i64* iv, i64 B, int P, int R,
 
     if (!pl.multi) {
         if (int rc = check_device()) return rc;
+        if (takes_run_kernel(1, B, n)) return launch_run(ts, le, iv, 0, 1, B, P, R, barrier, iters, wait, status, st);
         const int rshift = (R & (R - 1)) == 0 ? __builtin_ctz((unsigned)R) : -1;
         const dim3 grid((unsigned)B);
 #define LAUNCH_INSTANCE(NT_, ITEMS_)                                                                        \
@@ -632,6 +662,13 @@ int ebsp_simulate_supersteps(const int64_t* last_end0, const int64_t* interval, 
     hipStream_t st = (hipStream_t)stream;
     i64* start = (i64*)((char*)workspace + search_bytes);
     const i64 per = B * (i64)P;
+    if (!pl.multi && S <= 0x7fffffffll && B <= 0x7fffffffll && takes_run_kernel(S, B, (i64)P * R)) {
+        if (int rc = check_device()) return rc;
+        if (int rc = launch_run(nullptr, (const i64*)last_end0, (const i64*)interval, (i64)sync_cost, S, B, P, R, (i64*)barrier,
+                                iters, (i64*)wait, status, st)) return rc;
+        if (g_prof.on && g_prof.calls < g_prof.max_calls) ++g_prof.calls;
+        return EBSP_OK;
+    }
     for (i64 s = 0; s < S; ++s) {
         const i64* from = s == 0 ? (const i64*)last_end0 : start;
         int* flags = status ? status + s * B : nullptr;

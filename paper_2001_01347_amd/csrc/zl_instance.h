@@ -5,27 +5,80 @@
 
 namespace {
 
-// One workgroup per instance (P*R <= NT*ITEMS): the whole search in LDS.
-template <int NT, int ITEMS, bool PRED>        // PRED: rows are le[p] + (i + 1) * iv[p] instead of stored
-__global__ __launch_bounds__(NT) void zl_instance_kernel(
-    const i64* __restrict__ ts, const i64* __restrict__ le, const i64* __restrict__ iv, int P, int R, int rshift,
-    i64* __restrict__ barrier, int* __restrict__ iters, i64* __restrict__ wait,
-    int* __restrict__ status)
+// Where an instance's rows come from, and what a search of it found.
+struct Source {
+    const i64* inst;    // stored rows, or
+    const i64* le;      // predicted ones: le[p] + (i + 1) * iv[p],
+    const i64* iv;
+    i64 start;          // (RUN) start + (i + 1) * iv[p] if `common`
+    bool common;
+};
+struct Found {
+    i64 bar;
+    u64 wait;
+    u32 flags;
+};
+
+template <bool PRED>
+__device__ __forceinline__ Source source_of(const i64* ts, const i64* le, const i64* iv, i64 b, int P, int R)
+{
+    Source s;
+    s.inst = PRED ? nullptr : ts + b * (i64)(P * R);
+    s.le = PRED ? le + b * (i64)P : nullptr;
+    s.iv = PRED ? iv + b * (i64)P : nullptr;
+    s.start = 0;
+    s.common = false;
+    return s;
+}
+
+// An instance's outputs, or the mark that leaves it to zl_instance_general_kernel.
+template <int NT>
+struct StoreFound {
+    const Source& src;
+    i64 b;
+    int P, R;
+    i64* __restrict__ barrier;
+    int* __restrict__ iters;
+    i64* __restrict__ wait;
+    int* __restrict__ status;
+    __device__ __forceinline__ void none() const { if (threadIdx.x == 0) wait[b] = DEFERRED; }
+    __device__ __forceinline__ void operator()(const Found& f) const
+    {
+        if (threadIdx.x == 0) {
+            barrier[b] = f.bar;
+            wait[b] = (i64)f.wait;
+            if (status) status[b] = (int)f.flags;
+        }
+        for (int p = threadIdx.x; p < P; p += NT)
+            iters[b * (i64)P + p] = zl_iters_of(src.inst, src.le, src.iv, p, R, f.bar);
+    }
+};
+// The same kept for the caller.
+struct KeepFound {
+    bool& found;
+    Found& f;
+    __device__ __forceinline__ void none() const { found = false; }
+    __device__ __forceinline__ void operator()(const Found& g) const { found = true; f = g; }
+};
+
+// One workgroup per instance (P*R <= NT*ITEMS): the whole search in LDS (smem: HotCfg::BYTES of it).  out
+// gets what it found, or none(): left to the general search.  On return some threads may still be reading LDS.
+template <int NT, int ITEMS, bool PRED, bool RUN, class Out>        // PRED: rows are predicted; RUN: src.common may be set
+__device__ __forceinline__ void zl_instance_search(unsigned char* smem, const Source& src, int P, int R, int rshift, const Out& out)
 {
     using H = HotCfg<NT, ITEMS>;
-    __shared__ __align__(16) unsigned char smem[H::BYTES];
     const Smem sm = carve_hot<NT, ITEMS>(smem);
 
     const int tid = threadIdx.x;
-    const i64 b = blockIdx.x;
     const int n = P * R;
-    const i64* __restrict__ inst = PRED ? nullptr : ts + b * (i64)n;
-    const i64* __restrict__ lep = PRED ? le + b * (i64)P : nullptr;
-    const i64* __restrict__ ivp = PRED ? iv + b * (i64)P : nullptr;
+    const i64* __restrict__ inst = src.inst;
+    const i64* __restrict__ lep = src.le;
+    const i64* __restrict__ ivp = src.iv;
     auto at = [&](int e) -> i64 {                       // element e of the instance
         if (!PRED) return inst[e];
         const int p = rshift >= 0 ? (e >> rshift) : (e / R);
-        return (i64)((u64)lep[p] + (u64)(e - p * R + 1) * (u64)ivp[p]);
+        const i64 from = RUN && src.common ? src.start : lep[p];
+        return (i64)((u64)from + (u64)(e - p * R + 1) * (u64)ivp[p]);
     };
 
     // zl_delta.  Every element is loaded once, all loads of a thread in flight
@@ -75,11 +128,7 @@ __global__ __launch_bounds__(NT) void zl_instance_kernel(
     u32 flags = 0;
     if (range > (u64)INT64_MAX / (u64)P) flags |= EBSP_STATUS_OVERFLOW;
 
-    if (range >> 32) {
-        // deltas need more than 32 bits: left to zl_instance_general_kernel
-        if (tid == 0) wait[b] = DEFERRED;
-        return;
-    }
+    if (range >> 32) { out.none(); return; }          // deltas need more than 32 bits
     // a row's first delta is its key relative to base
     for (int p = tid; p < P; p += NT) {
         const u64 r = sm.recs[(size_t)p * R];
@@ -137,17 +186,22 @@ __global__ __launch_bounds__(NT) void zl_instance_kernel(
     u64 best_wait;
     u32 bkey;
     if (!zl_bucket_finish<NT, ITEMS, false>(sm, key, StoredDeltas<ITEMS>{dl}, bucket, SlotsBelow<NT>{n}, 0ull, thr, (u32)P, 0ull, best_wait, bkey)) {
-        if (tid == 0) wait[b] = DEFERRED;      // clustered values: left to zl_instance_general_kernel
+        out.none();                            // clustered values
         return;
     }
-    const i64 bar = (i64)((u64)base + bkey);
-    if (tid == 0) {
-        barrier[b] = bar;
-        wait[b] = (i64)best_wait;
-        if (status) status[b] = (int)flags;
-    }
-    for (int p = tid; p < P; p += NT)
-        iters[b * (i64)P + p] = zl_iters_of(inst, lep, ivp, p, R, bar);
+    out(Found{(i64)((u64)base + bkey), best_wait, flags});
+}
+
+template <int NT, int ITEMS, bool PRED>
+__global__ __launch_bounds__(NT) void zl_instance_kernel(
+    const i64* __restrict__ ts, const i64* __restrict__ le, const i64* __restrict__ iv, int P, int R, int rshift,
+    i64* __restrict__ barrier, int* __restrict__ iters, i64* __restrict__ wait,
+    int* __restrict__ status)
+{
+    __shared__ __align__(16) unsigned char smem[HotCfg<NT, ITEMS>::BYTES];
+    const i64 b = blockIdx.x;
+    const Source src = source_of<PRED>(ts, le, iv, b, P, R);
+    zl_instance_search<NT, ITEMS, PRED, false>(smem, src, P, R, rshift, StoreFound<NT>{src, b, P, R, barrier, iters, wait, status});
 }
 
 // The same search for the larger single-workgroup instances (1024 < P*R <= NT*ITEMS) with the
@@ -336,6 +390,36 @@ __global__ __launch_bounds__(NT, (NT == 1024 ? 8 : (NT == 128 ? 5 : 6))) void zl
         iters[b * (i64)P + p] = zl_iters_of(inst, lep, ivp, p, R, bar);
 }
 
+// The general search over whole rows of one instance (value spread of 2^32 or more, or values too clustered for
+// the bucket search): 64-bit keys and deltas, any spread in one piece (or as few as its entries need).
+template <int NT, int ITEMS, class RW>
+__device__ __forceinline__ void zl_instance_general_search(const Smem& sm, RW& rw, int P, int R, Found& out)
+{
+    rw.P = P; rw.R = R;
+    rw.cr = nullptr; rw.narrow = false; rw.wide = false; rw.stride = 0; rw.k0 = rw.k1 = 0;
+    i64 mn = INT64_MAX, mxf = INT64_MIN, mxl = INT64_MIN;
+    for (int p = threadIdx.x; p < P; p += NT) {
+        const i64 f = rw.value(p, 0), l = rw.value(p, (u32)R - 1);
+        mn = f < mn ? f : mn;
+        mxf = f > mxf ? f : mxf;
+        mxl = l > mxl ? l : mxl;
+    }
+    i64 base, first_max, last_max;
+    block_bounds<NT>(mn, mxf, mxl, (i64*)sm.red, base, first_max, last_max);
+    const u64 range = (u64)last_max - (u64)base;
+    const u64 thr = (u64)first_max - (u64)base;
+    u32 flags = 0;
+    if (range > (u64)INT64_MAX / (u64)P) flags |= EBSP_STATUS_OVERFLOW;
+    rw.base = (u64)base;
+    int bad = 0;
+    u64 best_wait = U64_MAX, best_rel = 0;
+    zl_window<NT, ITEMS, true, true>(sm, rw, thr, 0ull, range, best_wait, best_rel, bad);
+    if (__syncthreads_or(bad)) flags |= EBSP_STATUS_UNSORTED;
+    out.bar = (i64)((u64)base + best_rel);
+    out.wait = best_wait;
+    out.flags = flags;
+}
+
 // The instances zl_instance_kernel deferred (value spread of 2^32 or more, or
 // values too clustered for the bucket search): the general window search over
 // whole rows.  A small fixed grid; every workgroup looks through its share of
@@ -362,43 +446,69 @@ __global__ __launch_bounds__(NT) void zl_instance_general_kernel(
             const u32 b = block_reduce<u32, NT>(mine ? idx : 0xffffffffu, (u32*)sm.red, OpMin());
             if (b == 0xffffffffu) break;
             if (b == idx) mine = false;
-            const i64* __restrict__ inst = ts ? ts + (i64)b * P * R : nullptr;
-            Rows ends;                            // only to read the rows' first and last entries
-            ends.inst = inst; ends.le = le ? le + (i64)b * P : nullptr; ends.iv = iv ? iv + (i64)b * P : nullptr;
-            ends.R = R;
-            i64 mn = INT64_MAX, mxf = INT64_MIN, mxl = INT64_MIN;
-            for (int p = tid; p < P; p += NT) {
-                const i64 f = ends.value(p, 0), l = ends.value(p, (u32)R - 1);
-                mn = f < mn ? f : mn;
-                mxf = f > mxf ? f : mxf;
-                mxl = l > mxl ? l : mxl;
-            }
-            i64 base, first_max, last_max;
-            block_bounds<NT>(mn, mxf, mxl, (i64*)sm.red, base, first_max, last_max);
-            const u64 range = (u64)last_max - (u64)base;
-            const u64 thr = (u64)first_max - (u64)base;
-            u32 flags = 0;
-            if (range > (u64)INT64_MAX / (u64)P) flags |= EBSP_STATUS_OVERFLOW;
-
             Rows rw;
-            rw.inst = inst; rw.le = le ? le + (i64)b * P : nullptr; rw.iv = iv ? iv + (i64)b * P : nullptr;
-            rw.P = P; rw.R = R; rw.base = (u64)base;
-            rw.cr = nullptr; rw.narrow = false; rw.wide = false; rw.stride = 0; rw.k0 = rw.k1 = 0;
-            int bad = 0;
-            u64 best_wait = U64_MAX, best_rel = 0;
-            // the 64-bit-delta form serves every deferred instance, narrow ones included
-            // 64-bit keys: an instance of any value spread in one piece (or as few as its entries need)
-            zl_window<NT, ITEMS, true, true>(sm, rw, thr, 0ull, range, best_wait, best_rel, bad);
-            if (__syncthreads_or(bad)) flags |= EBSP_STATUS_UNSORTED;
-            const i64 bar = (i64)((u64)base + best_rel);
+            rw.inst = ts ? ts + (i64)b * P * R : nullptr; rw.le = le ? le + (i64)b * P : nullptr; rw.iv = iv ? iv + (i64)b * P : nullptr;
+            Found f;
+            zl_instance_general_search<NT, ITEMS>(sm, rw, P, R, f);
             if (tid == 0) {
-                barrier[b] = bar;
-                wait[b] = (i64)best_wait;
-                if (status) status[b] = (int)flags;
+                barrier[b] = f.bar;
+                wait[b] = (i64)f.wait;
+                if (status) status[b] = (int)f.flags;
             }
-            for (int p = tid; p < P; p += NT)
-                iters[(i64)b * P + p] = zl_iters_of(inst, ends.le, ends.iv, p, R, bar);
+            for (int p = tid; p < P; p += NT) iters[(i64)b * P + p] = zl_iters_of(rw.inst, rw.le, rw.iv, p, R, f.bar);
         }
+    }
+}
+
+// Both searches in one workgroup, over S supersteps: a workgroup takes an instance through all of them, the general
+// search where the fast one gives up.  S == 1 is a single search (stored or predicted rows).  Batches that fit the
+// chip at once are bound by launches and by the latency of one workgroup's chain, so one launch instead of three per
+// superstep (search, general search, start times) is what counts; the general search's LDS costs occupancy that such
+// batches do not use.  Registers (the general search's) leave room for three workgroups of 256 per CU: held to four
+// by spilling, the 256 instances of 16 x 60 took 8.1 us per superstep instead of 7.6 (13.8 in three launches).
+template <int NT, int ITEMS, int GITEMS, bool PRED>
+__global__ __launch_bounds__(NT) void zl_run_kernel(
+    const i64* __restrict__ ts, const i64* __restrict__ le, const i64* __restrict__ iv, i64 sync_cost, int S, i64 B, int P, int R,
+    int rshift, i64* __restrict__ barrier, int* __restrict__ iters, i64* __restrict__ wait, int* __restrict__ status)
+{
+    using H = HotCfg<NT, ITEMS>;
+    using C = WinCfg<NT, GITEMS>;
+    static_assert(C::CAP_WIDE >= NT * ITEMS, "the general search takes an instance in one piece");
+    __shared__ __align__(16) unsigned char smem[H::BYTES > C::BYTES ? H::BYTES : C::BYTES];
+    const int tid = threadIdx.x;
+    const i64 b = blockIdx.x;
+    Source src = source_of<PRED>(ts, le, iv, b, P, R);
+    for (int s = 0; s < S; ++s) {
+        // the next superstep's intervals are asked for a superstep ahead: they come from HBM
+        i64 ahead = 0;
+        if (PRED && s + 1 < S && tid < P) ahead = src.iv[B * (i64)P + tid];
+        Found f;
+        bool found;
+        zl_instance_search<NT, ITEMS, PRED, PRED>(smem, src, P, R, rshift, KeepFound{found, f});
+        RunRows rw;
+        rw.inst = src.inst; rw.le = src.le; rw.iv = src.iv;
+        rw.common = PRED && src.common; rw.start = src.start;
+        rw.R = R;
+        if (!found) {
+            __syncthreads();                              // the fast search may still be reading LDS
+            const Smem sm = carve<NT, GITEMS>(smem);
+            zl_instance_general_search<NT, GITEMS>(sm, rw, P, R, f);
+        }
+        const i64 at = (i64)s * B + b;
+        if (tid == 0) {
+            barrier[at] = f.bar;
+            wait[at] = (i64)f.wait;
+            if (status) status[at] = (int)f.flags;
+        }
+        for (int p = tid; p < P; p += NT) iters[at * P + p] = rw.iters(p, f.bar);
+        // after the barrier and the synchronisation every worker starts together; where the search raised a status
+        // bit there is no barrier and the workers keep their start times
+        if (PRED) {
+            if (!status || f.flags == 0) { src.common = true; src.start = (i64)((u64)f.bar + (u64)sync_cost); }
+            src.iv += B * (i64)P;
+        }
+        asm volatile("" :: "v"(ahead));
+        if (s + 1 < S) __syncthreads();                   // LDS is written again
     }
 }
 

@@ -5,6 +5,29 @@
 
 namespace {
 
+// ---------------------------------------------------------------------------
+// zl_iters: number of entries of a sorted row that are <= v.
+__device__ __forceinline__ int zl_iters(const i64* __restrict__ row, int R, i64 v)
+{
+    u32 lo = 0, hi = (u32)R;               // unsigned: lo + hi may pass 2^31
+    while (lo < hi) {
+        const u32 m = (lo + hi) >> 1;
+        if (row[m] <= v) lo = m + 1; else hi = m;
+    }
+    return (int)lo;
+}
+
+// The same for the predicted row l + (i + 1) * s, i < R.
+__device__ __forceinline__ int zl_iters_pred(i64 l, i64 s, int R, i64 v)
+{
+    u32 lo = 0, hi = (u32)R;
+    while (lo < hi) {
+        const u32 m = (lo + hi) >> 1;
+        if ((i64)((u64)l + (u64)(m + 1) * (u64)s) <= v) lo = m + 1; else hi = m;
+    }
+    return (int)lo;
+}
+
 // Rows of one instance and, per row, the index range under consideration:
 // the whole row, or [cross[p][k0], cross[p][k1]) from zl_partition.
 struct Rows {
@@ -51,8 +74,25 @@ struct Rows {
     __device__ __forceinline__ u64 rel(int p, u32 i) const { return (u64)value(p, i) - base; }
 };
 
+// Whole rows whose workers may all start at one time (a run of supersteps: after the first barrier they do).
+struct RunRows : Rows {
+    bool common;        // predicted rows: every worker starts at `start` (le is then not read)
+    i64 start;
+    __device__ __forceinline__ i64 value(int p, u32 i) const
+    {
+        if (inst) return inst[(size_t)p * R + i];
+        return (i64)((u64)(common ? start : le[p]) + (u64)(i + 1) * (u64)iv[p]);
+    }
+    __device__ __forceinline__ u64 rel(int p, u32 i) const { return (u64)value(p, i) - base; }
+    __device__ __forceinline__ int iters(int p, i64 v) const
+    {
+        return inst ? zl_iters(inst + (size_t)p * R, R, v) : zl_iters_pred(common ? start : le[p], iv[p], R, v);
+    }
+};
+
 // First index in [lo, hi) of row p whose relative value is >= v (hi if none).
-__device__ __forceinline__ u32 row_lower_bound(const Rows& rw, int p, u32 lo, u32 hi, u64 v)
+template <class RW>
+__device__ __forceinline__ u32 row_lower_bound(const RW& rw, int p, u32 lo, u32 hi, u64 v)
 {
     while (lo < hi) {
         const u32 m = (lo + hi) >> 1;
@@ -63,7 +103,8 @@ __device__ __forceinline__ u32 row_lower_bound(const Rows& rw, int p, u32 lo, u3
 
 // Index range of row p inside the value interval [a, el] (both inclusive).
 // lx / rx: the interval starts / ends exactly where the row ranges do.
-__device__ __forceinline__ void sub_range(const Rows& rw, int p, u64 a, u64 el, bool lx, bool rx,
+template <class RW>
+__device__ __forceinline__ void sub_range(const RW& rw, int p, u64 a, u64 el, bool lx, bool rx,
                                           u32& lo, u32& hi)
 {
     rw.range(p, lo, hi);
@@ -71,29 +112,11 @@ __device__ __forceinline__ void sub_range(const Rows& rw, int p, u64 a, u64 el, 
     if (!rx && el != U64_MAX) hi = row_lower_bound(rw, p, lo, hi, el + 1);
 }
 
-// ---------------------------------------------------------------------------
-// zl_iters: number of entries of a sorted row that are <= v.
-__device__ __forceinline__ int zl_iters(const i64* __restrict__ row, int R, i64 v)
-{
-    u32 lo = 0, hi = (u32)R;               // unsigned: lo + hi may pass 2^31
-    while (lo < hi) {
-        const u32 m = (lo + hi) >> 1;
-        if (row[m] <= v) lo = m + 1; else hi = m;
-    }
-    return (int)lo;
-}
-
-// The same for row p of stored (inst != nullptr) or predicted rows.
+// Number of entries <= v of row p of stored (inst != nullptr) or predicted rows.
 __device__ __forceinline__ int zl_iters_of(const i64* inst, const i64* le, const i64* iv, int p, int R, i64 v)
 {
     if (inst) return zl_iters(inst + (size_t)p * R, R, v);
-    const i64 l = le[p], s = iv[p];
-    u32 lo = 0, hi = (u32)R;
-    while (lo < hi) {
-        const u32 m = (lo + hi) >> 1;
-        if ((i64)((u64)l + (u64)(m + 1) * (u64)s) <= v) lo = m + 1; else hi = m;
-    }
-    return (int)lo;
+    return zl_iters_pred(le[p], iv[p], R, v);
 }
 
 }  // namespace

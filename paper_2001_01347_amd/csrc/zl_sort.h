@@ -244,8 +244,8 @@ __device__ __forceinline__ void fill_sentinels_hi(u32* ext, int total, int items
 // of row p before the interval).  Rows are taken NT at a time: a block scan of
 // the segment lengths gives every row its first slot, then consecutive threads
 // take consecutive slots, so reads within a segment coalesce.
-template <int NT, bool WIDE, bool PAD, bool KEY64 = false>
-__device__ __forceinline__ int zl_delta(const Smem& sm, const Rows& rw, u64 a, u64 el, bool lx, bool rx,
+template <int NT, bool WIDE, bool PAD, bool KEY64 = false, class RW = Rows>
+__device__ __forceinline__ int zl_delta(const Smem& sm, const RW& rw, u64 a, u64 el, bool lx, bool rx,
                                         int cap, u64& w0, int& bad)
 {
     static_assert(WIDE || !KEY64, "64-bit keys go with the three-plane layout");

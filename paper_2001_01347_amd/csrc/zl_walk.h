@@ -6,8 +6,8 @@
 namespace {
 
 // Number of entries of the rows inside [a, el].
-template <int NT>
-__device__ __forceinline__ u32 count_interval(const Smem& sm, const Rows& rw, u64 a, u64 el, bool lx)
+template <int NT, class RW>
+__device__ __forceinline__ u32 count_interval(const Smem& sm, const RW& rw, u64 a, u64 el, bool lx)
 {
     u32 c = 0;
     for (int p = threadIdx.x; p < rw.P; p += NT) {
@@ -26,8 +26,8 @@ __device__ __forceinline__ u32 count_interval(const Smem& sm, const Rows& rw, u6
 // a single value that alone occurs more than `cap` times is one candidate and
 // is evaluated directly from the rows.  (bw, bb) is updated with the first
 // minimum found: smaller wait, then smaller barrier (relative to base).
-template <int NT, int ITEMS, bool WIDE, bool KEY64 = false>
-__device__ __forceinline__ void zl_window(const Smem& sm, const Rows& rw, u64 thr, u64 A, u64 Elast,
+template <int NT, int ITEMS, bool WIDE, bool KEY64 = false, class RW = Rows>
+__device__ __forceinline__ void zl_window(const Smem& sm, const RW& rw, u64 thr, u64 A, u64 Elast,
                                           u64& bw, u64& bb, int& bad)
 {
     using C = WinCfg<NT, ITEMS>;

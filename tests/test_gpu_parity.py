@@ -459,3 +459,15 @@ def test_the_yardstick_kernels_copy_and_read_everything(zl, nbytes):
     assert int(sink.sum().item()) == int(src.to(torch.int64).sum().item())
     with pytest.raises(ValueError):
         zl.ebsp_zipline_read_probe(src, sink[:1])
+
+
+@pytest.mark.parametrize("P,R,B", [(16, 16, 2048), (16, 16, 2049), (257, 1, 768), (16, 64, 768), (16, 64, 769)])
+def test_small_instances_at_the_edges_of_the_one_launch_search(zl, oracle, P, R, B):
+    rng = np.random.default_rng(P * R + B)
+    ts = np.cumsum(rng.integers(1, 2000, size=(B, P, R), dtype=np.int64), axis=2)
+    ts[::5] *= 1 << 20                     # spreads beyond 32 bits
+    ts[1::7] = ts[1::7] // (1 << 40)       # all equal
+    bar, it, w, st = gpu_run(zl, ts)
+    ob, oi, ow, rc, _ = oracle.zipline(ts, "sweep", threads=16)
+    assert (rc == 0).all() and (st == 0).all()
+    assert np.array_equal(bar, ob) and np.array_equal(w, ow) and np.array_equal(it, oi)

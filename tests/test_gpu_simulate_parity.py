@@ -216,3 +216,35 @@ def test_hand_worked_fixture(zl):
                                  c["R"], c["sync_cost"])
         assert (st == 0).all(), c["name"]
         assert bar.tolist() == c["barrier"] and w.tolist() == c["wait"] and it.tolist() == c["iters"], c["name"]
+
+
+@pytest.mark.parametrize("P,R,B", [(16, 16, 3), (257, 1, 3), (64, 16, 2), (41, 25, 2), (4, 15, 4096), (4, 15, 4097),
+                                   (5, 60, 1536), (5, 60, 1537)])
+def test_runs_in_one_launch_and_their_neighbours(zl, oracle, P, R, B):
+    """Instances and batches at the edges of the runs that one launch takes whole; among the supersteps some whose
+    values are clustered (zero intervals) or spread over 2^32 and more, which the general search finishes."""
+    rng = np.random.default_rng(P * R + B)
+    S = 4
+    iv = rng.integers(80_000, 120_000, size=(S, B, P)).astype(np.int64)
+    iv[1, ::2] = 0
+    iv[2, 1::3] *= 1 << 20
+    le = rng.integers(0, 80_000, size=(B, P)).astype(np.int64) + EPOCH
+    assert_same(zl, oracle, le, iv, R, 2000, f"P={P} R={R} B={B}")
+
+
+def test_a_run_in_one_launch_keeps_the_starts_of_flagged_instances(zl, oracle):
+    # a negative interval raises the status bit for its superstep alone; the workers then keep their start times
+    rng = np.random.default_rng(9)
+    iv = rng.integers(80, 120, size=(4, 3, 8)).astype(np.int64)
+    le = rng.integers(0, 80, size=(3, 8)).astype(np.int64)
+    bad = iv.copy()
+    bad[0, 1, 2] = bad[2, 1, 5] = -7
+    bar, it, w, st = gpu_run(zl, le, bad, 20, 3)
+    assert (st[:, (0, 2)] == 0).all() and st[:, 1].tolist() == [1, 0, 1, 0]
+    ob, oi, ow, rc, _ = oracle.simulate(le, iv, 20, 3)
+    assert np.array_equal(bar[:, (0, 2)], ob[:, (0, 2)]) and np.array_equal(w[:, (0, 2)], ow[:, (0, 2)])
+    first = oracle.zipline(oracle.predicted_rows(le[1:2], bad[1, 1:2], 20))       # still from its first start times
+    assert bar[1, 1] == first[0][0] and w[1, 1] == first[2][0]
+    start = np.full((1, 8), first[0][0] + 3, dtype=np.int64)
+    last = oracle.zipline(oracle.predicted_rows(start, bad[3, 1:2], 20))
+    assert bar[3, 1] == last[0][0] and w[3, 1] == last[2][0]
