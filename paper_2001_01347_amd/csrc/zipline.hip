@@ -241,6 +241,10 @@ hipEvent_t* prof_slot(int kid, int which)
         }                                                                                  \
     } while (0)
 
+// Batches of more windows than this (max_win is about twice the windows there are) first find out how far the
+// values can win (zl_bounds): below it the windows are all searched at once and dropping some saves no time.
+constexpr i64 CUT_MIN_WINDOWS = 2048;
+
 // The front of the multi-window path, shared by the objectives: per-instance facts and
 // fine-bin map, crossing indices, exact bin counts, windows.
 int plan_windows(const Plan& pl, const i64* ts, const i64* le, const i64* iv, i64 B, int P, int R,
@@ -260,8 +264,13 @@ int plan_windows(const Plan& pl, const i64* ts, const i64* le, const i64* iv, i6
     const i64 kblocks = (pl.stride + 255) / 256;
     const i64 widest = pl.part_stored > pl.part_pred ? pl.part_stored : pl.part_pred;
     if (kblocks * B > 0x7fffffffll || widest * B > 0x7fffffffll) return fail(EBSP_ERR_SHAPE, "batch too large for one call");
-    LAUNCH(K_BOUNDS, (zl_bounds_kernel<256>), dim3((unsigned)B), dim3(256), ts, le, iv, P, R, pl.bins, info, segtab, rowpar, status, summed,
-           (i64*)nullptr);
+    const bool cut = B * (i64)pl.max_win > CUT_MIN_WINDOWS;
+    if (cut && P > 256)       // a thread per row: each is a chain of dependent loads there
+        LAUNCH(K_BOUNDS, (zl_bounds_kernel<1024>), dim3((unsigned)B), dim3(1024), ts, le, iv, P, R, pl.bins, info, segtab, rowpar, status, summed,
+               cut, (i64*)nullptr);
+    else
+        LAUNCH(K_BOUNDS, (zl_bounds_kernel<256>), dim3((unsigned)B), dim3(256), ts, le, iv, P, R, pl.bins, info, segtab, rowpar, status, summed,
+               cut, (i64*)nullptr);
     int part_rows;                                    // rows of partial column sums per instance (0: none, count from cross)
     if (pred) {
         part_rows = pl.part_pred;
@@ -368,7 +377,7 @@ int run_batch(const i64* ts, const i64* le, const i64* iv, i64 B, int P, int R,
         Partial* spartial = (Partial*)(wsp + pl.off_spartial);
         i64* best = (i64*)(wsp + pl.off_best);
         LAUNCH(K_BOUNDS, (zl_bounds_kernel<256>), dim3((unsigned)B), dim3(256), ts, le, iv, P, R, pl.nslices, info, segtab,
-               (uint2*)nullptr, status, true, best);
+               (uint2*)nullptr, status, true, false, best);
         const dim3 sgrid((unsigned)(B * (i64)pl.nslices));
         LAUNCH(K_SWEEP, (zl_sweep_kernel<SWEEP_NT, SWEEP_LINES, SWEEP_BUCKETS, SWEEP_LIST, SWEEP_PMAX>), sgrid, dim3(SWEEP_NT),
                ts, B, P, R, pl.nslices, pl.lines, info, segtab, best, spartial, status);

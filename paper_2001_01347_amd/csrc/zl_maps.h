@@ -20,7 +20,7 @@ struct InstInfo {
     u64 thr;     // max_p t[p][0] - base: earliest admissible barrier
     u32 segshift; // segment of the fine-bin map that (v >> wshift) falls in: (v >> wshift) >> segshift
     u32 wshift;  // 0 unless the range needs more than 32 bits
-    u32 nb;      // number of fine bins, bin(range) + 1
+    u32 nb;      // number of fine bins that are searched: bin(range) + 1, or fewer where zl_bounds found that no later value can win
     u32 nwin;    // number of windows (set by zl_plan)
     u32 flags;   // EBSP_STATUS_* bits found so far
     u32 wide_steps; // how often a row steps by 2^32 or more from one entry to the next (counted by zl_partition)
@@ -51,7 +51,17 @@ ZL_FN u32 fine_bin(u64 rel, const InstInfo& ii, const SegEntry* tab)
     const u32 k = (u32)((e.G + (u64)(x - (s << ii.segshift)) * e.slope) >> 32);
     return k < ii.nb ? k : ii.nb - 1;
 }
-// Smallest relative value that falls in bin k or later (k < nb).
+// The same with nb for every value behind the bins that are searched.
+ZL_FN u32 fine_bin_or_nb(u64 rel, const InstInfo& ii, const SegEntry* tab)
+{
+    if (rel > ii.range) rel = ii.range;
+    const u32 x = (u32)(rel >> ii.wshift);
+    const u32 s = x >> ii.segshift;
+    const SegEntry e = tab[s];
+    const u32 k = (u32)((e.G + (u64)(x - (s << ii.segshift)) * e.slope) >> 32);
+    return k < ii.nb ? k : ii.nb;
+}
+// Smallest relative value that falls in bin k or later (k <= bin(range)).
 ZL_FN u64 fine_bin_start(u32 k, const InstInfo& ii, const SegEntry* tab)
 {
     const u64 wmax = (1ull << ii.segshift) - 1;
@@ -67,7 +77,11 @@ ZL_FN u64 fine_bin_start(u32 k, const InstInfo& ii, const SegEntry* tab)
     if (want > e.G && e.slope) off = (want - e.G + e.slope - 1) / e.slope;
     return (((u64)lo << ii.segshift) + off) << ii.wshift;
 }
-
+// Last relative value of the bins that are searched.
+ZL_FN u64 searched_end(const InstInfo& ii, const SegEntry* tab)
+{
+    return fine_bin_or_nb(ii.range, ii, tab) < ii.nb ? ii.range : fine_bin_start(ii.nb, ii, tab) - 1;
+}
 
 // Slope (bins per value of x, 32.32 fixed point, rounded down) of a segment that is to get the share
 // (est + even) / total2 of the bins - 1 bins of the grid over its `len` values in use.

@@ -7,21 +7,102 @@ namespace {
 
 // Multi-window path.
 
+// Values that cannot win are not searched.  Once a worker's row has ended its share of the wait only grows: a
+// barrier c waits at least lb(c) = sum_p max(0, c - last entry of row p).  For any value x >= thr the largest entry
+// up to x is a candidate and waits at most ub = sum_p (x - last entry of row p up to x).  So no value above C with
+// lb(C) >= ub can be the minimum (beyond C lb grows strictly; ties below it are kept), and the fine bins behind C's
+// are dropped: the crossing table, the bin counts and the windows all end there.  The range objective has
+// max_p instead of the sum in ub and c - (the earliest row end) for lb.  x = the earliest row end (or thr): until then
+// lb is 0.  Rows are searched for x from where evenly spaced entries would put it, C is found from above by Newton's
+// method on the convex lb.  Rows are read whole for their order check all the same.
+// Config 5 (workers whose iterations take 20 to 200 ms) keeps a third of its entries, two groups 2.5 times apart nine
+// tenths.  Costs up to 30 us of latency, so only where the windows are more than the chip takes at once.
+constexpr int CUT_ROWS = 2048;          // rows whose ends are kept in LDS for it (instances with more rows keep all bins)
+constexpr int CUT_STEPS = 16;
+
+// The last entry up to x of a sorted row (f <= x; values relative to base).
+__device__ __forceinline__ u64 cut_last_up_to(const Rows& ends, int p, u64 base, u64 f, u64 l, u64 x)
+{
+    if (l <= x || l <= f) return l <= x ? l : f;
+    u32 lo = 0, hi = (u32)ends.R - 1;                 // the entry at lo is <= x (vlo), the one at hi above
+    u64 vlo = f;
+    u32 g = (u32)((double)(x - f) / (double)(l - f) * (double)hi);
+    g = g < hi ? g : hi - 1;
+    auto at = [&](u32 i) { return (u64)ends.value(p, i) - base; };
+    u64 v = at(g);
+    u32 step = 1;
+    if (v <= x) {
+        lo = g; vlo = v;
+        while (lo + step < hi) {
+            v = at(lo + step);
+            if (v <= x) { lo += step; vlo = v; step *= 2; } else { hi = lo + step; break; }
+        }
+    } else {
+        hi = g;
+        while (hi > lo + step) {
+            v = at(hi - step);
+            if (v > x) { hi -= step; step *= 2; } else { lo = hi - step; vlo = v; break; }
+        }
+    }
+    while (hi - lo > 1) {
+        const u32 m = lo + ((hi - lo) >> 1);
+        v = at(m);
+        if (v <= x) { lo = m; vlo = v; } else hi = m;
+    }
+    return vlo;
+}
+
+// The last value that can win (see above), at most ii.range.
+template <int NT>
+__device__ __forceinline__ u64 cut_value(const Rows& ends, int P, const InstInfo& ii, u64 min_last, bool summed,
+                                         u64* row_end, u64* red)
+{
+    constexpr int NW = NT / WAVE;
+    const int tid = threadIdx.x, lane = tid & (WAVE - 1), wave = tid >> 6;
+    const u64 x = min_last > ii.thr ? min_last : ii.thr;
+    u64 mine = 0;
+    for (int p = tid; p < P; p += NT) {
+        const u64 f = (u64)ends.value(p, 0) - (u64)ii.base, l = (u64)ends.value(p, (u32)ends.R - 1) - (u64)ii.base;
+        row_end[p] = l;                               // (read by this thread alone)
+        const u64 gone = x - cut_last_up_to(ends, p, (u64)ii.base, f, l, x);
+        mine = summed ? mine + gone : (gone > mine ? gone : mine);
+    }
+    const u64 ub = summed ? block_reduce<u64, NT>(mine, red, OpAdd()) : block_reduce<u64, NT>(mine, red, OpMax());
+    if (!summed) return ii.range - min_last > ub ? min_last + ub : ii.range;
+    u64 C = ii.range;
+    for (int it = 0; it < CUT_STEPS; ++it) {
+        u64 lb = 0, n = 0;
+        for (int p = tid; p < P; p += NT) {
+            const u64 l = row_end[p];
+            if (l < C) { lb += C - l; ++n; }
+        }
+        lb = wave_scan(lb, OpAdd());
+        n = wave_scan(n, OpAdd());
+        if (lane == WAVE - 1) { red[wave] = lb; red[NW + wave] = n; }
+        __syncthreads();
+        lb = red[0]; n = red[NW];
+#pragma unroll
+        for (int w = 1; w < NW; ++w) { lb += red[w]; n += red[NW + w]; }
+        __syncthreads();
+        if (lb <= ub || lb - ub < n) break;           // (the same in every thread)
+        C -= (lb - ub) / n;
+    }
+    return C;
+}
+
 // zl_bounds: per-instance base, range, thr and the fine-bin grid.
 template <int NT>
 __global__ __launch_bounds__(NT) void zl_bounds_kernel(
     const i64* __restrict__ ts, const i64* __restrict__ le, const i64* __restrict__ iv, int P, int R, int bins,
     InstInfo* __restrict__ info, SegEntry* __restrict__ segtab, uint2* __restrict__ rowpar, int* __restrict__ status,
-    bool summed, i64* __restrict__ best = nullptr)
+    bool summed, bool cut, i64* __restrict__ best = nullptr)
 {
     static_assert(NT >= SEGS, "one thread per segment");
     if (best && threadIdx.x == 0) best[blockIdx.x] = INT64_MAX;     // the instance's best upper bound so far (the sweep's slices share it)
-    __shared__ i64 red[NT / WAVE];
+    __shared__ i64 red[3 * (NT / WAVE)];
+    __shared__ u64 row_end[CUT_ROWS];
     __shared__ u64 seg_part[SEGS];        // entries of rows that begin or end in a segment (x 2^16)
     __shared__ u64 seg_diff[SEGS + 1];    // difference array: entries per segment of the rows that cover it whole (x 2^16)
-    __shared__ u64 seg_est[SEGS];
-    __shared__ u64 seg_step[SEGS];
-    __shared__ u32 seg_slope[SEGS];
     const int tid = threadIdx.x;
     const i64 b = blockIdx.x;
     Rows ends;                                        // only to read the rows' first and last entries
@@ -29,20 +110,21 @@ __global__ __launch_bounds__(NT) void zl_bounds_kernel(
     ends.le = le ? le + b * (i64)P : nullptr;
     ends.iv = iv ? iv + b * (i64)P : nullptr;
     ends.R = R;
-    i64 mn = INT64_MAX, mxf = INT64_MIN, mxl = INT64_MIN;
+    i64 mn = INT64_MAX, mxf = INT64_MIN, mxl = INT64_MIN, mnl = INT64_MAX;
     int backwards = 0;
+#pragma unroll 4
     for (int p = tid; p < P; p += NT) {
         const i64 f = ends.value(p, 0), l = ends.value(p, (u32)R - 1);
         mn = f < mn ? f : mn;
         mxf = f > mxf ? f : mxf;
         mxl = l > mxl ? l : mxl;
+        mnl = l < mnl ? l : mnl;
         if (!ends.inst && R > 1 && ends.iv[p] < 0) backwards = 1;     // predicted rows: a negative interval
     }
     if (tid < SEGS) { seg_part[tid] = 0; seg_diff[tid] = 0; }
     if (tid == 0) seg_diff[SEGS] = 0;
-    const i64 base = block_reduce<i64, NT>(mn, red, OpMin());
-    const i64 first_max = block_reduce<i64, NT>(mxf, red, OpMax());
-    const i64 last_max = block_reduce<i64, NT>(mxl, red, OpMax());
+    i64 base, first_max, last_max;
+    block_bounds<NT>(mn, mxf, mxl, red, base, first_max, last_max);
     backwards = __syncthreads_or(backwards);
     if (rowpar)                                       // predicted rows, for the window gather: low words of the first value and the interval
         for (int p = tid; p < P; p += NT)
@@ -63,6 +145,12 @@ __global__ __launch_bounds__(NT) void zl_bounds_kernel(
     ii.segshift = tl > 6 ? (u32)(tl - 6) : 0u;        // top >> segshift < SEGS
     const u64 W = 1ull << ii.segshift;
     const int nseg = (int)(top >> ii.segshift) + 1;
+    u64 end = ii.range;                               // the last value that is searched
+    if (cut && P <= CUT_ROWS && ii.flags == 0) {      // (the same in every thread)
+        const i64 last_min = block_reduce<i64, NT>(mnl, red, OpMin());
+        if (last_min >= base) end = cut_value<NT>(ends, P, ii, (u64)last_min - (u64)base, summed, row_end, (u64*)red);
+    }
+    const u64 xend = end >> ii.wshift;
     // how many entries each segment holds if every row's R entries are evenly spaced from its first to its last value
     constexpr double FIX = 65536.0;
     for (int p = tid; p < P; p += NT) {
@@ -84,38 +172,28 @@ __global__ __launch_bounds__(NT) void zl_bounds_kernel(
         }
     }
     __syncthreads();
-    if (tid < SEGS) {
-        u64 cover = 0;
-        for (int j = 0; j <= tid; ++j) cover += seg_diff[j];
-        seg_est[tid] = tid < nseg ? seg_part[tid] + cover : 0;
-    }
-    __syncthreads();
-    if (tid < SEGS) {
-        u64 total = 0;
-        for (int j = 0; j < nseg; ++j) total += seg_est[j];
+    if (tid < SEGS) {                                 // the first wave, a lane per segment
+        static_assert(SEGS == WAVE, "one segment per lane");
+        const u64 cover = wave_scan(seg_diff[tid], OpAdd());
+        const u64 est = tid < nseg ? seg_part[tid] + cover : 0;
+        const u64 total = last_lane(wave_scan(est, OpAdd()));
         // an eighth of the bins is spread evenly, in case the rows are far from evenly spaced
         const u64 even = total / (8ull * (u64)nseg) + 1;
         const u64 total2 = total + even * (u64)nseg;
         u32 slope = 0;
         if (tid < nseg) {
             const u64 len = tid == nseg - 1 ? top - ((u64)tid << ii.segshift) + 1 : W;       // values of the segment in use
-            slope = seg_slope_of(seg_est[tid], even, total2, bins, len);
+            slope = seg_slope_of(est, even, total2, bins, len);
         }
-        seg_step[tid] = W * (u64)slope;
-        seg_slope[tid] = slope;
-    }
-    __syncthreads();
-    if (tid < SEGS) {
-        const u32 slope = seg_slope[tid];
-        u64 G = 0;
-        for (int j = 0; j < tid; ++j) G += seg_step[j];
+        const u64 seg_step = W * (u64)slope;
+        const u64 G = wave_scan(seg_step, OpAdd()) - seg_step;
         SegEntry e;
         e.G = G;
         e.slope = slope;
         e.pad_ = 0;
         segtab[b * (i64)SEGS + tid] = e;
-        if (tid == nseg - 1) {
-            ii.nb = (u32)((G + (top - ((u64)tid << ii.segshift)) * (u64)slope) >> 32) + 1u;
+        if (tid == (int)(xend >> ii.segshift)) {          // (the last segment unless later values cannot win)
+            ii.nb = (u32)((G + (xend - ((u64)tid << ii.segshift)) * (u64)slope) >> 32) + 1u;
             info[b] = ii;
             if (status) status[b] = (int)ii.flags;
         }
@@ -138,6 +216,7 @@ __device__ __forceinline__ void partition_row(const i64* __restrict__ row, int R
     int carry = -1;                        // bin of the element before lane 0's
     i64 carry_t = INT64_MIN;               // and its value
     bool bad = false;
+    const int nb = (int)ii.nb;
     const bool wide = (ii.range >> 32) != 0;          // only then can two neighbours be 2^32 or more apart
     int farbin = 0;                                   // the window kernels hold deltas in 32 bits: the bin such a
     u32 far = 0;                                      // step ends in is remembered (this lane's last one, and how many)
@@ -153,21 +232,22 @@ __device__ __forceinline__ void partition_row(const i64* __restrict__ row, int R
             const u32 i = i0 + (u32)(u * WAVE + lane);
             if (i0 + (u32)(u * WAVE) < (u32)R) {      // (the same in every lane)
                 const i64 t = tv[u];
-                int bin = -1;
-                if (i < (u32)R) bin = (int)fine_bin((u64)t - base, ii, tab);
                 // the neighbour's bin and value by a lane shift inside the vector ALU (lane 0: what the wave saw last)
-                const int pb = dpp_take<DPP_WAVE_SHR1, 0xf>(carry, bin);
                 const i64 pt = dpp_take<DPP_WAVE_SHR1, 0xf>(carry_t, t);
                 bad |= t < pt;
-                if (wide && i > 0 && i < (u32)R && (((u64)t - (u64)pt) >> 32) != 0) { farbin = bin; ++far; }
+                carry_t = (i64)((u64)(u32)__builtin_amdgcn_readlane((int)(u32)(u64)t, WAVE - 1) |
+                                ((u64)(u32)__builtin_amdgcn_readlane((int)(u32)((u64)t >> 32), WAVE - 1) << 32));
+                if (carry >= nb) continue;            // behind the bins that are searched: the order is all there is to check
+                int bin = -1;
+                if (i < (u32)R) bin = (int)fine_bin_or_nb((u64)t - base, ii, tab);
+                const int pb = dpp_take<DPP_WAVE_SHR1, 0xf>(carry, bin);
+                if (wide && bin < nb && i > 0 && i < (u32)R && (((u64)t - (u64)pt) >> 32) != 0) { farbin = bin; ++far; }
                 if (i < (u32)R)
                     for (int k = pb + 1; k <= bin; ++k) {
                         out[k] = (CT)i;
                         if (SUMS) atomicAdd(&sums[k], i);
                     }
                 carry = __builtin_amdgcn_readlane(bin, WAVE - 1);
-                carry_t = (i64)((u64)(u32)__builtin_amdgcn_readlane((int)(u32)(u64)t, WAVE - 1) |
-                                ((u64)(u32)__builtin_amdgcn_readlane((int)(u32)((u64)t >> 32), WAVE - 1) << 32));
             }
         }
     }
@@ -176,8 +256,8 @@ __device__ __forceinline__ void partition_row(const i64* __restrict__ row, int R
         const u32 slot = atomicAdd(&info[b].wide_steps, far == 1 ? 1u : WIDE_MARKS + 1u);
         if (far == 1 && slot < WIDE_MARKS) widebin[b * (i64)WIDE_MARKS + slot] = (u32)farbin;
     }
-    const int last_bin = (int)fine_bin((u64)row[R - 1] - base, ii, tab);
-    for (int k = last_bin + 1 + lane; k <= (int)ii.nb; k += WAVE) {
+    const int last_bin = (int)fine_bin_or_nb((u64)row[R - 1] - base, ii, tab);
+    for (int k = last_bin + 1 + lane; k <= nb; k += WAVE) {
         out[k] = (CT)R;
         if (SUMS) atomicAdd(&sums[k], (u32)R);
     }
@@ -268,11 +348,12 @@ __global__ __launch_bounds__(256) void zl_partition_pred_kernel(
     __syncthreads();
     if (k > (int)ii.nb) return;
     const bool broken = (ii.flags & EBSP_STATUS_UNSORTED) != 0;      // a negative interval: indices stay zero
-    // bin nb and beyond (the row's padding): everything lies below
+    // beyond bin nb (the row's padding), and at nb unless values behind it are left out: everything lies below
+    const u32 all_from = fine_bin_or_nb(ii.range, ii, segtab + b * (i64)SEGS) < ii.nb ? ii.nb : ii.nb + 1;
     u64 edge[KPT];
 #pragma unroll
     for (int j = 0; j < KPT; ++j)
-        edge[j] = k + j >= (int)ii.nb ? U64_MAX : fine_bin_start((u32)(k + j), ii, segtab + b * (i64)SEGS);
+        edge[j] = (u32)(k + j) >= all_from ? U64_MAX : fine_bin_start((u32)(k + j), ii, segtab + b * (i64)SEGS);
     CT* __restrict__ out = cross + (b * (i64)P) * stride + k;
     const bool narrow_values = (ii.range >> 32) == 0;
     u32 sum[KPT] = {};
@@ -401,7 +482,7 @@ __global__ __launch_bounds__(NT) void zl_plan_kernel(
         __syncthreads();                                  // (the first time round also: tab is there)
         if (wide) {
             for (int i = tid; i <= cnt; i += NT)
-                vstart[i] = k0 + i < nb ? fine_bin_start((u32)(k0 + i), ii, tab) : ii.range + 1;
+                vstart[i] = k0 + i < nb ? fine_bin_start((u32)(k0 + i), ii, tab) : searched_end(ii, tab) + 1;
             __syncthreads();
         }
         int s0 = 0;
@@ -471,7 +552,7 @@ __global__ __launch_bounds__(NT) void zl_plan_kernel(
     const u32 nwin = found_all;
     for (u32 j = tid; j < nwin; j += NT) {
         const u64 first = fine_bin_start(ws[j], ii, tab);
-        const u64 last = j + 1 < nwin ? fine_bin_start(ws[j + 1], ii, tab) - 1 : ii.range;
+        const u64 last = j + 1 < nwin ? fine_bin_start(ws[j + 1], ii, tab) - 1 : searched_end(ii, tab);
         const u64 span = last - first;
         const u32 scale = linear_scale(span <= 0xffffffffull ? span : 0xffffffffull, buckets);
         WinVal v;

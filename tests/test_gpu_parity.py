@@ -471,3 +471,43 @@ def test_small_instances_at_the_edges_of_the_one_launch_search(zl, oracle, P, R,
     ob, oi, ow, rc, _ = oracle.zipline(ts, "sweep", threads=16)
     assert (rc == 0).all() and (st == 0).all()
     assert np.array_equal(bar, ob) and np.array_equal(w, ow) and np.array_equal(it, oi)
+
+
+@pytest.mark.parametrize("P,R", [(16, 4096), (300, 220), (1, 70000), (40, 1700)])
+@pytest.mark.parametrize("scale", [1, 1 << 14])
+def test_values_behind_which_nothing_can_win_are_left_out(zl, oracle, P, R, scale):
+    """Batches of enough windows for zl_bounds to end the fine bins where no later value can be the minimum: rows that
+    end early and late, all together, before the last worker's first entry, and rows that jump; every objective that
+    cuts windows, stored and predicted rows (scale: values of more than 32 bits)."""
+    rng = np.random.default_rng(P * R + scale)
+    B = 12
+    mean = rng.integers(20, 400, size=(B, P, 1))
+    d = np.maximum(1, (mean * rng.lognormal(0, 0.3, size=(B, P, R))).astype(np.int64)) * 100
+    d[1] = 1000                                                        # identical workers
+    d[2, :, : R // 2] = 1                                              # rows far from evenly spaced
+    d[3, :, R // 2:] *= 50
+    off = rng.integers(0, 2000, size=(B, P, 1))
+    off[4, P - 1] += int(d[4, :, :].sum(axis=1).max()) + 12345         # the last worker starts when the others are through
+    off[5, P // 2] += int(d[5, :, :].sum(axis=1).min()) // 2
+    ts = (np.cumsum(d, axis=2) + off) * scale
+    iv = mean[:, :, 0].astype(np.int64) * 100 * scale
+    iv[1] = 5
+    le = off[:, :, 0].astype(np.int64) * scale
+    zl.ebsp_zipline_tune(4096, 1024, 512)
+    try:
+        bar, it, w, st = gpu_run(zl, ts)
+        rb, ri, rd, rs = [x.cpu().numpy() for x in zl.ebsp_zipline_range_batch(torch.from_numpy(ts).cuda())]
+        pb, pi, pw, ps = [x.cpu().numpy() for x in
+                          zl.ebsp_predict_zipline_batch(torch.from_numpy(le).cuda(), torch.from_numpy(iv).cuda(), R)]
+        bad = ts.copy()
+        bad[0, 0, R - 2:] = bad[0, 0, R - 2:][::-1]                     # out of order behind everything that is searched
+        flagged = gpu_run(zl, bad)[3]
+    finally:
+        zl.ebsp_zipline_tune(0, 0, 0)
+    assert (st == 0).all() and (rs == 0).all() and (ps == 0).all() and flagged[0] == 1 and (flagged[1:] == 0).all()
+    ob, oi, ow, rc, _ = oracle.zipline(ts, "sweep", threads=16)
+    assert (rc == 0).all() and np.array_equal(bar, ob) and np.array_equal(w, ow) and np.array_equal(it, oi)
+    ob, oi, od, rc, _ = oracle.zipline_range(ts, "sweep", threads=16)
+    assert (rc == 0).all() and np.array_equal(rb, ob) and np.array_equal(rd, od) and np.array_equal(ri, oi)
+    ob, oi, ow, rc, _ = oracle.zipline(oracle.predicted_rows(le, iv, R), "sweep", threads=16)
+    assert (rc == 0).all() and np.array_equal(pb, ob) and np.array_equal(pw, ow) and np.array_equal(pi, oi)
