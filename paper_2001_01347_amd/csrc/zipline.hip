@@ -446,23 +446,29 @@ int run_batch(const i64* ts, const i64* le, const i64* iv, i64 B, int P, int R,
     if (pblocks * B > 0x7fffffffll) return fail(EBSP_ERR_SHAPE, "batch too large for one call");
     if (int rc = check_device()) return rc;
     if (int rc = plan_windows(pl, ts, le, iv, B, P, R, wsp, status, true, st)) return rc;
-    const u32 groups = (u32)(pl.max_win / WINDOWS_PER_BLOCK);
+    // Batches whose windows are all on the chip at once (two workgroups per CU; max_win is about twice the windows
+    // there are) are as fast as one workgroup: a window each instead of two.
+    const bool one_each = pl.narrow && total_win <= 4 * GENERAL_GRID;
+    const u32 groups = (u32)(one_each ? pl.max_win : pl.max_win / WINDOWS_PER_BLOCK);
     const u32 groups_inv = groups > 1 ? (u32)((1ull << 32) / groups) : 0xffffffffu;
     const unsigned wgrid = (unsigned)((B * (i64)groups + 7) / 8 * 8);
-#define LAUNCH_WINDOW(NT_, CT_)                                                                              \
+#define LAUNCH_WINDOW(NT_, CT_, W_)                                                                          \
     do {                                                                                                     \
-        if (pred) LAUNCH(K_WINDOW, (zl_window_kernel<NT_, 16, CT_, true>), dim3(wgrid), dim3(NT_), ts, rowpar, B, P, R, info, \
+        if (pred) LAUNCH(K_WINDOW, (zl_window_kernel<NT_, 16, CT_, true, W_>), dim3(wgrid), dim3(NT_), ts, rowpar, B, P, R, info, \
                          (const CT_*)cross, pl.stride, winstart, winval, pl.max_win, groups, groups_inv, partial); \
-        else LAUNCH(K_WINDOW, (zl_window_kernel<NT_, 16, CT_, false>), dim3(wgrid), dim3(NT_), ts, rowpar, B, P, R, info, \
+        else LAUNCH(K_WINDOW, (zl_window_kernel<NT_, 16, CT_, false, W_>), dim3(wgrid), dim3(NT_), ts, rowpar, B, P, R, info, \
                     (const CT_*)cross, pl.stride, winstart, winval, pl.max_win, groups, groups_inv, partial);  \
     } while (0)
-    if (pl.cap == 16384) {
-        if (pl.narrow) LAUNCH_WINDOW(1024, unsigned short); else LAUNCH_WINDOW(1024, u32);
-    } else if (pl.cap == 8192) {
-        if (pl.narrow) LAUNCH_WINDOW(512, unsigned short); else LAUNCH_WINDOW(512, u32);
-    } else {
-        if (pl.narrow) LAUNCH_WINDOW(256, unsigned short); else LAUNCH_WINDOW(256, u32);
-    }
+#define LAUNCH_WINDOWS(NT_)                                                                                  \
+    do {                                                                                                     \
+        if (one_each) LAUNCH_WINDOW(NT_, unsigned short, 1);                                                 \
+        else if (pl.narrow) LAUNCH_WINDOW(NT_, unsigned short, WINDOWS_PER_BLOCK);                           \
+        else LAUNCH_WINDOW(NT_, u32, WINDOWS_PER_BLOCK);                                                     \
+    } while (0)
+    if (pl.cap == 16384) LAUNCH_WINDOWS(1024);
+    else if (pl.cap == 8192) LAUNCH_WINDOWS(512);
+    else LAUNCH_WINDOWS(256);
+#undef LAUNCH_WINDOWS
 #undef LAUNCH_WINDOW
     if (pl.cap <= 4096)       // such windows fit a 512-thread workgroup's general search: two workgroups per CU
         LAUNCH(K_WINDOW_GENERAL, (zl_window_general_kernel<512, 16>),

@@ -130,13 +130,13 @@ struct SumSearch {
     }
 };
 
-// One workgroup per WINDOWS_PER_BLOCK consecutive windows of an instance; each
+// One workgroup per W consecutive windows of an instance; each
 // window's best candidate goes to `partial`.  Handles the normal case (32-bit
 // value spread, the window fits in LDS) and marks every other window as deferred
 // to the general kernel.  A window's upper crossings are the next window's lower
 // ones, and those of the window after are fetched while the current one is
 // being searched.  `Search` does one window.
-template <int NT, int ITEMS, class CT, class Search>
+template <int NT, int ITEMS, class CT, class Search, int W = WINDOWS_PER_BLOCK>
 __device__ __forceinline__ void window_pairs(
     const Smem& sm, const i64* __restrict__ ts, const uint2* __restrict__ rowpar, i64 B, int P, int R,
     const InstInfo* __restrict__ info, const CT* __restrict__ cross, int stride,
@@ -154,13 +154,12 @@ __device__ __forceinline__ void window_pairs(
     u32 group = slot - b * groups;
     if (group >= groups) { ++b; group -= groups; }
     if ((i64)b >= B) return;
-    const int j0 = (int)group * WINDOWS_PER_BLOCK;
+    const int j0 = (int)group * W;
     const u32* ws = winstart + b * (i64)(max_win + 1);       // max_win + 1 entries
     const WinVal* wv = winval + b * (i64)max_win;
     // fine bins where the windows start and end and the windows' values: asked for together
     // with the instance's facts, before anything depends on those (j0 + W <= max_win, so the
     // addresses are valid even where the instance has fewer windows)
-    constexpr int W = WINDOWS_PER_BLOCK;
     u32 bins[W + 1];
     WinVal vals[W];
 #pragma unroll
@@ -168,7 +167,7 @@ __device__ __forceinline__ void window_pairs(
 #pragma unroll
     for (int i = 0; i < W; ++i) vals[i] = wv[j0 + i];
     const InstInfo ii = info[b];
-    const int jend = j0 + WINDOWS_PER_BLOCK < (int)ii.nwin ? j0 + WINDOWS_PER_BLOCK : (int)ii.nwin;
+    const int jend = j0 + W < (int)ii.nwin ? j0 + W : (int)ii.nwin;
     if (j0 >= jend) return;
     Partial* out = partial + b * (i64)max_win;
     // The fast search holds keys relative to its window and deltas between neighbours in 32 bits.  That
@@ -207,7 +206,7 @@ __device__ __forceinline__ void window_pairs(
     }
 }
 
-template <int NT, int ITEMS, class CT, bool PRED>
+template <int NT, int ITEMS, class CT, bool PRED, int W = WINDOWS_PER_BLOCK>
 __global__ __launch_bounds__(NT, (!PRED && NT == 256 ? 5 : 4)) void zl_window_kernel(
     const i64* __restrict__ ts, const uint2* __restrict__ rowpar, i64 B, int P, int R,
     const InstInfo* __restrict__ info, const CT* __restrict__ cross, int stride,
@@ -217,7 +216,7 @@ __global__ __launch_bounds__(NT, (!PRED && NT == 256 ? 5 : 4)) void zl_window_ke
     using L = WinHot<NT, ITEMS, PRED>;
     __shared__ __align__(16) unsigned char smem[L::BYTES];
     const Smem sm = L::carve(smem);
-    window_pairs<NT, ITEMS, CT, SumSearch<NT, ITEMS, CT, PRED>>(sm, ts, rowpar, B, P, R, info, cross, stride, winstart,
+    window_pairs<NT, ITEMS, CT, SumSearch<NT, ITEMS, CT, PRED>, W>(sm, ts, rowpar, B, P, R, info, cross, stride, winstart,
                                                                winval, max_win, groups, groups_inv, partial);
 }
 
