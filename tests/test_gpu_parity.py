@@ -511,3 +511,27 @@ def test_values_behind_which_nothing_can_win_are_left_out(zl, oracle, P, R, scal
     assert (rc == 0).all() and np.array_equal(rb, ob) and np.array_equal(rd, od) and np.array_equal(ri, oi)
     ob, oi, ow, rc, _ = oracle.zipline(oracle.predicted_rows(le, iv, R), "sweep", threads=16)
     assert (rc == 0).all() and np.array_equal(pb, ob) and np.array_equal(pw, ow) and np.array_equal(pi, oi)
+
+
+@pytest.mark.parametrize("P,R", [(40, 26), (2, 1000), (1, 2049), (1025, 2), (64, 64), (61, 241), (128, 128), (3, 5461)])
+def test_single_workgroup_instances_of_wide_spread(zl, oracle, P, R):
+    """Values spread over 2^32 and more: the bucket search of whole values, and what it leaves to the sort (few distinct
+    values, rows in clusters, spreads whose sums need more than its words hold, rows out of order)."""
+    rng = np.random.default_rng(P * R)
+    B = 7
+    d = rng.integers(1, 2000, size=(B, P, R), dtype=np.int64) * 1_000_003
+    d[1] = (1 << 40) // R + 1                                           # every worker alike
+    d[2, :, 1:] = 1
+    d[2, 0, -1] += 1 << 41                                              # a cluster and one value far away
+    d[3] *= max(1, (1 << 46) // (P * int(d[3].sum(axis=1).max())) + 1)  # around the largest spread the words take
+    d[4, :, 0] += rng.integers(0, 1 << 36, size=P)
+    ts = np.cumsum(d, axis=2) + 1_700_000_000_000_000_000
+    ts[5] = ts[5] // (1 << 30) * (1 << 30)                              # ties
+    bar, it, w, st = gpu_run(zl, ts)
+    ob, oi, ow, rc, _ = oracle.zipline(ts, "sweep", threads=16)
+    assert (rc == 0).all() and (st == 0).all()
+    assert np.array_equal(bar, ob) and np.array_equal(w, ow) and np.array_equal(it, oi)
+    if R > 1:
+        ts[6, P // 2, -2:] = ts[6, P // 2, -2:][::-1].copy()
+        st = gpu_run(zl, ts)[3]
+        assert st[6] == 1 and (st[:6] == 0).all()
