@@ -480,7 +480,7 @@ def test_values_behind_which_nothing_can_win_are_left_out(zl, oracle, P, R, scal
     end early and late, all together, before the last worker's first entry, and rows that jump; every objective that
     cuts windows, stored and predicted rows (scale: values of more than 32 bits)."""
     rng = np.random.default_rng(P * R + scale)
-    B = 12
+    B = 72                                                             # more than 16384 windows of 512 entries at most
     mean = rng.integers(20, 400, size=(B, P, 1))
     d = np.maximum(1, (mean * rng.lognormal(0, 0.3, size=(B, P, R))).astype(np.int64)) * 100
     d[1] = 1000                                                        # identical workers
