@@ -64,9 +64,11 @@ int ebsp_zipline_tune_sweep(int32_t sweep_min, int32_t slice_keys, int32_t lines
  * Per-kernel timing for benchmarks.  Between ebsp_zipline_profile_begin() and
  * ebsp_zipline_profile_end() every search call made by the calling thread
  * (any of the batch entry points; every superstep of ebsp_simulate_supersteps
- * counts as a call of its own) records a pair of HIP events around each kernel
- * it launches, on the call's own stream, without synchronising (events are
- * created up front, for at most max_calls calls; further calls run untimed).
+ * counts as a call of its own, also where one kernel takes a run of them whole)
+ * records a pair of HIP events around each kernel it launches, on the call's own
+ * stream, without synchronising (events are created up front, for at most
+ * max_calls calls; further calls run untimed, and of a kernel whose run of
+ * supersteps passes max_calls only the part up to there is counted).
  * Do not capture a stream into a HIP graph while a profile is open.
  * ebsp_zipline_profile_end() synchronises the device, writes to kernel_ms
  * (HOST array of ebsp_zipline_kernel_count() floats, may be NULL) the summed

@@ -219,8 +219,19 @@ struct Profile {
     int max_calls = 0, calls = 0;
     hipEvent_t* ev = nullptr;      // [max_calls][K_COUNT][2]
     bool* used = nullptr;          // [max_calls][K_COUNT]
+    float* share = nullptr;        // [max_calls]: what part of the durations recorded there the profile counts
 };
 thread_local Profile g_prof;
+
+// The launches since the last count stood for n calls (the supersteps of a run that one launch takes whole).  Their
+// durations are recorded with the first of them; of a run that passes max_calls the supersteps up to there count.
+void prof_count(i64 n = 1)
+{
+    if (!g_prof.on || g_prof.calls >= g_prof.max_calls) return;
+    const i64 left = g_prof.max_calls - g_prof.calls;
+    g_prof.share[g_prof.calls] = n <= left ? 1.f : (float)left / (float)n;
+    g_prof.calls += (int)(n <= left ? n : left);
+}
 
 hipEvent_t* prof_slot(int kid, int which)
 {
@@ -611,7 +622,7 @@ int ebsp_zipline_batch_static(const int64_t* ts, int64_t B, int32_t P, int32_t R
         if (int rc = static_scratch(&ptr)) return rc;
     const int rc = run_batch((const i64*)ts, nullptr, nullptr, B, P, R, (i64*)barrier, iters, (i64*)wait, status,
                              ptr, (size_t)EBSP_STATIC_SCRATCH_BYTES, (hipStream_t)stream);
-    if (g_prof.on && rc == EBSP_OK && B > 0 && g_prof.calls < g_prof.max_calls) ++g_prof.calls;
+    if (rc == EBSP_OK && B > 0) prof_count();
     return rc;
 }
 
@@ -637,7 +648,7 @@ int ebsp_zipline_batch(const int64_t* ts, int64_t B, int32_t P, int32_t R,
     if (!ts && B > 0) return fail(EBSP_ERR_NULL, "ts must not be NULL");
     const int rc = run_batch((const i64*)ts, nullptr, nullptr, B, P, R, (i64*)barrier, iters, (i64*)wait, status,
                              workspace, workspace_bytes, (hipStream_t)stream);
-    if (g_prof.on && rc == EBSP_OK && B > 0 && g_prof.calls < g_prof.max_calls) ++g_prof.calls;
+    if (rc == EBSP_OK && B > 0) prof_count();
     return rc;
 }
 
@@ -648,7 +659,7 @@ int ebsp_predict_zipline_batch(const int64_t* last_end, const int64_t* interval,
     if ((!last_end || !interval) && B > 0) return fail(EBSP_ERR_NULL, "last_end and interval must not be NULL");
     const int rc = run_batch(nullptr, (const i64*)last_end, (const i64*)interval, B, P, R, (i64*)barrier, iters,
                              (i64*)wait, status, workspace, workspace_bytes, (hipStream_t)stream);
-    if (g_prof.on && rc == EBSP_OK && B > 0 && g_prof.calls < g_prof.max_calls) ++g_prof.calls;
+    if (rc == EBSP_OK && B > 0) prof_count();
     return rc;
 }
 
@@ -682,7 +693,7 @@ int ebsp_simulate_supersteps(const int64_t* last_end0, const int64_t* interval, 
         if (int rc = check_device()) return rc;
         if (int rc = launch_run(nullptr, (const i64*)last_end0, (const i64*)interval, (i64)sync_cost, S, B, P, R, (i64*)barrier,
                                 iters, (i64*)wait, status, st)) return rc;
-        if (g_prof.on && g_prof.calls < g_prof.max_calls) ++g_prof.calls;
+        prof_count(S);
         return EBSP_OK;
     }
     for (i64 s = 0; s < S; ++s) {
@@ -694,7 +705,7 @@ int ebsp_simulate_supersteps(const int64_t* last_end0, const int64_t* interval, 
         if (s + 1 < S)       // the workers' start times of the next superstep (after the last one barrier[S-1] says it all)
             LAUNCH(K_ADVANCE, zl_advance_kernel, dim3((unsigned)((per + 255) / 256)), dim3(256),
                    (const i64*)barrier + s * B, (const int*)flags, from, start, (i64)sync_cost, B, P);
-        if (g_prof.on && g_prof.calls < g_prof.max_calls) ++g_prof.calls;
+        prof_count();
     }
     return EBSP_OK;
 }
@@ -733,7 +744,7 @@ int ebsp_gridscan_batch(const int64_t* ts, int64_t B, int32_t P, int32_t R, int3
         LAUNCH(K_GRIDSCAN, zl_gridscan_long_kernel, dim3((unsigned)blocks), dim3(GRID_NT), (const i64*)ts, P, R, full ? 1 : 0, best, status);
     LAUNCH(K_GRIDSCAN_FINISH, zl_gridscan_finish_kernel, dim3((unsigned)B), dim3(GRID_NT), (const i64*)ts, P, R, (int)pieces,
            (const GridBest*)best, (i64*)barrier, iters, (i64*)dz);
-    if (g_prof.on && g_prof.calls < g_prof.max_calls) ++g_prof.calls;
+    prof_count();
     return EBSP_OK;
 }
 
@@ -750,7 +761,7 @@ int ebsp_zipline_range_batch(const int64_t* ts, int64_t B, int32_t P, int32_t R,
 {
     const int rc = run_range_batch((const i64*)ts, B, P, R, (i64*)barrier, iters, (i64*)dmin, status,
                                    workspace, workspace_bytes, (hipStream_t)stream);
-    if (g_prof.on && rc == EBSP_OK && B > 0 && g_prof.calls < g_prof.max_calls) ++g_prof.calls;
+    if (rc == EBSP_OK && B > 0) prof_count();
     return rc;
 }
 
@@ -804,7 +815,7 @@ int ebsp_zipline_copy_probe(const void* src, void* dst, size_t bytes, void* stre
     i64 blocks = (n + 2047) / 2048;                     // pieces of 32 KiB or more
     if (blocks > 256 * 256) blocks = 256 * 256;
     LAUNCH(K_COPY, zl_copy_kernel, dim3((unsigned)blocks), dim3(256), (const uint4*)src, (uint4*)dst, n);
-    if (g_prof.on && g_prof.calls < g_prof.max_calls) ++g_prof.calls;
+    prof_count();
     return EBSP_OK;
 }
 
@@ -821,7 +832,7 @@ int ebsp_zipline_read_probe(const void* src, size_t bytes, uint64_t* sink, void*
     i64 blocks = (n + 2047) / 2048;                     // pieces of 32 KiB or more
     if (blocks > 256 * 256) blocks = 256 * 256;
     LAUNCH(K_READ, zl_read_kernel, dim3((unsigned)blocks), dim3(256), (const uint4*)src, n, (u64*)sink);
-    if (g_prof.on && g_prof.calls < g_prof.max_calls) ++g_prof.calls;
+    prof_count();
     return EBSP_OK;
 }
 
@@ -845,10 +856,11 @@ int ebsp_zipline_profile_begin(int32_t max_calls)
     const size_t n = (size_t)max_calls * K_COUNT;
     g_prof.ev = new hipEvent_t[2 * n];
     g_prof.used = new bool[n]();
+    g_prof.share = new float[max_calls]();
     for (size_t i = 0; i < 2 * n; ++i)
         if (hipEventCreate(&g_prof.ev[i]) != hipSuccess) {
             for (size_t k = 0; k < i; ++k) (void)hipEventDestroy(g_prof.ev[k]);
-            delete[] g_prof.ev; delete[] g_prof.used;
+            delete[] g_prof.ev; delete[] g_prof.used; delete[] g_prof.share;
             g_prof = Profile();
             return fail(EBSP_ERR_LAUNCH, "hipEventCreate failed");
         }
@@ -871,12 +883,13 @@ int ebsp_zipline_profile_end(float* kernel_ms, int32_t* calls)
                 if (g_prof.used[c * K_COUNT + k]) {
                     float ms = 0.f;
                     const size_t i = ((size_t)c * K_COUNT + k) * 2;
-                    if (hipEventElapsedTime(&ms, g_prof.ev[i], g_prof.ev[i + 1]) == hipSuccess) kernel_ms[k] += ms;
+                    if (hipEventElapsedTime(&ms, g_prof.ev[i], g_prof.ev[i + 1]) == hipSuccess) kernel_ms[k] += ms * g_prof.share[c];
                 }
     if (calls) *calls = g_prof.calls;
     for (size_t i = 0; i < 2 * n; ++i) (void)hipEventDestroy(g_prof.ev[i]);
     delete[] g_prof.ev;
     delete[] g_prof.used;
+    delete[] g_prof.share;
     g_prof = Profile();
     return rc;
 }

@@ -248,3 +248,21 @@ def test_a_run_in_one_launch_keeps_the_starts_of_flagged_instances(zl, oracle):
     start = np.full((1, 8), first[0][0] + 3, dtype=np.int64)
     last = oracle.zipline(oracle.predicted_rows(start, bad[3, 1:2], 20))
     assert bar[3, 1] == last[0][0] and w[3, 1] == last[2][0]
+
+
+@pytest.mark.parametrize("P,R,B,kernel", [(16, 60, 3, "zl_run_kernel"), (100, 150, 2, "zl_instance_reg_kernel")])
+def test_a_profile_counts_every_superstep_as_a_call(zl, P, R, B, kernel):
+    # runs that one launch takes whole, and runs of a launch per superstep; the second run passes max_calls
+    rng = np.random.default_rng(P)
+    iv = torch.from_numpy(rng.integers(80, 120, size=(5, B, P))).cuda()
+    le = torch.from_numpy(rng.integers(0, 80, size=(B, P))).cuda()
+    counts, ms = [], []
+    for max_calls, runs in ((10, 1), (10, 2), (7, 2), (3, 1)):
+        zl.ebsp_zipline_profile_begin(max_calls)
+        for _ in range(runs):
+            zl.ebsp_simulate_supersteps(le, iv, R, 3)
+        spent, calls = zl.ebsp_zipline_profile_end()
+        counts.append(calls)
+        ms.append(spent[kernel])
+    assert counts == [5, 10, 7, 3]
+    assert all(m > 0.0 for m in ms)
