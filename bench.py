@@ -75,13 +75,18 @@ def kernel_sources_sha256() -> str:
     return h.hexdigest()
 
 
-def algorithmic_bytes(kernel: str, B: int, P: int, R: int, bins: int, windows: int, predicted: bool = False) -> float:
-    """Bytes a kernel must move per launch (inputs it has to read once + what it has to write)."""
+def algorithmic_bytes(kernel: str, B: int, P: int, R: int, bins: int, windows: int, predicted: bool = False,
+                      supersteps: int = 0) -> float:
+    """Bytes a kernel must move per search (inputs it has to read once + what it has to write)."""
     n = float(B) * P * R
     cw = 2.0 if R < 65536 else 4.0          # bytes of one crossing index
     rows = 16.0 * B * P if predicted else 8.0 * n       # predicted rows: 16 bytes per worker stand for R timestamps
     if kernel in ("zl_instance_kernel", "zl_instance_reg_kernel"):      # every timestamp once, all three outputs
         return rows + B * (16.0 + 4.0 * P)
+    if kernel == "zl_run_kernel":           # the same; of a run's rows the start times once and every superstep's intervals
+        return (8.0 * B * P * (1.0 + 1.0 / supersteps) if supersteps else rows) + B * (16.0 + 4.0 * P)
+    if kernel == "zl_advance_kernel":       # the barriers, every worker's next start time
+        return 8.0 * B + 8.0 * B * P
     if kernel == "zl_window_kernel":        # every timestamp once, two crossing rows per window, one result
         return rows + windows * (2.0 * cw * P + 16.0)
     groups = (P + 63) // 64 if predicted else (P + 15) // 16    # rows of partial column sums per instance (stored rows: when the bins fit LDS)
@@ -109,7 +114,9 @@ def algorithmic_bytes(kernel: str, B: int, P: int, R: int, bins: int, windows: i
         import math                         # (predicted rows: nothing is probed), outputs
         probes = 0.0 if predicted else 64.0 * 3.0
         return 16.0 * windows + B * P * (probes + 4.0) + 16.0 * B
-    return 0.0
+    if kernel in ("zl_window_general_kernel", "zl_instance_general_kernel"):    # next to nothing where nothing is left to them
+        return 0.0
+    raise ValueError(f"no byte model for {kernel}")
 
 
 # Table II of the paper (run time in microseconds on its 24-core Xeon server, mean of 10 trials): context only.
@@ -365,14 +372,14 @@ def main() -> int:
     if "zl_sweep_kernel" in per_kernel:     # the frontier sweep: one partial result per slice, no windows
         windows = B * shape["slices"]
     dom = max(per_kernel, key=per_kernel.get)
-    dom_bytes = algorithmic_bytes(dom, B, P, R, bins, windows, args.predicted)
+    dom_bytes = algorithmic_bytes(dom, B, P, R, bins, windows, args.predicted, S)
     achieved = dom_bytes / (per_kernel[dom] * 1e-3) / 1e9
     counted = COUNTED_TRAFFIC.get((args.objective, bool(args.predicted), args.config))
     tuned = bool(args.window_cap or args.single_max or args.window_fill or args.sweep_min or args.slice_keys or args.sweep_lines)
     traffic = call_traffic = None
     if counted and counted[0] == dom and not tuned and not S and kernel_sources_sha256() == COUNTED_SOURCES_SHA256:
         traffic, call_traffic = float(counted[1]), float(counted[2])
-    total_bytes = searches * sum(algorithmic_bytes(k, B, P, R, bins, windows, args.predicted) for k in per_kernel)
+    total_bytes = searches * sum(algorithmic_bytes(k, B, P, R, bins, windows, args.predicted, S) for k in per_kernel)
 
     # CPU oracle on a bounded sample of the same workload (baseline, not a target)
     import oracle
