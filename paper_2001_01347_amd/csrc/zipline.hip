@@ -277,8 +277,13 @@ int plan_windows(const Plan& pl, const i64* ts, const i64* le, const i64* iv, i6
     const i64 widest = pl.part_stored > pl.part_pred ? pl.part_stored : pl.part_pred;
     if (kblocks * B > 0x7fffffffll || widest * B > 0x7fffffffll) return fail(EBSP_ERR_SHAPE, "batch too large for one call");
     const bool cut = B * (i64)pl.max_win > CUT_MIN_WINDOWS;
-    if (cut && P > 256)       // a thread per row: each is a chain of dependent loads there
-        LAUNCH(K_BOUNDS, (zl_bounds_kernel<1024>), dim3((unsigned)B), dim3(1024), ts, le, iv, P, R, pl.bins, info, segtab, rowpar, status, summed,
+    // With the cut a thread's rows are chains of dependent loads and the workgroup steps through reductions.  512 threads
+    // where the batch leaves CUs free anyway, fewer rows per chain; 256 beyond, more workgroups at once.  Calls with
+    // 256 / 512 / 1024 threads, us: 64 x 1024 x 4096 939 / 932 / 942, 64 x 2048 x 1161 698 / 688 / 694, 192 x 600 x 654
+    // 306 / 306 / 314, 320 x 600 x 392 349 / 351 / 362, 8000 x 300 x 60 1621 / 1629 / 1856, predicted 2542 x 378 x 239
+    // 919 / 943 / 1032 (923 without the cut) and 3619 x 401 x 60 362 / 396 / 523 (472).
+    if (cut && P > 512 && B <= GENERAL_GRID)
+        LAUNCH(K_BOUNDS, (zl_bounds_kernel<512>), dim3((unsigned)B), dim3(512), ts, le, iv, P, R, pl.bins, info, segtab, rowpar, status, summed,
                cut, (i64*)nullptr);
     else
         LAUNCH(K_BOUNDS, (zl_bounds_kernel<256>), dim3((unsigned)B), dim3(256), ts, le, iv, P, R, pl.bins, info, segtab, rowpar, status, summed,

@@ -473,7 +473,7 @@ def test_small_instances_at_the_edges_of_the_one_launch_search(zl, oracle, P, R,
     assert np.array_equal(bar, ob) and np.array_equal(w, ow) and np.array_equal(it, oi)
 
 
-@pytest.mark.parametrize("P,R", [(16, 4096), (300, 220), (1, 70000), (40, 1700)])
+@pytest.mark.parametrize("P,R", [(16, 4096), (300, 220), (1, 70000), (40, 1700), (600, 110), (2048, 33), (2049, 33)])
 @pytest.mark.parametrize("scale", [1, 1 << 14])
 def test_values_behind_which_nothing_can_win_are_left_out(zl, oracle, P, R, scale):
     """Batches of enough windows for zl_bounds to end the fine bins where no later value can be the minimum: rows that
