@@ -741,10 +741,35 @@ int ebsp_gridscan_batch(const int64_t* ts, int64_t B, int32_t P, int32_t R, int3
     i64 pieces = full ? P : 1;                       // results per instance, in (row, point) order
     if (R <= GRID_RMAX) {
         const i64 points = full ? (i64)P * R : R;
-        const i64 per = (i64)grid_point_threads(points, R) * GRID_SCAN_JPT;
-        pieces = (points + per - 1) / per;           // no more than there are designated rows: a piece has R points or more
-        LAUNCH(K_GRIDSCAN, zl_gridscan_kernel, dim3((unsigned)(B * pieces)), dim3(GRID_SCAN_NT), (const i64*)ts, P, R, full ? 1 : 0,
-               (int)pieces, best, status);
+        int least = 1024, per_thread = 4;
+        auto count = [&] {
+            const i64 per = (i64)grid_point_threads(points, R, least, per_thread) * per_thread;
+            return (points + per - 1) / per;         // no more than there are designated rows: a piece has R points or more
+        };
+        // Four consecutive points per thread, each search going on from the one before; one where the chip is not full and
+        // rows are short: a chain of one search instead of four, and no wave whose threads pass the end of a row and search
+        // anew.  Four / one, us: FullGridScan of 63 of 11 x 198 25.5 / 20.3, 2 of 233 x 119 98 / 54, 64 of 100 x 15 56 / 30;
+        // GridScan of one of 185 x 15 32.0 / 19.7, one of 1000 x 150 206 / 185, one of 1000 x 240 234 / 245.
+        if (R <= (full ? 256 : 192) && B * count() < 2 * GENERAL_GRID) per_thread = 1;
+        // Pieces of 1024 points; smaller ones, whose threads share out the rows as well, where those would leave CUs idle.
+        // FullGridScan with pieces of 1024 / 256, us: one of 497 x 113 719 / 200, one of 100 x 15 111 / 37, 8 of 46 x 61
+        // 72 / 30 (128: the same); with a workgroup on every CU, 256 of 10 x 60 in pieces of 1024 / 512, 19.4 / 21.3.
+        while (least > 256 && B * count() < GENERAL_GRID) least /= 2;
+        pieces = count();
+        // Workgroups of 1024 threads that would have no second row for a thread, and more of them than the chip takes at
+        // once: as many threads as the points need, so that more share a CU.  1024 / 256 threads, us: 16384 of 4 x 15
+        // 316 / 89, FullGridScan of them 350 / 105, 1024 of 10 x 15 27.4 / 19.7, 520 of 8 x 512 31.9 / 25.7; with more
+        // rows 520 of 100 x 15 43.8 / 54.2, FullGridScan of 520 of 16 x 60 42.9 / 50.9.
+        const int pthreads = grid_point_threads(points, R, least, per_thread);
+        const bool small = B * pieces > 2 * GENERAL_GRID && (i64)pthreads * P <= 1024;
+#define LAUNCH_GRIDSCAN(NT_, PER_)                                                                                        \
+    LAUNCH(K_GRIDSCAN, (zl_gridscan_kernel<NT_, PER_>), dim3((unsigned)(B * pieces)), dim3(NT_), (const i64*)ts, P, R,   \
+           full ? 1 : 0, (int)pieces, pthreads, best, status)
+        if (per_thread == 1) LAUNCH_GRIDSCAN(1024, 1);
+        else if (small && pthreads <= 256) LAUNCH_GRIDSCAN(256, 4);
+        else if (small && pthreads <= 512) LAUNCH_GRIDSCAN(512, 4);
+        else LAUNCH_GRIDSCAN(1024, 4);
+#undef LAUNCH_GRIDSCAN
     } else
         LAUNCH(K_GRIDSCAN, zl_gridscan_long_kernel, dim3((unsigned)blocks), dim3(GRID_NT), (const i64*)ts, P, R, full ? 1 : 0, best, status);
     LAUNCH(K_GRIDSCAN_FINISH, zl_gridscan_finish_kernel, dim3((unsigned)B), dim3(GRID_NT), (const i64*)ts, P, R, (int)pieces,

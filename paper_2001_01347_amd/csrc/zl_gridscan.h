@@ -26,17 +26,15 @@ namespace {
 constexpr int GRID_NT = 256;
 constexpr int GRID_JPT = 16;                 // designated points a thread of zl_gridscan_long_kernel handles at a time
 constexpr int GRID_RMAX = 4096;              // longest row that is staged in LDS
-constexpr int GRID_SCAN_NT = 1024;
-constexpr int GRID_SCAN_JPT = 4;             // consecutive designated points of a thread of zl_gridscan_kernel
-constexpr int GRID_STAGE = 65536;            // bytes of rows in LDS at a time: two workgroups per CU
+constexpr int GRID_STAGE_PER_THREAD = 64;    // bytes of rows in LDS at a time: as many workgroups per CU as their threads allow
 
 // How many threads of zl_gridscan_kernel share out a piece's points (a multiple of 64); the workgroup's other
 // waves take the same points against other rows.  A piece has at least R points, so that there are no more
-// pieces than designated rows, and 1024 or more where the instance has them: the rows are staged once per piece.
-__host__ __device__ inline int grid_point_threads(i64 points, int R)
+// pieces than designated rows, and `least` or more where the instance has them: the rows are staged once per piece.
+inline int grid_point_threads(i64 points, int R, int least, int per_thread)
 {
-    i64 t = points < 1024 ? points : (R > 1024 ? (i64)R : 1024);
-    t = (t + GRID_SCAN_JPT - 1) / GRID_SCAN_JPT;
+    i64 t = points < least ? points : (R > least ? (i64)R : least);
+    t = (t + per_thread - 1) / per_thread;
     return (int)((t + WAVE - 1) / WAVE * WAVE);
 }
 
@@ -195,27 +193,27 @@ __device__ __forceinline__ u32 grid_seek(const VT* row, u32 R, VT e, u32 hint)
     return lo;
 }
 
-// The points [first, first + GRID_SCAN_JPT) of the flattened designated rows `drow` against every row of the
+// The points [first, first + PER) of the flattened designated rows `drow` against every row of the
 // instance, values relative to base in VT.  Threads of the first slice end with the thread's best (d, point).
-template <class VT>
+template <int NT, int PER, class VT>
 __device__ __forceinline__ void grid_scan_points(const i64* __restrict__ inst, const i64* __restrict__ drow, u64 base, int P, int R,
                                                  u32 first, u32 points, int slice, int slices, int pthreads, int pt,
                                                  unsigned char* stage, bool check, int& bad, u64& bd, u32& bj)
 {
     VT* const staged = (VT*)stage;
     const int tid = threadIdx.x;
-    VT e[GRID_SCAN_JPT], mx[GRID_SCAN_JPT], mn[GRID_SCAN_JPT];
+    VT e[PER], mx[PER], mn[PER];
 #pragma unroll
-    for (int k = 0; k < GRID_SCAN_JPT; ++k) {
+    for (int k = 0; k < PER; ++k) {
         const u32 j = first + (u32)k < points ? first + (u32)k : points - 1;      // (beyond the end: the last point again)
         e[k] = mx[k] = mn[k] = (VT)((u64)drow[j] - base);
     }
-    const int batch = (int)(GRID_STAGE / sizeof(VT)) / R;               // rows in LDS at a time: one or more
+    const int batch = (int)(NT * GRID_STAGE_PER_THREAD / sizeof(VT)) / R;   // rows in LDS at a time: one or more (R <= 4 NT)
     for (int p0 = 0; p0 < P; p0 += batch) {
         const int rows = P - p0 < batch ? P - p0 : batch;
         const i64* __restrict__ src = inst + (size_t)p0 * R;
         __syncthreads();                                                // the rows staged before have been searched
-        for (int i = tid; i < rows * R; i += GRID_SCAN_NT) {
+        for (int i = tid; i < rows * R; i += NT) {
             const i64 v = src[i];
             staged[i] = (VT)((u64)v - base);
             if (check && i % R != 0) bad |= v < src[i - 1];
@@ -231,7 +229,7 @@ __device__ __forceinline__ void grid_scan_points(const i64* __restrict__ inst, c
                 }
                 pos = lo;
 #pragma unroll
-                for (int k = 0; k < GRID_SCAN_JPT; ++k) {
+                for (int k = 0; k < PER; ++k) {
                     if (k > 0) pos = grid_seek<VT>(row, (u32)R, e[k], pos);
                     // at a row's end both are the entry there (the designated row itself gives e)
                     const VT below = row[pos > 0 ? pos - 1 : 0], above = row[pos < (u32)R ? pos : (u32)R - 1];
@@ -242,21 +240,21 @@ __device__ __forceinline__ void grid_scan_points(const i64* __restrict__ inst, c
             }
     }
     if (slices > 1) {                                                   // the slices' max(Z) and min(Z) per point
-        VT* const top = staged;                                         // at most 2048 points each where there are slices
-        VT* const bot = staged + pthreads * GRID_SCAN_JPT;
+        VT* const top = staged;                                         // at most 2 NT points each where there are slices
+        VT* const bot = staged + pthreads * PER;
         __syncthreads();
         if (slice == 0)
-            for (int k = 0; k < GRID_SCAN_JPT; ++k) { top[k * pthreads + pt] = mx[k]; bot[k * pthreads + pt] = mn[k]; }
+            for (int k = 0; k < PER; ++k) { top[k * pthreads + pt] = mx[k]; bot[k * pthreads + pt] = mn[k]; }
         __syncthreads();
         if (slice > 0 && slice < slices)
-            for (int k = 0; k < GRID_SCAN_JPT; ++k) { atomicMax(&top[k * pthreads + pt], mx[k]); atomicMin(&bot[k * pthreads + pt], mn[k]); }
+            for (int k = 0; k < PER; ++k) { atomicMax(&top[k * pthreads + pt], mx[k]); atomicMin(&bot[k * pthreads + pt], mn[k]); }
         __syncthreads();
         if (slice == 0)
-            for (int k = 0; k < GRID_SCAN_JPT; ++k) { mx[k] = top[k * pthreads + pt]; mn[k] = bot[k * pthreads + pt]; }
+            for (int k = 0; k < PER; ++k) { mx[k] = top[k * pthreads + pt]; mn[k] = bot[k * pthreads + pt]; }
     }
     if (slice == 0)
 #pragma unroll
-        for (int k = 0; k < GRID_SCAN_JPT; ++k) {
+        for (int k = 0; k < PER; ++k) {
             const u64 d = (u64)(VT)(mx[k] - mn[k]);
             if (first + (u32)k < points && d < bd) { bd = d; bj = first + (u32)k; }
         }
@@ -264,14 +262,15 @@ __device__ __forceinline__ void grid_scan_points(const i64* __restrict__ inst, c
 
 // Bound by LDS latency and the vector ALU: P searches per designated point.  Four consecutive points per thread
 // (the next point's place in a row is a step or two further), values in 32 bits where the instance's spread allows
-// (half the LDS, half the instructions), all 1024 threads at work whatever R is, one staging per 64 KB of rows.
+// (half the LDS, half the instructions), all threads at work whatever R is, one staging per 64 bytes of rows and thread.
 // FullGridScan of 64 instances of 100 x 150: 1.04 ms with a workgroup of 256 threads per designated row, a row staged
-// at a time and every search a bisection of 64-bit values, 0.30 ms so.
-__global__ __launch_bounds__(GRID_SCAN_NT, 8) void zl_gridscan_kernel(
-    const i64* __restrict__ ts, int P, int R, int full, int pieces, GridBest* __restrict__ best, int* __restrict__ status)
+// at a time and every search a bisection of 64-bit values, 0.30 ms so (1024 threads; the other sizes: ebsp_gridscan_batch).
+template <int NT, int PER>
+__global__ __launch_bounds__(NT, 8) void zl_gridscan_kernel(
+    const i64* __restrict__ ts, int P, int R, int full, int pieces, int pthreads, GridBest* __restrict__ best, int* __restrict__ status)
 {
-    __shared__ __align__(16) unsigned char stage[GRID_STAGE];
-    constexpr int NW = GRID_SCAN_NT / WAVE;
+    __shared__ __align__(16) unsigned char stage[NT * GRID_STAGE_PER_THREAD];
+    constexpr int NW = NT / WAVE;
     __shared__ u64 red[3 * NW];
     const int tid = threadIdx.x, lane = tid & (WAVE - 1), wave = tid >> 6;
     const i64 b = blockIdx.x / (u32)pieces;
@@ -279,30 +278,29 @@ __global__ __launch_bounds__(GRID_SCAN_NT, 8) void zl_gridscan_kernel(
     const i64* __restrict__ inst = ts + b * (i64)P * R;
     i64 mn = INT64_MAX, mxf = INT64_MIN, mxl = INT64_MIN;
     u32 who = 0xffffffffu;                                      // the thread's row with the smallest first timestamp
-    for (int p = tid; p < P; p += GRID_SCAN_NT) {
+    for (int p = tid; p < P; p += NT) {
         const i64 f = inst[(size_t)p * R], l = inst[(size_t)p * R + (R - 1)];
         if (f < mn || who == 0xffffffffu) { mn = f; who = (u32)p; }   // (p grows: the first of equal values stays)
         mxl = l > mxl ? l : mxl;
     }
     const i64 my_min = mn;
     i64 base, top;
-    block_bounds<GRID_SCAN_NT>(mn, mxf, mxl, (i64*)red, base, mxf, top);
+    block_bounds<NT>(mn, mxf, mxl, (i64*)red, base, mxf, top);
     u32 pb = 0;
-    if (!full) pb = block_reduce<u32, GRID_SCAN_NT>(who != 0xffffffffu && my_min == base ? who : 0xffffffffu, (u32*)red, OpMin());
+    if (!full) pb = block_reduce<u32, NT>(who != 0xffffffffu && my_min == base ? who : 0xffffffffu, (u32*)red, OpMin());
     const u32 points = full ? (u32)(P * R) : (u32)R;
     const i64* __restrict__ drow = inst + (size_t)pb * R;
-    const int pthreads = grid_point_threads(points, R);
-    const int slices = GRID_SCAN_NT / pthreads;
+    const int slices = NT / pthreads;
     const int slice = tid / pthreads, pt = tid - slice * pthreads;
-    const u32 first = (u32)piece * (u32)(pthreads * GRID_SCAN_JPT) + (u32)(pt * GRID_SCAN_JPT);
+    const u32 first = (u32)piece * (u32)(pthreads * PER) + (u32)(pt * PER);
     const bool checker = status != nullptr && piece == 0;       // one workgroup per instance checks the rows' order
     int bad = 0;
     u64 bd = U64_MAX;
     u32 bj = 0xffffffffu;
     if ((((u64)top - (u64)base) >> 32) == 0)
-        grid_scan_points<u32>(inst, drow, (u64)base, P, R, first, points, slice, slices, pthreads, pt, stage, checker, bad, bd, bj);
+        grid_scan_points<NT, PER, u32>(inst, drow, (u64)base, P, R, first, points, slice, slices, pthreads, pt, stage, checker, bad, bd, bj);
     else
-        grid_scan_points<u64>(inst, drow, (u64)base, P, R, first, points, slice, slices, pthreads, pt, stage, checker, bad, bd, bj);
+        grid_scan_points<NT, PER, u64>(inst, drow, (u64)base, P, R, first, points, slice, slices, pthreads, pt, stage, checker, bad, bd, bj);
     // first minimum over the designated points: smaller d_Z, then the earlier point
     wave_argmin(bd, bj);
     __syncthreads();

@@ -142,3 +142,12 @@ def test_pieces_and_batches(zl, oracle, P, R, scale):
     rng = np.random.default_rng(77 * P + R)
     ts = np.stack([workloads.random_small(rng, P, R, 1, 5000, ties=(i == 0)) for i in range(3)]) * scale
     assert_same(zl, oracle, ts + EPOCH, f"P={P} R={R} scale={scale}")
+
+
+@pytest.mark.parametrize("P,R", [(1, 1), (2, 4), (4, 15), (8, 128), (9, 128), (16, 60), (4, 1024), (2, 1025), (2, 2048), (1, 2049)])
+@pytest.mark.parametrize("scale", [1, 1 << 22])
+def test_batches_of_more_workgroups_than_the_chip_takes(zl, oracle, P, R, scale):
+    """Workgroups of 256, 512 and 1024 threads, at the largest rows and points of each; values of 32 and 64 bits."""
+    rng = np.random.default_rng(91 * P + R)
+    ts = np.cumsum(rng.integers(0, 2000, size=(513, P, R)), axis=2) + rng.integers(0, 2000, size=(513, P, 1))
+    assert_same(zl, oracle, ts * scale + EPOCH, f"P={P} R={R} scale={scale}")
