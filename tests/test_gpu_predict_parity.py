@@ -106,6 +106,16 @@ def test_degenerate_and_wide_inputs(zl, oracle):
     assert_same(zl, oracle, le * 100_000_007 + EPOCH, iv * 100_000_007, 512, "wide, multi-window")
 
 
+@pytest.mark.parametrize("P,R", [(40, 26), (2, 1000), (6, 2000), (61, 241), (3, 5461)])
+def test_wide_single_workgroup_instances(zl, oracle, P, R):
+    # spreads around 2^35 in one workgroup: the bucket search of whole values, in one round and (few workers) in several
+    rng = np.random.default_rng(P * R)
+    le, iv = random_inputs(rng, 5, P, 50, 1000, False)
+    iv[3] = 777                                            # every worker alike
+    scale = (1 << 34) // (400 * R) + 7
+    assert_same(zl, oracle, le * scale + EPOCH, iv * scale, R, f"P={P} R={R}")
+
+
 def test_negative_interval_is_flagged(zl, oracle):
     for P, R in ((16, 64), (128, 512)):
         rng = np.random.default_rng(P)
