@@ -75,20 +75,65 @@ def kernel_sources_sha256() -> str:
     return h.hexdigest()
 
 
-def algorithmic_bytes(kernel: str, B: int, P: int, R: int, bins: int, windows: int, predicted: bool = False,
-                      supersteps: int = 0) -> float:
-    """Bytes a kernel must move per search (inputs it has to read once + what it has to write)."""
+# Batches of more planned windows than the first of these end the search behind the last value that can win
+# (zl_bounds_kernel), where an instance has no more rows than the second: the library's own limits.
+CUT_MIN_WINDOWS, CUT_ROWS, CUT_STEPS = 16384, 2048, 16
+
+
+def last_value_that_can_win(first, last, last_up_to, summed: bool) -> int:
+    """The value behind which zl_bounds_kernel leaves an instance's entries out, from the rows' first and last entries
+    and last_up_to(x), the last entry of every row that is at most x: some candidate at or below x waits no longer than
+    ub, and a barrier c no shorter than what the rows that have ended before it wait."""
+    x = max(int(last.min()), int(first.max()))
+    gone = x - last_up_to(x)
+    C = int(last.max())
+    if not summed:
+        return min(C, int(last.min()) + int(gone.max()))
+    ub = int(gone.sum())
+    for _ in range(CUT_STEPS):
+        ended = last[last < C]
+        over = int((C - ended).sum()) - ub
+        if over <= 0 or over < ended.size:
+            break
+        C -= over // ended.size
+    return C
+
+
+def searched_entries(rows, summed: bool) -> float:
+    """How many entries of a batch lie at or below its instances' last values that can win.  rows: [B, P, R] stored ones,
+    or (last_end, interval, R) predicted ones."""
+    import numpy as np
+    total = 0
+    if isinstance(rows, tuple):
+        le, iv, R = rows
+        for l, s in zip(le, iv):
+            upto = lambda x: np.clip((x - l) // s, 1, R)             # entries of each row up to x >= every first entry
+            total += int(upto(last_value_that_can_win(l + s, l + R * s, lambda x: l + upto(x) * s, summed)).sum())
+        return float(total)
+    for t in rows:
+        upto = lambda x: np.array([row.searchsorted(x, side="right") for row in t])
+        C = last_value_that_can_win(t[:, 0], t[:, -1], lambda x: t[np.arange(len(t)), upto(x) - 1], summed)
+        total += int(upto(C).sum())
+    return float(total)
+
+
+def algorithmic_bytes(kernel: str, B: int, P: int, R: int, bins: float, windows: float, predicted: bool = False,
+                      supersteps: int = 0, searched: float = 0.0) -> float:
+    """Bytes a kernel must move per search (inputs it has to read once + what it has to write).  bins (per instance) and
+    windows (of the batch) are those searched, `searched` the entries in them (0: all, no value is left out)."""
     n = float(B) * P * R
+    cut, entries = searched > 0.0, searched or n
     cw = 2.0 if R < 65536 else 4.0          # bytes of one crossing index
     rows = 16.0 * B * P if predicted else 8.0 * n       # predicted rows: 16 bytes per worker stand for R timestamps
+    inside = 16.0 * B * P if predicted else 8.0 * entries
     if kernel in ("zl_instance_kernel", "zl_instance_reg_kernel"):      # every timestamp once, all three outputs
         return rows + B * (16.0 + 4.0 * P)
     if kernel == "zl_run_kernel":           # the same; of a run's rows the start times once and every superstep's intervals
         return (8.0 * B * P * (1.0 + 1.0 / supersteps) if supersteps else rows) + B * (16.0 + 4.0 * P)
     if kernel == "zl_advance_kernel":       # the barriers, every worker's next start time
         return 8.0 * B + 8.0 * B * P
-    if kernel == "zl_window_kernel":        # every timestamp once, two crossing rows per window, one result
-        return rows + windows * (2.0 * cw * P + 16.0)
+    if kernel == "zl_window_kernel":        # every searched timestamp once, two crossing rows per window, one result
+        return inside + windows * (2.0 * cw * P + 16.0)
     groups = (P + 63) // 64 if predicted else (P + 15) // 16    # rows of partial column sums per instance (stored rows: when the bins fit LDS)
     if kernel == "zl_partition_kernel":     # every timestamp once, one crossing index per (row, bin), partial column sums
         return 8.0 * n + cw * B * P * (bins + 1) + (4.0 * B * groups * (bins + 1) if bins + 1 <= 8200 else 0.0)
@@ -96,14 +141,16 @@ def algorithmic_bytes(kernel: str, B: int, P: int, R: int, bins: int, windows: i
         return 16.0 * B * P + cw * B * P * (bins + 1) + 4.0 * B * ((P + 63) // 64) * (bins + 1)
     if kernel == "zl_bincount_kernel":      # the partial column sums once (else the crossing indices), one count per bin
         return (4.0 * B * groups if predicted or bins + 1 <= 8200 else cw * B * P) * (bins + 1) + 4.0 * B * (bins + 1)
-    if kernel == "zl_bounds_kernel":        # first and last timestamp of every row (one 64-byte line each)
-        return 128.0 * B * P
+    if kernel == "zl_bounds_kernel":        # first and last timestamp of every row (one 64-byte line each), a third line where
+        if predicted:                       # the last value that can win is looked for; predicted rows: 16 bytes in, 8 out
+            return 24.0 * B * P
+        return (192.0 if cut else 128.0) * B * P
     if kernel == "zl_plan_kernel":
         return 4.0 * B * (bins + 1) + 4.0 * windows
     if kernel in ("zl_range_fast_kernel", "zl_range_window_kernel"):
-        # every timestamp once (a neighbour comes in the same line), crossing rows, one result.  The sort-based
+        # every searched timestamp once (a neighbour comes in the same line), crossing rows, one result.  The sort-based
         # kernel only takes the windows the fast one leaves to it: priced at the whole input, its figure is a ceiling.
-        return 8.0 * n + windows * (2.0 * cw * P + 16.0)
+        return inside + windows * (2.0 * cw * P + 16.0)
     if kernel == "zl_range_instance_kernel":
         return 8.0 * n + B * (16.0 + 4.0 * P)
     if kernel == "zl_sweep_kernel":         # every timestamp once, one partial result per slice
@@ -111,8 +158,7 @@ def algorithmic_bytes(kernel: str, B: int, P: int, R: int, bins: int, windows: i
     if kernel == "zl_sweep_finish_kernel":  # partial results; per row two probes of its entries, outputs
         return 16.0 * windows + B * P * (64.0 * 2.0 + 4.0) + 16.0 * B
     if kernel == "zl_finish_kernel":        # window results; per row its crossing indices at the barrier's bin and two probes
-        import math                         # (predicted rows: nothing is probed), outputs
-        probes = 0.0 if predicted else 64.0 * 3.0
+        probes = 0.0 if predicted else 64.0 * 3.0       # (predicted rows: nothing is probed), outputs
         return 16.0 * windows + B * P * (probes + 4.0) + 16.0 * B
     if kernel in ("zl_window_general_kernel", "zl_instance_general_kernel"):    # next to nothing where nothing is left to them
         return 0.0
@@ -367,19 +413,29 @@ def main() -> int:
     fill = shape["window_fill"]
     if ranged and shape["multi"]:           # this objective leaves room for its short list behind a window's entries
         fill -= shape["window_cap"] // (2 if P < 128 else 4)
-    windows = B * ((P * R + fill - 1) // fill) if shape["multi"] else 0
-    per_kernel = {k: v / calls for k, v in kernel_ms.items() if v > 0.0}      # per launch
+    per_kernel = {k: v / calls for k, v in kernel_ms.items() if v > 0.0}      # per search
+    # the entries behind an instance's last value that can win are in no window (batches of enough windows, whose
+    # planned number the library rounds up to a whole number of workgroups of two)
+    searched = 0.0
+    if shape["multi"] and "zl_sweep_kernel" not in per_kernel and P <= CUT_ROWS and B * ((2 * P * R // fill + 4) // 2 * 2) > CUT_MIN_WINDOWS:
+        if S:                               # after the first superstep every worker starts at the barrier before
+            starts = [le_host] + [np.repeat(b[:, None] + args.sync_cost, P, axis=1) for b in barrier[:-1].cpu().numpy()]
+            searched = sum(searched_entries((l, iv, R), True) for l, iv in zip(starts, iv_host)) / S
+        else:
+            searched = searched_entries((le_host, iv_host, R) if args.predicted else host, not ranged)
+        bins *= searched / (float(B) * P * R)           # (fine bins hold about the same number of entries)
+    windows = (searched or float(B) * P * R) / fill if shape["multi"] else 0.0
     if "zl_sweep_kernel" in per_kernel:     # the frontier sweep: one partial result per slice, no windows
         windows = B * shape["slices"]
     dom = max(per_kernel, key=per_kernel.get)
-    dom_bytes = algorithmic_bytes(dom, B, P, R, bins, windows, args.predicted, S)
+    dom_bytes = algorithmic_bytes(dom, B, P, R, bins, windows, args.predicted, S, searched)
     achieved = dom_bytes / (per_kernel[dom] * 1e-3) / 1e9
     counted = COUNTED_TRAFFIC.get((args.objective, bool(args.predicted), args.config))
     tuned = bool(args.window_cap or args.single_max or args.window_fill or args.sweep_min or args.slice_keys or args.sweep_lines)
     traffic = call_traffic = None
     if counted and counted[0] == dom and not tuned and not S and kernel_sources_sha256() == COUNTED_SOURCES_SHA256:
         traffic, call_traffic = float(counted[1]), float(counted[2])
-    total_bytes = searches * sum(algorithmic_bytes(k, B, P, R, bins, windows, args.predicted, S) for k in per_kernel)
+    total_bytes = searches * sum(algorithmic_bytes(k, B, P, R, bins, windows, args.predicted, S, searched) for k in per_kernel)
 
     # CPU oracle on a bounded sample of the same workload (baseline, not a target)
     import oracle
@@ -449,6 +505,7 @@ def main() -> int:
                      "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS, "traffic": traffic,
                      "kernel_ms": per_kernel[dom], "algorithmic_bytes": dom_bytes},
         "whole_call": {"algorithmic_bytes": total_bytes,
+                       "searched_share": searched / (float(B) * P * R) if searched else 1.0,
                        "achieved_GBs": total_bytes / (ms_per_step * 1e-3) / 1e9,
                        "floor_bytes": 8.0 * n_keys,
                        "floor_GBs": 8.0 * n_keys / (ms_per_step * 1e-3) / 1e9,
