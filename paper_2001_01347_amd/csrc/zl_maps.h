@@ -42,24 +42,21 @@ struct SegEntry {        // one segment of an instance's map
     u32 slope;
     u32 pad_;
 };
-ZL_FN u32 fine_bin(u64 rel, const InstInfo& ii, const SegEntry* tab)
+// The bin of a value, nb for every value behind the bins that are searched.
+ZL_FN u32 fine_bin_or_nb(u64 rel, const InstInfo& ii, const SegEntry* tab)
 {
     if (rel > ii.range) rel = ii.range;              // only reachable for unsorted rows
     const u32 x = (u32)(rel >> ii.wshift);
     const u32 s = x >> ii.segshift;
     const SegEntry e = tab[s];
     const u32 k = (u32)((e.G + (u64)(x - (s << ii.segshift)) * e.slope) >> 32);
-    return k < ii.nb ? k : ii.nb - 1;
-}
-// The same with nb for every value behind the bins that are searched.
-ZL_FN u32 fine_bin_or_nb(u64 rel, const InstInfo& ii, const SegEntry* tab)
-{
-    if (rel > ii.range) rel = ii.range;
-    const u32 x = (u32)(rel >> ii.wshift);
-    const u32 s = x >> ii.segshift;
-    const SegEntry e = tab[s];
-    const u32 k = (u32)((e.G + (u64)(x - (s << ii.segshift)) * e.slope) >> 32);
     return k < ii.nb ? k : ii.nb;
+}
+// The bin of a value that is searched (any other: the last one).
+ZL_FN u32 fine_bin(u64 rel, const InstInfo& ii, const SegEntry* tab)
+{
+    const u32 k = fine_bin_or_nb(rel, ii, tab);
+    return k < ii.nb ? k : ii.nb - 1;
 }
 // Smallest relative value that falls in bin k or later (k <= bin(range)).
 ZL_FN u64 fine_bin_start(u32 k, const InstInfo& ii, const SegEntry* tab)
@@ -81,6 +78,49 @@ ZL_FN u64 fine_bin_start(u32 k, const InstInfo& ii, const SegEntry* tab)
 ZL_FN u64 searched_end(const InstInfo& ii, const SegEntry* tab)
 {
     return fine_bin_or_nb(ii.range, ii, tab) < ii.nb ? ii.range : fine_bin_start(ii.nb, ii, tab) - 1;
+}
+
+// The last entry up to x of a sorted row whose entries are at(0) = f <= x, ..., at(last) = l: from where evenly spaced
+// entries would put it, galloping.  (Any row: at() is asked for entries 0..last alone, and the search ends.)
+template <class At>
+ZL_FN u64 last_up_to(const At& at, u32 last, u64 f, u64 l, u64 x)
+{
+    if (l <= x || l <= f) return l <= x ? l : f;
+    u32 lo = 0, hi = last;                            // the entry at lo is <= x (vlo), the one at hi above
+    u64 vlo = f;
+    u32 g = (u32)((double)(x - f) / (double)(l - f) * (double)hi);
+    g = g < hi ? g : hi - 1;
+    u64 v = at(g);
+    u32 step = 1;
+    if (v <= x) {
+        lo = g; vlo = v;
+        while (lo + step < hi) {
+            v = at(lo + step);
+            if (v <= x) { lo += step; vlo = v; step *= 2; } else { hi = lo + step; break; }
+        }
+    } else {
+        hi = g;
+        while (hi > lo + step) {
+            v = at(hi - step);
+            if (v > x) { hi -= step; step *= 2; } else { lo = hi - step; vlo = v; break; }
+        }
+    }
+    while (hi - lo > 1) {
+        const u32 m = lo + ((hi - lo) >> 1);
+        v = at(m);
+        if (v <= x) { lo = m; vlo = v; } else hi = m;
+    }
+    return vlo;
+}
+
+// One of Newton's steps from above toward the smallest C with lb(C) >= ub, for lb(c) = sum over the rows of
+// max(0, c - the row's end): lb here and n, the rows that have ended before C.  Rounded so that lb stays at ub or above.
+// False: C stays.
+ZL_FN bool cut_step(u64& C, u64 lb, u64 n, u64 ub)
+{
+    if (lb <= ub || lb - ub < n) return false;
+    C -= (lb - ub) / n;
+    return true;
 }
 
 // Slope (bins per value of x, 32.32 fixed point, rounded down) of a segment that is to get the share

@@ -20,38 +20,6 @@ namespace {
 constexpr int CUT_ROWS = 2048;          // rows whose ends are kept in LDS for it (instances with more rows keep all bins)
 constexpr int CUT_STEPS = 16;
 
-// The last entry up to x of a sorted row (f <= x; values relative to base).
-__device__ __forceinline__ u64 cut_last_up_to(const Rows& ends, int p, u64 base, u64 f, u64 l, u64 x)
-{
-    if (l <= x || l <= f) return l <= x ? l : f;
-    u32 lo = 0, hi = (u32)ends.R - 1;                 // the entry at lo is <= x (vlo), the one at hi above
-    u64 vlo = f;
-    u32 g = (u32)((double)(x - f) / (double)(l - f) * (double)hi);
-    g = g < hi ? g : hi - 1;
-    auto at = [&](u32 i) { return (u64)ends.value(p, i) - base; };
-    u64 v = at(g);
-    u32 step = 1;
-    if (v <= x) {
-        lo = g; vlo = v;
-        while (lo + step < hi) {
-            v = at(lo + step);
-            if (v <= x) { lo += step; vlo = v; step *= 2; } else { hi = lo + step; break; }
-        }
-    } else {
-        hi = g;
-        while (hi > lo + step) {
-            v = at(hi - step);
-            if (v > x) { hi -= step; step *= 2; } else { lo = hi - step; vlo = v; break; }
-        }
-    }
-    while (hi - lo > 1) {
-        const u32 m = lo + ((hi - lo) >> 1);
-        v = at(m);
-        if (v <= x) { lo = m; vlo = v; } else hi = m;
-    }
-    return vlo;
-}
-
 // The last value that can win (see above), at most ii.range.
 template <int NT>
 __device__ __forceinline__ u64 cut_value(const Rows& ends, int P, const InstInfo& ii, u64 min_last, bool summed,
@@ -64,7 +32,7 @@ __device__ __forceinline__ u64 cut_value(const Rows& ends, int P, const InstInfo
     for (int p = tid; p < P; p += NT) {
         const u64 f = (u64)ends.value(p, 0) - (u64)ii.base, l = (u64)ends.value(p, (u32)ends.R - 1) - (u64)ii.base;
         row_end[p] = l;                               // (read by this thread alone)
-        const u64 gone = x - cut_last_up_to(ends, p, (u64)ii.base, f, l, x);
+        const u64 gone = x - last_up_to([&](u32 i) { return (u64)ends.value(p, i) - (u64)ii.base; }, (u32)ends.R - 1, f, l, x);
         mine = summed ? mine + gone : (gone > mine ? gone : mine);
     }
     const u64 ub = summed ? block_reduce<u64, NT>(mine, red, OpAdd()) : block_reduce<u64, NT>(mine, red, OpMax());
@@ -84,8 +52,7 @@ __device__ __forceinline__ u64 cut_value(const Rows& ends, int P, const InstInfo
 #pragma unroll
         for (int w = 1; w < NW; ++w) { lb += red[w]; n += red[NW + w]; }
         __syncthreads();
-        if (lb <= ub || lb - ub < n) break;           // (the same in every thread)
-        C -= (lb - ub) / n;
+        if (!cut_step(C, lb, n, ub)) break;           // (the same in every thread)
     }
     return C;
 }

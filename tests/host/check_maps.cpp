@@ -4,6 +4,10 @@
 //   LinearMap / TableMap   lo(b) <= k <= hi(b) for every key k in [0, span] that the map sends to bucket b;
 //                          the map never decreases and stays below the bucket count;
 //   fine_bin               never decreases, ends at nb - 1;  fine_bin_start(k) is the smallest value of bin >= k.
+//   fine_bin_or_nb, searched_end   the same grid where the bins end early: nb for every value behind them, and the last
+//                          value that is not;
+//   last_up_to, cut_step   the last entry up to x of a sorted row; Newton's steps end at a C behind which every barrier
+//                          waits longer than the bound.
 // A bound that is too tight would drop a bucket holding the optimum: the search would still return a barrier, only
 // not the best one, and parity tests would see it only on the inputs that happen to hit it.
 #include <cstdio>
@@ -261,6 +265,27 @@ static void fine_case(u64 range, int bins, int kind)
         if (k != exact(rel) || k < prev || k >= ii.nb) FAIL("fine_bin: range %llu bins %d kind %d value %llu bin %u exact %u prev %u", range, bins, kind, rel, k, exact(rel), prev);
         prev = k;
     }
+    // the bins end early, as zl_bounds lets them behind the bin of the last value that can win
+    const u32 all = ii.nb;
+    for (int t = 0; t < 6; ++t) {
+        const u64 end = t == 0 ? 0 : t == 1 ? range : rnd() % (range + 1);
+        ii.nb = all;
+        ii.nb = exact(end) + 1;
+        const u64 last = searched_end(ii, tab);
+        ++checks;
+        if (last < end || last > range || fine_bin_or_nb(last, ii, tab) >= ii.nb) FAIL("searched_end: range %llu bins %d kind %d end %llu gives %llu", range, bins, kind, end, last);
+        if (last < range && fine_bin_or_nb(last + 1, ii, tab) != ii.nb) FAIL("searched_end too early: range %llu bins %d kind %d end %llu gives %llu", range, bins, kind, end, last);
+        if (ii.nb == all && last != range) FAIL("searched_end of all bins: range %llu bins %d kind %d gives %llu", range, bins, kind, last);
+        for (int i = 0; i < 200; ++i) {
+            const u64 near = last + (u64)(i % 8) - 4, rel = i < 100 ? rnd() % (range + 1) : near <= range ? near : range;
+            const u64 x = rel >> ii.wshift, s = x >> ii.segshift;
+            const u64 full = (u64)(((u128)tab[s].G + (u128)(x - (s << ii.segshift)) * tab[s].slope) >> 32);
+            const u32 want = full < ii.nb ? (u32)full : ii.nb;
+            ++checks;
+            if (fine_bin_or_nb(rel, ii, tab) != want || fine_bin(rel, ii, tab) != (want < ii.nb ? want : ii.nb - 1) || (rel <= last) != (want < ii.nb))
+                FAIL("fine_bin_or_nb: range %llu bins %d kind %d nb %u value %llu gives %u", range, bins, kind, ii.nb, rel, fine_bin_or_nb(rel, ii, tab));
+        }
+    }
 }
 
 static void check_fine()
@@ -302,8 +327,83 @@ static void check_reciprocal()
     }
 }
 
+// The value cut of one instance: the last entry up to x of its rows, and the C that Newton's steps reach.
+static std::vector<u64> sorted_row(u32 R, u64 span, int kind)
+{
+    std::vector<u64> row(R);
+    for (u32 i = 0; i < R; ++i) {
+        u64 v = 0;
+        switch (kind) {
+        case 0: v = rnd() % (span + 1); break;                                             // any
+        case 1: v = (u64)((u128)span * i / (R > 1 ? R - 1 : 1)); break;                    // evenly spaced
+        case 2: v = i < R / 2 ? rnd() % (span / 1000 + 1) : span - rnd() % (span / 1000 + 1); break;    // both ends
+        case 3: v = span / 2; break;                                                       // all equal
+        case 4: v = rnd() % 5 * (span / 5); break;                                         // few values
+        default: v = span >> (rnd() % 64); break;                                          // geometric
+        }
+        row[i] = v;
+    }
+    for (u32 i = 1; i < R; ++i)                                                            // insertion sort: short rows
+        for (u32 j = i; j > 0 && row[j] < row[j - 1]; --j) { const u64 t = row[j]; row[j] = row[j - 1]; row[j - 1] = t; }
+    return row;
+}
+
+static void check_cut()
+{
+    for (int it = 0; it < 6000; ++it) {
+        const u32 R = it % 7 == 0 ? 1 + rnd() % 3 : 1 + rnd() % 150;
+        const u64 span = (rnd() >> 2) >> (rnd() % 61);                                     // up to 2^62
+        std::vector<u64> row = sorted_row(R, span, it % 6);
+        if (it % 11 == 10)                                                                 // out of order: in bounds, and it ends
+            for (u32 i = 0; i < R; ++i) row[i] = rnd() >> (rnd() % 64);
+        bool out = false;
+        long long asked = 0;
+        auto at = [&](u32 i) { ++asked; out |= i >= R; return row[i < R ? i : 0]; };
+        for (int k = 0; k < 12; ++k) {
+            const u64 f = row[0], l = row[R - 1];
+            u64 x = k < 4 ? row[rnd() % R] + (u64)(k & 1) : f + (l >= f ? rnd() % (l - f + 2) : rnd() % 9);
+            if (x < f) x = f;
+            asked = 0;
+            const u64 got = last_up_to(at, R - 1, f, l, x);
+            ++checks;
+            if (out || asked > 40) FAIL("last_up_to asks beyond the row or too often: R %u it %d asked %lld", R, it, asked);
+            if (it % 11 == 10) continue;
+            u64 want = f;
+            for (u64 v : row) if (v <= x) want = v;
+            if (got != want) FAIL("last_up_to: R %u span %llu kind %d x %llu gives %llu, want %llu", R, span, it % 6, x, got, want);
+        }
+    }
+    for (int it = 0; it < 20000; ++it) {
+        const u32 P = 1 + rnd() % (it % 3 ? 40 : 3);
+        const u64 most = 0x7fffffffffffffffull / P, range = most >> (rnd() % 62);          // P waits are summed in 63 bits
+        std::vector<u64> ends(P);
+        u64 top = 0, low = ~0ull;
+        for (u64& e : ends) {
+            e = it % 4 == 0 ? range - rnd() % (range / 50 + 1) : it % 4 == 1 ? (range >> (rnd() % 40)) : rnd() % (range + 1);
+            top = e > top ? e : top;
+            low = e < low ? e : low;
+        }
+        const u64 x = low + rnd() % (top - low + 1);                                       // the bound's value: the first end or later
+        u128 ub128 = 0;
+        for (u64 e : ends) ub128 += x > e ? x - e : (it % 5 ? rnd() % (x / P + 1) : 0);    // what the rows lag behind x
+        const u64 ub = ub128 > 0x7fffffffffffffffull ? 0x7fffffffffffffffull : (u64)ub128;
+        auto lb = [&](u64 c, u64& n) { u128 s = 0; n = 0; for (u64 e : ends) if (e < c) { s += c - e; ++n; } return s; };
+        u64 C = top, n;
+        for (int k = 0; k < 16; ++k) if (!cut_step(C, (u64)lb(C, n), (lb(C, n), n), ub)) break;
+        ++checks;
+        if (C > top || (C < x && C < top)) FAIL("cut: C %llu outside [%llu, %llu]", C, x, top);
+        for (int k = 0; k < 8 && C < top; ++k) {
+            const u64 c = k < 4 ? (C + 1 + k < top ? C + 1 + k : top) : C + 1 + rnd() % (top - C);
+            ++checks;
+            if (lb(c, n) <= ub) FAIL("cut: P %u range %llu C %llu leaves out %llu, which may wait no longer than the bound", P, range, C, c);
+        }
+    }
+}
+
 int main()
 {
+    check_cut();
+    std::printf("value cut: %lld checks, %lld failures so far\n", checks, failures);
     check_reciprocal();
     std::printf("reciprocals: %lld checks, %lld failures so far\n", checks, failures);
     check_linear();
