@@ -252,9 +252,19 @@ hipEvent_t* prof_slot(int kid, int which)
         }                                                                                  \
     } while (0)
 
-// Batches of more windows than this (max_win is about twice the windows there are) first find out how far the
-// values can win (zl_bounds).  That takes some 25 us, and where workers are alike it leaves out little: a call of
-// 315 us took 340 with it, config 5 (66 000 here) 940 instead of 1825, config 4's range search (135 000) 1820 of 2030.
+// Batches of more planned windows than this (max_win is about twice the windows there are) first find out how far the
+// values can win (zl_bounds).  What that saves grows with the batch and with how early some workers are through; what it
+// costs hardly does: 7 to 25 us, with thousands of short-rowed instances more.  Calls without / with it, us, for workers
+// of 95 to 105 ms, which leave nothing out | config 4's two groups | config 5's 20 to 200 ms:
+//     68 x 1024 x 240   ( 4 352 planned)   164 / 172  |   160 / 170   |   164 / 140
+//      8 x 1024 x 4096  ( 8 224)           288 / 290  |   298 / 250   |   287 / 170
+//     64 x  256 x 1024  ( 8 448)           127 / 134  |   122 / 122   |   119 / 98
+//    128 x  256 x 1024  (16 896)           207 / 211  |   200 / 187   |   199 / 140
+//    273 x 1024 x 240   (17 472)           583 / 579  |   540 / 546   |   567 / 410
+//     64 x 2048 x 1024  (16 640)          1226 / 1224 |  1206 / 1065  |  1191 / 620
+//     64 x 1024 x 4096  (65 792)          1816 / 1785 |  1784 / 1555  |  1824 / 934
+// and config 4's range search (178 176) 2020 / 1816.  The line lies where workers all alike
+// lose no more than 2 % (the worst of some thousand drawn batches: predicted 8690 x 246 x 114, 1125 / 1164).
 constexpr i64 CUT_MIN_WINDOWS = 16384;
 
 // The front of the multi-window path, shared by the objectives: per-instance facts and
@@ -339,10 +349,11 @@ int plan_windows(const Plan& pl, const i64* ts, const i64* le, const i64* iv, i6
 
 // Instances of 1024 entries or fewer take both searches in one launch, all supersteps of a run included
 // (zl_run_kernel), where the batch's workgroups are on the chip together; a run's launches weigh more, so twice as
-// many there.  Measured, us per superstep in separate launches / in one: 256 instances of 16 x 60 13.8 / 7.6, 1024
-// 17.6 / 10.8, 2048 24.6 / 20.9, 4096 37.8 / 40.1; 4096 of 16 x 15 21.4 / 16.8.  Single searches: one of 16 x 15
-// 13.5 / 10.6, 2048 of them 16.9 / 14.8, 4096 19.2 / 19.5, 2048 of 16 x 60 21.6 / 22.0.  Larger instances keep the
-// separate kernels: with the general search in the same kernel 100 x 150 predicted took 55.6 us instead of 29.2.
+// many there.  Measured, us per superstep (64 of them) in separate launches / in one: 256 instances of 16 x 60 13.6 / 7.6,
+// 1024 17.4 / 15.2, 1536 21.7 / 17.9, 2048 24.6 / 24.8, 3072 31.3 / 35.2; of 16 x 15 2048 16.5 / 8.2, 4096 21.4 / 15.8,
+// 6144 (beyond the line) 27.9 / 23.0.  Single searches: 256 of 16 x 60 14.1 / 12.4, 1024 16.4 / 19.9, 1536 20.4 / 23.4;
+// 2048 of 16 x 15 16.4 / 13.5, 3072 18.6 / 18.2, 4096 20.3 / 20.8.  Larger instances keep the separate kernels: with the
+// general search in the same kernel 100 x 150 predicted took 55.6 us instead of 29.2.
 bool takes_run_kernel(i64 S, i64 B, i64 n)
 {
     if (n > 1024) return false;

@@ -393,7 +393,7 @@ __global__ __launch_bounds__(NT, (NT == 1024 ? 8 : (NT == 128 ? 5 : 6))) void zl
 // Instances whose values spread over 2^32 and more (timestamps in nanoseconds) but evenly enough: the bucket search
 // of zl_bucket_finish with 64-bit values.  Buckets and bounds come from the values shifted down to 32 bits (a bucket's
 // bounds in whole values are its lowest shifted key with the lost bits zero, and its highest with them set), the
-// buckets' words hold exact sums of exact deltas (P * range below 2^SUM_BITS: half an hour of nanoseconds at P = 64),
+// buckets' words hold exact sums of exact deltas (P * range below 2^SUM_BITS: 18 minutes of nanoseconds at P = 64),
 // the list holds whole values.  Values are read again for each of the three passes instead of kept in registers (the
 // instance stays in L2).  `smem` has BYTES; false: nothing found out (the sort does it).  1021 instances of 61 x 241
 // in nanoseconds: 820 us by the radix sort in 64-bit pieces, 297 us so.  Not for instances of at most 1024 entries:

@@ -15,8 +15,8 @@ namespace {
 // max_p instead of the sum in ub and c - (the earliest row end) for lb.  x = the earliest row end (or thr): until then
 // lb is 0.  Rows are searched for x from where evenly spaced entries would put it, C is found from above by Newton's
 // method on the convex lb.  Rows are read whole for their order check all the same.
-// Config 5 (workers whose iterations take 20 to 200 ms) keeps a third of its entries, two groups 2.5 times apart nine
-// tenths.  Costs up to 30 us of latency, so only where the windows are more than the chip takes at once.
+// Config 5 (workers whose iterations take 20 to 200 ms) keeps 28 % of its entries, config 4 (two groups 2.5 times apart)
+// 81 %.  On config 5 it takes 22 us (zl_bounds 15 -> 37); for which batches: CUT_MIN_WINDOWS.
 constexpr int CUT_ROWS = 2048;          // rows whose ends are kept in LDS for it (instances with more rows keep all bins)
 constexpr int CUT_STEPS = 16;
 
