@@ -42,23 +42,26 @@ HBM_PEAK_GBS = 8000.0          # MI355X HBM3E, published peak
 # reads for the plain copy kernel of known size (FETCH_SIZE x 2048 B, WRITE_SIZE x 1024 B per count).  The
 # figures below are the counters' per-dispatch averages, kernel by kernel in launch order.  They hold only for
 # the kernel sources they were taken from: `traffic` is null once those have changed.
-COUNTED_SOURCES_SHA256 = "8a357e189d87dc08d46985853e941fb98f575fecc7a2489b26f751e3dec9a5a9"
+COUNTED_SOURCES_SHA256 = "bc1445eca2532209ad5fcc147d6256bcd5568be195b3a80510604d3d64c99b2e"
 FETCH_UNIT, WRITE_UNIT = 2048, 1024      # bytes per count: what the copy kernel's 2 GiB in, 2 GiB out read as (1 048 607 and 2 097 152)
 COUNTED_TRAFFIC = {     # (objective, predicted, config) -> (dominant kernel, its bytes, bytes of all kernels of a call)
-    ("sum", False, 5): ("zl_window_kernel", 2263792 * FETCH_UNIT + 1238 * WRITE_UNIT,
-                        (16448 + 1049297 + 35886 + 658 + 2263792 + 358 + 8502) * FETCH_UNIT
-                        + (70 + 608424 + 1025 + 1239 + 1238 + 8192 + 258) * WRITE_UNIT),
-    ("sum", False, 3): ("zl_instance_reg_kernel", 1405244 * FETCH_UNIT + 144188 * WRITE_UNIT,
-                        (1405244 + 97) * FETCH_UNIT + (144188 + 16384) * WRITE_UNIT),
-    ("range", False, 5): ("zl_range_fast_kernel", 2461671 * FETCH_UNIT + 2071 * WRITE_UNIT,
-                          (16447 + 1049295 + 35886 + 670 + 2461671 + 617 + 8911) * FETCH_UNIT
-                          + (70 + 608466 + 1025 + 1716 + 2071 + 14459 + 258) * WRITE_UNIT),
-    ("sum", True, 5): ("zl_window_kernel", 267414 * FETCH_UNIT + 561 * WRITE_UNIT,
-                       (575 + 10356 + 9004 + 658 + 267414 + 357 + 1666) * FETCH_UNIT
-                       + (582 + 548866 + 1024 + 1240 + 561 + 8192 + 258) * WRITE_UNIT),
-    ("sum", False, 4): ("zl_window_kernel", 2054930 * FETCH_UNIT + 2672 * WRITE_UNIT,
-                        (65606 + 1053106 + 18132 + 1875 + 2054930 + 656 + 36371) * FETCH_UNIT
-                        + (1120 + 306295 + 2048 + 2519 + 2672 + 0 + 1088) * WRITE_UNIT),
+    ("sum", False, 5): ("zl_partition_kernel", 1049001 * FETCH_UNIT + 164756 * WRITE_UNIT,
+                        (29467 + 1049001 + 9710 + 267 + 639621 + 130 + 7711) * FETCH_UNIT
+                        + (70 + 164756 + 272 + 352 + 358 + 8192 + 258) * WRITE_UNIT),
+    ("sum", False, 3): ("zl_instance_reg_kernel", 1404682 * FETCH_UNIT + 144347 * WRITE_UNIT,
+                        (1404682 + 88) * FETCH_UNIT + 144347 * WRITE_UNIT),
+    ("range", False, 5): ("zl_range_fast_kernel", 660934 * FETCH_UNIT + 557 * WRITE_UNIT,
+                          (29470 + 1049010 + 8737 + 256 + 660934 + 285 + 7786) * FETCH_UNIT
+                          + (70 + 150182 + 247 + 446 + 557 + 14177 + 258) * WRITE_UNIT),
+    ("sum", True, 5): ("zl_window_kernel", 73721 * FETCH_UNIT + 157 * WRITE_UNIT,
+                       (620 + 4772 + 2451 + 266 + 73721 + 129 + 881) * FETCH_UNIT
+                       + (582 + 149538 + 271 + 350 + 157 + 8192 + 258) * WRITE_UNIT),
+    ("sum", False, 4): ("zl_window_kernel", 1761277 * FETCH_UNIT + 2181 * WRITE_UNIT,
+                        (123917 + 1053099 + 14182 + 1630 + 1761277 + 558 + 36253) * FETCH_UNIT
+                        + (1122 + 232418 + 1554 + 2065 + 2181 + 0 + 1088) * WRITE_UNIT),
+    ("range", False, 4): ("zl_range_fast_kernel", 2049917 * FETCH_UNIT + 3407 * WRITE_UNIT,
+                          (124012 + 1053099 + 13990 + 1642 + 2049917 + 818 + 36402) * FETCH_UNIT
+                          + (1122 + 228900 + 1530 + 2805 + 3407 + 0 + 1088) * WRITE_UNIT),
 }
 
 
