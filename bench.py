@@ -42,7 +42,7 @@ HBM_PEAK_GBS = 8000.0          # MI355X HBM3E, published peak
 # reads for the plain copy kernel of known size (FETCH_SIZE x 2048 B, WRITE_SIZE x 1024 B per count).  The
 # figures below are the counters' per-dispatch averages, kernel by kernel in launch order.  They hold only for
 # the kernel sources they were taken from: `traffic` is null once those have changed.
-COUNTED_SOURCES_SHA256 = "bc1445eca2532209ad5fcc147d6256bcd5568be195b3a80510604d3d64c99b2e"
+COUNTED_SOURCES_SHA256 = "732355e5336ede996ab3e438c3664e7adfb95ab73d3f92c65f4c02021103d3bc"
 FETCH_UNIT, WRITE_UNIT = 2048, 1024      # bytes per count: what the copy kernel's 2 GiB in, 2 GiB out read as (1 048 607 and 2 097 152)
 COUNTED_TRAFFIC = {     # (objective, predicted, config) -> (dominant kernel, its bytes, bytes of all kernels of a call)
     ("sum", False, 5): ("zl_partition_kernel", 1049001 * FETCH_UNIT + 164756 * WRITE_UNIT,

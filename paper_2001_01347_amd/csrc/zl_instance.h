@@ -394,10 +394,11 @@ __global__ __launch_bounds__(NT, (NT == 1024 ? 8 : (NT == 128 ? 5 : 6))) void zl
 // of zl_bucket_finish with 64-bit values.  Buckets and bounds come from the values shifted down to 32 bits (a bucket's
 // bounds in whole values are its lowest shifted key with the lost bits zero, and its highest with them set), the
 // buckets' words hold exact sums of exact deltas (P * range below 2^SUM_BITS: 18 minutes of nanoseconds at P = 64),
-// the list holds whole values.  Values are read again for each of the three passes instead of kept in registers (the
-// instance stays in L2).  `smem` has BYTES; false: nothing found out (the sort does it).  1021 instances of 61 x 241
+// the list holds whole values.  Values are read again for each of the passes instead of kept in registers (not all of
+// them stay in the L2: 356 MiB fetched for 115).  `smem` has BYTES; false: nothing found out (the sort does it).  1021 instances of 61 x 241
 // in nanoseconds: 820 us by the radix sort in 64-bit pieces, 297 us so.  Not for instances of at most 1024 entries:
-// one piece of the sort, and the kernel that has both starts 1 us later where nothing is left to it.
+// one piece of the sort, and the kernel that has both starts 1 us later where nothing is left to it.  What it gives up
+// (a bucket too deep) has paid for two passes: rows that all jump by 2^40 half way, 17 to 29 % more than by the sort alone.
 template <int NT, size_t BYTES, class RW>
 __device__ __forceinline__ bool zl_wide_search(unsigned char* smem, const RW& rw, int P, int R, u64 range, u64 thr,
                                                u64& best_wait, u64& best_rel)
