@@ -50,18 +50,12 @@ COUNTED_TRAFFIC = {     # (objective, predicted, config) -> (dominant kernel, it
                         + (70 + 164756 + 272 + 352 + 358 + 8192 + 258) * WRITE_UNIT),
     ("sum", False, 3): ("zl_instance_reg_kernel", 1404682 * FETCH_UNIT + 144347 * WRITE_UNIT,
                         (1404682 + 88) * FETCH_UNIT + 144347 * WRITE_UNIT),
-    ("range", False, 5): ("zl_range_fast_kernel", 660934 * FETCH_UNIT + 557 * WRITE_UNIT,
-                          (29470 + 1049010 + 8737 + 256 + 660934 + 285 + 7786) * FETCH_UNIT
-                          + (70 + 150182 + 247 + 446 + 557 + 14177 + 258) * WRITE_UNIT),
     ("sum", True, 5): ("zl_window_kernel", 73721 * FETCH_UNIT + 157 * WRITE_UNIT,
                        (620 + 4772 + 2451 + 266 + 73721 + 129 + 881) * FETCH_UNIT
                        + (582 + 149538 + 271 + 350 + 157 + 8192 + 258) * WRITE_UNIT),
     ("sum", False, 4): ("zl_window_kernel", 1761277 * FETCH_UNIT + 2181 * WRITE_UNIT,
                         (123917 + 1053099 + 14182 + 1630 + 1761277 + 558 + 36253) * FETCH_UNIT
                         + (1122 + 232418 + 1554 + 2065 + 2181 + 0 + 1088) * WRITE_UNIT),
-    ("range", False, 4): ("zl_range_fast_kernel", 2049917 * FETCH_UNIT + 3407 * WRITE_UNIT,
-                          (124012 + 1053099 + 13990 + 1642 + 2049917 + 818 + 36402) * FETCH_UNIT
-                          + (1122 + 228900 + 1530 + 2805 + 3407 + 0 + 1088) * WRITE_UNIT),
 }
 
 
@@ -150,12 +144,10 @@ def algorithmic_bytes(kernel: str, B: int, P: int, R: int, bins: float, windows:
         return (192.0 if cut else 128.0) * B * P
     if kernel == "zl_plan_kernel":
         return 4.0 * B * (bins + 1) + 4.0 * windows
-    if kernel in ("zl_range_fast_kernel", "zl_range_window_kernel"):
-        # every searched timestamp once (a neighbour comes in the same line), crossing rows, one result.  The sort-based
-        # kernel only takes the windows the fast one leaves to it: priced at the whole input, its figure is a ceiling.
-        return inside + windows * (2.0 * cw * P + 16.0)
-    if kernel == "zl_range_instance_kernel":
+    if kernel in ("zl_range_instance_kernel", "zl_range_fast_kernel"):      # every timestamp once, all three outputs
         return 8.0 * n + B * (16.0 + 4.0 * P)
+    if kernel == "zl_range_window_kernel":      # the outputs of instances in slices (next to nothing is left to its search)
+        return B * (16.0 + 4.0 * P)
     if kernel == "zl_sweep_kernel":         # every timestamp once, one partial result per slice
         return rows + 16.0 * windows
     if kernel == "zl_sweep_finish_kernel":  # partial results; per row two probes of its entries, outputs
@@ -408,24 +400,17 @@ def main() -> int:
     # shape-dependent constants of the multi-window path (for the byte model only)
     shape = zipline.ebsp_zipline_shape_info(B, P, R)
     bins = shape["bins"]
-    if ranged and P * R > 8192 and not shape["multi"]:
-        # this objective cuts instances of more than 8192 entries into windows: the shape as the library plans it
-        zipline.ebsp_zipline_tune(args.window_cap, 8192, args.window_fill)
-        shape = zipline.ebsp_zipline_shape_info(B, P, R)
-        zipline.ebsp_zipline_tune(args.window_cap, args.single_max, args.window_fill)
     fill = shape["window_fill"]
-    if ranged and shape["multi"]:           # this objective leaves room for its short list behind a window's entries
-        fill -= shape["window_cap"] // (2 if P < 128 else 4)
     per_kernel = {k: v / calls for k, v in kernel_ms.items() if v > 0.0}      # per search
     # the entries behind an instance's last value that can win are in no window (batches of enough windows, whose
     # planned number the library rounds up to a whole number of workgroups of two)
     searched = 0.0
-    if shape["multi"] and "zl_sweep_kernel" not in per_kernel and P <= CUT_ROWS and B * ((2 * P * R // fill + 4) // 2 * 2) > CUT_MIN_WINDOWS:
+    if shape["multi"] and not ranged and "zl_sweep_kernel" not in per_kernel and P <= CUT_ROWS and B * ((2 * P * R // fill + 4) // 2 * 2) > CUT_MIN_WINDOWS:
         if S:                               # after the first superstep every worker starts at the barrier before
             starts = [le_host] + [np.repeat(b[:, None] + args.sync_cost, P, axis=1) for b in barrier[:-1].cpu().numpy()]
             searched = sum(searched_entries((l, iv, R), True) for l, iv in zip(starts, iv_host)) / S
         else:
-            searched = searched_entries((le_host, iv_host, R) if args.predicted else host, not ranged)
+            searched = searched_entries((le_host, iv_host, R) if args.predicted else host, True)
         bins *= searched / (float(B) * P * R)           # (fine bins hold about the same number of entries)
     windows = (searched or float(B) * P * R) / fill if shape["multi"] else 0.0
     if "zl_sweep_kernel" in per_kernel:     # the frontier sweep: one partial result per slice, no windows

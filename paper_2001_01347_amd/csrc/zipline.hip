@@ -82,12 +82,12 @@ int check_device()
 }
 
 enum KernelId { K_INSTANCE = 0, K_INSTANCE_GENERAL, K_BOUNDS, K_PARTITION, K_BINCOUNT, K_PLAN, K_WINDOW,
-                K_WINDOW_GENERAL, K_FINISH, K_COPY, K_RANGE_INSTANCE, K_RANGE_WINDOW, K_PARTITION_PRED, K_RANGE_FAST, K_ADVANCE, K_SWEEP, K_SWEEP_FINISH, K_GRIDSCAN, K_GRIDSCAN_FINISH, K_READ, K_INSTANCE_REG, K_RUN, K_COUNT };
+                K_WINDOW_GENERAL, K_FINISH, K_COPY, K_RANGE_INSTANCE, K_RANGE_FAST, K_PARTITION_PRED, K_RANGE_WINDOW, K_ADVANCE, K_SWEEP, K_SWEEP_FINISH, K_GRIDSCAN, K_GRIDSCAN_FINISH, K_READ, K_INSTANCE_REG, K_RUN, K_COUNT };
 const char* const kKernelNames[K_COUNT] = {
     "zl_instance_kernel", "zl_instance_general_kernel", "zl_bounds_kernel", "zl_partition_kernel",
     "zl_bincount_kernel", "zl_plan_kernel", "zl_window_kernel", "zl_window_general_kernel",
-    "zl_finish_kernel", "zl_copy_kernel", "zl_range_instance_kernel", "zl_range_window_kernel",
-    "zl_partition_pred_kernel", "zl_range_fast_kernel", "zl_advance_kernel", "zl_sweep_kernel", "zl_sweep_finish_kernel", "zl_gridscan_kernel",
+    "zl_finish_kernel", "zl_copy_kernel", "zl_range_instance_kernel", "zl_range_fast_kernel",
+    "zl_partition_pred_kernel", "zl_range_window_kernel", "zl_advance_kernel", "zl_sweep_kernel", "zl_sweep_finish_kernel", "zl_gridscan_kernel",
     "zl_gridscan_finish_kernel", "zl_read_kernel", "zl_instance_reg_kernel", "zl_run_kernel"};
 
 size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
@@ -138,7 +138,7 @@ struct Plan {
 };
 
 // single_limit: the most entries one workgroup takes whole on the path the plan is for;
-// list_room: windows leave a quarter or more of the workgroup's records free (the fast range search keeps its short list there)
+// list_room: the range objective's scratch, whose size counts windows that leave a quarter or more of a workgroup's records free
 bool make_plan(i64 B, int P, int R, Plan& pl, int single_limit = SINGLE_MAX, bool list_room = false, bool stored_sum = false)
 {
     if (B < 0 || P < 1 || R < 1) return false;
@@ -263,14 +263,13 @@ hipEvent_t* prof_slot(int kid, int which)
 //    273 x 1024 x 240   (17 472)           583 / 579  |   540 / 546   |   567 / 410
 //     64 x 2048 x 1024  (16 640)          1226 / 1224 |  1206 / 1065  |  1191 / 620
 //     64 x 1024 x 4096  (65 792)          1816 / 1785 |  1784 / 1555  |  1824 / 934
-// and config 4's range search (178 176) 2020 / 1816.  The line lies where workers all alike
+// The line lies where workers all alike
 // lose no more than 2 % (the worst of some thousand drawn batches: predicted 8690 x 246 x 114, 1125 / 1164).
 constexpr i64 CUT_MIN_WINDOWS = 16384;
 
-// The front of the multi-window path, shared by the objectives: per-instance facts and
-// fine-bin map, crossing indices, exact bin counts, windows.
+// The front of the multi-window path: per-instance facts and fine-bin map, crossing indices, exact bin counts, windows.
 int plan_windows(const Plan& pl, const i64* ts, const i64* le, const i64* iv, i64 B, int P, int R,
-                 char* wsp, int* status, bool summed, hipStream_t st)
+                 char* wsp, int* status, hipStream_t st)
 {
     const bool pred = ts == nullptr;
     InstInfo* info = (InstInfo*)(wsp + pl.off_info);
@@ -293,10 +292,10 @@ int plan_windows(const Plan& pl, const i64* ts, const i64* le, const i64* iv, i6
     // 306 / 306 / 314, 320 x 600 x 392 349 / 351 / 362, 8000 x 300 x 60 1621 / 1629 / 1856, predicted 2542 x 378 x 239
     // 919 / 943 / 1032 (923 without the cut) and 3619 x 401 x 60 362 / 396 / 523 (472).
     if (cut && P > 512 && B <= GENERAL_GRID)
-        LAUNCH(K_BOUNDS, (zl_bounds_kernel<512>), dim3((unsigned)B), dim3(512), ts, le, iv, P, R, pl.bins, info, segtab, rowpar, status, summed,
+        LAUNCH(K_BOUNDS, (zl_bounds_kernel<512>), dim3((unsigned)B), dim3(512), ts, le, iv, P, R, pl.bins, info, segtab, rowpar, status,
                cut, (i64*)nullptr);
     else
-        LAUNCH(K_BOUNDS, (zl_bounds_kernel<256>), dim3((unsigned)B), dim3(256), ts, le, iv, P, R, pl.bins, info, segtab, rowpar, status, summed,
+        LAUNCH(K_BOUNDS, (zl_bounds_kernel<256>), dim3((unsigned)B), dim3(256), ts, le, iv, P, R, pl.bins, info, segtab, rowpar, status,
                cut, (i64*)nullptr);
     int part_rows;                                    // rows of partial column sums per instance (0: none, count from cross)
     if (pred) {
@@ -405,7 +404,7 @@ int run_batch(const i64* ts, const i64* le, const i64* iv, i64 B, int P, int R,
         Partial* spartial = (Partial*)(wsp + pl.off_spartial);
         i64* best = (i64*)(wsp + pl.off_best);
         LAUNCH(K_BOUNDS, (zl_bounds_kernel<256>), dim3((unsigned)B), dim3(256), ts, le, iv, P, R, pl.nslices, info, segtab,
-               (uint2*)nullptr, status, true, false, best);
+               (uint2*)nullptr, status, false, best);
         const dim3 sgrid((unsigned)(B * (i64)pl.nslices));
         LAUNCH(K_SWEEP, (zl_sweep_kernel<SWEEP_NT, SWEEP_LINES, SWEEP_BUCKETS, SWEEP_LIST, SWEEP_PMAX>), sgrid, dim3(SWEEP_NT),
                ts, B, P, R, pl.nslices, pl.lines, info, segtab, best, spartial, status);
@@ -473,7 +472,7 @@ int run_batch(const i64* ts, const i64* le, const i64* iv, i64 B, int P, int R,
     const i64 pblocks = (P + 255) / 256;
     if (pblocks * B > 0x7fffffffll) return fail(EBSP_ERR_SHAPE, "batch too large for one call");
     if (int rc = check_device()) return rc;
-    if (int rc = plan_windows(pl, ts, le, iv, B, P, R, wsp, status, true, st)) return rc;
+    if (int rc = plan_windows(pl, ts, le, iv, B, P, R, wsp, status, st)) return rc;
     // Batches whose windows are all on the chip at once (two workgroups per CU; max_win is about twice the windows
     // there are) are as fast as one workgroup: a window each instead of two.
     const bool one_each = pl.narrow && total_win <= 4 * GENERAL_GRID;
@@ -512,10 +511,9 @@ int run_batch(const i64* ts, const i64* le, const i64* iv, i64 B, int P, int R,
     return EBSP_OK;
 }
 
-// The search under the paper's formal objective; the multi-window path shares the
-// kernels that cut an instance into windows.
-constexpr int RANGE_SINGLE_MAX = WinCfg<LARGE_NT, LARGE_ITEMS>::CAP_WIDE;
-
+// The search under the paper's formal objective: small instances in registers, others in slices of their values.
+constexpr int RANGE_SINGLE_MAX = WinCfg<LARGE_NT, LARGE_ITEMS>::CAP_WIDE;      // larger ones need a workspace
+constexpr i64 RANGE_SMALL = 32768;               // entries of a slice that is small
 
 int run_range_batch(const i64* ts, i64 B, int P, int R, i64* barrier, int* iters, i64* dmin, int* status,
                     void* workspace, size_t workspace_bytes, hipStream_t st)
@@ -526,67 +524,71 @@ int run_range_batch(const i64* ts, i64 B, int P, int R, i64* barrier, int* iters
     if (B == 0) return EBSP_OK;
     if (!ts || !barrier || !iters || !dmin) return fail(EBSP_ERR_NULL, "ts, barrier, iters and dmin must not be NULL");
     if (B > 0x7fffffffll) return fail(EBSP_ERR_SHAPE, "B must be below 2^31");
-    if (!pl.multi) {
-        if (int rc = check_device()) return rc;
-        // the smallest workgroup whose records hold the instance (half of NT * ITEMS in the 12-byte form):
-        // several small instances share a CU
-        const i64 n = (i64)P * R;
-        if (n <= 1024)
-            LAUNCH(K_RANGE_INSTANCE, (zl_range_instance_kernel<256, 8>), dim3((unsigned)B), dim3(256),
-                   ts, P, R, barrier, iters, dmin, status);
-        else if (n <= 2048)
-            LAUNCH(K_RANGE_INSTANCE, (zl_range_instance_kernel<256, 16>), dim3((unsigned)B), dim3(256),
-                   ts, P, R, barrier, iters, dmin, status);
-        else if (n <= 4096)
-            LAUNCH(K_RANGE_INSTANCE, (zl_range_instance_kernel<512, 16>), dim3((unsigned)B), dim3(512),
-                   ts, P, R, barrier, iters, dmin, status);
-        else
-            LAUNCH(K_RANGE_INSTANCE, (zl_range_instance_kernel<LARGE_NT, LARGE_ITEMS>), dim3((unsigned)B), dim3(LARGE_NT),
-                   ts, P, R, barrier, iters, dmin, status);
+    const i64 n = (i64)P * R, pblocks = (P + 255) / 256;
+    if (pl.multi) {
+        if (!workspace) return fail(EBSP_ERR_NULL, "this shape needs a workspace");
+        if (workspace_bytes < pl.bytes) return fail(EBSP_ERR_WORKSPACE, "workspace smaller than ebsp_zipline_range_workspace_bytes()");
+        if (((uintptr_t)workspace & 255u) != 0) return fail(EBSP_ERR_WORKSPACE, "workspace must be 256-byte aligned");
+        if (B * (i64)pl.max_win + 8 > 0x7fffffffll || pblocks * B > 0x7fffffffll)
+            return fail(EBSP_ERR_SHAPE, "batch too large for one call");
+    }
+    if (int rc = check_device()) return rc;
+    const int knob = tuning().single_max;
+    // In registers where an instance has at most 4096 entries and eight cells or more per iteration (fewer leave too many
+    // entries to evaluate).  In registers / as one slice, us: 8192 of 64 x 64 128 / 214, 16384 of 64 x 30 160 / 261, 8000 of
+    // 200 x 20 135 / 202; larger ones 8192 of 64 x 128 316 / 262, 4096 of 64 x 256 513 / 172 (32 waves of 64 registers per
+    // CU, spilling); long rows 8192 of 4 x 1000 with 4096 cells in registers 1110, as a slice of 8192 cells 333.
+    if (n <= 4096 && n <= (knob > 0 ? knob : SINGLE_MAX) && 8ll * R <= (n <= 256 && R <= 64 ? 512 : n <= 1024 ? 2048 : 4096)) {
+        const int rshift = (R & (R - 1)) == 0 ? __builtin_ctz((unsigned)R) : -1;
+#define LAUNCH_RANGE(NT_, ITEMS_, NB_, REST_)                                                                \
+    LAUNCH(K_RANGE_INSTANCE, (zl_range_instance_kernel<NT_, ITEMS_, NB_, REST_>), dim3((unsigned)B), dim3(NT_), \
+           ts, P, R, rshift, barrier, iters, dmin, status)
+        // Two waves for up to 1024 entries: with one / two / four, us: 4096 of 16 x 64 28.9 / 23.6 / 34.7, 16384 of them
+        // 73 / 69 / 109, 512 of them 19.6 / 15.0 / 16.5; with half the cells 32.3 / 29.3 and more.
+        if (n <= 256 && R <= 64) { LAUNCH_RANGE(64, 4, 512, false); return EBSP_OK; }
+        if (n <= 1024) { LAUNCH_RANGE(128, 8, 2048, false); return EBSP_OK; }      // (they never give up)
+        LAUNCH_RANGE(256, 16, 4096, true);
+#undef LAUNCH_RANGE
+        LAUNCH(K_RANGE_WINDOW, (zl_range_window_kernel<512, 16>), dim3((unsigned)(B < 2 * GENERAL_GRID ? B : 2 * GENERAL_GRID)),
+               dim3(512), ts, B, P, R, 1u, (const RangePart*)nullptr, barrier, iters, dmin, status);
         return EBSP_OK;
     }
-    if (!workspace) return fail(EBSP_ERR_NULL, "this shape needs a workspace");
-    if (workspace_bytes < pl.bytes) return fail(EBSP_ERR_WORKSPACE, "workspace smaller than ebsp_zipline_range_workspace_bytes()");
-    if (((uintptr_t)workspace & 255u) != 0) return fail(EBSP_ERR_WORKSPACE, "workspace must be 256-byte aligned");
-    const i64 total_win = B * (i64)pl.max_win;
-    if (total_win + 8 > 0x7fffffffll || B * (i64)P > (0x7fffffffll * 4)) return fail(EBSP_ERR_SHAPE, "batch too large for one call");
-
-    char* wsp = (char*)workspace;
-    InstInfo* info = (InstInfo*)(wsp + pl.off_info);
-    void* cross = (void*)(wsp + pl.off_cross);
-    u32* winstart = (u32*)(wsp + pl.off_winstart);
-    WinVal* winval = (WinVal*)(wsp + pl.off_winval);
-    Partial* partial = (Partial*)(wsp + pl.off_partial);
-
-    const i64 pblocks = (P + 255) / 256;
-    if (pblocks * B > 0x7fffffffll) return fail(EBSP_ERR_SHAPE, "batch too large for one call");
-    if (int rc = check_device()) return rc;
-    if (int rc = plan_windows(pl, ts, nullptr, nullptr, B, P, R, wsp, status, false, st)) return rc;
-    const u32 groups = (u32)(pl.max_win / WINDOWS_PER_BLOCK);
-    const u32 groups_inv = groups > 1 ? (u32)((1ull << 32) / groups) : 0xffffffffu;
-    const unsigned wgrid = (unsigned)((B * (i64)groups + 7) / 8 * 8);
-#define LAUNCH_RANGE(NT_, CT_)                                                                               \
-    LAUNCH(K_RANGE_FAST, (zl_range_fast_kernel<NT_, 16, CT_>), dim3(wgrid), dim3(NT_), ts, B, P, R, info,   \
-           (const CT_*)cross, pl.stride, winstart, winval, pl.max_win, groups, groups_inv, partial)
-    if (pl.cap == 16384) {
-        if (pl.narrow) LAUNCH_RANGE(1024, unsigned short); else LAUNCH_RANGE(1024, u32);
-    } else if (pl.cap == 8192) {
-        if (pl.narrow) LAUNCH_RANGE(512, unsigned short); else LAUNCH_RANGE(512, u32);
-    } else {
-        if (pl.narrow) LAUNCH_RANGE(256, unsigned short); else LAUNCH_RANGE(256, u32);
+    RangePart* part = pl.multi ? (RangePart*)workspace : nullptr;        // (one slice needs none)
+    i64 slices = 1;
+    if (pl.multi) {
+        // Two workgroups on every CU; one where that leaves a slice little to read against what it pays per row (its ends
+        // and two searches), and four entries of a row or more.  Slices 4 / 8 / 16 / 32 / 64, us: 64 of 1024 x 4096 804 / 604
+        // / 767 / 1066 / 1651, 8 of them - / - / 251 / 226 / 243; 16 of 1000 x 150 116 / 83 / 74 / 92 / -, one of them 87 /
+        // 53 / 41 / 38 / -.
+        slices = 2 * GENERAL_GRID / B;
+        if (slices > 1 && n / slices <= RANGE_SMALL) slices = GENERAL_GRID / B;
+        const i64 most = n / 2048 < R / 4 ? n / 2048 : R / 4;
+        if (slices > most) slices = most;
+        if (slices < (R + 2047) / 2048) slices = (R + 2047) / 2048;      // eight cells per iteration
+        const i64 room = (i64)(pl.bytes / (sizeof(RangePart) * (size_t)B));
+        if (slices > room) slices = room;
+        if (slices > 0x7fffffffll / B) slices = 0x7fffffffll / B;
+        if (slices < 1) slices = 1;
     }
-#undef LAUNCH_RANGE
-    // what the fast kernel left: the sort-based search, one workgroup per marked window
-    // the windows the fast kernel marked; more workgroups than fit at once, so that uneven shares even out
-    if (pl.cap <= 4096)       // such windows fit a 512-thread workgroup's sort (three workgroups per CU)
-        LAUNCH(K_RANGE_WINDOW, (zl_range_window_kernel<512, 16>), dim3(8 * GENERAL_GRID), dim3(512),
-               ts, B, P, R, info, cross, pl.narrow, pl.stride, winstart, winval, pl.max_win, partial, status);
-    else
-        LAUNCH(K_RANGE_WINDOW, (zl_range_window_kernel<LARGE_NT, LARGE_ITEMS>), dim3(4 * GENERAL_GRID), dim3(LARGE_NT),
-               ts, B, P, R, info, cross, pl.narrow, pl.stride, winstart, winval, pl.max_win, partial, status);
-    LAUNCH(K_FINISH, (zl_finish_kernel<256>), dim3((unsigned)(pblocks * B)), dim3(256),
-           ts, nullptr, nullptr, P, R, info, (const SegEntry*)(wsp + pl.off_seg), (const void*)cross, pl.narrow, pl.stride,
-           partial, pl.max_win, barrier, iters, dmin);
+    // whole waves walk a row's stretch where it is long enough
+    int lanes_log = 6;
+    while (lanes_log > 0 && (1ll << lanes_log) * slices * 4 > 5 * (i64)R) --lanes_log;
+    const i64 cells = 8 * (R / slices);
+    const dim3 grid((unsigned)(B * slices));
+#define LAUNCH_SLICE(NT_, NB_)                                                                               \
+    LAUNCH(K_RANGE_FAST, (zl_range_fast_kernel<NT_, NB_>), grid, dim3(NT_), ts, P, R, (u32)slices, lanes_log, part, \
+           barrier, iters, dmin, status)
+    // Workgroups of 512 threads and 16384 cells (two per CU) for slices of many entries, of 256 and 4096 (six) for others,
+    // of 512 where few of them have many rows to search.  512 x 16384 / 256 x 4096, us: 1024 of 256 x 1024 518 / 830 (8192
+    // cells), 1000 of 300 x 300 244 / 283, 1000 of 500 x 100 223 / 244; 2000 of 300 x 60 254 / 225, 4096 of 64 x 256 258 /
+    // 172.  256 / 512 threads, 4096 cells: one of 1000 x 150 41.8 / 38.1, 8000 of 300 x 30 422 / 497.
+    if (n / slices > RANGE_SMALL || cells > 8192) LAUNCH_SLICE(512, 16384);
+    else if (cells > 4096) LAUNCH_SLICE(256, 8192);
+    else if (P > 256 && B * slices <= 2 * GENERAL_GRID) LAUNCH_SLICE(512, 4096);
+    else LAUNCH_SLICE(256, 4096);
+#undef LAUNCH_SLICE
+    LAUNCH(K_RANGE_WINDOW, (zl_range_window_kernel<512, 16>), dim3((unsigned)(B < 2 * GENERAL_GRID ? B : 2 * GENERAL_GRID)),
+           dim3(512), ts, B, P, R, (u32)slices, (const RangePart*)part, barrier, iters, dmin, status);
     return EBSP_OK;
 }
 

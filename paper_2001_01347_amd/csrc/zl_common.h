@@ -66,6 +66,8 @@ __device__ __forceinline__ u64 uniform(u64 x) { return (u64)uniform((u32)x) | ((
 
 // The value that lane 63 holds, for every lane (scalar registers).
 __device__ __forceinline__ u32 last_lane(u32 x) { return (u32)__builtin_amdgcn_readlane((int)x, WAVE - 1); }
+__device__ __forceinline__ u64 last_lane(u64 x);
+__device__ __forceinline__ i64 last_lane(i64 x) { return (i64)last_lane((u64)x); }
 __device__ __forceinline__ u64 last_lane(u64 x) { return (u64)last_lane((u32)x) | ((u64)last_lane((u32)(x >> 32)) << 32); }
 
 struct OpMin {

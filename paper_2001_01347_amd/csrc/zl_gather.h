@@ -27,7 +27,7 @@ namespace {
 // Returns the number of entries; nothing is loaded if it exceeds `cap`.
 constexpr u64 FIRST_OF_ROW = 1ull << 32, FIRST_OF_SEGMENT = 1ull << 33;      // predicted rows
 constexpr int PRED_ROW_SHIFT = 34;        // predicted rows: the row number sits above the two flags
-constexpr u32 SRC_INDEX = (1u << 29) - 1u, SRC_ROW = 1u << 29, SRC_SEGMENT = 1u << 30, SRC_LAST = 1u << 31;   // stored rows
+constexpr u32 SRC_INDEX = (1u << 29) - 1u, SRC_ROW = 1u << 29, SRC_SEGMENT = 1u << 30;   // stored rows
 // rows a thread takes per round of sweep 1: one round covers 1024 rows
 template <int NT> constexpr int ROWS_PER_THREAD = NT >= 1024 ? 1 : 1024 / NT;
 constexpr int WINDOWS_PER_BLOCK = 2;      // consecutive windows a workgroup handles, one after the other
@@ -115,14 +115,12 @@ __device__ __forceinline__ void gather_batch(const u64* recs, const char* bytes,
 // Sweep 1 of the window gather (see above): a source word for every entry of the window in
 // its slot.  Returns the number of entries (none is written if they exceed `cap`).  For the rows
 // without an entry in the window the distances from their last value before it to the window
-// start are summed into before_sum and their maximum goes to before_max.  WITH_LAST marks a
-// row's very last entry too (stored rows only).
-template <int NT, class CT, bool PRED, bool WITH_LAST>
+// start are summed into before_sum.
+template <int NT, class CT, bool PRED>
 __device__ __forceinline__ int zl_place_rows(const Smem& sm, const Rows& rw, u64 start64, int cap,
                                              const u32 (&lo0)[ROWS_PER_THREAD<NT>], const u32 (&hi0)[ROWS_PER_THREAD<NT>],
-                                             u64& before_sum, u32& before_max)
+                                             u64& before_sum)
 {
-    static_assert(!(PRED && WITH_LAST), "the last-of-row mark is for stored rows");
     const u32 start = (u32)start64;                          // low word of the window's first value (absolute)
     const bool wide = rw.wide;                               // the instance's value spread needs more than 32 bits
     const int tid = threadIdx.x;
@@ -190,17 +188,13 @@ __device__ __forceinline__ int zl_place_rows(const Smem& sm, const Rows& rw, u64
                         dst[i + 1] = first + i + 1;
                     }
                     if (i < n) dst[i] = first + i;
-                    if (WITH_LAST && hi[c] == (u32)rw.R)             // the row's very last entry (after the stores above, same thread)
-                        dst[n - 1] = (first + n - 1) | (n == 1 ? marks : 0u) | SRC_LAST;
                 }
                 slot += n;
             }
         }
 #pragma unroll
         for (int c = 0; c < RPT; ++c) {                      // below 2^32 in an instance whose value spread is (the others: above)
-            const u32 gone = start - before[c];
-            before_sum += (u64)gone;
-            before_max = gone > before_max ? gone : before_max;   // (only searches of such instances use the maximum)
+            before_sum += (u64)(start - before[c]);
         }
     }
     __syncthreads();
@@ -215,8 +209,7 @@ __device__ __forceinline__ int zl_delta_rows(const Smem& sm, const Rows& rw, u64
     const u64* recs = sm.recs;
     const char* bytes = (const char*)rw.inst;
     const u32 start = (u32)(rw.base + a);                    // low word of the window's first value
-    u32 unused = 0;
-    const int total = zl_place_rows<NT, CT, PRED, false>(sm, rw, rw.base + a, cap, lo0, hi0, w0, unused);
+    const int total = zl_place_rows<NT, CT, PRED>(sm, rw, rw.base + a, cap, lo0, hi0, w0);
     if (total > cap) return total;
 
     constexpr int G0 = ITEMS < GATHER_BATCH ? ITEMS : GATHER_BATCH;

@@ -11,9 +11,8 @@ namespace {
 // barrier c waits at least lb(c) = sum_p max(0, c - last entry of row p).  For any value x >= thr the largest entry
 // up to x is a candidate and waits at most ub = sum_p (x - last entry of row p up to x).  So no value above C with
 // lb(C) >= ub can be the minimum (beyond C lb grows strictly; ties below it are kept), and the fine bins behind C's
-// are dropped: the crossing table, the bin counts and the windows all end there.  The range objective has
-// max_p instead of the sum in ub and c - (the earliest row end) for lb.  x = the earliest row end (or thr): until then
-// lb is 0.  Rows are searched for x from where evenly spaced entries would put it, C is found from above by Newton's
+// are dropped: the crossing table, the bin counts and the windows all end there.  x = the earliest row end (or thr): until
+// then lb is 0.  Rows are searched for x from where evenly spaced entries would put it, C is found from above by Newton's
 // method on the convex lb.  Rows are read whole for their order check all the same.
 // Config 5 (workers whose iterations take 20 to 200 ms) keeps 28 % of its entries, config 4 (two groups 2.5 times apart)
 // 81 %.  On config 5 it takes 22 us (zl_bounds 15 -> 37); for which batches: CUT_MIN_WINDOWS.
@@ -22,7 +21,7 @@ constexpr int CUT_STEPS = 16;
 
 // The last value that can win (see above), at most ii.range.
 template <int NT>
-__device__ __forceinline__ u64 cut_value(const Rows& ends, int P, const InstInfo& ii, u64 min_last, bool summed,
+__device__ __forceinline__ u64 cut_value(const Rows& ends, int P, const InstInfo& ii, u64 min_last,
                                          u64* row_end, u64* red)
 {
     constexpr int NW = NT / WAVE;
@@ -33,10 +32,9 @@ __device__ __forceinline__ u64 cut_value(const Rows& ends, int P, const InstInfo
         const u64 f = (u64)ends.value(p, 0) - (u64)ii.base, l = (u64)ends.value(p, (u32)ends.R - 1) - (u64)ii.base;
         row_end[p] = l;                               // (read by this thread alone)
         const u64 gone = x - last_up_to([&](u32 i) { return (u64)ends.value(p, i) - (u64)ii.base; }, (u32)ends.R - 1, f, l, x);
-        mine = summed ? mine + gone : (gone > mine ? gone : mine);
+        mine += gone;
     }
-    const u64 ub = summed ? block_reduce<u64, NT>(mine, red, OpAdd()) : block_reduce<u64, NT>(mine, red, OpMax());
-    if (!summed) return ii.range - min_last > ub ? min_last + ub : ii.range;
+    const u64 ub = block_reduce<u64, NT>(mine, red, OpAdd());
     u64 C = ii.range;
     for (int it = 0; it < CUT_STEPS; ++it) {
         u64 lb = 0, n = 0;
@@ -62,7 +60,7 @@ template <int NT>
 __global__ __launch_bounds__(NT) void zl_bounds_kernel(
     const i64* __restrict__ ts, const i64* __restrict__ le, const i64* __restrict__ iv, int P, int R, int bins,
     InstInfo* __restrict__ info, SegEntry* __restrict__ segtab, uint2* __restrict__ rowpar, int* __restrict__ status,
-    bool summed, bool cut, i64* __restrict__ best = nullptr)
+    bool cut, i64* __restrict__ best = nullptr)
 {
     static_assert(NT >= SEGS, "one thread per segment");
     if (best && threadIdx.x == 0) best[blockIdx.x] = INT64_MAX;     // the instance's best upper bound so far (the sweep's slices share it)
@@ -103,7 +101,7 @@ __global__ __launch_bounds__(NT) void zl_bounds_kernel(
     ii.nwin = 0;
     ii.flags = backwards ? (u32)EBSP_STATUS_UNSORTED : 0u;
     ii.wide_steps = 0;
-    if (summed && ii.range > (u64)INT64_MAX / (u64)P) ii.flags |= EBSP_STATUS_OVERFLOW;    // P waits are summed
+    if (ii.range > (u64)INT64_MAX / (u64)P) ii.flags |= EBSP_STATUS_OVERFLOW;    // P waits are summed
     if (backwards) ii.range = 0;                      // nothing downstream may rely on such rows
     const int bl = bit_length(ii.range);
     ii.wshift = bl > 32 ? (u32)(bl - 32) : 0u;
@@ -115,7 +113,7 @@ __global__ __launch_bounds__(NT) void zl_bounds_kernel(
     u64 end = ii.range;                               // the last value that is searched
     if (cut && P <= CUT_ROWS && ii.flags == 0) {      // (the same in every thread)
         const i64 last_min = block_reduce<i64, NT>(mnl, red, OpMin());
-        if (last_min >= base) end = cut_value<NT>(ends, P, ii, (u64)last_min - (u64)base, summed, row_end, (u64*)red);
+        if (last_min >= base) end = cut_value<NT>(ends, P, ii, (u64)last_min - (u64)base, row_end, (u64*)red);
     }
     const u64 xend = end >> ii.wshift;
     // how many entries each segment holds if every row's R entries are evenly spaced from its first to its last value

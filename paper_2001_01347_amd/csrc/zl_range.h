@@ -10,8 +10,8 @@ namespace {
 // d(c) = c - min_p last_p(c); the search returns the first minimum over the
 // timestamps c >= max_p t[p][0] (Algorithm 2 evaluates exactly these states of Z).
 //
-// One value interval [a, el] of the rows in `rw` (all of an instance, or one window
-// of the multi-window path) is handled by one workgroup: the entries are gathered as
+// The general search (zl_range_window), for what the search by successors below gives up: one value
+// interval [a, el] of whole rows is handled by one workgroup: the entries are gathered as
 // (key = value - a, next = the same worker's next value - a, or NEVER) plus, for the
 // first entry of a row inside the interval, gone = a - the worker's last value
 // before the interval (NEVER if the worker has none: it has not finished an
@@ -283,394 +283,829 @@ __device__ __forceinline__ void zl_range_window(const Smem& sm, const Rows& rw, 
 }
 
 // ---------------------------------------------------------------------------
-// The fast form of the range search for one window of the multi-window path:
-// value buckets instead of a sort, as for the summed wait.  With next(x) = the same
-// worker's next value and gone(x) = how far the worker's previous value lies
-// before the window (for a row's first entry in it; 0 otherwise),
-//   min(Z) at time c  =  - max{ gone(x) : x > c }              if that is positive
-//                        (some worker still stands before the window), else
-//                     =  min{ x <= c : next(x) > c }.
-// Per bucket b: reach(b) = max next, far(b) = max gone, both by LDS atomics while the
-// entries are gathered.  M = prefix maximum of reach, F = suffix maximum of far.  The
-// entry that is min(Z) at time c lies in the first bucket with M > c, so for every c
-// of bucket b: lo(first bucket with M > lo(b)) <= min(Z) <= hi(first bucket with M >
-// hi(b)) (or -F on either side while F > 0): an upper bound of d for some candidate of
-// the bucket and a lower bound for all of them.  Buckets whose lower bound exceeds the
-// smallest upper bound are dropped.  For the candidates that remain, and for the
-// entries of the buckets that can hold their min(Z) (buckets where M rises, between
-// the bounds of the remaining candidates), key, next and gone are read again through
-// the source words and d is evaluated exactly from that short list.
-// Returns false if the window has to be left to the sort-based search (too many
-// entries for the list to fit behind them, or too many listed).
-template <int NT> constexpr int RANGE_LIST_WORDS = 4 * 2 * NT;      // the short list: 2*NT entries of four words
-
-
-template <int NT, int ITEMS, class CT>
-__device__ __forceinline__ bool zl_range_bucket_search(const Smem& sm, const Rows& rw, const WinVal& wv, u64 thr,
-                                                       const u32 (&lo)[ROWS_PER_THREAD<NT>],
-                                                       const u32 (&hi)[ROWS_PER_THREAD<NT>],
-                                                       u64& best_d, u32& best_key)
+// The search by successors.  For an entry x let g(x) be the latest of all workers' first entries at or after x, the
+// smallest barrier whose set Z holds nothing before x.  min over c of c - min(Z at c) is the minimum of g(x) - x over
+// the entries x up to `lim`, the earliest of the rows' ends (behind it some worker has no successor): at the best c
+// x = min(Z) gives g(x) <= c, and every g(x) is a candidate whose Z begins at x or later.  g never decreases, so of
+// equal minima the first x has the first barrier.
+//
+// With prev(y) the entry before y in its row (a row's first entry: before everything, so g >= thr), g(x) is the
+// largest y with prev(y) < x.  So no order, count or sum is needed: one LDS word per value cell keeps the largest y
+// whose predecessor falls in the cell, a prefix maximum over the cells gives G, and for x in cell c
+//     G(c - 1) <= g(x) <= G(c)        (exactly G(c - 1) if no predecessor in the cell is below x).
+// A cell is 2^sh values wide; the cells span the values up to lim alone, where all rows are still running and their
+// entries lie evenly.
+//
+// Each thread owns NB / NT neighbouring cells: their prefix maximum in place, `seed` before the first of them.
+template <int NT, int NB>
+__device__ __forceinline__ void cells_prefix_max(u32* cells, u32 seed, u32* red)
 {
-    using H = HotCfg<NT, ITEMS, false>;
-    constexpr int NB = H::NB;
-    constexpr int NW = NT / WAVE;
-    static_assert(NB == 2 * NT, "two buckets per thread");
-    constexpr int RANGE_LIST_CAP = 2 * NT;                  // entries of the short list (four words each, behind the source words)
-    const int tid = threadIdx.x;
-    u64* recs = sm.recs;
-    u32* reach = (u32*)(sm.red - H::NB);                    // NB words, later M
-    u32* far = reach + NB;                                  // NB words, later F (exclusive)
-    u32* flag = sm.cnt;                                     // NB words: entry counts, later what a bucket is kept for
-    u32* misc = (u32*)(sm.red + H::RED_WORDS - 3);          // listed holders, lowest and highest kept value, absent rows, listed others
-    reach[tid] = 0; reach[tid + NT] = 0;
-    far[tid] = 0; far[tid + NT] = 0;
-    flag[tid] = 0; flag[tid + NT] = 0;
-    if (tid == 0) { misc[0] = 0; misc[1] = 0xffffffffu; misc[2] = 0; misc[3] = 0; misc[4] = 0; }
-    const char* bytes = (const char*)rw.inst;
-    const u64 a = wv.A;
-    const u32 start = (u32)(rw.base + a);                   // low word of the window's first value
-    u64 unused = 0;
-    u32 absent = 0;
-    const int total = zl_place_rows<NT, CT, false, true>(sm, rw, rw.base + a, H::CAP, lo, hi, unused, absent);
-    best_d = U64_MAX;
-    best_key = 0;
-    if (total > H::CAP - 2 * RANGE_LIST_CAP) return false;
-    if (total == 0) return true;
-    const LinearMap bucket = linear_map((u32)(wv.Elast - a), NB, wv.scale ? wv.scale : 1u, wv.inv52);
-    const u32* words = (const u32*)recs;                    // the source words
-    auto read_entry = [&](u32 src, u32& key, u32& next, u32& gone) {     // an entry through its source word
-        const u32 at = src & SRC_INDEX;
-        const bool inner = (src & SRC_SEGMENT) && !(src & SRC_ROW);   // has a predecessor before the window
-        const bool last = (src & SRC_LAST) != 0;
-        const u32 cur = *(const u32*)(bytes + (at << 3));
-        const u32 nxt = *(const u32*)(bytes + ((at + (last ? 0u : 1u)) << 3));
-        const u32 prv = *(const u32*)(bytes + ((at - (inner ? 1u : 0u)) << 3));
-        key = cur - start;
-        next = last ? NEVER : nxt - start;
-        gone = inner ? start - prv : 0u;
-    };
-    // sweep 2: reach, far and the entry count of every bucket; the keys stay in registers.  The three
-    // words of every entry of a batch are asked for before any of them is used.
-    u32 key[ITEMS];
-    constexpr int RB = ITEMS;                               // (measured: all of a thread's entries at once, 2 % over batches of 8)
-    static_assert(ITEMS % RB == 0, "batches must tile the items");
+    constexpr int CPT = NB / NT;
+    static_assert(CPT >= 4 && CPT % 4 == 0 && NB % NT == 0, "whole 16-byte words per thread");
+    uint4* mine = (uint4*)cells + threadIdx.x * (CPT / 4);
+    u32 top = 0;
 #pragma unroll
-    for (int g = 0; g < ITEMS; g += RB) {
-#pragma unroll
-        for (int j = 0; j < RB; ++j) key[g + j] = 0;
-        if (g * NT < total) {
-            u32 src[RB];
-            u32 cur[RB], nxt[RB], prv[RB];
-#pragma unroll
-            for (int j = 0; j < RB; ++j) {
-                const int q = (g + j) * NT + tid;
-                src[j] = q < total ? words[q] : (SRC_ROW | SRC_LAST);          // beyond the end: entry 0 alone, harmless
-            }
-#pragma unroll
-            for (int j = 0; j < RB; ++j) {
-                const u32 at = src[j] & SRC_INDEX;
-                const u32 up = src[j] >> 29;                                   // the marks: row, segment, last
-                const u32 inner = (up >> 1) & ~up & 1u;                       // has a predecessor before the window
-                const u32 more = ~(up >> 2) & 1u;                              // not the row's last entry
-                cur[j] = *(const u32*)(bytes + (at << 3));
-                nxt[j] = *(const u32*)(bytes + ((at + more) << 3));
-                prv[j] = *(const u32*)(bytes + ((at - inner) << 3));
-            }
-#pragma unroll
-            for (int j = 0; j < RB; ++j) {
-                const int q = (g + j) * NT + tid;
-                const u32 up = src[j] >> 29;
-                const bool inner = ((up >> 1) & ~up & 1u) != 0, last = ((up >> 2) & 1u) != 0;
-                key[g + j] = cur[j] - start;
-                if (q < total) {
-                    const u32 b = bucket(key[g + j]);
-                    atomicAdd(&flag[b], 1u);
-                    atomicMax(&reach[b], last ? NEVER : nxt[j] - start);
-                    if (inner && start != prv[j]) atomicMax(&far[b], start - prv[j]);
-                }
-            }
-        }
+    for (int i = 0; i < CPT / 4; ++i) {
+        const uint4 q = mine[i];
+        const u32 a = q.x > q.y ? q.x : q.y, b = q.z > q.w ? q.z : q.w, m = a > b ? a : b;
+        top = m > top ? m : top;
     }
-    if (absent) atomicMax(&misc[3], absent);
-    __syncthreads();
-    const u32 absent_all = misc[3];
-    const u32 c0 = flag[2 * tid], c1 = flag[2 * tid + 1];
-    const u32 r0 = reach[2 * tid], r1 = reach[2 * tid + 1];
-    const u32 g0 = far[2 * tid], g1 = far[2 * tid + 1];
-    // M: prefix maximum of reach (inclusive), F: maximum of far over the buckets behind (and the absent rows)
-    const u32 m_before = block_excl_scan_op<u32, NT>(r0 > r1 ? r0 : r1, (u32*)sm.red, OpMax());
-    const u32 M0 = m_before > r0 ? m_before : r0, M1 = M0 > r1 ? M0 : r1;
-    u32* mirror = (u32*)recs + ((total + 3) & ~3);          // NT words behind the source words
-    mirror[NT - 1 - tid] = g0 > g1 ? g0 : g1;
-    __syncthreads();
-    const u32 mv = mirror[tid];
-    __syncthreads();
-    const u32 behind_m = block_excl_scan_op<u32, NT>(mv, (u32*)sm.red, OpMax());
-    mirror[NT - 1 - tid] = behind_m;
-    __syncthreads();
-    u32 F1 = mirror[tid];                                   // buckets behind 2*tid + 1
-    F1 = absent_all > F1 ? absent_all : F1;
-    const u32 F0 = g1 > F1 ? g1 : F1;                       // buckets behind 2*tid
-    reach[2 * tid] = M0; reach[2 * tid + 1] = M1;
-    far[2 * tid] = g0 > F0 ? g0 : F0;                       // from here on: the bucket itself included
-    far[2 * tid + 1] = g1 > F1 ? g1 : F1;
-    __syncthreads();
-    // bounds of d over each bucket
-    const u64 need = thr > a ? thr - a : 0;                 // keys >= need are admissible
-    u32 lo0, hi0, lo1, hi1;
-    bucket.bounds_pair(2 * tid, lo0, hi0, lo1, hi1);
-    auto first_above = [&](u32 v) {                          // first bucket with M > v (NB if none)
-        int l = 0, h = NB;
-        while (l < h) { const int m = (l + h) >> 1; if (reach[m] > v) h = m; else l = m + 1; }
-        return l;
-    };
-    auto bounds_of = [&](u32 k, u32 c, u32 g, u32 F, u32 lok, u32 hik, i64& ub, i64& lb) {
-        ub = INT64_MAX; lb = INT64_MAX;
-        if (!c) return;
-        const u32 Fin = g > F ? g : F;                       // workers that may still stand before the window
-        i64 zlow, zhigh;                                     // min(Z) over the bucket lies in [zlow, zhigh]
-        if (Fin) zlow = -(i64)Fin;
-        else {
-            u32 jl = (u32)first_above(lok);
-            jl = jl < k ? jl : k;
-            u32 l2, h2;
-            bucket.bounds(jl, l2, h2);
-            zlow = (i64)l2;
-        }
-        if (F) zhigh = -(i64)F;
-        else {
-            const u32 jh = (u32)first_above(hik);
-            u32 l2, h2 = hik;
-            if (jh < k) bucket.bounds(jh, l2, h2);
-            zhigh = (i64)(h2 < hik ? h2 : hik);
-        }
-        lb = (i64)lok - zhigh;
-        if ((u64)lok >= need) ub = (i64)hik - zlow;
-    };
-    i64 ub0, lb0, ub1, lb1;
-    bounds_of(2 * tid, c0, g0, F0, lo0, hi0, ub0, lb0);
-    bounds_of(2 * tid + 1, c1, g1, F1, lo1, hi1, ub1, lb1);
-    const i64 ubmin = block_reduce<i64, NT>(ub0 < ub1 ? ub0 : ub1, (i64*)sm.red, OpMin());
-    const bool live0 = c0 && (u64)hi0 >= need && lb0 <= ubmin;
-    const bool live1 = c1 && (u64)hi1 >= need && lb1 <= ubmin;
-    if (live0 || live1) {
-        atomicMin(&misc[1], live0 ? lo0 : lo1);
-        atomicMax(&misc[2], live1 ? hi1 : hi0);
-    }
-    __syncthreads();
-    const u32 clo = misc[1], chi = misc[2];                 // all remaining candidates lie in [clo, chi]
-    // buckets where M rises hold the entries that are min(Z) at some time: those between clo and chi
-    const bool holds0 = r0 > m_before && M0 > clo && m_before <= chi;
-    const bool holds1 = r1 > M0 && M1 > clo && M0 <= chi;
-    flag[2 * tid] = (live0 ? 1u : 0u) | (holds0 ? 2u : 0u);
-    flag[2 * tid + 1] = (live1 ? 1u : 0u) | (holds1 ? 2u : 0u);
-    __syncthreads();
-    // the short list: slot and purpose first, then the entries themselves.  Entries of the
-    // buckets that can hold min(Z) fill it from the front, mere candidates from the back.
-    u32* lslot = mirror;                                    // RANGE_LIST_CAP words each
-    u32* lkey = lslot + RANGE_LIST_CAP;
-    u32* lnext = lkey + RANGE_LIST_CAP;
-    u32* lgone = lnext + RANGE_LIST_CAP;
+    u32 run = block_excl_scan_op<u32, NT>(top, red, OpMax());
+    run = seed > run ? seed : run;
 #pragma unroll
-    for (int j = 0; j < ITEMS; ++j) {
-        const int q = j * NT + tid;
-        if (q < total) {
-            const u32 f = flag[bucket(key[j])];
-            if (f & 2u) {
-                const u32 at = atomicAdd(&misc[0], 1u);
-                if (at < (u32)RANGE_LIST_CAP) lslot[at] = (u32)q | (f << 16);
-            } else if (f) {
-                const u32 at = atomicAdd(&misc[4], 1u);
-                if (at < (u32)RANGE_LIST_CAP) lslot[RANGE_LIST_CAP - 1 - at] = (u32)q | (f << 16);
-            }
-        }
+    for (int i = 0; i < CPT / 4; ++i) {
+        uint4 q = mine[i];
+        run = q.x > run ? q.x : run; q.x = run;
+        run = q.y > run ? q.y : run; q.y = run;
+        run = q.z > run ? q.z : run; q.z = run;
+        run = q.w > run ? q.w : run; q.w = run;
+        mine[i] = q;
     }
-    __syncthreads();
-    const int holders = (int)misc[0], others = (int)misc[4];
-    if (holders + others > RANGE_LIST_CAP) return false;
-    const int back = RANGE_LIST_CAP - others;               // the list is [0, holders) and [back, RANGE_LIST_CAP)
-    for (int i = tid; i < holders + others; i += NT) {
-        const int e = i < holders ? i : back + (i - holders);
-        read_entry(words[lslot[e] & 0xffffu], lkey[e], lnext[e], lgone[e]);
-    }
-    __syncthreads();
-    u64 bd = U64_MAX;
-    u32 bk = 0xffffffffu;
-    for (int i = tid; i < holders + others; i += NT) {
-        const int me = i < holders ? i : back + (i - holders);
-        if (!(lslot[me] & 0x10000u)) continue;              // not a candidate, only a possible min(Z)
-        const u32 c = lkey[me];
-        if ((u64)c < need) continue;
-        const u32 b = bucket(c);
-        u32 out = 0;                                         // how far back the workers stand whose first entry lies behind c
-        if (far[b]) {
-            out = b + 1 < (u32)NB ? far[b + 1] : absent_all;
-            for (int e = 0; e < holders; ++e)
-                if (lkey[e] > c && lgone[e] > out) out = lgone[e];
-            for (int e = back; e < RANGE_LIST_CAP; ++e)
-                if (lkey[e] > c && lgone[e] > out) out = lgone[e];
-        }
-        u64 d;
-        if (out) {
-            d = (u64)c + out;
-        } else {
-            u32 z = c;                                       // the candidate itself is in Z unless its successor is equal
-            for (int e = 0; e < holders; ++e)
-                if (lkey[e] <= c && lnext[e] > c && lkey[e] < z) z = lkey[e];
-            d = (u64)(c - z);
-        }
-        if (d < bd || (d == bd && c < bk)) { bd = d; bk = c; }
-    }
-    wave_argmin(bd, bk);
-    const int lane = tid & (WAVE - 1), wave = tid >> 6;
-    u64* red = sm.red;
-    if (lane == WAVE - 1) { red[wave] = bd; red[NW + wave] = bk; }
-    __syncthreads();
-    bd = red[0];
-    bk = (u32)red[NW];
-#pragma unroll
-    for (int w = 1; w < NW; ++w) {
-        const u64 od = red[w];
-        const u32 ok = (u32)red[NW + w];
-        if (od < bd || (od == bd && ok < bk)) { bd = od; bk = ok; }
-    }
-    best_d = bd;
-    best_key = bk;
-    return true;
 }
 
-template <int NT, int ITEMS, class CT>
-struct RangeSearch {
-    static constexpr bool PREDICTED = false;
-    __device__ __forceinline__ static void run(const Smem& sm, const Rows& rw, const WinVal& wv, const InstInfo& ii, bool hot,
-                                               const u32 (&lo)[ROWS_PER_THREAD<NT>], const u32 (&hi)[ROWS_PER_THREAD<NT>],
-                                               Partial* __restrict__ out)
-    {
-        Partial r;
-        r.wait = U64_MAX;
-        r.brel = 0;
-        if (wv.Elast >= wv.A) {
-            bool done = false;
-            if (hot && !(ii.range >> 31)) {                  // `gone` and `next` as positive 32-bit numbers
-                u32 key;
-                done = zl_range_bucket_search<NT, ITEMS, CT>(sm, rw, wv, ii.thr, lo, hi, r.wait, key);
-                if (done) r.brel = r.wait == U64_MAX ? 0 : wv.A + key;
-            }
-            if (!done) { r.wait = U64_MAX; r.brel = DEFERRED_WINDOW; }
-        }
-        __syncthreads();                          // everyone is done with LDS before the next window
-        if (threadIdx.x == 0) *out = r;
-    }
+// First of equal minima (d, x) over the workgroup, for every thread: two words, or (NARROW: both below 2^32) packed in one.
+struct Best {
+    u64 d, x;
+    __device__ __forceinline__ bool before(const Best& o) const { return d < o.d || (d == o.d && x < o.x); }
 };
-
-// The fast range search over all windows; windows it cannot take are marked for
-// zl_range_window_kernel.
-template <int NT, int ITEMS, class CT>
-__global__ __launch_bounds__(NT, (NT > 512 ? 4 : 6)) void zl_range_fast_kernel(
-    const i64* __restrict__ ts, i64 B, int P, int R,
-    const InstInfo* __restrict__ info, const CT* __restrict__ cross, int stride,
-    const u32* __restrict__ winstart, const WinVal* __restrict__ winval, int max_win, u32 groups, u32 groups_inv,
-    Partial* __restrict__ partial)
+template <class T, int NT, class Op>
+__device__ __forceinline__ T block_reduce_any(T v, u64* red, Op op)
 {
-    // the source words of at most CAP - 2 * (2*NT) entries, then the short list
-    using L = WinHot<NT, ITEMS, false, RANGE_LIST_WORDS<NT> - 4 * NT>;
-    __shared__ __align__(16) unsigned char smem[L::BYTES];
-    const Smem sm = L::carve(smem);
-    window_pairs<NT, ITEMS, CT, RangeSearch<NT, ITEMS, CT>>(sm, ts, nullptr, B, P, R, info, cross, stride, winstart,
-                                                           winval, max_win, groups, groups_inv, partial);
+    if constexpr (NT == WAVE) return last_lane(wave_scan(v, op));
+    else return block_reduce<T, NT>(v, (T*)red, op);
+}
+template <int NT>
+__device__ __forceinline__ Best block_first_min(Best v, u64* red)
+{
+    constexpr int NW = NT / WAVE;
+    wave_argmin(v.d, v.x);
+    if constexpr (NW == 1) return Best{last_lane(v.d), last_lane(v.x)};
+    const int lane = threadIdx.x & (WAVE - 1), wave = threadIdx.x >> 6;
+    if (lane == WAVE - 1) { red[wave] = v.d; red[NW + wave] = v.x; }
+    __syncthreads();
+    v = Best{red[0], red[NW]};
+#pragma unroll 4
+    for (int w = 1; w < NW; ++w) {
+        const Best o{red[w], red[NW + w]};
+        if (o.before(v)) v = o;
+    }
+    __syncthreads();
+    return v;
 }
 
-// Instances of at most CAP_WIDE entries: one workgroup each.
-template <int NT, int ITEMS>
-__global__ __launch_bounds__(NT) void zl_range_instance_kernel(
-    const i64* __restrict__ ts, int P, int R,
-    i64* __restrict__ barrier, int* __restrict__ iters, i64* __restrict__ dmin,
-    int* __restrict__ status)
+// An instance's facts from the ends of its rows.
+struct RowEnds {
+    i64 base;            // smallest first entry; the rest relative to it
+    u64 thr, lim, range; // largest first, smallest last and largest last entry
+};
+template <int NT>                                          // own_first, own_last: of row threadIdx.x
+__device__ __forceinline__ RowEnds row_ends(const i64* __restrict__ inst, int P, int R, u64* red, u64& own_first, u64& own_last)
 {
-    using C = WinCfg<NT, ITEMS>;
-    __shared__ __align__(16) unsigned char smem[C::BYTES];
-    const Smem sm = carve<NT, ITEMS>(smem);
-    const int tid = threadIdx.x;
-    const i64 b = blockIdx.x;
-    const i64* __restrict__ inst = ts + b * (i64)P * R;
-    i64 mn = INT64_MAX, mxf = INT64_MIN, mxl = INT64_MIN;
-    for (int p = tid; p < P; p += NT) {
+    i64 mn = INT64_MAX, mxf = INT64_MIN, mxl = INT64_MIN, nml = INT64_MIN;       // the last one: of ~last
+    own_first = own_last = 0;
+    for (int p = threadIdx.x; p < P; p += NT) {
         const i64 f = inst[(size_t)p * R], l = inst[(size_t)p * R + R - 1];
+        if (p < NT) { own_first = (u64)f; own_last = (u64)l; }
         mn = f < mn ? f : mn;
         mxf = f > mxf ? f : mxf;
         mxl = l > mxl ? l : mxl;
+        nml = ~l > nml ? ~l : nml;
     }
-    i64 base, first_max, last_max;
-    block_bounds<NT>(mn, mxf, mxl, (i64*)sm.red, base, first_max, last_max);
-    const u64 range = (u64)last_max - (u64)base;
-    const u64 thr = (u64)first_max - (u64)base;
-    u32 flags = 0;
-    u64 best_d = U64_MAX, best_rel = 0;
-    int bad = 0;
-    Rows rw;
-    rw.inst = inst; rw.le = nullptr; rw.iv = nullptr; rw.P = P; rw.R = R; rw.base = (u64)base;
-    rw.cr = nullptr; rw.narrow = false; rw.wide = false; rw.stride = 0; rw.k0 = rw.k1 = 0;
-    if (range > RANGE_PIECE_MAX) zl_range_window<NT, ITEMS, true>(sm, rw, thr, 0ull, range, best_d, best_rel, bad);
-    else zl_range_window<NT, ITEMS, false>(sm, rw, thr, 0ull, range, best_d, best_rel, bad);
-    if (__syncthreads_or(bad)) flags |= EBSP_STATUS_UNSORTED;
-    if (best_d == U64_MAX) { best_d = 0; best_rel = 0; }
-    const i64 bar = (i64)((u64)base + best_rel);
-    if (tid == 0) {
-        barrier[b] = bar;
-        dmin[b] = (i64)best_d;
-        if (status) status[b] = (int)flags;
-    }
-    for (int p = tid; p < P; p += NT)
-        iters[b * (i64)P + p] = zl_iters(inst + (size_t)p * R, R, bar);
+    mn = block_reduce_any<i64, NT>(mn, red, OpMin());
+    mxf = block_reduce_any<i64, NT>(mxf, red, OpMax());
+    mxl = block_reduce_any<i64, NT>(mxl, red, OpMax());
+    nml = block_reduce_any<i64, NT>(nml, red, OpMax());
+    RowEnds e;
+    e.base = (i64)uniform((u64)mn);
+    own_first -= (u64)e.base;
+    own_last -= (u64)e.base;
+    e.thr = uniform((u64)mxf - (u64)mn);
+    e.range = uniform((u64)mxl - (u64)mn);
+    e.lim = ~nml < mn ? 0ull : uniform((u64)~nml - (u64)mn);      // (below base only in unsorted rows)
+    return e;
+}
+__device__ __forceinline__ u32 cell_shift(u64 span, int log2_cells)     // smallest sh with span >> sh below 2^log2_cells
+{
+    const int bl = bit_length(span);
+    return bl > log2_cells ? (u32)(bl - log2_cells) : 0u;
 }
 
-// The windows zl_range_fast_kernel marked: the sort-based search.  A fixed grid; every
-// workgroup looks through its share of the window results for the marks and handles the
-// marked windows one after the other.  Results go to `partial` (reduced by
-// zl_finish_kernel like those of the summed-wait search).
+// First index in [0, R) of a sorted row whose value relative to base is at least v (R: none), given the row's ends f and
+// l (relative): eight neighbouring entries at once from where evenly spaced ones would put it (one round trip; where
+// iteration times vary by a fifth they hold it as a rule), galloping from there.  (Any row: the search ends and stays
+// inside.)
+struct RowProbe {
+    static constexpr u32 W = 8;
+    const i64* row;
+    u32 R, s;
+    u64 base, v, f, l;
+    i64 w[W];
+    __device__ __forceinline__ RowProbe(const i64* row_, u32 R_, u64 base_, u64 f_, u64 l_, u64 v_)
+        : row(row_), R(R_), base(base_), v(v_), f(f_), l(l_)
+    {
+        s = 0;
+        if (R > W && f < v && v <= l) {
+            s = (u32)((float)(v - f) / (float)(l - f) * (float)(R - 1));
+            s = s > W / 2 - 1 ? s - (W / 2 - 1) : 0u;
+            s = s < R - W ? s : R - W;
+        }
+#pragma unroll
+        for (u32 k = 0; k < W; ++k) w[k] = row[s + k < R ? s + k : R - 1];
+    }
+    __device__ __forceinline__ u32 index() const
+    {
+        if (f >= v) return 0;
+        if (l < v) return R;
+        u32 below = 0;
+#pragma unroll
+        for (u32 k = 0; k < W; ++k) below += (u64)w[k] - base < v ? 1u : 0u;
+        if (R <= W) return below < R ? below : R;          // (the last entry stands for those that are not there: not below)
+        if (below > 0 && below < W) return s + below;
+        u32 lo = 0, hi = R - 1, step = W;                  // the entry at lo is below v, the one at hi not
+        if (below) {
+            lo = s + W - 1;
+            while (lo + step < hi) {
+                if ((u64)row[lo + step] - base < v) { lo += step; step *= 2; } else { hi = lo + step; break; }
+            }
+        } else {
+            hi = s;                                        // (s > 0, or the row is not sorted)
+            while (hi > lo + step) {
+                if ((u64)row[hi - step] - base >= v) { hi -= step; step *= 2; } else { lo = hi - step; break; }
+            }
+        }
+        while (hi > lo + 1) {
+            const u32 m = lo + ((hi - lo) >> 1);
+            if ((u64)row[m] - base < v) lo = m; else hi = m;
+        }
+        return hi;
+    }
+};
+__device__ __forceinline__ u32 row_first_at_least(const i64* __restrict__ row, u32 R, u64 base, u64 v)
+{
+    return RowProbe(row, R, base, (u64)row[0] - base, (u64)row[R - 1] - base, v).index();
+}
+
+// Every row's entries up to the barrier (relative to base); thread p knows the ends of row p.
+template <int NT>
+__device__ __forceinline__ void store_iters(const i64* __restrict__ inst, int P, int R, u64 base, u64 barrier, u64 own_first, u64 own_last,
+                                            int* __restrict__ iters)
+{
+    for (int p = threadIdx.x; p < P; p += NT) {
+        const i64* row = inst + (size_t)p * R;
+        const u64 f = p < NT ? own_first : (u64)row[0] - base, l = p < NT ? own_last : (u64)row[R - 1] - base;
+        iters[p] = (int)RowProbe(row, (u32)R, base, f, l, barrier + 1).index();
+    }
+}
+
+// Instances of at most 4096 entries: one workgroup each, the entries held in registers (wave w holds elements
+// [w * 64 * items, (w + 1) * 64 * items), 64 neighbouring ones per item: prev(y) sits in the neighbouring lane).
+// Every entry reads the two words of its own cell, so its bounds are tight: G(c - 1) - x and G(c) - x.  The entry with
+// the smallest upper bound is the answer unless some entry's lower bound is smaller; those are evaluated one by one, the
+// smallest first, each by one pass over the registers, until none is left below the best.  How many that takes depends
+// on the values alone (about one where iteration times vary); RANGE_TRIES of them leave the instance to
+// zl_range_window_kernel where SORT_REST says that it follows.
+// Bound by the chain of one workgroup's steps and by the vector ALU.  4096 of 16 x 64: 77.8 us by a radix sort of
+// every instance, 23.2 so; 16384 of 64 x 30: 607, 160.
+constexpr int RANGE_TRIES = 96;
+
+// Values spread over 2^32 and more (`wide`): keys, cells and bounds from the values shifted down to 32 bits, which widens
+// the bounds; the candidates are then entries, evaluated from the values in memory.
+template <int NT, int ITEMS, int NB, bool SORT_REST>
+__device__ __forceinline__ bool zl_range_registers(u32* cells, u64* red, const i64* __restrict__ inst, int wbase, const i64 (&v)[ITEMS],
+                                                   i64 ahead, u32 have, u32 heads, const RowEnds& ends, Best& best, int& bad)
+{
+    constexpr int LOG = __builtin_ctz((unsigned)NB);
+    const bool wide = (ends.range >> 32) != 0;
+    const u32 ms = wide ? (u32)bit_length(ends.range) - 32u : 0u;
+    const u32 lim = (u32)(ends.lim >> ms), thr = (u32)(ends.thr >> ms);
+    const u32 sh = cell_shift(lim, LOG);
+    const int lane = threadIdx.x & (WAVE - 1);
+    u32 inner = have & ~heads;                             // items with an entry before them in their row
+    u32 key[ITEMS];
+    u32 over = 0;
+#pragma unroll
+    for (int j = 0; j < ITEMS; ++j) {
+        const u64 rel = ((u64)v[j] - (u64)ends.base) >> ms;
+        over |= (have >> j) & 1u ? (u32)(rel >> 32) : 0u;  // beyond the range only in unsorted rows
+        key[j] = (u32)rel;
+    }
+    bad |= over != 0;
+    asm volatile("" : "+v"(have), "+v"(inner));            // (the items' tests as lane masks would fill the scalar registers)
+    const u32 first_prev = (u32)(((u64)ahead - (u64)ends.base) >> ms);
+    auto prev_of = [&](int j) -> u32 {
+        const u32 p = dpp_take<DPP_WAVE_SHR1, 0xf>(0u, key[j]);
+        const u32 edge = j > 0 ? last_lane(key[j > 0 ? j - 1 : 0]) : first_prev;
+        return lane == 0 ? edge : p;
+    };
+#pragma unroll
+    for (int j = 0; j < ITEMS; ++j) {
+        const u32 p = prev_of(j);
+        if ((inner >> j) & 1u) {
+            bad |= p > key[j];
+            if (p <= lim) atomicMax(&cells[p >> sh], key[j]);
+        }
+    }
+    asm volatile("" : "+v"(have), "+v"(inner));
+    if (wide) {                                            // the order of values whose keys are equal
+#pragma unroll 1
+        for (int j = 0; j < ITEMS; ++j)
+            if ((inner >> j) & 1u) {
+                const i64* e = inst + (wbase + j * WAVE + lane);
+                bad |= e[0] < e[-1];
+            }
+    }
+    __syncthreads();
+    cells_prefix_max<NT, NB>(cells, thr, (u32*)red);
+    if (threadIdx.x == 0) cells[-1] = thr;
+    __syncthreads();
+    // A bound (in keys) and what its candidate is called, in one word: its key, or (wide) its index.
+    auto lower = [&](int j) -> u64 {
+        const u32 g0 = cells[(int)(key[j] >> sh) - 1];
+        return ((u64)(g0 > key[j] ? g0 - key[j] : 0u) << 32) | (wide ? (u32)(wbase + j * WAVE + lane) : key[j]);
+    };
+    u64 ub = U64_MAX, next = U64_MAX;
+#pragma unroll
+    for (int j = 0; j < ITEMS; ++j)
+        if (((have >> j) & 1u) && key[j] <= lim) {
+            const u32 g1 = cells[key[j] >> sh];
+            const u64 u = ((u64)(g1 > key[j] ? g1 - key[j] : 0u) << 32) | key[j], l = lower(j);
+            ub = u < ub ? u : ub;
+            next = l < next ? l : next;
+        }
+    ub = block_reduce_any<u64, NT>(ub, red, OpMin());
+    next = block_reduce_any<u64, NT>(next, red, OpMin());
+    // (wide: the bound is no candidate, and an entry as good as it may be the first)
+    Best top{ub >> 32, ub & 0xffffffffull};
+    if (wide) top = Best{((ub >> 32) << ms) | ((1ull << ms) - 1), U64_MAX};
+    for (int tries = 0;; ++tries) {
+        const u64 d0 = next >> 32;
+        if (next == U64_MAX) break;
+        if (wide ? (d0 ? ((d0 - 1) << ms) + 1 : 0ull) > top.d : next >= ((top.d << 32) | top.x)) break;
+        if (SORT_REST && tries == RANGE_TRIES) return false;
+        // nothing below is worth keeping in registers from one try to the next
+#pragma unroll
+        for (int j = 0; j < ITEMS; ++j) asm volatile("" : "+v"(key[j]));
+        asm volatile("" : "+v"(have), "+v"(inner));
+        Best got;
+        if (wide) {
+            const u64 x = (u64)inst[(u32)next] - (u64)ends.base;
+            u64 g = ends.thr;
+#pragma unroll 1
+            for (int j = 0; j < ITEMS; ++j)
+                if ((inner >> j) & 1u) {
+                    const i64* e = inst + (wbase + j * WAVE + lane);
+                    const u64 p = (u64)e[-1] - (u64)ends.base, y = (u64)e[0] - (u64)ends.base;
+                    if (p < x) g = y > g ? y : g;
+                }
+            g = block_reduce_any<u64, NT>(g, red, OpMax());
+            got = x <= ends.lim ? Best{g > x ? g - x : 0ull, x} : Best{U64_MAX, U64_MAX};
+        } else {
+            const u32 x = (u32)next;
+            u32 g = thr;
+#pragma unroll
+            for (int j = 0; j < ITEMS; ++j) {
+                const u32 p = prev_of(j);
+                if (((inner >> j) & 1u) && p < x) g = key[j] > g ? key[j] : g;
+            }
+            g = block_reduce_any<u32, NT>(g, red, OpMax());
+            got = Best{(u64)(g > x ? g - x : 0u), (u64)x};
+        }
+        if (got.before(top)) top = got;
+        u64 after = U64_MAX;
+#pragma unroll
+        for (int j = 0; j < ITEMS; ++j)
+            if (((have >> j) & 1u) && key[j] <= lim) {
+                const u64 l = lower(j);
+                if (l > next) after = l < after ? l : after;
+            }
+        next = block_reduce_any<u64, NT>(after, red, OpMin());
+    }
+    best = top;
+    return true;
+}
+
+template <int NT, int ITEMS, int NB, bool SORT_REST>
+__global__ __launch_bounds__(NT, (NT == 64 ? 5 : 6)) void zl_range_instance_kernel(
+    const i64* __restrict__ ts, int P, int R, int rshift,
+    i64* __restrict__ barrier, int* __restrict__ iters, i64* __restrict__ dmin, int* __restrict__ status)
+{
+    static_assert(ITEMS <= 32, "item masks are one word");
+    __shared__ __align__(16) u32 cellmem[4 + NB];
+    __shared__ u64 red[2 * (NT / WAVE) + 2];
+    u32* const cells = cellmem + 4;                        // cells[-1]: the largest value before the first cell
+    const int tid = threadIdx.x, lane = tid & (WAVE - 1), wave = tid >> 6;
+    const i64 b = blockIdx.x;
+    const int n = P * R;
+    const i64* __restrict__ inst = ts + b * (i64)n;
+    const int items = (n + NT - 1) / NT;
+    const int wbase = wave * WAVE * items;
+    i64 v[ITEMS];
+#pragma unroll
+    for (int j = 0; j < ITEMS; ++j) {
+        const int e = wbase + j * WAVE + lane;
+        v[j] = (j < items && e < n) ? inst[e] : 0;
+    }
+    const i64 ahead = (wbase > 0 && wbase < n) ? inst[wbase - 1] : 0;     // element before the wave's first
+    for (int c = tid; c < NB / 4; c += NT) ((uint4*)cells)[c] = make_uint4(0u, 0u, 0u, 0u);
+    u64 own_first, own_last;                               // the ends of row `tid`
+    const RowEnds ends = row_ends<NT>(inst, P, R, red, own_first, own_last);
+    if constexpr (NT == WAVE) __syncthreads();             // (row_ends passed barriers otherwise)
+    // which items exist, and which are a row's first entry (e / R for e < 2^16 by the rounded-up reciprocal)
+    u32 have = 0, heads = 0;
+    {
+        const int e0 = wbase + lane;
+        const int p0 = rshift >= 0 ? (e0 >> rshift) : (int)__umulhi((u32)e0, 0xffffffffu / (u32)R + 1u);
+        int i = e0 - p0 * R;
+        const int step = WAVE % R;
+#pragma unroll
+        for (int j = 0; j < ITEMS; ++j) {
+            if (j < items && e0 + j * WAVE < n) {
+                have |= 1u << j;
+                if (i == 0) heads |= 1u << j;
+            }
+            i += step;
+            i = i >= R ? i - R : i;
+        }
+    }
+    Best best;
+    int bad = 0;
+    const bool found = zl_range_registers<NT, ITEMS, NB, SORT_REST>(cells, red, inst, wbase, v, ahead, have, heads, ends, best, bad);
+    bad = __syncthreads_or(bad);
+    if (!found) {
+        if (tid == 0) dmin[b] = DEFERRED;
+        return;
+    }
+    const i64 bar = (i64)((u64)ends.base + best.x + best.d);
+    if (tid == 0) {
+        barrier[b] = bar;
+        dmin[b] = (i64)best.d;
+        if (status) status[b] = bad ? (int)EBSP_STATUS_UNSORTED : 0;
+    }
+    store_iters<NT>(inst, P, R, (u64)ends.base, best.x + best.d, own_first, own_last, iters + b * (i64)P);
+}
+
+// ---------------------------------------------------------------------------
+// Larger instances: one workgroup per slice of the values up to lim (all of them, where the batch fills the chip by
+// itself).  The entries are read once, from HBM, and not kept: what bounds it is that one reading (1024 of 256 x 1024:
+// 390 us, 5.5 TB/s, without what follows it) and, behind it, two or three dependent round trips to HBM per cell looked
+// at.  1024 of 256 x 1024: 1822 us by windows of an instance's sorted-out segments (a counting pass, then each entry
+// again with both neighbours), 513 so; 64 of 1024 x 4096 1071, 605; 4096 of 64 x 256 859, 172; one of 1000 x 150 76, 37.
+
+// What a slice found.
+struct RangePart {
+    u64 d, g;            // smallest max(Z) - min(Z) and its barrier, relative to base (d == U64_MAX: no entry)
+    u32 flags;
+    u32 left;            // the slice gave up: the instance is zl_range_window_kernel's
+};
+
+// The pairs of neighbouring entries (i - 1, i), from < i <= to, of a row, by LANES = 2^lanes_log lanes: f(before, entry).
+// Whole waves walk 64 entries a step, four steps asked for ahead, the entry before from the neighbouring lane; fewer
+// lanes (short stretches) load both.
+constexpr int ROW_AHEAD = 4;
+template <class F>
+__device__ __forceinline__ void row_pairs(const i64* __restrict__ row, u32 from, u32 to, int lanes_log, const F& f)
+{
+    const u32 lane = threadIdx.x & (WAVE - 1);
+    if (lanes_log == 6) {
+        constexpr int U = ROW_AHEAD;
+        i64 carry = 0;
+        for (u64 s = from; s <= to; s += U * WAVE) {       // (64 bits: to may be near 2^31)
+            i64 v[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const u64 i = s + u * WAVE + lane;
+                v[u] = row[i <= to ? i : (u64)to];
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const u64 i = s + u * WAVE + lane;
+                i64 p = dpp_take<DPP_WAVE_SHR1, 0xf>((i64)0, v[u]);
+                if (lane == 0) p = carry;
+                carry = (i64)last_lane((u64)v[u]);
+                if (i > from && i <= to) f(p, v[u]);
+            }
+        }
+    } else {
+        const u32 lanes = 1u << lanes_log;
+        for (u64 i = (u64)from + 1 + (lane & (lanes - 1)); i <= to; i += lanes) f(row[i - 1], row[i]);
+    }
+}
+
+// One slice.  Each cell's bounds follow from G at its two ends; cells whose lower bound exceeds the smallest upper bound
+// are dropped.  The cell with the smallest lower bound is looked at first, which as a rule leaves none.  A cell's entries
+// and their successors are found by one search per row, listed, and evaluated exactly (inside a cell only successors of
+// earlier entries of the cell can lie behind G of its first value).  A cell of more entries than the list holds is cut
+// into cells of its own later: such intervals wait on a stack, and where a cell is one value, no list is needed.
+// `cells` words hold (y >> ms) + 1, 0 where no predecessor falls in the cell.
+constexpr int RANGE_ROUND_CELLS = 64;                     // cells looked at together
+constexpr int RANGE_STACK = 96;                           // intervals that wait
+template <int NT, int NB>
+struct SliceSmem {
+    static constexpr int LIST = NT < 512 ? NT : 512;      // entries of the cells looked at together
+    static constexpr int LIVE = NT;                       // cells gathered at a time
+    static_assert(NB <= 65536, "cells are kept as 16-bit numbers");
+    u32 pad[4];
+    u32 cells[NB];                                        // cells[-1] is pad[3]
+    union {
+        struct { u32 lo[NT], hi[NT]; };                   // index ranges of NT rows, while the entries are read
+        struct {
+            u64 lx[LIST], ln[LIST];                       // an entry and its successor
+            u16 lc[LIST], cell[LIVE];                     // its cell's number among those looked at; the cells gathered
+        };
+    };
+    u64 at_start[RANGE_ROUND_CELLS];                      // g of the cell's first value
+    u64 red[2 * (NT / WAVE) + 2];
+    u64 from[RANGE_STACK], to[RANGE_STACK], least[RANGE_STACK];       // intervals and their lower bounds
+    u32 listed, waiting;
+};
+template <bool WIDE> struct SliceWord { using type = u32; };          // values relative to base: below 2^31, or any
+template <> struct SliceWord<true> { using type = u64; };
+
+template <int NT, int NB, bool WIDE>
+__device__ __forceinline__ void zl_range_slice(SliceSmem<NT, NB>& sm, const i64* __restrict__ inst, int P, int R, u32 slices, u32 k,
+                                               int lanes_log, const RowEnds& ends, u64 own_first, u64 own_last, RangePart& out)
+{
+    using V = typename SliceWord<WIDE>::type;
+    constexpr int LOG = __builtin_ctz((unsigned)NB), NW = NT / WAVE, STEPS = NB / NT / 4;
+    static_assert(NB % (4 * NT) == 0 && 4 * STEPS <= 32, "whole steps; a thread's cells are bits of a word");
+    const int tid = threadIdx.x;
+    const u64 base = (u64)ends.base;
+    const u64 width = ends.lim / slices + 1;
+    u64 A = width * k;
+    out = RangePart{U64_MAX, 0ull, 0u, 0u};
+    const bool empty = A > ends.lim;
+    u64 E = ends.lim - A < width ? ends.lim : A + width - 1;              // (if not empty)
+    u32 sh = empty ? 0u : cell_shift(E - A, LOG);
+    const u32 ms = WIDE ? (u32)bit_length(ends.range) - 31u : 0u;
+    const V rest = WIDE ? (V)((1ull << ms) - 1) : (V)0;
+    int bad = 0;
+    u64 start = ends.thr;                                  // g(A)
+    auto pair = [&](i64 p, i64 y) {
+        if (WIDE) {
+            const u64 pr = (u64)p - base, yr = (u64)y - base;
+            bad |= yr < pr;
+            if (pr - A <= E - A) atomicMax(&sm.cells[(u32)((pr - A) >> sh)], (u32)(yr >> ms) + 1u);
+        } else {
+            const u64 yr = (u64)y - base;
+            const u32 p32 = (u32)((u64)p - base), y32 = (u32)yr;
+            bad |= (int)(y32 < p32) | (int)(yr >> 32);     // (in sorted rows all values are below 2^31)
+            if (p32 - (u32)A <= (u32)(E - A)) atomicMax(&sm.cells[(p32 - (u32)A) >> sh], y32 + 1u);
+        }
+    };
+    // the ends of row p, which thread p kept since the first pass over them
+    auto first_in = [&](int p) -> u64 { return p == tid ? own_first : (u64)inst[(size_t)p * R] - base; };
+    auto last_in = [&](int p) -> u64 { return p == tid ? own_last : (u64)inst[(size_t)p * R + R - 1] - base; };
+    const int groups = NT >> lanes_log, group = tid >> lanes_log;
+    if (slices > 1) {
+        // the order of what lies behind lim: the rows' stretches there are shared out among the slices
+        const u32 pieces = (slices + (u32)P - 1u) / (u32)P;
+        const u64 units = (u64)P * pieces;
+        const u64 u0 = units * k / slices, u1 = units * (k + 1) / slices;
+        for (u64 u = u0 + group; u < u1; u += groups) {
+            const i64* row = inst + (size_t)(u / pieces) * R;
+            const u32 q = (u32)(u % pieces);
+            const u32 t0 = row_first_at_least(row, (u32)R, base, ends.lim + 1);     // pairs up to (t0 - 1, t0) are the slices'
+            if (t0 + 1 >= (u32)R) continue;
+            const u64 len = (u64)R - 1 - t0;
+            const u32 from = t0 + (u32)(len * q / pieces), to = t0 + (u32)(len * (q + 1) / pieces);
+            row_pairs(row, from, to, lanes_log, [&](i64 p, i64 y) { bad |= y < p; });
+        }
+    }
+    if (tid == 0) { sm.listed = 0; sm.waiting = 0; }
+    Best best{U64_MAX, U64_MAX};
+    u64 top = U64_MAX;                                     // the best is no larger
+    for (bool whole = slices == 1;; whole = false) {
+        // the entries of all rows in [A, E]; `start` becomes g(A)
+        if (!empty) {
+            u64 far = whole ? start : 0ull;
+            for (int p0 = 0; p0 < P; p0 += NT) {
+                if (p0 > 0) __syncthreads();
+                if (p0 + tid < P && !whole) {
+                    const i64* row = inst + (size_t)(p0 + tid) * R;
+                    const u64 f = first_in(p0 + tid), l = last_in(p0 + tid);
+                    const RowProbe pa(row, (u32)R, base, f, l, A), pe(row, (u32)R, base, f, l, E + 1);
+                    const u32 i0 = pa.index(), i1 = pe.index();
+                    bad |= i1 < i0 || i0 >= (u32)R;
+                    if (i0 < (u32)R) { const u64 s = (u64)row[i0] - base; far = s > far ? s : far; }
+                    sm.lo[tid] = i0;
+                    sm.hi[tid] = i1 < i0 ? i0 : i1;
+                }
+                __syncthreads();
+                const int rows = P - p0 < NT ? P - p0 : NT;
+                for (int r = group; r < rows; r += groups) {
+                    const u32 i0 = whole ? 0u : sm.lo[r], i1 = whole ? (u32)R : sm.hi[r];
+                    const u32 to = i1 < (u32)R ? i1 : (u32)R - 1u;
+                    if (i0 < to) row_pairs(inst + (size_t)(p0 + r) * R, i0, to, lanes_log, pair);
+                }
+            }
+            start = block_reduce_any<u64, NT>(far, sm.red, OpMax());
+        }
+        bad = __syncthreads_or(bad);
+        if (bad) out.flags = EBSP_STATUS_UNSORTED;
+        if (empty || bad) return;
+        // lim is an entry (without a successor)
+        if (E == ends.lim && tid == 0) atomicMax(&sm.cells[(u32)((E - A) >> sh)], 1u);
+        __syncthreads();
+        // G in place.  Every wave owns NB / NW neighbouring cells and walks them 256 at a time, four to a lane.
+        const V A_ = (V)A, E_ = (V)E, wide_cell = (V)((1ull << sh) - 1);
+        auto first_of = [&](u32 c) -> V { return A_ + ((V)c << sh); };
+        auto last_of = [&](u32 c) -> V { const V h = A_ + ((V)c << sh) + wide_cell; return h < E_ ? h : E_; };
+        auto low_bound = [&](u32 g0, u32 c) -> V {        // of cell c, g0 the word before it
+            const V g = (V)(g0 - 1u) << ms, h = last_of(c);
+            return g > h ? g - h : (V)0;
+        };
+        // (the best itself is the first of its kind: of equal ones behind it none can win)
+        auto wins = [&](V lb, u32 c) -> bool { return (u64)lb < top || ((u64)lb == top && (u64)first_of(c) <= best.x); };
+        auto may_win = [&](u32 c) -> bool { return wins(low_bound(sm.cells[(int)c - 1], c), c); };
+        const u32 lane = tid & (WAVE - 1), wave = tid >> 6;
+        const u32 mine = wave * (NB / NW) + 4 * lane;      // the thread's k-th cell:
+        auto cell_of = [&](int i) -> u32 { return mine + (u32)(i >> 2) * 256u + (u32)(i & 3); };
+        const u32 seed = (u32)(start >> ms) + 1u;
+        u32 todo = 0;                                      // cells that hold entries and have not been looked at
+        Best low{U64_MAX, U64_MAX};                        // the smallest lower bound and its cell,
+        u64 second = U64_MAX;                              // the thread's next one,
+        Best first_low;                                    // and its own smallest
+        {
+            u32 m = 0;
+#pragma unroll
+            for (int i = 0; i < STEPS; ++i) {
+                const uint4 q = *(const uint4*)(sm.cells + mine + i * 256);
+                const u32 x = q.x > q.y ? q.x : q.y, y = q.z > q.w ? q.z : q.w, z = x > y ? x : y;
+                m = z > m ? z : m;
+            }
+            m = last_lane(wave_scan(m, OpMax()));
+            if (lane == 0) ((u32*)sm.red)[wave] = m;
+            if (tid == 0) sm.pad[3] = seed;                // cells[-1]
+            __syncthreads();
+            u32 run = seed;
+            for (u32 w = 0; w < wave; ++w) { const u32 x = ((u32*)sm.red)[w]; run = x > run ? x : run; }
+            run = uniform(run);
+            __syncthreads();
+            V ub = std::numeric_limits<V>::max(), lb1 = ub, lb2 = ub;
+            u32 lc1 = 0;
+#pragma unroll 2
+            for (int i = 0; i < STEPS; ++i) {
+                const u32 c = mine + i * 256;
+                uint4 q = *(const uint4*)(sm.cells + c);
+                todo |= ((q.x ? 1u : 0u) | (q.y ? 2u : 0u) | (q.z ? 4u : 0u) | (q.w ? 8u : 0u)) << (4 * i);
+                const u32 x = q.x > q.y ? q.x : q.y, y = q.z > q.w ? q.z : q.w;
+                const u32 inc = wave_scan(x > y ? x : y, OpMax());
+                u32 before = dpp_take<DPP_WAVE_SHR1, 0xf>(0u, inc);
+                before = lane == 0 ? 0u : before;
+                before = before > run ? before : run;
+                const u32 end = last_lane(inc);
+                run = end > run ? end : run;
+                u32 g = before;
+                auto cell = [&](u32& word, u32 at) {
+                    const u32 g1 = word > g ? word : g;
+                    if (word) {
+                        const V lo = first_of(c + at), v = ((V)(g1 - 1u) << ms) | rest, u = v > lo ? v - lo : (V)0;
+                        ub = u < ub ? u : ub;
+                        const V l = low_bound(g, c + at);
+                        if (l < lb1) { lb2 = lb1; lb1 = l; lc1 = c + at; }
+                        else if (l < lb2) lb2 = l;
+                    }
+                    word = g = g1;
+                };
+                cell(q.x, 0u); cell(q.y, 1u); cell(q.z, 2u); cell(q.w, 3u);
+                *(uint4*)(sm.cells + c) = q;
+            }
+            if (todo) { first_low = Best{(u64)lb1, (u64)lc1}; second = lb2 == std::numeric_limits<V>::max() ? U64_MAX : (u64)lb2; }
+            else first_low = low;
+            const u64 all_ub = block_reduce_any<V, NT>(ub, sm.red, OpMin());
+            top = all_ub < top ? all_ub : top;
+            low = block_first_min<NT>(first_low, sm.red);
+        }
+        // the gathered cells r .. r + K - 1, those that may still win; false: more entries than the list holds
+        auto look_at = [&](u32 r, u32 K) -> bool {
+            auto cell_at = [&](u32 ci) -> u32 { return sm.cell[r + ci]; };
+            for (u32 c = tid; c < K; c += NT) sm.at_start[c] = 0;
+            __syncthreads();
+            for (u64 q = tid; q < (u64)K * (u32)P; q += NT) {
+                const u32 ci = (u32)(q / (u32)P);
+                const int p = (int)(q - (u64)ci * (u32)P);
+                const u32 c = cell_at(ci);
+                if (!may_win(c)) continue;
+                const i64* row = inst + (size_t)p * R;
+                u32 i = RowProbe(row, (u32)R, base, first_in(p), last_in(p), first_of(c)).index();
+                if (i >= (u32)R) continue;                 // (never: the cell begins at lim or before)
+                u64 x = (u64)row[i] - base, nx = (u64)row[i + 1 < (u32)R ? i + 1 : i] - base;
+                atomicMax(&sm.at_start[ci], x);
+                if (sh == 0) continue;
+                const u64 hi = last_of(c);
+                while (x <= hi) {
+                    const u32 at = atomicAdd(&sm.listed, 1u);
+                    if (at >= (u32)sm.LIST) break;
+                    sm.lx[at] = x; sm.ln[at] = nx; sm.lc[at] = (u16)ci;
+                    if (++i >= (u32)R) break;
+                    x = nx;
+                    nx = (u64)row[i + 1 < (u32)R ? i + 1 : i] - base;
+                }
+            }
+            __syncthreads();
+            const u32 total = sm.listed;
+            __syncthreads();
+            if (tid == 0) sm.listed = 0;
+            if (total > (u32)sm.LIST) return false;
+            Best got{U64_MAX, U64_MAX};
+            if (sh == 0) {                                 // the cell is its only value
+                for (u32 ci = tid; ci < K; ci += NT)
+                    if (may_win(cell_at(ci))) {
+                        const u64 x = first_of(cell_at(ci));
+                        const Best one{sm.at_start[ci] - x, x};
+                        if (one.before(got)) got = one;
+                    }
+            } else
+                for (u32 e = tid; e < total; e += NT) {
+                    const u64 x = sm.lx[e];
+                    const u32 ci = sm.lc[e];
+                    u64 g = sm.at_start[ci];
+                    for (u32 o = 0; o < total; ++o)
+                        if (sm.lc[o] == ci && sm.lx[o] < x && sm.ln[o] > g) g = sm.ln[o];
+                    const Best one{g > x ? g - x : 0ull, x};
+                    if (one.before(got)) got = one;
+                }
+            got = block_first_min<NT>(got, sm.red);        // (ends with a barrier: the list may be written again)
+            if (got.before(best)) best = got;
+            top = best.d < top ? best.d : top;
+            __syncthreads();
+            return true;
+        };
+        u32 K = (u32)(4 * NT) / (u32)P;
+        K = K < 1u ? 1u : (K > (u32)RANGE_ROUND_CELLS ? (u32)RANGE_ROUND_CELLS : K);
+        for (int round = 0;; ++round) {
+            // gathered: first the cell with the smallest lower bound, then what may still win, in most slices nothing (no
+            // thread's smallest bound that was not looked at is among it)
+            u32 now_mask = 0;
+            if (round == 0) {
+                const u32 c = (u32)low.x - wave * (NB / NW);                  // inside the wave's cells
+                if (low.d != U64_MAX && c < NB / NW && (c & 255u) >> 2 == lane) {
+                    now_mask = 1u << ((c >> 8) * 4 + (c & 3u));
+                    first_low.d = second;
+                }
+                todo &= ~now_mask;
+            } else {
+                if (round == 1 && !__syncthreads_or(first_low.d <= top)) break;
+#pragma unroll 2
+                for (int i = 0; i < STEPS; ++i) {
+                    const u32 c = mine + i * 256;
+                    const uint4 q = *(const uint4*)(sm.cells + c);
+                    const u32 g0 = sm.cells[(int)c - 1];
+                    if (wins(low_bound(g0, c), c)) now_mask |= 1u << (4 * i);
+                    if (wins(low_bound(q.x, c + 1), c + 1)) now_mask |= 2u << (4 * i);
+                    if (wins(low_bound(q.y, c + 2), c + 2)) now_mask |= 4u << (4 * i);
+                    if (wins(low_bound(q.z, c + 3), c + 3)) now_mask |= 8u << (4 * i);
+                }
+                now_mask &= todo;
+                todo = now_mask;
+            }
+            u32 all;
+            u32 at = block_excl_scan<u32, NT>((u32)__popc(now_mask), (u32*)sm.red, all);
+            for (; now_mask; now_mask &= now_mask - 1, ++at)
+                if (at < (u32)sm.LIVE) {
+                    const int i = __ffs(now_mask) - 1;
+                    sm.cell[at] = (u16)cell_of(i);
+                    todo &= ~(1u << i);
+                }
+            __syncthreads();
+            if (all == 0) break;                           // (an interval without entries has no smallest bound)
+            const u32 have = all < (u32)sm.LIVE ? all : (u32)sm.LIVE;
+            u32 step = K;
+            for (u32 r = 0; r < have;) {
+                const u32 now = have - r < step ? have - r : step;
+                if (look_at(r, now)) { r += now; continue; }
+                step = 1;                                  // one at a time then
+                if (now > 1) continue;
+                if (tid == 0) {                            // this one is cut into cells of its own later
+                    const u32 c = sm.cell[r], to = sm.waiting;
+                    if (to < (u32)RANGE_STACK) {
+                        sm.from[to] = first_of(c);
+                        sm.to[to] = last_of(c);
+                        sm.least[to] = low_bound(sm.cells[(int)c - 1], c);
+                    }
+                    sm.waiting = to + 1;
+                }
+                ++r;
+            }
+            __syncthreads();
+        }
+        __syncthreads();
+        u32 waiting = sm.waiting;
+        if (waiting > (u32)RANGE_STACK) { out.left = 1; return; }
+        while (waiting > 0 && (sm.least[waiting - 1] > top || (sm.least[waiting - 1] == top && sm.from[waiting - 1] > best.x))) --waiting;
+        if (waiting == 0) break;
+        A = sm.from[waiting - 1];
+        E = sm.to[waiting - 1];
+        sh = cell_shift(E - A, LOG);
+        for (int c = tid; c < NB / 4; c += NT) ((uint4*)sm.cells)[c] = make_uint4(0u, 0u, 0u, 0u);
+        __syncthreads();
+        if (tid == 0) sm.waiting = waiting - 1;
+    }
+    out.d = best.d;
+    out.g = best.x + best.d;
+}
+
+// With one slice per instance the results go straight to the caller's arrays (dmin: DEFERRED where the slice gave up).
+template <int NT, int NB>
+__global__ __launch_bounds__(NT, (NB == 8192 ? 3 : 4)) void zl_range_fast_kernel(
+    const i64* __restrict__ ts, int P, int R, u32 slices, int lanes_log, RangePart* __restrict__ part,
+    i64* __restrict__ barrier, int* __restrict__ iters, i64* __restrict__ dmin, int* __restrict__ status)
+{
+    __shared__ __align__(16) SliceSmem<NT, NB> sm;
+    const int tid = threadIdx.x;
+    const i64 b = blockIdx.x / slices;
+    const u32 k = blockIdx.x % slices;
+    const i64* __restrict__ inst = ts + (size_t)b * P * R;
+    for (int c = tid; c < NB / 4; c += NT) ((uint4*)sm.cells)[c] = make_uint4(0u, 0u, 0u, 0u);
+    u64 own_first, own_last;                               // the ends of row `tid`
+    const RowEnds ends = row_ends<NT>(inst, P, R, sm.red, own_first, own_last);
+    const u64 base = (u64)ends.base;
+    RangePart r;
+    if (ends.range >> 31) zl_range_slice<NT, NB, true>(sm, inst, P, R, slices, k, lanes_log, ends, own_first, own_last, r);
+    else zl_range_slice<NT, NB, false>(sm, inst, P, R, slices, k, lanes_log, ends, own_first, own_last, r);
+    if (slices > 1) {
+        if (tid == 0) part[blockIdx.x] = r;
+        return;
+    }
+    if (r.d == U64_MAX) r.d = r.g = 0;                     // (unsorted rows only, or nothing found out)
+    if (tid == 0) {
+        barrier[b] = (i64)(base + r.g);
+        dmin[b] = r.left ? DEFERRED : (i64)r.d;
+        if (status) status[b] = (int)r.flags;
+    }
+    store_iters<NT>(inst, P, R, base, r.g, own_first, own_last, iters + b * (i64)P);
+}
+
+// The instances the kernels above gave up (values clustered beyond what their cells resolve): the sort-based search over
+// whole rows; and, for instances in slices, the best of the slices and the iteration counts.  A fixed grid; every
+// workgroup looks through its share of the instances.
 template <int NT, int ITEMS>
 __global__ __launch_bounds__(NT) void zl_range_window_kernel(
-    const i64* __restrict__ ts, i64 B, int P, int R,
-    const InstInfo* __restrict__ info, const void* __restrict__ cross, bool narrow, int stride,
-    const u32* __restrict__ winstart, const WinVal* __restrict__ winval, int max_win,
-    Partial* __restrict__ partial, int* __restrict__ status)
+    const i64* __restrict__ ts, i64 B, int P, int R, u32 slices, const RangePart* __restrict__ part,
+    i64* __restrict__ barrier, int* __restrict__ iters, i64* __restrict__ dmin, int* __restrict__ status)
 {
     using C = WinCfg<NT, ITEMS>;
     __shared__ __align__(16) unsigned char smem[C::BYTES];
     const Smem sm = carve<NT, ITEMS>(smem);
-    const u32 total = (u32)(B * (i64)max_win);
+    const int tid = threadIdx.x;
+    auto store = [&](i64 b, i64 base, Best best, int flags) {            // best.x: the barrier, relative to base
+        if (best.d == U64_MAX) best = Best{0ull, 0ull};                  // (unsorted rows only)
+        if (tid == 0) {
+            barrier[b] = (i64)((u64)base + best.x);
+            dmin[b] = (i64)best.d;
+            if (status) status[b] = flags ? (int)EBSP_STATUS_UNSORTED : 0;
+        }
+        for (int p = tid; p < P; p += NT)
+            iters[b * (i64)P + p] = (int)row_first_at_least(ts + ((size_t)b * P + p) * R, (u32)R, (u64)base, best.x + 1);
+    };
+    auto search = [&](i64 b) {
+        const i64* __restrict__ inst = ts + (size_t)b * P * R;
+        u64 first, last;
+        const RowEnds ends = row_ends<NT>(inst, P, R, sm.red, first, last);
+        Rows rw;
+        rw.inst = inst; rw.le = nullptr; rw.iv = nullptr; rw.par = nullptr; rw.P = P; rw.R = R; rw.base = (u64)ends.base;
+        rw.cr = nullptr; rw.narrow = false; rw.wide = false; rw.stride = 0; rw.k0 = rw.k1 = 0;
+        u64 d = U64_MAX, g = 0;
+        int bad = 0;
+        if (ends.range > RANGE_PIECE_MAX) zl_range_window<NT, ITEMS, true>(sm, rw, ends.thr, 0ull, ends.range, d, g, bad);
+        else zl_range_window<NT, ITEMS, false>(sm, rw, ends.thr, 0ull, ends.range, d, g, bad);
+        store(b, ends.base, Best{d, g}, __syncthreads_or(bad));
+    };
+    if (slices > 1) {
+        for (i64 b = blockIdx.x; b < B; b += gridDim.x) {
+            Best best{U64_MAX, U64_MAX};
+            int flags = 0, left = 0;
+            for (u32 k = tid; k < slices; k += NT) {
+                const RangePart r = part[b * slices + k];
+                const Best got{r.d, r.g};
+                if (got.before(best)) best = got;
+                flags |= (int)r.flags;
+                left |= (int)r.left;
+            }
+            if (__syncthreads_or(left)) { search(b); continue; }
+            i64 base = INT64_MAX;
+            for (int p = tid; p < P; p += NT) { const i64 f = ts[((size_t)b * P + p) * R]; base = f < base ? f : base; }
+            base = block_reduce<i64, NT>(base, (i64*)sm.red, OpMin());
+            best = block_first_min<NT>(best, sm.red);
+            store(b, base, best, __syncthreads_or(flags));
+        }
+        return;
+    }
+    const u32 total = (u32)B;
     const u32 share = (total + gridDim.x - 1) / gridDim.x;
     const u32 first = blockIdx.x * share;
     const u32 end = first + share < total ? first + share : total;
-
-    for (u32 base = first; base < end; base += NT) {
-        const u32 idx = base + threadIdx.x;
-        bool mine = false;
-        if (idx < end) {
-            const u32 b = idx / (u32)max_win, j = idx % (u32)max_win;
-            if (j < info[b].nwin) mine = partial[idx].wait == U64_MAX && partial[idx].brel == DEFERRED_WINDOW;
-        }
+    int any = 0;                                          // mostly nothing is marked: out before anything is set up
+    for (u32 idx = first + tid; idx < end; idx += NT) any |= dmin[idx] == DEFERRED;
+    if (!__syncthreads_or(any)) return;
+    for (u32 base0 = first; base0 < end; base0 += NT) {
+        const u32 idx = base0 + tid;
+        bool mine = idx < end && dmin[idx] == DEFERRED;
         for (;;) {
-            const u32 pick = block_reduce<u32, NT>(mine ? idx : 0xffffffffu, (u32*)sm.red, OpMin());
-            if (pick == 0xffffffffu) break;
-            if (pick == idx) mine = false;
-            const i64 b = pick / (u32)max_win;
-            const InstInfo ii = info[b];
-            const WinPos w = locate_window(b, (int)(pick % (u32)max_win), ii, ts, nullptr, nullptr, P, R, cross, narrow,
-                                           stride, winstart, winval, max_win);
-            Partial r;
-            r.wait = U64_MAX;
-            r.brel = 0;
-            int bad = 0;
-            if (w.valid) {
-                if (ii.range > RANGE_PIECE_MAX) zl_range_window<NT, ITEMS, true>(sm, w.rw, ii.thr, w.A, w.Elast, r.wait, r.brel, bad);
-                else zl_range_window<NT, ITEMS, false>(sm, w.rw, ii.thr, w.A, w.Elast, r.wait, r.brel, bad);
-            }
-            bad = __syncthreads_or(bad);
-            if (threadIdx.x == 0) {
-                partial[pick] = r;
-                if (status && bad) atomicOr(status + b, (int)EBSP_STATUS_UNSORTED);
-            }
+            const u32 b = block_reduce<u32, NT>(mine ? idx : 0xffffffffu, (u32*)sm.red, OpMin());
+            if (b == 0xffffffffu) break;
+            if (b == idx) mine = false;
+            search((i64)b);
         }
     }
 }

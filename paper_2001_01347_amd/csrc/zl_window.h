@@ -55,13 +55,12 @@ __device__ __forceinline__ WinPos locate_window(i64 b, int j, const InstInfo& ii
 // entries and then the entries that survive the bounds.  Stored rows: 4 bytes per source word, so
 // the area is half the size and holds records for half the entries (more survivors than that are
 // listed in rounds); with the bucket words after it the LDS of a CU takes three workgroups of 512
-// threads (how many run is then a matter of registers: three of the range search, two of the
-// summed-wait search, five of its 256-thread form).  EXTRA_WORDS: room behind the source words.
-template <int NT, int ITEMS, bool PRED, int EXTRA_WORDS = 0>
+// threads (how many run is then a matter of registers: two, and five of the 256-thread form).
+template <int NT, int ITEMS, bool PRED>
 struct WinHot {
     using H = HotCfg<NT, ITEMS, false>;                  // windows use the linear bucket map: no coarse table
     static constexpr int LIST = PRED ? 0 : H::CAP / 2;    // records of the compact list (0: one per entry)
-    static constexpr size_t REC_BYTES = PRED ? (size_t)H::BSUM_AT * 8 : (size_t)H::CAP * 4 + (size_t)EXTRA_WORDS * 4;
+    static constexpr size_t REC_BYTES = PRED ? (size_t)H::BSUM_AT * 8 : (size_t)H::CAP * 4;
     static constexpr size_t BYTES = REC_BYTES + (size_t)H::NB * 8 + (size_t)H::RED_WORDS * 8 + (size_t)H::NB * 4;
     static_assert(REC_BYTES % 8 == 0, "the bucket words are 8 bytes each");
     __device__ __forceinline__ static Smem carve(unsigned char* smem)

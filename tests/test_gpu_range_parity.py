@@ -194,3 +194,53 @@ def test_value_spread_beyond_32_bits(zl, oracle):
     big = np.array([[[0, 2 ** 61, 2 ** 62 - 1], [5, 2 ** 61 + 7, 2 ** 62 - 3]]], dtype=np.int64)
     assert_same(zl, oracle, big, "values up to 2^62")
     assert_same(zl, oracle, big - 2 ** 61, "values from -2^61")
+
+
+def _steps(rng, B, P, R, spread):
+    mean = rng.uniform(80, 120, size=(B, P, 1)) * spread
+    steps = np.maximum(1, np.rint(mean * rng.lognormal(0, 0.15, size=(B, P, R)))).astype(np.int64)
+    return np.cumsum(steps, axis=2) + rng.integers(0, 100 * spread, size=(B, P, 1))
+
+
+# (B, P, R): one wave and two, items that end inside a wave and rows that end inside an item, the last entries of the
+# register form and the first of the slices, of one slice and several, fewer lanes than a wave per row, rows one longer
+# than a wave's step, more rows than threads, rows too long for the register form, rows that end long before the others
+@pytest.mark.parametrize("B,P,R", [(9, 4, 64), (9, 5, 51), (9, 4, 65), (9, 16, 64), (9, 4, 256), (9, 3, 257), (9, 8, 128), (5, 8, 512),
+                                   (5, 7, 513), (5, 64, 64), (5, 241, 17), (3, 63, 130), (3, 64, 256), (600, 33, 300), (3, 130, 127),
+                                   (2, 520, 33), (1, 1030, 40), (3, 20, 3000), (1, 3, 9000), (1, 7, 5000)])
+@pytest.mark.parametrize("spread", [10, 1000, 3_000_000])
+def test_edges_of_the_search_by_successors(zl, oracle, B, P, R, spread):
+    # spreads below 2^31, and (where rows are long) between 2^31 and 2^32 or beyond 2^32
+    rng = np.random.default_rng(B + 31 * P + R + spread)
+    ts = _steps(rng, B, P, R, spread)
+    assert_same(zl, oracle, ts + EPOCH, f"B={B} P={P} R={R} spread {spread}")
+    ts[:, ::3] = ts[:, ::3, :1] + (ts[:, ::3] - ts[:, ::3, :1]) // 7      # every third worker is through early: lim is small
+    assert_same(zl, oracle, ts, f"B={B} P={P} R={R} spread {spread}, some workers through early")
+    ts -= ts % (20 * spread)                                              # ties between workers and inside rows
+    assert_same(zl, oracle, ts, f"B={B} P={P} R={R} spread {spread}, ties")
+
+
+# values that cells do not resolve: more entries in a cell than its list holds, in more cells than may wait (520 x 150);
+# more candidates than are tried in registers (20 x 150); intervals cut again and again
+@pytest.mark.parametrize("B,P,R", [(520, 520, 150), (7, 20, 150), (3, 100, 30), (2, 700, 60), (1, 300, 400)])
+def test_clusters_that_cells_do_not_resolve(zl, oracle, B, P, R):
+    rng = np.random.default_rng(B + P)
+    ts = np.arange(R, dtype=np.int64)[None, None, :] * 1_000_000_007 + rng.integers(0, 900, size=(B, P, R))
+    assert_same(zl, oracle, ts, f"an iteration of every worker at a time, P={P} R={R}")
+    near = rng.integers(0, 40, size=(min(B, 8), P, R), dtype=np.int64).cumsum(axis=2)
+    near[:, :, R // 2:] += 1 << 40
+    assert_same(zl, oracle, near, f"two dense stretches, P={P} R={R}")
+
+
+@pytest.mark.parametrize("B,P,R", [(3, 16, 60), (3, 60, 60), (3, 30, 600), (520, 30, 600), (1, 700, 90)])
+def test_rows_out_of_order_anywhere(zl, oracle, B, P, R):
+    # one step back, at the start, in the middle, at the end and behind the earliest end of the rows, small and large
+    rng = np.random.default_rng(P * R)
+    ts = _steps(rng, B, P, R, 1000)
+    ts[:, 1] = ts[:, 1, :1] + (ts[:, 1] - ts[:, 1, :1]) // 4              # through early
+    for k, i in enumerate((1, R // 2, R - 1, R - 2, R // 3)):
+        bad = ts.copy()
+        p = P - 1 if k % 2 else P // 2
+        bad[0, p, i] = bad[0, p, i - 1] - (1 if k < 3 else 50_000_000)
+        st = gpu_run(zl, bad)[3]
+        assert st[0] & zl.STATUS_UNSORTED and (st[1:] == 0).all(), (k, i)
