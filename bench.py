@@ -127,6 +127,10 @@ def algorithmic_bytes(kernel: str, B: int, P: int, R: int, bins: float, windows:
         return rows + B * (16.0 + 4.0 * P)
     if kernel == "zl_run_kernel":           # the same; of a run's rows the start times once and every superstep's intervals
         return (8.0 * B * P * (1.0 + 1.0 / supersteps) if supersteps else rows) + B * (16.0 + 4.0 * P)
+    if kernel == "zl_direct_kernel":        # predicted rows, every candidate evaluated: 16 bytes per worker, all three outputs
+        return 16.0 * B * P + B * (16.0 + 4.0 * P)
+    if kernel == "zl_direct_finish_kernel":     # the same once more, and 16 bytes per workgroup (P / 4 of them at most)
+        return 16.0 * B * P + B * (16.0 + 8.0 * P)
     if kernel == "zl_advance_kernel":       # the barriers, every worker's next start time
         return 8.0 * B + 8.0 * B * P
     if kernel == "zl_window_kernel":        # every searched timestamp once, two crossing rows per window, one result

@@ -82,13 +82,14 @@ int check_device()
 }
 
 enum KernelId { K_INSTANCE = 0, K_INSTANCE_GENERAL, K_BOUNDS, K_PARTITION, K_BINCOUNT, K_PLAN, K_WINDOW,
-                K_WINDOW_GENERAL, K_FINISH, K_COPY, K_RANGE_INSTANCE, K_RANGE_FAST, K_PARTITION_PRED, K_RANGE_WINDOW, K_ADVANCE, K_SWEEP, K_SWEEP_FINISH, K_GRIDSCAN, K_GRIDSCAN_FINISH, K_READ, K_INSTANCE_REG, K_RUN, K_COUNT };
+                K_WINDOW_GENERAL, K_FINISH, K_COPY, K_RANGE_INSTANCE, K_RANGE_FAST, K_PARTITION_PRED, K_RANGE_WINDOW, K_ADVANCE, K_SWEEP, K_SWEEP_FINISH, K_GRIDSCAN, K_GRIDSCAN_FINISH, K_READ, K_INSTANCE_REG, K_RUN, K_DIRECT, K_DIRECT_FINISH, K_COUNT };
 const char* const kKernelNames[K_COUNT] = {
     "zl_instance_kernel", "zl_instance_general_kernel", "zl_bounds_kernel", "zl_partition_kernel",
     "zl_bincount_kernel", "zl_plan_kernel", "zl_window_kernel", "zl_window_general_kernel",
     "zl_finish_kernel", "zl_copy_kernel", "zl_range_instance_kernel", "zl_range_fast_kernel",
     "zl_partition_pred_kernel", "zl_range_window_kernel", "zl_advance_kernel", "zl_sweep_kernel", "zl_sweep_finish_kernel", "zl_gridscan_kernel",
-    "zl_gridscan_finish_kernel", "zl_read_kernel", "zl_instance_reg_kernel", "zl_run_kernel"};
+    "zl_gridscan_finish_kernel", "zl_read_kernel", "zl_instance_reg_kernel", "zl_run_kernel", "zl_direct_kernel",
+    "zl_direct_finish_kernel"};
 
 size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
@@ -376,10 +377,71 @@ int launch_run(const i64* ts, const i64* le, const i64* iv, i64 sync_cost, i64 S
     return EBSP_OK;
 }
 
-// The rows are either stored (ts != nullptr) or predicted: t[p][i] = le[p] + (i + 1) * iv[p] (ts == nullptr).
+// Which searches of predicted rows evaluate every candidate (zl_direct_kernel).  Its time goes with entries x workers, that
+// of the bucket searches with the entries, so few workers are one reason, a batch that leaves the chip idle the other.
+// Bucket searches / direct, us:
+//   few workers    4096 of 16 x 64 34 / 18, of 32 x 32 33 / 25, of 40 x 25 36 / 28, of 48 x 20 35 / 32, of 64 x 16 34 / 41;
+//                  4096 of 24 x 170 149 / 66, 2048 of 32 x 500 255 / 159, 1000 of 48 x 300 103 / 124;
+//                  500 of 16 x 4096 228 / 102, 1000 of 24 x 2000 354 / 197, 100 of 32 x 4096 139 / 91
+//   small batches  one of 100 x 150 28.6 / 14.5, of 1024 x 15 26.7 / 22.6, 64 of 64 x 256 35 / 19, 40 of 200 x 60 26.5 / 25,
+//                  128 of 100 x 150 31 / 41; one of 1000 x 150 60 / 45, 2 of 1000 x 100 101 / 52, 20 of 256 x 120 84 / 38;
+//                  up to 1024 entries one of 100 x 10 10.6 / 10.9, of 128 x 8 11.4 / 12.1 (one launch as well)
+//   supersteps     (per superstep, the searches side by side) 256 of 16 x 60 7.6 / 0.9, 1000 of 64 x 15 15 / 9.5, 500 of 100
+//                  x 10 8.7 / 9; 64 of 64 x 60 29 / 2.5, 16 of 100 x 150 32 / 4.7, 8 of 1000 x 60 104 / 58
+constexpr i64 DIRECT_NMAX = 1 << 18;             // a search has P / 4 workgroups at most: with more entries they are too few
+bool takes_direct(i64 B, int P, i64 n, bool run)
+{
+    if (P > DIRECT_PMAX || n > DIRECT_NMAX) return false;
+    if (P <= (n > 1024 ? 40 : run ? 64 : 48)) return true;
+    return n > 1024 && B * n * P <= (n > 16384 ? 300000000ll : 100000000ll);
+}
+
+// Searches at0 .. at0 + count - 1 (zl_direct_kernel), recorded as kernel `kid`.  Batches that fill the chip: a wave per search of
+// up to 4096 entries and 64 workers, four for larger ones (2048 of 16 x 1000 98 us with four, 109 with one; 4096 of 16 x 64
+// 24 and 17).  Others: as many workgroups per search as its iters hold results for; with many workers, split among a
+// workgroup's waves (one of 1000 x 150 45 us split, 55 not; of 256 x 60 14 and 20; of 256 x 240 22 and 20).
+int launch_direct(int kid, const i64* le, const i64* iv, i64 B, i64 at0, i64 count, int P, int R, i64* barrier, int* iters, i64* wait,
+                  int* status, hipStream_t st)
+{
+    const i64 n = (i64)P * R;
+    const bool full = count * n >= 1 << 20;          // two waves of eight candidates a thread per SIMD
+    const bool split = P > 64 && !full && count * n <= 1 << 18;
+    const int nt = full && P <= 64 && n <= 4096 ? 64 : 256;
+    int k = 4;
+    if (nt == 64)                                    // as many candidates a thread as leave the fewest lanes empty
+        for (const int more : {5, 8})
+            if ((n + 64 * more - 1) / (64 * more) * more <= (n + 64 * k - 1) / (64 * k) * k) k = more;
+    const i64 chunk = split ? 256 : (i64)nt * k;
+    i64 G = (n + chunk - 1) / chunk;
+    if (G > P / 4) G = P / 4;
+    if (G < 1 || nt == 64 || count >= 2048 || n <= 1024) G = 1;
+    const i64 per = ((n + G - 1) / G + chunk - 1) / chunk * chunk;
+    G = (n + per - 1) / per;
+#define LAUNCH_DIRECT(NT_, PM_, K_, SPLIT_)                                                                  \
+    LAUNCH(kid, (zl_direct_kernel<NT_, PM_, K_, SPLIT_>), dim3((unsigned)(count * G)), dim3(NT_), le, iv, B, at0, P, R, \
+           (int)G, (int)per, barrier, iters, wait, status)
+    if (nt == 64) {
+        if (k == 4) LAUNCH_DIRECT(64, 64, 4, false);
+        else if (k == 5) LAUNCH_DIRECT(64, 64, 5, false);
+        else LAUNCH_DIRECT(64, 64, 8, false);
+    } else if (split) LAUNCH_DIRECT(256, DIRECT_PMAX, 4, true);
+    else if (P <= 64) LAUNCH_DIRECT(256, 64, 4, false);
+    else LAUNCH_DIRECT(256, DIRECT_PMAX, 4, false);
+#undef LAUNCH_DIRECT
+    if (G > 1) {
+        if (P <= 64) LAUNCH(K_DIRECT_FINISH, (zl_direct_finish_kernel<64, 64>), dim3((unsigned)count), dim3(64), le, iv, B, at0, P, R, (int)G,
+                            barrier, iters, wait, status);
+        else LAUNCH(K_DIRECT_FINISH, (zl_direct_finish_kernel<256, DIRECT_PMAX>), dim3((unsigned)count), dim3(256), le, iv, B, at0, P, R, (int)G,
+                    barrier, iters, wait, status);
+    }
+    return EBSP_OK;
+}
+
+// The rows are either stored (ts != nullptr) or predicted: t[p][i] = le[p] + (i + 1) * iv[p] (ts == nullptr; direct: every
+// candidate may be evaluated).
 int run_batch(const i64* ts, const i64* le, const i64* iv, i64 B, int P, int R,
               i64* barrier, int* iters, i64* wait, int* status,
-              void* workspace, size_t workspace_bytes, hipStream_t st)
+              void* workspace, size_t workspace_bytes, hipStream_t st, bool direct = true)
 {
     Plan pl;
     const bool pred = ts == nullptr;
@@ -415,6 +477,7 @@ int run_batch(const i64* ts, const i64* le, const i64* iv, i64 B, int P, int R,
 
     if (!pl.multi) {
         if (int rc = check_device()) return rc;
+        if (pred && direct && takes_direct(B, P, n, false)) return launch_direct(K_DIRECT, le, iv, B, 0, B, P, R, barrier, iters, wait, status, st);
         if (takes_run_kernel(1, B, n)) return launch_run(ts, le, iv, 0, 1, B, P, R, barrier, iters, wait, status, st);
         const int rshift = (R & (R - 1)) == 0 ? __builtin_ctz((unsigned)R) : -1;
         const dim3 grid((unsigned)B);
@@ -472,6 +535,7 @@ int run_batch(const i64* ts, const i64* le, const i64* iv, i64 B, int P, int R,
     const i64 pblocks = (P + 255) / 256;
     if (pblocks * B > 0x7fffffffll) return fail(EBSP_ERR_SHAPE, "batch too large for one call");
     if (int rc = check_device()) return rc;
+    if (pred && direct && takes_direct(B, P, n, false)) return launch_direct(K_DIRECT, le, iv, B, 0, B, P, R, barrier, iters, wait, status, st);
     if (int rc = plan_windows(pl, ts, le, iv, B, P, R, wsp, status, st)) return rc;
     // Batches whose windows are all on the chip at once (two workgroups per CU; max_win is about twice the windows
     // there are) are as fast as one workgroup: a window each instead of two.
@@ -707,6 +771,26 @@ int ebsp_simulate_supersteps(const int64_t* last_end0, const int64_t* interval, 
     hipStream_t st = (hipStream_t)stream;
     i64* start = (i64*)((char*)workspace + search_bytes);
     const i64 per = B * (i64)P;
+    const i64 n = (i64)P * R;
+    // All supersteps side by side (zl_direct_kernel); of instances of more than 1024 entries the first one, whose workers
+    // have start times of their own, by a bucket search.
+    if (S > 1 && S * B * (P / 4 + 1) <= 0x7fffffffll && takes_direct(B, P, n, true)) {
+        if (int rc = check_device()) return rc;
+        const i64 s0 = n > 1024 ? 1 : 0;
+        if (s0 == 1) {
+            if (int rc = run_batch(nullptr, (const i64*)last_end0, (const i64*)interval, B, P, R, (i64*)barrier, iters, (i64*)wait, status,
+                                   workspace, search_bytes, st, false)) return rc;
+            prof_count();
+        }
+        if (int rc = launch_direct(K_RUN, (const i64*)last_end0, (const i64*)interval, B, s0 * B, (S - s0) * B, P, R, (i64*)barrier, iters,
+                                   (i64*)wait, status, st)) return rc;
+        if (P <= 64) LAUNCH(K_ADVANCE, (zl_direct_starts_kernel<64, 4>), dim3((unsigned)B), dim3(WAVE), (const i64*)last_end0,
+                            (const i64*)interval, (i64)sync_cost, (int)S, B, P, R, (i64*)barrier, iters, (i64*)wait, status);
+        else LAUNCH(K_ADVANCE, (zl_direct_starts_kernel<DIRECT_PMAX, 4>), dim3((unsigned)B), dim3(WAVE), (const i64*)last_end0,
+                    (const i64*)interval, (i64)sync_cost, (int)S, B, P, R, (i64*)barrier, iters, (i64*)wait, status);
+        prof_count(S - s0);
+        return EBSP_OK;
+    }
     if (!pl.multi && S <= 0x7fffffffll && B <= 0x7fffffffll && takes_run_kernel(S, B, (i64)P * R)) {
         if (int rc = check_device()) return rc;
         if (int rc = launch_run(nullptr, (const i64*)last_end0, (const i64*)interval, (i64)sync_cost, S, B, P, R, (i64*)barrier,

@@ -142,6 +142,19 @@ ZL_FN u32 div_by_reciprocal(u32 n, u32 d, u32 m)
     return q - ((u64)q * (u64)d > (u64)n ? 1u : 0u);
 }
 
+// The entry of the row first, first + step, ... that a barrier c >= first has reached last, min((c - first) / step, top),
+// in double precision, for whole numbers with |first|, |c| and step * (top + 1) at most 2^DIRECT_BITS.  (c - first + 1/2) /
+// step - 1/2 is at least 1/(2 step) away from where rounding it to the nearest whole number changes; rcp and shift round off
+// less than (|first| + step) / 2^53 step, and the quotient itself (as long as it matters: up to top) top / 2^51.  step = 0: the
+// entries are one value, 0 is as good as any.
+constexpr int DIRECT_BITS = 48;
+ZL_FN double direct_rcp(double step) { return step > 0.0 ? 1.0 / step : 0.0; }
+ZL_FN double direct_shift(double first, double step, double rcp) { return (0.5 - 0.5 * step - first) * rcp; }
+ZL_FN double direct_quotient(double c, double rcp, double shift, double top)
+{
+    return __builtin_fmin(__builtin_rint(__builtin_fma(c, rcp, shift)), top);
+}
+
 // Monotone maps of keys onto value buckets [0, NB).
 // LinearMap: bucket = (key * scale) >> 32, equal slices of [0, span]; right when the
 // keys are spread evenly, as inside a window of the multi-window path.

@@ -400,8 +400,46 @@ static void check_cut()
     }
 }
 
+// direct_quotient against the whole-number quotient: rows of every kind inside its limits, barriers at, before and behind
+// entries of the row, between them and far behind the last.
+static void check_direct()
+{
+    const i64 most = (i64)1 << DIRECT_BITS;
+    for (int t = 0; t < 60000; ++t) {
+        const i64 R = 1 + (i64)(rnd() >> (rnd() % 22 + 42));
+        i64 step = (i64)(rnd() >> (16 + rnd() % 48)) % (most / R + 1);
+        if (t % 50 == 0) step = most / R;
+        if (t % 50 == 1) step = 1;
+        if (t % 50 == 2) step = 0;
+        i64 first = (i64)(rnd() >> (16 + rnd() % 40)) % (most + 1);
+        if (t % 3 == 0) first = -first;
+        if (t % 50 == 3) first = most - R * step;
+        if (t % 50 == 4) first = -most;
+        const double rcp = direct_rcp((double)step), shift = direct_shift((double)first, (double)step, rcp);
+        for (int k = 0; k < 60; ++k) {
+            i64 x = 0;
+            switch (k % 6) {
+            case 0: x = (i64)(rnd() % (u64)R) * step; break;
+            case 1: x = (i64)(rnd() % (u64)R) * step + step - 1; break;
+            case 2: x = (i64)(rnd() % (u64)R) * step + 1; break;
+            case 3: x = (R - 1) * step + (i64)(rnd() % 3) - 1; break;
+            case 4: x = (i64)(rnd() % (u64)(R * step + 1)); break;
+            default: x = most - first; break;
+            }
+            if (x < 0 || first + x > most) continue;
+            const i64 q = step ? x / step : 0, want = q < R - 1 ? q : R - 1;
+            ++checks;
+            if ((i64)direct_quotient((double)(first + x), rcp, shift, (double)(R - 1)) != want) {
+                if (++failures < 20) std::printf("direct: first %lld step %lld R %lld x %lld want %lld\n", first, step, R, x, want);
+            }
+        }
+    }
+}
+
 int main()
 {
+    check_direct();
+    std::printf("quotients in double precision: %lld checks, %lld failures so far\n", checks, failures);
     check_cut();
     std::printf("value cut: %lld checks, %lld failures so far\n", checks, failures);
     check_reciprocal();

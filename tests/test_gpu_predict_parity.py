@@ -148,3 +148,48 @@ def test_full_size_configs(zl, oracle, k):
     assert ((it == cfg.R) | (stop + iv > bar[:, None])).all()
     assert (stop.max(axis=1) == bar).all()
     assert ((bar[:, None] - stop).sum(axis=1) == w).all()
+
+
+# few workers or few instances: every candidate is evaluated.  A wave per search and four, with candidates that end inside a
+# wave's step; several workgroups per search; workers split among waves; either side of the limits on workers and batch
+DIRECT = [(2000, 4, 60), (2100, 16, 65), (1200, 40, 103), (4400, 16, 15), (300, 41, 90), (3, 48, 21), (3, 49, 20), (3, 49, 21), (300, 16, 300),
+          (5, 12, 400), (3, 64, 500), (2, 65, 200), (1, 100, 163), (1, 101, 180), (1, 257, 61), (2, 1024, 17), (1, 1023, 30), (1, 1025, 20),
+          (1, 1, 5000), (2, 3, 9000)]
+
+
+@pytest.mark.parametrize("B,P,R", DIRECT)
+def test_every_candidate_evaluated(zl, oracle, B, P, R):
+    rng = np.random.default_rng(B + 7 * P + R)
+    for ties in (False, True):
+        le, iv = random_inputs(rng, B, P, 500, 1000, ties)
+        assert_same(zl, oracle, le + EPOCH, iv, R, f"B={B} P={P} R={R} ties={ties}")
+    iv[:, ::3] //= 50                                                      # through early, or standing still
+    iv[: (B + 1) // 2, 0] = 0
+    assert_same(zl, oracle, le, iv, R, f"B={B} P={P} R={R}, very different workers")
+    assert_same(zl, oracle, np.zeros_like(le), np.full_like(iv, 12_345), R, f"B={B} P={P} R={R}, all alike")
+
+
+@pytest.mark.parametrize("P,R", [(2, 3), (16, 60), (16, 300), (100, 150), (300, 60)])
+def test_every_candidate_evaluated_at_the_limits_of_double_precision(zl, oracle, P, R):
+    # the largest values that are divided in double precision, and beyond them, where they are divided as whole numbers
+    rng = np.random.default_rng(P * R)
+    most = (1 << 47) // P
+    for first, step in ((most - most // R, most // R), (most, most // R + 1), (1 << 55 - P.bit_length(), 1 << 54 - (P * R).bit_length())):
+        iv = step - rng.integers(0, 1 + step // 1000, size=(3, P)).astype(np.int64)
+        le = first - rng.integers(0, 1 + step // 3, size=(3, P)).astype(np.int64)
+        le[:, 0] = 0                                                       # the value that the others are taken relative to
+        iv[1] -= iv[1] % 1000
+        assert_same(zl, oracle, le, iv, R, f"P={P} R={R} first {first} step {step}")
+        assert_same(zl, oracle, -le, iv, R, f"P={P} R={R} first -{first} step {step}")
+
+
+@pytest.mark.parametrize("P,R", [(16, 60), (16, 300), (100, 150)])
+def test_every_candidate_evaluated_flags(zl, oracle, P, R):
+    rng = np.random.default_rng(P)
+    le, iv = random_inputs(rng, 4, P, 500, 1000, False)
+    iv[1, P // 2] = -3
+    iv[2, P - 1] = (1 << 62) // R
+    st = gpu_run(zl, le, iv, R)
+    assert st[3][1] & zl.STATUS_UNSORTED and st[3][2] & zl.STATUS_OVERFLOW and st[3][0] == 0 and st[3][3] == 0
+    ob, oi, ow, rc, _ = oracle.zipline(oracle.predicted_rows(le[::3], iv[::3], R), "sweep", threads=4)
+    assert np.array_equal(st[0][::3], ob) and np.array_equal(st[1][::3], oi) and np.array_equal(st[2][::3], ow)

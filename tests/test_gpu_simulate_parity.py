@@ -266,3 +266,35 @@ def test_a_profile_counts_every_superstep_as_a_call(zl, P, R, B, kernel):
         ms.append(spent[kernel])
     assert counts == [5, 10, 7, 3]
     assert all(m > 0.0 for m in ms)
+
+
+@pytest.mark.parametrize("S,B,P,R", [(2, 1, 1, 1), (70, 3, 16, 60), (129, 2, 8, 20), (5, 300, 16, 15), (3, 40, 64, 16), (3, 5, 65, 15),
+                                     (4, 3, 64, 60), (3, 2, 100, 150), (3, 2, 30, 700), (3, 1, 300, 90)])
+def test_supersteps_side_by_side(zl, oracle, S, B, P, R):
+    rng = np.random.default_rng(S + B + P + R)
+    iv = rng.integers(80_000, 120_000, size=(S, B, P)).astype(np.int64)
+    iv[S // 2] -= iv[S // 2] % 1000
+    iv[-1, :, ::2] = 0
+    le = rng.integers(0, 80_000, size=(B, P)).astype(np.int64) + EPOCH
+    assert_same(zl, oracle, le, iv, R, 2000, f"S={S} B={B} P={P} R={R}")
+    assert_same(zl, oracle, le, iv << 24, R, 0, f"S={S} B={B} P={P} R={R}, values beyond double precision")
+
+
+@pytest.mark.parametrize("P,R,S", [(8, 20, 70), (16, 90, 70), (70, 40, 5)])
+def test_flagged_supersteps_side_by_side(zl, oracle, P, R, S):
+    # flagged from the first superstep on: the workers keep start times of their own for several supersteps
+    rng = np.random.default_rng(P)
+    iv = rng.integers(80, 120, size=(S, 3, P)).astype(np.int64)
+    le = rng.integers(0, 80, size=(3, P)).astype(np.int64)
+    for s in (0, 1, 2, S - 2):
+        iv[s, 1, P // 2] = -7
+    bar, it, w, st = gpu_run(zl, le, iv, R, 3)
+    assert st[:, 1].nonzero()[0].tolist() == [0, 1, 2, S - 2] and (st[:, (0, 2)] == 0).all()
+    start = le[1:2].copy()
+    for s in range(S):
+        if st[s, 1] == 0:
+            ob, oi, ow = oracle.zipline(oracle.predicted_rows(start, iv[s, 1:2], R))[:3]
+            assert bar[s, 1] == ob[0] and w[s, 1] == ow[0] and np.array_equal(it[s, 1], oi[0]), s
+            start = np.full((1, P), ob[0] + 3, dtype=np.int64)
+    ob, oi, ow = oracle.simulate(le[::2], np.ascontiguousarray(iv[:, ::2]), R, 3)[:3]
+    assert np.array_equal(bar[:, ::2], ob) and np.array_equal(w[:, ::2], ow) and np.array_equal(it[:, ::2], oi)
