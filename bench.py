@@ -123,7 +123,7 @@ def algorithmic_bytes(kernel: str, B: int, P: int, R: int, bins: float, windows:
     cw = 2.0 if R < 65536 else 4.0          # bytes of one crossing index
     rows = 16.0 * B * P if predicted else 8.0 * n       # predicted rows: 16 bytes per worker stand for R timestamps
     inside = 16.0 * B * P if predicted else 8.0 * entries
-    if kernel in ("zl_instance_kernel", "zl_instance_reg_kernel"):      # every timestamp once, all three outputs
+    if kernel in ("zl_instance_kernel", "zl_instance_reg_kernel", "zl_cells_kernel"):      # every timestamp once, all three outputs
         return rows + B * (16.0 + 4.0 * P)
     if kernel == "zl_run_kernel":           # the same; of a run's rows the start times once and every superstep's intervals
         return (8.0 * B * P * (1.0 + 1.0 / supersteps) if supersteps else rows) + B * (16.0 + 4.0 * P)

@@ -82,14 +82,14 @@ int check_device()
 }
 
 enum KernelId { K_INSTANCE = 0, K_INSTANCE_GENERAL, K_BOUNDS, K_PARTITION, K_BINCOUNT, K_PLAN, K_WINDOW,
-                K_WINDOW_GENERAL, K_FINISH, K_COPY, K_RANGE_INSTANCE, K_RANGE_FAST, K_PARTITION_PRED, K_RANGE_WINDOW, K_ADVANCE, K_SWEEP, K_SWEEP_FINISH, K_GRIDSCAN, K_GRIDSCAN_FINISH, K_READ, K_INSTANCE_REG, K_RUN, K_DIRECT, K_DIRECT_FINISH, K_COUNT };
+                K_WINDOW_GENERAL, K_FINISH, K_COPY, K_RANGE_INSTANCE, K_RANGE_FAST, K_PARTITION_PRED, K_RANGE_WINDOW, K_ADVANCE, K_SWEEP, K_SWEEP_FINISH, K_GRIDSCAN, K_GRIDSCAN_FINISH, K_READ, K_INSTANCE_REG, K_RUN, K_DIRECT, K_DIRECT_FINISH, K_CELLS, K_COUNT };
 const char* const kKernelNames[K_COUNT] = {
     "zl_instance_kernel", "zl_instance_general_kernel", "zl_bounds_kernel", "zl_partition_kernel",
     "zl_bincount_kernel", "zl_plan_kernel", "zl_window_kernel", "zl_window_general_kernel",
     "zl_finish_kernel", "zl_copy_kernel", "zl_range_instance_kernel", "zl_range_fast_kernel",
     "zl_partition_pred_kernel", "zl_range_window_kernel", "zl_advance_kernel", "zl_sweep_kernel", "zl_sweep_finish_kernel", "zl_gridscan_kernel",
     "zl_gridscan_finish_kernel", "zl_read_kernel", "zl_instance_reg_kernel", "zl_run_kernel", "zl_direct_kernel",
-    "zl_direct_finish_kernel"};
+    "zl_direct_finish_kernel", "zl_cells_kernel"};
 
 size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
@@ -437,6 +437,23 @@ int launch_direct(int kid, const i64* le, const i64* iv, i64 B, i64 at0, i64 cou
     return EBSP_OK;
 }
 
+// Which stored instances are searched over value cells (zl_cells_kernel): those of few rows (their ends are one wave's
+// work), whose cells are narrow enough: a cell of range / NB values blurs a wait by P times that, R * sqrt(12 P) / NB of the
+// standard deviation of the waits, and where that nears 1 too many entries have to be listed.  Bucket search / cells, us:
+//   NB = 4096, 16 P R^2 / NB^2 = 0.6: 4000 of 24 x 160 138 / 84;  1.0: 4000 of 16 x 256 134 / 85;
+//   1.2: 1000 of 8 x 400 42 / 58;  1.4: 1000 of 4 x 600 37 / 67
+//   NB = 8192, 0.7: 4000 of 32 x 300 269 / 231;  1.0: 8000 of 64 x 256 588 / 494 (2000 of them 159 / 146);
+//   1.4: 1000 of 24 x 500 85 / 105;  3.8: 1000 of 16 x 1000 170 / 358
+// More rows: 8000 of 100 x 24 123 / 143, of 200 x 40 289 / 383, of 200 x 60 488 / 549.  Up to 2048 entries there is
+// little to save (16384 of 64 x 30 162 / 179); between 4097 and 8192, with a chip's worth of instances or less (1 of 64 x 100
+// 20.5 / 17, 300 27 / 27, 8192 of 64 x 128 310 / 364).
+bool takes_cells(i64 B, int P, int R)
+{
+    const i64 n = (i64)P * R, nb = n <= 8192 ? 4096 : 8192;
+    if (P > WAVE || 16 * n * R > nb * nb) return false;
+    return (n > 2048 && n <= 4096) || n > 8192 || (n > 4096 && B <= GENERAL_GRID);
+}
+
 // The rows are either stored (ts != nullptr) or predicted: t[p][i] = le[p] + (i + 1) * iv[p] (ts == nullptr; direct: every
 // candidate may be evaluated).
 int run_batch(const i64* ts, const i64* le, const i64* iv, i64 B, int P, int R,
@@ -478,9 +495,9 @@ int run_batch(const i64* ts, const i64* le, const i64* iv, i64 B, int P, int R,
     if (!pl.multi) {
         if (int rc = check_device()) return rc;
         if (pred && direct && takes_direct(B, P, n, false)) return launch_direct(K_DIRECT, le, iv, B, 0, B, P, R, barrier, iters, wait, status, st);
-        if (takes_run_kernel(1, B, n)) return launch_run(ts, le, iv, 0, 1, B, P, R, barrier, iters, wait, status, st);
         const int rshift = (R & (R - 1)) == 0 ? __builtin_ctz((unsigned)R) : -1;
         const dim3 grid((unsigned)B);
+        if (takes_run_kernel(1, B, n)) return launch_run(ts, le, iv, 0, 1, B, P, R, barrier, iters, wait, status, st);
 #define LAUNCH_INSTANCE(NT_, ITEMS_)                                                                        \
     do {                                                                                                    \
         if (pred) LAUNCH(K_INSTANCE, (zl_instance_kernel<NT_, ITEMS_, true>), grid, dim3(NT_), ts, le, iv, P, R, rshift, \
@@ -488,6 +505,8 @@ int run_batch(const i64* ts, const i64* le, const i64* iv, i64 B, int P, int R,
         else LAUNCH(K_INSTANCE, (zl_instance_kernel<NT_, ITEMS_, false>), grid, dim3(NT_), ts, le, iv, P, R, rshift, \
                     barrier, iters, wait, status);                                                          \
     } while (0)
+#define LAUNCH_CELLS(NT_, ITEMS_, NB_)                                                                      \
+    LAUNCH(K_CELLS, (zl_cells_kernel<NT_, ITEMS_, NB_>), grid, dim3(NT_), ts, P, R, rshift, barrier, iters, wait, status)
         // larger instances keep their records in registers: less LDS, several workgroups per CU
 #define LAUNCH_INSTANCE_REG(NT_, ITEMS_)                                                                    \
     do {                                                                                                    \
@@ -497,12 +516,20 @@ int run_batch(const i64* ts, const i64* le, const i64* iv, i64 B, int P, int R,
                     barrier, iters, wait, status);                                                          \
     } while (0)
         if (n <= 256) LAUNCH_INSTANCE(128, 2);
-        else if (n <= 1024) LAUNCH_INSTANCE(256, 4);       // (batches of so small instances are often small too: the shorter chain per thread wins)
+        else if (!pred && takes_cells(B, P, R)) {
+            // small batches: the shorter chain per thread wins (1 of 64 x 60 15.6 us, with 256 threads 17.4; 8000 178 / 156)
+            if (n <= 4096 && B <= GENERAL_GRID) LAUNCH_CELLS(512, 8, 4096);
+            else if (n <= 4096) LAUNCH_CELLS(256, 16, 4096);
+            else if (n <= 8192) LAUNCH_CELLS(512, 16, 4096);
+            else if (B <= GENERAL_GRID) LAUNCH_CELLS(1024, 16, 8192);
+            else LAUNCH_CELLS(512, 32, 8192);
+        } else if (n <= 1024) LAUNCH_INSTANCE(256, 4);       // (batches of so small instances are often small too: the shorter chain per thread wins)
         else if (n <= 2048) LAUNCH_INSTANCE_REG(256, 8);
         else if (n <= 4096) LAUNCH_INSTANCE_REG(256, 16);
         else if (n <= 8192) LAUNCH_INSTANCE_REG(512, 16);
         else LAUNCH_INSTANCE_REG(1024, 16);
 #undef LAUNCH_INSTANCE_REG
+#undef LAUNCH_CELLS
 #undef LAUNCH_INSTANCE
         // what the kernel above left: the general search in the smallest workgroup whose records hold an
         // instance (half of NT * ITEMS with 64-bit deltas), as many workgroups as fit the chip at once

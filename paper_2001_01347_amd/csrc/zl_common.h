@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include <limits>
+#include <type_traits>
 
 #include "ebsp_zipline.h"
 
@@ -48,7 +49,9 @@ template <int CTRL, int ROWS, class T>
 __device__ __forceinline__ T dpp_take(T fill, T v)
 {
     static_assert(sizeof(T) == 4 || sizeof(T) == 8, "one or two words");
-    if constexpr (sizeof(T) == 4) {
+    if constexpr (std::is_same<T, float>::value) {
+        return __uint_as_float(dpp_word<CTRL, ROWS>(__float_as_uint(fill), __float_as_uint(v)));
+    } else if constexpr (sizeof(T) == 4) {
         return (T)dpp_word<CTRL, ROWS>((u32)fill, (u32)v);
     } else {
         const u64 f = (u64)fill, x = (u64)v;
@@ -68,6 +71,7 @@ __device__ __forceinline__ u64 uniform(u64 x) { return (u64)uniform((u32)x) | ((
 __device__ __forceinline__ u32 last_lane(u32 x) { return (u32)__builtin_amdgcn_readlane((int)x, WAVE - 1); }
 __device__ __forceinline__ u64 last_lane(u64 x);
 __device__ __forceinline__ i64 last_lane(i64 x) { return (i64)last_lane((u64)x); }
+__device__ __forceinline__ float last_lane(float x) { return __uint_as_float(last_lane(__float_as_uint(x))); }
 __device__ __forceinline__ u64 last_lane(u64 x) { return (u64)last_lane((u32)x) | ((u64)last_lane((u32)(x >> 32)) << 32); }
 
 struct OpMin {

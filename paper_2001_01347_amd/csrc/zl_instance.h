@@ -607,9 +607,8 @@ __device__ __forceinline__ void zl_instance_general_search(const Smem& sm, RW& r
     out.flags = flags;
 }
 
-// The instances zl_instance_kernel deferred (value spread of 2^32 or more, or
-// values too clustered for the bucket search): the general window search over
-// whole rows.  A small fixed grid; every workgroup looks through its share of
+// The instances that zl_instance_kernel, zl_instance_reg_kernel and zl_cells_kernel deferred (value spread of 2^32
+// or more, or values too clustered): the general window search over whole rows.  A small fixed grid; every workgroup looks through its share of
 // wait[] for deferred marks and handles the marked instances one after the other.
 template <int NT, int ITEMS>
 __global__ __launch_bounds__(NT) void zl_instance_general_kernel(

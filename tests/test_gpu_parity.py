@@ -535,3 +535,60 @@ def test_single_workgroup_instances_of_wide_spread(zl, oracle, P, R):
         ts[6, P // 2, -2:] = ts[6, P // 2, -2:][::-1].copy()
         st = gpu_run(zl, ts)[3]
         assert st[6] == 1 and (st[:6] == 0).all()
+
+
+# few rows, searched over value cells: either side of the limits on entries, rows, cells and batch; rows of one wave; the
+# smallest and largest instances of each workgroup
+CELLS = [(3, 64, 32), (3, 41, 50), (3, 64, 33), (2, 16, 256), (2, 16, 257), (300, 10, 205), (300, 64, 64), (3, 64, 64), (3, 65, 60), (2, 13, 284), (2, 13, 283),
+         (256, 64, 65), (257, 64, 65), (2, 64, 128), (3, 61, 135), (2, 16, 512), (2, 33, 249), (300, 63, 131), (2, 64, 256), (257, 64, 256), (2, 29, 380),
+         (257, 28, 386)]
+
+
+@pytest.mark.parametrize("B,P,R", CELLS)
+def test_value_cells(zl, oracle, B, P, R):
+    rng = np.random.default_rng(B + 3 * P + R)
+
+    def check(d, what, first=EPOCH):
+        ts = np.cumsum(d, axis=2, dtype=np.int64) + first
+        ob, oi, ow, rc, _ = oracle.zipline(ts, "sweep", threads=8)
+        assert not rc.any()
+        bar, it, w, st = gpu_run(zl, ts)
+        for name, got, want in (("barrier", bar, ob), ("iters", it, oi), ("wait", w, ow)):
+            assert np.array_equal(got, want), f"B={B} P={P} R={R} {what}: {name}"
+        assert not st.any(), f"B={B} P={P} R={R} {what}: status"
+
+    mean = rng.uniform(500, 1500, size=(B, P, 1))
+    even = np.maximum(rng.normal(mean, mean / 5, size=(B, P, R)), 1).astype(np.int64)
+    check(even, "microseconds")
+    check(even * 997 + 13, "nanoseconds", -EPOCH)                    # shifted, or not, with the spread
+    check(even << 21, "wide")
+    check(even - even % 100, "coarse")                               # ties of waits and of values
+    check(np.ones_like(even), "one value per cell")
+    check(np.zeros_like(even), "one value", 5)
+    pause = even // 20
+    pause[:, ::2, R // 2] += 10 ** 8                                 # the rows' ends say little about the rest
+    check(pause, "half of the rows pause")
+    pause[:, :, R // 3] += 1 << 40
+    check(pause, "all rows pause")
+    check(np.exp(rng.normal(5, 3, size=(B, P, R))).astype(np.int64), "heavy tails")
+    late = even.copy()
+    late[:, :, 0] += rng.integers(0, even.sum(axis=2).max() * 2, size=(B, P))
+    check(late, "late starts")                                       # rows that end before others start
+
+
+@pytest.mark.parametrize("B,P,R", [(3, 16, 200), (300, 64, 60), (3, 64, 100), (2, 61, 241), (257, 61, 241)])
+def test_value_cells_flags(zl, oracle, B, P, R):
+    rng = np.random.default_rng(P)
+    ts = np.cumsum(rng.integers(50, 100, size=(B, P, R)), axis=2).astype(np.int64)
+    ob, oi, ow, rc, _ = oracle.zipline(ts, "sweep", threads=4)
+    odd = ts.copy()
+    odd[1, P // 2, R // 2] -= 1000                                   # in one instance: the others are searched as ever
+    bar, it, w, st = gpu_run(zl, odd)
+    ok = np.arange(B) != 1
+    assert st[1] & zl.STATUS_UNSORTED and not st[ok].any()
+    assert np.array_equal(bar[ok], ob[ok]) and np.array_equal(it[ok], oi[ok]) and np.array_equal(w[ok], ow[ok])
+    odd = ts.copy()
+    odd[1, 0] += (1 << 62) - (1 << 40)                               # too large a spread to be summed
+    bar, it, w, st = gpu_run(zl, odd)
+    assert st[1] & zl.STATUS_OVERFLOW and not st[ok].any()
+    assert np.array_equal(bar[ok], ob[ok]) and np.array_equal(it[ok], oi[ok]) and np.array_equal(w[ok], ow[ok])
