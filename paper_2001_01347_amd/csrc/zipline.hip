@@ -556,6 +556,7 @@ int run_batch(const i64* ts, const i64* le, const i64* iv, i64 B, int P, int R,
     void* cross = (void*)(wsp + pl.off_cross);
     u32* winstart = (u32*)(wsp + pl.off_winstart);
     WinVal* winval = (WinVal*)(wsp + pl.off_winval);
+    u32* below = (u32*)(wsp + pl.off_below);
     Partial* partial = (Partial*)(wsp + pl.off_partial);
     uint2* rowpar = pred ? (uint2*)(wsp + pl.off_rowpar) : nullptr;
 
@@ -573,9 +574,9 @@ int run_batch(const i64* ts, const i64* le, const i64* iv, i64 B, int P, int R,
 #define LAUNCH_WINDOW(NT_, CT_, W_)                                                                          \
     do {                                                                                                     \
         if (pred) LAUNCH(K_WINDOW, (zl_window_kernel<NT_, 16, CT_, true, W_>), dim3(wgrid), dim3(NT_), ts, rowpar, B, P, R, info, \
-                         (const CT_*)cross, pl.stride, winstart, winval, pl.max_win, groups, groups_inv, partial); \
+                         (const CT_*)cross, pl.stride, winstart, winval, pl.max_win, groups, groups_inv, below, partial); \
         else LAUNCH(K_WINDOW, (zl_window_kernel<NT_, 16, CT_, false, W_>), dim3(wgrid), dim3(NT_), ts, rowpar, B, P, R, info, \
-                    (const CT_*)cross, pl.stride, winstart, winval, pl.max_win, groups, groups_inv, partial);  \
+                    (const CT_*)cross, pl.stride, winstart, winval, pl.max_win, groups, groups_inv, below, partial);  \
     } while (0)
 #define LAUNCH_WINDOWS(NT_)                                                                                  \
     do {                                                                                                     \

@@ -99,7 +99,8 @@ __device__ __forceinline__ Smem carve_hot(unsigned char* smem)
 // Which of a thread's items exist is the caller's to say: Present::operator()(j).  The default
 // is the strided layout above (SlotsBelow).  LIST_CAP > 0: the record area holds only that many
 // records (at least 2 * BUCKET_LIMIT); if more entries survive the bounds they are scattered and
-// evaluated in rounds, whole buckets at a time (only with a map that has bounds).
+// evaluated in rounds, whole buckets at a time (only with a map that has bounds).  KNOWN: some candidate waits `known`;
+// where nothing here waits as little, best_wait is U64_MAX.
 template <int NT>
 struct SlotsBelow {           // item j of thread t is slot j*NT + t of `total`
     int total;
@@ -113,10 +114,10 @@ struct StoredDeltas {         // the deltas sit in registers
     __device__ __forceinline__ u32 operator()(int j) const { return dl[j]; }
 };
 template <int NT, int ITEMS, bool WITH_W0, class Map, int LIST_CAP = 0, class Present = SlotsBelow<NT>,
-          class Delta = StoredDeltas<ITEMS>>
+          class Delta = StoredDeltas<ITEMS>, bool KNOWN = false>
 __device__ __forceinline__ bool zl_bucket_finish(const Smem& sm, const u32 (&key)[ITEMS], const Delta delta,
                                                  const Map bucket, const Present present, u64 a, u64 thr, u32 P, u64 w0,
-                                                 u64& best_wait, u32& best_key)
+                                                 u64& best_wait, u32& best_key, i64 known = INT64_MAX)
 {
     using H = HotCfg<NT, ITEMS>;
     static_assert(LIST_CAP == 0 || (Map::HAS_BOUNDS && LIST_CAP >= 2 * (int)BUCKET_LIMIT), "a short list needs the bounds");
@@ -173,8 +174,9 @@ __device__ __forceinline__ bool zl_bucket_finish(const Smem& sm, const u32 (&key
         const u64 e0 = sbase + s0, e1 = e0 + s1;
         const i64 ub0 = (i64)((u64)P * hi0 - e0), ub1 = (i64)((u64)P * hi1 - e1);       // both without W0, like ubmin
         // (a bucket whose keys are all below `need` holds no candidate at all)
-        const bool live0 = c0 && hi0 >= need && ub0 - (i64)((u64)P * (hi0 - lo0)) <= ubmin;
-        const bool live1 = c1 && hi1 >= need && ub1 - (i64)((u64)P * (hi1 - lo1)) <= ubmin;
+        const i64 most = KNOWN && known - (i64)W0 < ubmin ? known - (i64)W0 : ubmin;
+        const bool live0 = c0 && hi0 >= need && ub0 - (i64)((u64)P * (hi0 - lo0)) <= most;
+        const bool live1 = c1 && hi1 >= need && ub1 - (i64)((u64)P * (hi1 - lo1)) <= most;
         u32 at0 = DROPPED, at1 = DROPPED;
         if (live0) at0 = atomicAdd(live_count, c0);
         if (live1) at1 = atomicAdd(live_count, c1);
@@ -185,6 +187,11 @@ __device__ __forceinline__ bool zl_bucket_finish(const Smem& sm, const u32 (&key
         bsum[2 * tid + 1] = e0 | ((u64)(live1 ? at1 : (LIST_CAP ? FIRST_MASK : 0u)) << SUM_BITS);
         __syncthreads();
         const int live = (int)*live_count;
+        if (KNOWN && live == 0) {                         // (everything here waits longer)
+            best_wait = U64_MAX;
+            best_key = 0;
+            return true;
+        }
         auto evaluate = [&](u32 k, u32 x, u32 e, u64 S) {           // candidate k: its bucket's records are [x, e)
             for (; x < e; ++x) {
                 const u64 r = recs[x];

@@ -403,9 +403,13 @@ struct WinVal {
     u32 pad_;
 };
 
+// The best wait that a window of instance b has found so far: the first words of its row of `below`, once zl_plan is through
+// with that.
+__device__ __forceinline__ u64* best_of(u32* below, i64 b, int stride) { return (u64*)(below + b * (i64)stride); }
+
 template <int NT, int PLAN_SLICE>       // PLAN_SLICE: fine bins held in LDS at a time
 __global__ __launch_bounds__(NT) void zl_plan_kernel(
-    InstInfo* __restrict__ info, const SegEntry* __restrict__ segtab, const u32* __restrict__ below, int stride,
+    InstInfo* __restrict__ info, const SegEntry* __restrict__ segtab, u32* __restrict__ below, int stride,
     const u32* __restrict__ widebin, bool pred, u32* __restrict__ winstart, WinVal* __restrict__ winval, int max_win,
     u32 fill, u32 buckets)
 {
@@ -543,6 +547,8 @@ __global__ __launch_bounds__(NT) void zl_plan_kernel(
         if (slow) v.scale = 0;
         wv[j] = v;
     }
+    __syncthreads();
+    if (tid == 0) *best_of(below, b, stride) = (u64)INT64_MAX;
 }
 
 }  // namespace

@@ -76,12 +76,19 @@ struct WinHot {
 
 // The fast search of one window (see zl_window_kernel); lo/hi hold the index
 // ranges of the thread's first ROWS_PER_THREAD<NT> rows.
+// Predicted rows: the best wait that any window of the instance has found so far (`best`; it only falls, so an old value
+// is as right as a new one) rules out most windows once their buckets are summed, and with them the scatter of
+// their entries, a third of a window's LDS atomics.  us, without / with: 64 of 1024 x 4096 415 / 391, 1024 of 256 x 1024 770 / 755,
+// 1000 of 60 x 1000 280 / 266.  Stored rows are bound by fetching lines that neighbouring windows share, and fetch more of
+// them the less the windows run in step: 1024 of 256 x 1024 1165 / 1304, 64 of 400 x 1000 170 / 191 (1000 of 60 x 1000 417 / 384).
 template <int NT, int ITEMS, class CT, bool PRED>
 __device__ __forceinline__ void window_search(const Smem& sm, const Rows& rw, const WinVal& wv, const InstInfo& ii, bool hot,
                                               const u32 (&lo)[ROWS_PER_THREAD<NT>], const u32 (&hi)[ROWS_PER_THREAD<NT>],
-                                              Partial* __restrict__ out)
+                                              u64* best, Partial* __restrict__ out)
 {
     using H = HotCfg<NT, ITEMS>;
+    // (asked for now, needed once the window's entries are in their buckets)
+    const u64 known = PRED ? __hip_atomic_load(best, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : (u64)INT64_MAX;
     {
         u64* bsum = sm.red - H::NB;
         bsum[threadIdx.x] = 0; bsum[threadIdx.x + NT] = 0;
@@ -99,10 +106,10 @@ __device__ __forceinline__ void window_search(const Smem& sm, const Rows& rw, co
             defer = total > H::CAP;
             if (!defer && total > 0) {
                 u32 bkey;
-                if (zl_bucket_finish<NT, ITEMS, true, LinearMap, WinHot<NT, ITEMS, PRED>::LIST>(sm, key, StoredDeltas<ITEMS>{dl},
+                if (zl_bucket_finish<NT, ITEMS, true, LinearMap, WinHot<NT, ITEMS, PRED>::LIST, SlotsBelow<NT>, StoredDeltas<ITEMS>, PRED>(sm, key, StoredDeltas<ITEMS>{dl},
                                                       linear_map((u32)(wv.Elast - wv.A), H::NB, wv.scale ? wv.scale : 1u,
                                                                  wv.inv52),
-                                                      SlotsBelow<NT>{total}, wv.A, ii.thr, (u32)rw.P, w0, r.wait, bkey))
+                                                      SlotsBelow<NT>{total}, wv.A, ii.thr, (u32)rw.P, w0, r.wait, bkey, (i64)known))
                     r.brel = wv.A + bkey;
                 else
                     defer = true;
@@ -114,7 +121,10 @@ __device__ __forceinline__ void window_search(const Smem& sm, const Rows& rw, co
         }
     }
     __syncthreads();                          // everyone is done with LDS before the next window
-    if (threadIdx.x == 0) *out = r;
+    if (threadIdx.x == 0) {
+        *out = r;
+        if (PRED && r.wait < known) atomicMin(best, r.wait);
+    }
 }
 
 // The summed-wait search of one window for window_pairs().
@@ -123,9 +133,9 @@ struct SumSearch {
     static constexpr bool PREDICTED = PRED;
     __device__ __forceinline__ static void run(const Smem& sm, const Rows& rw, const WinVal& wv, const InstInfo& ii, bool hot,
                                                const u32 (&lo)[ROWS_PER_THREAD<NT>], const u32 (&hi)[ROWS_PER_THREAD<NT>],
-                                               Partial* __restrict__ out)
+                                               u64* best, Partial* __restrict__ out)
     {
-        window_search<NT, ITEMS, CT, PRED>(sm, rw, wv, ii, hot, lo, hi, out);
+        window_search<NT, ITEMS, CT, PRED>(sm, rw, wv, ii, hot, lo, hi, best, out);
     }
 };
 
@@ -140,7 +150,7 @@ __device__ __forceinline__ void window_pairs(
     const Smem& sm, const i64* __restrict__ ts, const uint2* __restrict__ rowpar, i64 B, int P, int R,
     const InstInfo* __restrict__ info, const CT* __restrict__ cross, int stride,
     const u32* __restrict__ winstart, const WinVal* __restrict__ winval, int max_win, u32 groups, u32 groups_inv,
-    Partial* __restrict__ partial)
+    u32* __restrict__ below, Partial* __restrict__ partial)
 {
     constexpr bool PRED = Search::PREDICTED;
     constexpr int RPT = ROWS_PER_THREAD<NT>;
@@ -169,6 +179,7 @@ __device__ __forceinline__ void window_pairs(
     const int jend = j0 + W < (int)ii.nwin ? j0 + W : (int)ii.nwin;
     if (j0 >= jend) return;
     Partial* out = partial + b * (i64)max_win;
+    u64* const best = best_of(below, b, stride);
     // The fast search holds keys relative to its window and deltas between neighbours in 32 bits.  That
     // fits every window of an instance whose value spread does; in the others zl_plan has marked the
     // windows it does not fit (WinVal::scale == 0).
@@ -198,7 +209,7 @@ __device__ __forceinline__ void window_pairs(
             if (hot && i + 1 < W && j0 + i + 1 < jend) load_column<NT, CT>(rw, bins[i + 1 < W ? i + 2 : W], next);
             rw.k0 = bins[i];
             rw.k1 = bins[i + 1] > bins[i] ? bins[i + 1] : bins[i];
-            Search::run(sm, rw, vals[i], ii, hot, lo, hi, out + j0 + i);
+            Search::run(sm, rw, vals[i], ii, hot, lo, hi, best, out + j0 + i);
 #pragma unroll
             for (int c = 0; c < RPT; ++c) { lo[c] = hi[c]; hi[c] = next[c]; }
         }
@@ -210,13 +221,13 @@ __global__ __launch_bounds__(NT, (!PRED && NT == 256 ? 5 : 4)) void zl_window_ke
     const i64* __restrict__ ts, const uint2* __restrict__ rowpar, i64 B, int P, int R,
     const InstInfo* __restrict__ info, const CT* __restrict__ cross, int stride,
     const u32* __restrict__ winstart, const WinVal* __restrict__ winval, int max_win, u32 groups, u32 groups_inv,
-    Partial* __restrict__ partial)
+    u32* __restrict__ below, Partial* __restrict__ partial)
 {
     using L = WinHot<NT, ITEMS, PRED>;
     __shared__ __align__(16) unsigned char smem[L::BYTES];
     const Smem sm = L::carve(smem);
     window_pairs<NT, ITEMS, CT, SumSearch<NT, ITEMS, CT, PRED>, W>(sm, ts, rowpar, B, P, R, info, cross, stride, winstart,
-                                                               winval, max_win, groups, groups_inv, partial);
+                                                               winval, max_win, groups, groups_inv, below, partial);
 }
 
 // The windows zl_window_kernel deferred: the general window search.  A small

@@ -193,3 +193,19 @@ def test_every_candidate_evaluated_flags(zl, oracle, P, R):
     assert st[3][1] & zl.STATUS_UNSORTED and st[3][2] & zl.STATUS_OVERFLOW and st[3][0] == 0 and st[3][3] == 0
     ob, oi, ow, rc, _ = oracle.zipline(oracle.predicted_rows(le[::3], iv[::3], R), "sweep", threads=4)
     assert np.array_equal(st[0][::3], ob) and np.array_equal(st[1][::3], oi) and np.array_equal(st[2][::3], ow)
+
+
+# windows that are ruled out by what others of the instance have found: equal waits in all of them (the first is the answer),
+# the best one in the last, in the first, in a window without a rival; workgroups of 256, 512 and 1024 threads
+@pytest.mark.parametrize("B,P,R", [(2, 300, 1000), (1, 70, 4000), (3, 700, 400), (1, 1600, 170)])
+def test_windows_that_rule_each_other_out(zl, oracle, B, P, R):
+    rng = np.random.default_rng(P + R)
+    le, iv = random_inputs(rng, B, P, 500, 1000, False)
+    assert_same(zl, oracle, le + EPOCH, iv, R, f"P={P} R={R}")
+    assert_same(zl, oracle, np.zeros_like(le), np.full_like(iv, 12_000), R, f"P={P} R={R}, all alike")
+    group = 3000 * (1 << rng.integers(0, 3, size=(B, P))).astype(np.int64)
+    assert_same(zl, oracle, np.zeros_like(le), group, R, f"P={P} R={R}, the same wait again and again")
+    assert_same(zl, oracle, rng.integers(0, 40, size=(B, P)).astype(np.int64), group, R, f"P={P} R={R}, nearly the same wait")
+    for at in (R - 1, R // 2, 3):                                     # all workers meet once, after `at` iterations
+        iv = 2000 + rng.integers(-300, 300, size=(B, P)).astype(np.int64)
+        assert_same(zl, oracle, 3000 * R - at * iv, iv, R, f"P={P} R={R}, they meet after {at}")
