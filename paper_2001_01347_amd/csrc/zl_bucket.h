@@ -12,7 +12,8 @@ namespace {
 // element of bucket b is BP(b) + the deltas of the bucket's elements whose key
 // is <= its own; equal keys get equal values, so no run-end rule is needed.
 // The work is total + sum over buckets of size^2: a bucket with more than
-// BUCKET_LIMIT entries makes the caller fall back to the radix sort.
+// BUCKET_LIMIT entries makes the caller fall back to the radix sort, unless the
+// bounds rule it out (a map that has them).
 // One exchange for three block-wide results: the exclusive scan of h (a packed
 // count and sum: the two fields must not overflow into each other), (WITH_X) the
 // sum of x and (WITH_U) the minimum over all threads of local(i) - (sum of h's low
@@ -71,7 +72,12 @@ struct HotCfg {
 // deltas (lower SUM_BITS bits: at most 16384 deltas below 2^32 each).
 constexpr int SUM_BITS = 46;
 constexpr u64 SUM_MASK = (1ull << SUM_BITS) - 1;
-constexpr u32 BUCKET_LIMIT = 64;
+// Entries of a bucket that is looked into.  Workers that start together iterate in step at first: 1000 of them fill the first
+// buckets with 65 to 100 entries each, and the radix sort of that one window took as long as all the rest.  us, limit 64 / 128
+// / 256 (buckets that are ruled out not counted: 64 / 128): 1 of 1000 x 60 83 / 46 / 46 (83 / 45), 1 of 1000 x 100 89 / 48.5 / 48.6 (48.3 / 48.1),
+// 8 of 600 x 60 75 / 44 / 44 (75 / 43), 400 of 16 x 4096 342 / 308 / 314 (340 / 307); very different workers, 512 of 100 x 150
+// 394 / 388 / - (- / 60).  Rows that are all alike are the worst case: 1000 of 100 x 15 44 / 57 (- / 59).
+constexpr u32 BUCKET_LIMIT = 128;
 constexpr int GATHER_BATCH = 8;           // elements a thread loads before it uses any of them
 constexpr int GATHER_TAIL = 8;            // the same beyond the first batch
 
@@ -94,7 +100,7 @@ __device__ __forceinline__ Smem carve_hot(unsigned char* smem)
 // On entry the bucket words must be zero and a barrier must have passed since;
 // the record area may hold anything (it is overwritten).  On return some threads
 // may still be reading LDS: the caller passes a barrier before writing it again.
-// Returns false (nothing computed) if some bucket is over the limit.
+// Returns false (nothing computed) if some bucket that is to be looked into is over the limit.
 //
 // Which of a thread's items exist is the caller's to say: Present::operator()(j).  The default
 // is the strided layout above (SlotsBelow).  LIST_CAP > 0: the record area holds only that many
@@ -163,9 +169,9 @@ __device__ __forceinline__ bool zl_bucket_finish(const Smem& sm, const u32 (&key
     };
     u64 hbase, W0;
     i64 ubmin;
-    if ((c0 > c1 ? c0 : c1) > BUCKET_LIMIT) *deep = 1;
+    if (!PRUNE && (c0 > c1 ? c0 : c1) > BUCKET_LIMIT) *deep = 1;
     block_scan_pair<NT, WITH_W0, PRUNE>(h0 + h1, w0, local_bound, sm.red, SUM_MASK, hbase, W0, ubmin);
-    if (*deep) return false;
+    if (!PRUNE && *deep) return false;
     const u32 cbase = (u32)(hbase >> SUM_BITS);
     const u64 sbase = hbase & SUM_MASK;
     u64 bw = U64_MAX;
@@ -177,6 +183,7 @@ __device__ __forceinline__ bool zl_bucket_finish(const Smem& sm, const u32 (&key
         const i64 most = KNOWN && known - (i64)W0 < ubmin ? known - (i64)W0 : ubmin;
         const bool live0 = c0 && hi0 >= need && ub0 - (i64)((u64)P * (hi0 - lo0)) <= most;
         const bool live1 = c1 && hi1 >= need && ub1 - (i64)((u64)P * (hi1 - lo1)) <= most;
+        if ((live0 && c0 > BUCKET_LIMIT) || (live1 && c1 > BUCKET_LIMIT)) *deep = 1;       // (the others are not looked into)
         u32 at0 = DROPPED, at1 = DROPPED;
         if (live0) at0 = atomicAdd(live_count, c0);
         if (live1) at1 = atomicAdd(live_count, c1);
@@ -186,6 +193,7 @@ __device__ __forceinline__ bool zl_bucket_finish(const Smem& sm, const u32 (&key
         bsum[2 * tid] = sbase | ((u64)(live0 ? at0 : (LIST_CAP ? FIRST_MASK : 0u)) << SUM_BITS);
         bsum[2 * tid + 1] = e0 | ((u64)(live1 ? at1 : (LIST_CAP ? FIRST_MASK : 0u)) << SUM_BITS);
         __syncthreads();
+        if (*deep) return false;
         const int live = (int)*live_count;
         if (KNOWN && live == 0) {                         // (everything here waits longer)
             best_wait = U64_MAX;

@@ -547,8 +547,10 @@ __global__ __launch_bounds__(NT) void zl_plan_kernel(
         if (slow) v.scale = 0;
         wv[j] = v;
     }
-    __syncthreads();
-    if (tid == 0) *best_of(below, b, stride) = (u64)INT64_MAX;
+    if (pred) {                               // (windows of stored rows do not share it)
+        __syncthreads();
+        if (tid == 0) *best_of(below, b, stride) = (u64)INT64_MAX;
+    }
 }
 
 }  // namespace

@@ -592,3 +592,34 @@ def test_value_cells_flags(zl, oracle, B, P, R):
     bar, it, w, st = gpu_run(zl, odd)
     assert st[1] & zl.STATUS_OVERFLOW and not st[ok].any()
     assert np.array_equal(bar[ok], ob[ok]) and np.array_equal(it[ok], oi[ok]) and np.array_equal(w[ok], ow[ok])
+
+
+# value buckets of many entries: up to the limit, beyond it, and beyond it where nothing in them can win; whole instances in
+# one workgroup (staged and in registers) and in windows of 256, 512 and 1024 threads
+@pytest.mark.parametrize("B,P,R", [(3, 16, 15), (3, 30, 30), (2, 100, 15), (2, 100, 30), (2, 130, 60), (2, 100, 150), (2, 300, 70), (1, 1000, 60), (1, 1000, 100),
+                                   (1, 1600, 30)])
+def test_deep_buckets(zl, oracle, B, P, R):
+    rng = np.random.default_rng(P + R)
+    jitter = rng.integers(0, 1000, size=(B, P, R))
+
+    def check(d, what):
+        ts = np.cumsum(d, axis=2, dtype=np.int64) + EPOCH
+        ob, oi, ow, rc, _ = oracle.zipline(ts, "sweep", threads=8)
+        bar, it, w, st = gpu_run(zl, ts)
+        assert not rc.any() and not st.any()
+        for name, got, want in (("barrier", bar, ob), ("iters", it, oi), ("wait", w, ow)):
+            assert np.array_equal(got, want), f"B={B} P={P} R={R} {what}: {name}"
+
+    for spread in (1, 20, 400):                                      # in step at first, apart later
+        check(100_000 + jitter * spread // 10, f"iteration times within {100 * spread}")
+    check(100_000 + jitter * 40 * (np.arange(R) > R // 2), "in step for half of the time")
+    check((50 + jitter % 50) * np.logspace(0, 5, P).astype(np.int64)[None, :, None], "very different workers")
+    check(np.exp(rng.normal(5, 3, size=(B, P, R))).astype(np.int64), "heavy tails")
+    late = 50 + jitter % 50
+    late[:, :, 0] += rng.integers(0, 10 ** 7, size=(B, P))
+    check(late, "late starts")
+    check(1000 * (1 + jitter % 3), "few values")
+    for same in (63, 64, 65, 127, 128, 129):                         # as many rows alike, the others behind them
+        alike = 100_000 + 0 * jitter
+        alike[:, same:, 0] += 1 + jitter[:, same:, 0]
+        check(alike, f"{same} rows alike")
