@@ -22,7 +22,7 @@
 //     bounds per bucket drop the buckets that cannot hold the minimum, and
 //     only the entries of the remaining buckets are ordered and evaluated;
 //   * small instances (P*R <= 16384) are one window: one workgroup each, no
-//     scratch memory, one kernel.
+//     scratch memory.
 //
 // Device code, by header (each includes the one before it):
 //   zl_common.h    types, records, wave/block primitives, the fine-bin map
@@ -36,6 +36,8 @@
 //   zl_window.h    window kernels of the summed-wait search
 //   zl_range.h     the objective max(Z) - min(Z)
 //   zl_finish.h    reduction over windows, zl_iters; the copy yardstick
+//   zl_direct.h    predicted rows, every candidate evaluated; runs of supersteps side by side
+//   zl_cells.h     one workgroup per stored instance of few rows: value cells
 //   zl_sweep.h     the frontier sweep: stored rows searched in one pass, no crossing table
 //   zl_gridscan.h  GridScan and FullGridScan, the paper's comparators
 // This file: the host side (plans, launches, the C entry points).

@@ -25,12 +25,13 @@ namespace {
 // way; the entries that remain are evaluated from the rows in 64 bits.
 // What this gives up (too many entries to list: clustered values; sums beyond 32 bits; values behind C that may win) is left to
 // zl_instance_general_kernel.
-// Bound by the load of the entries where the batch is large (2 GiB: 2.2 TB/s; the passes over the keys in between are as long),
+// Bound by the load of the entries where the batch is large (2 GiB: 2.2 TB/s; vector ALU busy 68 %: the passes over the keys are as long as the load),
 // else by the workgroup's chain of steps.  The bucket search of zl_instance_reg_kernel counts the entries of coarse bins
 // first, which is one more LDS atomic per entry, a table and 14 more instructions per entry to look a bucket up, and leaves
-// spreads of 2^32 and more to the general search.  us, that one / this: 16384 of 64 x 256 1175 / 986, 8192 of 64 x 60
-// 181 / 159, 1 of 64 x 60 25 / 16; 1021 of 61 x 241 in nanoseconds 277 / 105.  Tried and not kept: the first loads and C
-// ahead of everything (in the shadow of the loads, but 80 registers spilled: 1270); all entries of a cell with D below the
+// spreads of 2^32 and more to the general search.  us, that one / this: 16384 of 64 x 256 1175 / 983, 8192 of 64 x 60
+// 181 / 159, 1 of 64 x 60 25 / 16; 1021 of 61 x 241 in nanoseconds 277 / 98.  Tried and not kept: the first loads and C
+// ahead of everything (in the shadow of the loads, but 80 registers spilled: 1270); 8 or 32 loads in flight instead of 16
+// (1024 and 1006; in nanoseconds 102 and 99 against 98); all entries of a cell with D below the
 // best bound listed without looking at them one by one (50 instead of 13: 1310); 1024 threads for large batches (1290).
 template <int NT, int ITEMS, int NB>
 struct CellSmem {
@@ -75,7 +76,7 @@ __global__ __launch_bounds__(NT, 4) void zl_cells_kernel(
     i64* __restrict__ barrier, int* __restrict__ iters, i64* __restrict__ wait, int* __restrict__ status)
 {
     using S = CellSmem<NT, ITEMS, NB>;
-    constexpr int LOG = __builtin_ctz((unsigned)NB), CPT = S::CPT, LB = ITEMS < 8 ? ITEMS : 8;
+    constexpr int LOG = __builtin_ctz((unsigned)NB), CPT = S::CPT, LB = ITEMS < 8 ? ITEMS : ITEMS > 16 ? 16 : 8;
     static_assert(ITEMS <= 32 && ITEMS % LB == 0, "item masks are one word; loads go in batches");
     static_assert(NB % NT == 0 && (CPT & (CPT - 1)) == 0 && NB <= 65536, "cells are numbered in 16 bits");
     __shared__ __align__(16) S sm;
@@ -296,6 +297,8 @@ __global__ __launch_bounds__(NT, 4) void zl_cells_kernel(
             const u32 limit = ms ? top + 2u * (u32)P : top;
             if (low <= limit) {
                 forget();
+                u32 first_index = (u32)(wbase + lane);
+                asm volatile("" : "+v"(first_index));        // (or the loads' indices are kept till here, spilled)
 #pragma unroll
                 for (int j = 0; j < ITEMS; ++j) {
                     if (!((used >> j) & 1u)) continue;
@@ -303,7 +306,7 @@ __global__ __launch_bounds__(NT, 4) void zl_cells_kernel(
                     if (lb <= limit) {
                         if (ms) {
                             const u32 at = atomicAdd(&sm.listed, 1u);
-                            if (at < (u32)S::LIST) { sm.key[at] = (u32)(wbase + j * WAVE + lane); sm.acc[at] = 0; }
+                            if (at < (u32)S::LIST) { sm.key[at] = first_index + (u32)(j * WAVE); sm.acc[at] = 0; }
                         } else
                             atomicOr(&sm.flag[c >> 5], 1u << (c & 31u));
                     }
