@@ -42,20 +42,22 @@ HBM_PEAK_GBS = 8000.0          # MI355X HBM3E, published peak
 # reads for the plain copy kernel of known size (FETCH_SIZE x 2048 B, WRITE_SIZE x 1024 B per count).  The
 # figures below are the counters' per-dispatch averages, kernel by kernel in launch order.  They hold only for
 # the kernel sources they were taken from: `traffic` is null once those have changed.
-COUNTED_SOURCES_SHA256 = "732355e5336ede996ab3e438c3664e7adfb95ab73d3f92c65f4c02021103d3bc"
+COUNTED_SOURCES_SHA256 = "e6f29f88c429095193295be0ece0fe4a1bc2e1b2e0b80fea609c7dbc4426f7a9"
 FETCH_UNIT, WRITE_UNIT = 2048, 1024      # bytes per count: what the copy kernel's 2 GiB in, 2 GiB out read as (1 048 607 and 2 097 152)
 COUNTED_TRAFFIC = {     # (objective, predicted, config) -> (dominant kernel, its bytes, bytes of all kernels of a call)
-    ("sum", False, 5): ("zl_partition_kernel", 1049001 * FETCH_UNIT + 164756 * WRITE_UNIT,
-                        (29467 + 1049001 + 9710 + 267 + 639621 + 130 + 7711) * FETCH_UNIT
-                        + (70 + 164756 + 272 + 352 + 358 + 8192 + 258) * WRITE_UNIT),
-    ("sum", False, 3): ("zl_instance_reg_kernel", 1404682 * FETCH_UNIT + 144347 * WRITE_UNIT,
-                        (1404682 + 88) * FETCH_UNIT + 144347 * WRITE_UNIT),
-    ("sum", True, 5): ("zl_window_kernel", 73721 * FETCH_UNIT + 157 * WRITE_UNIT,
-                       (620 + 4772 + 2451 + 266 + 73721 + 129 + 881) * FETCH_UNIT
-                       + (582 + 149538 + 271 + 350 + 157 + 8192 + 258) * WRITE_UNIT),
-    ("sum", False, 4): ("zl_window_kernel", 1761277 * FETCH_UNIT + 2181 * WRITE_UNIT,
-                        (123917 + 1053099 + 14182 + 1630 + 1761277 + 558 + 36253) * FETCH_UNIT
-                        + (1122 + 232418 + 1554 + 2065 + 2181 + 0 + 1088) * WRITE_UNIT),
+    ("sum", False, 5): ("zl_partition_kernel", 1048998 * FETCH_UNIT + 164728 * WRITE_UNIT,
+                        (29472 + 1048998 + 9705 + 258 + 639084 + 130 + 7711) * FETCH_UNIT
+                        + (70 + 164728 + 272 + 352 + 361 + 8192 + 258) * WRITE_UNIT),
+    ("sum", False, 3): ("zl_cells_kernel", 1204659 * FETCH_UNIT + 71294 * WRITE_UNIT,
+                        (1204659 + 88) * FETCH_UNIT + 71294 * WRITE_UNIT),
+    ("sum", True, 5): ("zl_window_kernel", 73979 * FETCH_UNIT + 276 * WRITE_UNIT,
+                       (617 + 4769 + 2445 + 257 + 73979 + 129 + 881) * FETCH_UNIT
+                       + (582 + 149532 + 271 + 352 + 276 + 8192 + 258) * WRITE_UNIT),
+    ("sum", False, 4): ("zl_window_kernel", 1761470 * FETCH_UNIT + 2180 * WRITE_UNIT,
+                        (123891 + 1053098 + 14177 + 1630 + 1761470 + 558 + 36257) * FETCH_UNIT
+                        + (1122 + 232409 + 1554 + 2065 + 2180 + 0 + 1088) * WRITE_UNIT),
+    ("range", False, 5): ("zl_range_fast_kernel", 1425147 * FETCH_UNIT + 24 * WRITE_UNIT,
+                          (1425147 + 18178) * FETCH_UNIT + (24 + 262) * WRITE_UNIT),
 }
 
 
