@@ -46,9 +46,12 @@ __device__ __forceinline__ DirectFacts direct_rows(DirectSmem<NT, PM, SPLIT>& sm
     double thr = -1e300, sum = 0.0;
     int off = 0, back = 0;
     for (int p = threadIdx.x; p < P; p += NT) {
-        const i64 s = iv[p], first = (i64)((le ? (u64)le[p] - (u64)f.ref : 0ull) + (u64)s);
+        // (start times may be anything: a difference that does not fit 64 bits would look small wrapped round)
+        const i64 s = iv[p];
+        i64 from, first;
+        const bool wraps = __builtin_sub_overflow(le ? le[p] : f.ref, f.ref, &from) | __builtin_add_overflow(from, s, &first);
         back |= s < 0;
-        off |= s < 0 || s > most_step || first > most || first < -most;
+        off |= wraps || s < 0 || s > most_step || first > most || first < -most;
         const double fs = (double)s, ff = (double)first, rcp = direct_rcp(fs);
         sm.row[p] = DirectRow{rcp, direct_shift(ff, fs, rcp)};
         sm.step[p] = fs;

@@ -195,6 +195,21 @@ def test_every_candidate_evaluated_flags(zl, oracle, P, R):
     assert np.array_equal(st[0][::3], ob) and np.array_equal(st[1][::3], oi) and np.array_equal(st[2][::3], ow)
 
 
+@pytest.mark.parametrize("P,R", [(2, 1), (16, 60), (16, 300), (100, 150), (300, 60)])
+def test_every_candidate_evaluated_flags_start_times_2_to_the_64_apart(zl, oracle, P, R):
+    # no row overflows, but the distance of two start times does: modulo 2^64 it looks small
+    rng = np.random.default_rng(P)
+    le, iv = random_inputs(rng, 4, P, 500, 1000, False)
+    for b, far in ((1, 1), (2, P - 1)):
+        le[b] -= le[b].min()
+        le[b, :far] += np.iinfo(np.int64).min
+        le[b, far:] = np.iinfo(np.int64).max - R * iv[b, far:]
+    st = gpu_run(zl, le, iv, R)
+    assert st[3].tolist() == [0, zl.STATUS_OVERFLOW, zl.STATUS_OVERFLOW, 0]
+    ob, oi, ow, rc, _ = oracle.zipline(oracle.predicted_rows(le[::3], iv[::3], R), "sweep", threads=4)
+    assert np.array_equal(st[0][::3], ob) and np.array_equal(st[1][::3], oi) and np.array_equal(st[2][::3], ow)
+
+
 # windows that are ruled out by what others of the instance have found: equal waits in all of them (the first is the answer),
 # the best one in the last, in the first, in a window without a rival; workgroups of 256, 512 and 1024 threads
 @pytest.mark.parametrize("B,P,R", [(2, 300, 1000), (1, 70, 4000), (3, 700, 400), (1, 1600, 170)])

@@ -298,3 +298,14 @@ def test_flagged_supersteps_side_by_side(zl, oracle, P, R, S):
             start = np.full((1, P), ob[0] + 3, dtype=np.int64)
     ob, oi, ow = oracle.simulate(le[::2], np.ascontiguousarray(iv[:, ::2]), R, 3)[:3]
     assert np.array_equal(bar[:, ::2], ob) and np.array_equal(w[:, ::2], ow) and np.array_equal(it[:, ::2], oi)
+
+
+@pytest.mark.parametrize("P,R", [(8, 20), (16, 90), (70, 40)])
+def test_supersteps_side_by_side_flag_start_times_2_to_the_64_apart(zl, oracle, P, R):
+    rng = np.random.default_rng(P)
+    iv = rng.integers(80, 120, size=(4, 2, P)).astype(np.int64)
+    le = rng.integers(0, 80, size=(2, P)).astype(np.int64)
+    le[1, 0] += np.iinfo(np.int64).min
+    le[1, 1:] += np.iinfo(np.int64).max - 80 - 120 * R
+    st = gpu_run(zl, le, iv, R, 3)[3]
+    assert (st[:, 0] == 0).all() and (st[:, 1] == zl.STATUS_OVERFLOW).all()      # (the workers keep their start times)
