@@ -814,8 +814,10 @@ __device__ __forceinline__ void zl_range_slice(SliceSmem<NT, NB>& sm, const i64*
             const V g = (V)(g0 - 1u) << ms, h = last_of(c);
             return g > h ? g - h : (V)0;
         };
-        // (the best itself is the first of its kind: of equal ones behind it none can win)
-        auto wins = [&](V lb, u32 c) -> bool { return (u64)lb < top || ((u64)lb == top && (u64)first_of(c) <= best.x); };
+        // (the best itself is the first of its kind: of equal ones behind it none can win.  Where `top` is only some cell's upper
+        // bound, the entry that is as good is still to be found, anywhere)
+        auto may_be = [&](u64 lb, u64 from) -> bool { return lb < top || (lb == top && (best.d > top || from <= best.x)); };
+        auto wins = [&](V lb, u32 c) -> bool { return may_be((u64)lb, (u64)first_of(c)); };
         auto may_win = [&](u32 c) -> bool { return wins(low_bound(sm.cells[(int)c - 1], c), c); };
         const u32 lane = tid & (WAVE - 1), wave = tid >> 6;
         const u32 mine = wave * (NB / NW) + 4 * lane;      // the thread's k-th cell:
@@ -992,7 +994,7 @@ __device__ __forceinline__ void zl_range_slice(SliceSmem<NT, NB>& sm, const i64*
         __syncthreads();
         u32 waiting = sm.waiting;
         if (waiting > (u32)RANGE_STACK) { out.left = 1; return; }
-        while (waiting > 0 && (sm.least[waiting - 1] > top || (sm.least[waiting - 1] == top && sm.from[waiting - 1] > best.x))) --waiting;
+        while (waiting > 0 && !may_be(sm.least[waiting - 1], sm.from[waiting - 1])) --waiting;
         if (waiting == 0) break;
         A = sm.from[waiting - 1];
         E = sm.to[waiting - 1];

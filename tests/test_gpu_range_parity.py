@@ -244,3 +244,23 @@ def test_rows_out_of_order_anywhere(zl, oracle, B, P, R):
         bad[0, p, i] = bad[0, p, i - 1] - (1 if k < 3 else 50_000_000)
         st = gpu_run(zl, bad)[3]
         assert st[0] & zl.STATUS_UNSORTED and (st[1:] == 0).all(), (k, i)
+
+
+# the answer is the earliest end of the rows, alone in a cell that begins there: that cell's two bounds are one value.  One
+# iteration of all workers at a time, equally far apart but for the last; the ends lie 1 apart from instance to
+# instance, or where cells of 2^shift values begin.  Workgroups of 256 and 512 threads, one slice and several, all numbers
+# of cells, small instances
+@pytest.mark.parametrize("B,P,R,ends", [(1100, 300, 30, 2_899_500), (64, 300, 30, 250_000), (300, 1100, 40, 3_900_000), (600, 300, 300, 16 * 2048 * 100),
+                                        (64, 40, 30, 200_000), (64, 16, 30, 6000), (4, 300, 30, 2832 << 33), (4, 40, 30, 2832 << 33), (4, 40, 30, 2832 << 15)])
+def test_the_answer_is_the_earliest_end(zl, oracle, B, P, R, ends):
+    rng = np.random.default_rng(B + P + R)
+    lim = ends + np.arange(B, dtype=np.int64) if ends < 1 << 25 else ends * (1 + np.arange(B, dtype=np.int64) % 2)
+    period = lim // (R - 1)
+    apart = np.minimum(period // 20, 1 << 30)
+    ts = np.arange(R, dtype=np.int64) * period[:, None, None] + (rng.random((B, P, R)) * apart[:, None, None]).astype(np.int64)
+    ts[:, 1, :] = np.arange(R, dtype=np.int64) * period[:, None]
+    ts[:, 2, :] = ts[:, 1, :] + apart[:, None]
+    ts[:, :, -1] = lim[:, None] + (rng.random((B, P)) * (apart - 4)[:, None]).astype(np.int64) + 1
+    ts[:, 1, -1] = lim
+    ts[:, 2, -1] = lim + apart - 3                         # (less than a cell is wide: others' lower bounds are smaller)
+    assert_same(zl, oracle, ts, f"B={B} P={P} R={R}")
