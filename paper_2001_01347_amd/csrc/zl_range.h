@@ -627,11 +627,11 @@ __global__ __launch_bounds__(NT, (NT == 64 ? 5 : 6)) void zl_range_instance_kern
             i = i >= R ? i - R : i;
         }
     }
-    Best best;
+    Best best{0ull, 0ull};
     int bad = 0;
     const bool found = zl_range_registers<NT, ITEMS, NB, SORT_REST>(cells, red, inst, wbase, v, ahead, have, heads, ends, best, bad);
     bad = __syncthreads_or(bad);
-    if (!found) {
+    if (!found && !bad) {                                  // (the order of the rows has been seen here)
         if (tid == 0) dmin[b] = DEFERRED;
         return;
     }
@@ -1084,12 +1084,14 @@ __global__ __launch_bounds__(NT) void zl_range_window_kernel(
                 flags |= (int)r.flags;
                 left |= (int)r.left;
             }
-            if (__syncthreads_or(left)) { search(b); continue; }
+            // (the slices have seen all neighbours in all rows; the search by pieces may miss a step back between two of them)
+            flags = __syncthreads_or(flags);
+            if (__syncthreads_or(left) && !flags) { search(b); continue; }
             i64 base = INT64_MAX;
             for (int p = tid; p < P; p += NT) { const i64 f = ts[((size_t)b * P + p) * R]; base = f < base ? f : base; }
             base = block_reduce<i64, NT>(base, (i64*)sm.red, OpMin());
             best = block_first_min<NT>(best, sm.red);
-            store(b, base, best, __syncthreads_or(flags));
+            store(b, base, best, flags);
         }
         return;
     }

@@ -264,3 +264,18 @@ def test_the_answer_is_the_earliest_end(zl, oracle, B, P, R, ends):
     ts[:, 1, -1] = lim
     ts[:, 2, -1] = lim + apart - 3                         # (less than a cell is wide: others' lower bounds are smaller)
     assert_same(zl, oracle, ts, f"B={B} P={P} R={R}")
+
+
+# workers in step, whose cells are given up, and one step back, anywhere and of any size, in every instance: the sort-based
+# search that takes over cuts such rows into pieces by value and may never see it.  Instances in slices, in registers
+@pytest.mark.parametrize("B,P,R,unit", [(64, 520, 1000, 0), (64, 520, 1000, 24), (64, 1030, 1000, 30), (64, 100, 40, 30)])
+@pytest.mark.parametrize("apart", [0, 20])
+def test_rows_out_of_order_where_cells_are_given_up(zl, B, P, R, unit, apart):
+    rng = np.random.default_rng(5)
+    ts = np.arange(R, dtype=np.int64) * (100_000 << unit) + (rng.random((B, P, R)) * (apart << unit)).astype(np.int64)
+    back = [1, 100, 1 << 30, 1 << 36, 1 << 40, 1 << 45] if unit else [1, 10, 100_000, 5_000_000, 50_000_000]
+    for b in range(B):
+        p, i = int(rng.integers(P)), int(rng.integers(1, R - 1))
+        ts[b, p, i] = ts[b, p, i - 1] - back[b % len(back)]
+    st = gpu_run(zl, ts)[3]
+    assert (st == zl.STATUS_UNSORTED).all(), np.nonzero(st != zl.STATUS_UNSORTED)[0]
