@@ -643,8 +643,8 @@ int run_range_batch(const i64* ts, i64 B, int P, int R, i64* barrier, int* iters
         if (n <= 1024) { LAUNCH_RANGE(128, 8, 2048, false); return EBSP_OK; }      // (they never give up)
         LAUNCH_RANGE(256, 16, 4096, true);
 #undef LAUNCH_RANGE
-        LAUNCH(K_RANGE_WINDOW, (zl_range_window_kernel<512, 16>), dim3((unsigned)(B < 2 * GENERAL_GRID ? B : 2 * GENERAL_GRID)),
-               dim3(512), ts, B, P, R, 1u, (const RangePart*)nullptr, barrier, iters, dmin, status);
+        LAUNCH(K_RANGE_WINDOW, (zl_range_window_kernel<512, 16, 16384, false>), dim3((unsigned)(B < 2 * GENERAL_GRID ? B : 2 * GENERAL_GRID)),
+               dim3(512), ts, B, P, R, 1u, 0, (RangePart*)nullptr, barrier, iters, dmin, status);
         return EBSP_OK;
     }
     RangePart* part = pl.multi ? (RangePart*)workspace : nullptr;        // (one slice needs none)
@@ -659,9 +659,8 @@ int run_range_batch(const i64* ts, i64 B, int P, int R, i64* barrier, int* iters
         const i64 most = n / 2048 < R / 4 ? n / 2048 : R / 4;
         if (slices > most) slices = most;
         if (slices < (R + 2047) / 2048) slices = (R + 2047) / 2048;      // eight cells per iteration
-        const i64 room = (i64)(pl.bytes / (sizeof(RangePart) * (size_t)B));
-        if (slices > room) slices = room;
         if (slices > 0x7fffffffll / B) slices = 0x7fffffffll / B;
+        while (slices > 1 && range_rest_bytes(B, slices) > pl.bytes) --slices;
         if (slices < 1) slices = 1;
     }
     // whole waves walk a row's stretch where it is long enough
@@ -676,13 +675,19 @@ int run_range_batch(const i64* ts, i64 B, int P, int R, i64* barrier, int* iters
     // of 512 where few of them have many rows to search.  512 x 16384 / 256 x 4096, us: 1024 of 256 x 1024 518 / 830 (8192
     // cells), 1000 of 300 x 300 244 / 283, 1000 of 500 x 100 223 / 244; 2000 of 300 x 60 254 / 225, 4096 of 64 x 256 258 /
     // 172.  256 / 512 threads, 4096 cells: one of 1000 x 150 41.8 / 38.1, 8000 of 300 x 30 422 / 497.
-    if (n / slices > RANGE_SMALL || cells > 8192) LAUNCH_SLICE(512, 16384);
+    const bool many = n / slices > RANGE_SMALL || cells > 8192;
+    if (many) LAUNCH_SLICE(512, 16384);
     else if (cells > 4096) LAUNCH_SLICE(256, 8192);
     else if (P > 256 && B * slices <= 2 * GENERAL_GRID) LAUNCH_SLICE(512, 4096);
     else LAUNCH_SLICE(256, 4096);
 #undef LAUNCH_SLICE
-    LAUNCH(K_RANGE_WINDOW, (zl_range_window_kernel<512, 16>), dim3((unsigned)(B < 2 * GENERAL_GRID ? B : 2 * GENERAL_GRID)),
-           dim3(512), ts, B, P, R, (u32)slices, (const RangePart*)part, barrier, iters, dmin, status);
+#define LAUNCH_REST(NB_)                                                                                     \
+    LAUNCH(K_RANGE_WINDOW, (zl_range_window_kernel<512, 16, NB_, true>),                                     \
+           dim3((unsigned)(slices > 1 ? B * slices : B < 2 * GENERAL_GRID ? B : 2 * GENERAL_GRID)),          \
+           dim3(512), ts, B, P, R, (u32)slices, lanes_log, part, barrier, iters, dmin, status)
+    if (many || cells > 4096) LAUNCH_REST(16384);
+    else LAUNCH_REST(4096);
+#undef LAUNCH_REST
     return EBSP_OK;
 }
 

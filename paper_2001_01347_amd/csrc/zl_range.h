@@ -445,6 +445,26 @@ __device__ __forceinline__ u32 row_first_at_least(const i64* __restrict__ row, u
     return RowProbe(row, R, base, (u64)row[0] - base, (u64)row[R - 1] - base, v).index();
 }
 
+// The same (R - 1: none) for a row that has been found as far as index `from`: galloping from there, or from where evenly
+// spaced entries would put it.
+__device__ __forceinline__ u32 row_seek(const i64* __restrict__ row, u32 R, u64 base, u32 from, u64 v)
+{
+    auto below = [&](u32 i) { return (u64)row[i] - base < v; };
+    if (!below(from)) return from;
+    u32 lo = from, step = 1;                               // the entry at lo is below v
+    const u64 f = (u64)row[0] - base, l = (u64)row[R - 1] - base;
+    u32 g = f < v && v < l ? (u32)((float)(v - f) / (float)(l - f) * (float)(R - 1)) : 0u;
+    g = g < R ? g : R - 1;
+    if (g > lo + 8 && below(g - 4)) lo = g - 4;
+    while (lo + step < R - 1 && below(lo + step)) { lo += step; step *= 2; }
+    u32 hi = lo + step < R - 1 ? lo + step : R - 1;
+    while (hi > lo + 1) {
+        const u32 m = lo + ((hi - lo) >> 1);
+        if (below(m)) lo = m; else hi = m;
+    }
+    return hi;
+}
+
 // Every row's entries up to the barrier (relative to base); thread p knows the ends of row p.
 template <int NT>
 __device__ __forceinline__ void store_iters(const i64* __restrict__ inst, int P, int R, u64 base, u64 barrier, u64 own_first, u64 own_last,
@@ -655,8 +675,15 @@ __global__ __launch_bounds__(NT, (NT == 64 ? 5 : 6)) void zl_range_instance_kern
 struct RangePart {
     u64 d, g;            // smallest max(Z) - min(Z) and its barrier, relative to base (d == U64_MAX: no entry)
     u32 flags;
-    u32 left;            // the slice gave up: the instance is zl_range_window_kernel's
+    u32 left;            // the slice gave up: it is zl_range_window_kernel's
 };
+// What the workspace holds behind the slices' results: those of the slices that were left, and how many of an instance's have ended.
+struct RangeRest {
+    RangePart* part;
+    u32* ended;
+};
+__device__ __forceinline__ RangeRest range_rest(RangePart* part, i64 all) { return RangeRest{part + all, (u32*)(part + 2 * all)}; }
+ZL_FN size_t range_rest_bytes(i64 B, i64 slices) { return (size_t)B * ((size_t)slices * 2 * sizeof(RangePart) + sizeof(u32)); }
 
 // The pairs of neighbouring entries (i - 1, i), from < i <= to, of a row, by LANES = 2^lanes_log lanes: f(before, entry).
 // Whole waves walk 64 entries a step, four steps asked for ahead, the entry before from the neighbouring lane; fewer
@@ -694,12 +721,20 @@ __device__ __forceinline__ void row_pairs(const i64* __restrict__ row, u32 from,
 // One slice.  Each cell's bounds follow from G at its two ends; cells whose lower bound exceeds the smallest upper bound
 // are dropped.  The cell with the smallest lower bound is looked at first, which as a rule leaves none.  A cell's entries
 // and their successors are found by one search per row, listed, and evaluated exactly (inside a cell only successors of
-// earlier entries of the cell can lie behind G of its first value).  A cell of more entries than the list holds is cut
-// into cells of its own later: such intervals wait on a stack, and where a cell is one value, no list is needed.
+// earlier entries of the cell can lie behind G of its first value).  Workers in step put a whole round of iterations
+// into a cell, more entries than the list holds: there the cell's first entry x is evaluated (g(x) is that of the cell's
+// first value) and settles the cell as a rule, because g of all entries behind it is the successor of x or later, an
+// iteration away.  What of such a cell may still win is cut into cells of its own later: such intervals wait on a stack,
+// and where a cell is one value, no list is needed.  Where an interval leaves more than RANGE_LEVEL of them (iterations
+// as short as a cell is wide), it is cut into RANGE_LEVEL pieces instead.
 // `cells` words hold (y >> ms) + 1, 0 where no predecessor falls in the cell.
+// Workers in step, a round within 20 us of 100 ms, us, with every such cell on the stack and whole instances left to one
+// workgroup's sort / so: 64 of 1024 x 4096 800 000 / 12 900, 300 of 600 x 100 13 900 / 500, 1100 of 300 x 300 41 800 / 2640,
+// 2000 of 300 x 60 9870 / 1120, 64 of 520 x 150 1320 / 290 (within 1000 us 2080 / 530), one of 1000 x 150 235 / 131.
 constexpr int RANGE_ROUND_CELLS = 64;                     // cells looked at together
+constexpr int RANGE_LEVEL = 16;                           // intervals that one interval leaves at most
 constexpr int RANGE_STACK = 96;                           // intervals that wait
-template <int NT, int NB>
+template <int NT, int NB, bool DEEP>
 struct SliceSmem {
     static constexpr int LIST = NT < 512 ? NT : 512;      // entries of the cells looked at together
     static constexpr int LIVE = NT;                       // cells gathered at a time
@@ -714,15 +749,19 @@ struct SliceSmem {
         };
     };
     u64 at_start[RANGE_ROUND_CELLS];                      // g of the cell's first value
+    u64 first[DEEP ? RANGE_ROUND_CELLS : 1];              // the cell's first entry
     u64 red[2 * (NT / WAVE) + 2];
-    u64 from[RANGE_STACK], to[RANGE_STACK], least[RANGE_STACK];       // intervals and their lower bounds
+    static constexpr int STACK = DEEP ? RANGE_STACK : 1;
+    u64 from[STACK], to[STACK], least[STACK];             // intervals and their lower bounds
     u32 listed, waiting;
 };
 template <bool WIDE> struct SliceWord { using type = u32; };          // values relative to base: below 2^31, or any
 template <> struct SliceWord<true> { using type = u64; };
 
-template <int NT, int NB, bool WIDE>
-__device__ __forceinline__ void zl_range_slice(SliceSmem<NT, NB>& sm, const i64* __restrict__ inst, int P, int R, u32 slices, u32 k,
+// DEEP: cells that are too full are gone into.  Otherwise the slice ends where it meets them, with false, for
+// zl_range_window_kernel to begin anew: that code beside the rest costs every other slice 2 to 8 %, in registers.
+template <int NT, int NB, bool WIDE, bool DEEP>
+__device__ __forceinline__ bool zl_range_slice(SliceSmem<NT, NB, DEEP>& sm, const i64* __restrict__ inst, int P, int R, u32 slices, u32 k,
                                                int lanes_log, const RowEnds& ends, u64 own_first, u64 own_last, RangePart& out)
 {
     using V = typename SliceWord<WIDE>::type;
@@ -802,7 +841,7 @@ __device__ __forceinline__ void zl_range_slice(SliceSmem<NT, NB>& sm, const i64*
         }
         bad = __syncthreads_or(bad);
         if (bad) out.flags = EBSP_STATUS_UNSORTED;
-        if (empty || bad) return;
+        if (empty || bad) return true;
         // lim is an entry (without a successor)
         if (E == ends.lim && tid == 0) atomicMax(&sm.cells[(u32)((E - A) >> sh)], 1u);
         __syncthreads();
@@ -878,10 +917,12 @@ __device__ __forceinline__ void zl_range_slice(SliceSmem<NT, NB>& sm, const i64*
             top = all_ub < top ? all_ub : top;
             low = block_first_min<NT>(first_low, sm.red);
         }
-        // the gathered cells r .. r + K - 1, those that may still win; false: more entries than the list holds
-        auto look_at = [&](u32 r, u32 K) -> bool {
+        // the gathered cells r .. r + K - 1, those that may still win; false: more entries than the list holds.  (Cell r + ci
+        // has the place slot + ci of at_start.)
+        auto look_at = [&](u32 r, u32 K, u32 slot) -> bool {
             auto cell_at = [&](u32 ci) -> u32 { return sm.cell[r + ci]; };
-            for (u32 c = tid; c < K; c += NT) sm.at_start[c] = 0;
+            u64* const at_start = sm.at_start + slot;
+            for (u32 c = tid; c < K; c += NT) at_start[c] = 0;
             __syncthreads();
             for (u64 q = tid; q < (u64)K * (u32)P; q += NT) {
                 const u32 ci = (u32)(q / (u32)P);
@@ -892,7 +933,7 @@ __device__ __forceinline__ void zl_range_slice(SliceSmem<NT, NB>& sm, const i64*
                 u32 i = RowProbe(row, (u32)R, base, first_in(p), last_in(p), first_of(c)).index();
                 if (i >= (u32)R) continue;                 // (never: the cell begins at lim or before)
                 u64 x = (u64)row[i] - base, nx = (u64)row[i + 1 < (u32)R ? i + 1 : i] - base;
-                atomicMax(&sm.at_start[ci], x);
+                atomicMax(&at_start[ci], x);
                 if (sh == 0) continue;
                 const u64 hi = last_of(c);
                 while (x <= hi) {
@@ -914,14 +955,14 @@ __device__ __forceinline__ void zl_range_slice(SliceSmem<NT, NB>& sm, const i64*
                 for (u32 ci = tid; ci < K; ci += NT)
                     if (may_win(cell_at(ci))) {
                         const u64 x = first_of(cell_at(ci));
-                        const Best one{sm.at_start[ci] - x, x};
+                        const Best one{at_start[ci] - x, x};
                         if (one.before(got)) got = one;
                     }
             } else
                 for (u32 e = tid; e < total; e += NT) {
                     const u64 x = sm.lx[e];
                     const u32 ci = sm.lc[e];
-                    u64 g = sm.at_start[ci];
+                    u64 g = at_start[ci];
                     for (u32 o = 0; o < total; ++o)
                         if (sm.lc[o] == ci && sm.lx[o] < x && sm.ln[o] > g) g = sm.ln[o];
                     const Best one{g > x ? g - x : 0ull, x};
@@ -933,20 +974,70 @@ __device__ __forceinline__ void zl_range_slice(SliceSmem<NT, NB>& sm, const i64*
             __syncthreads();
             return true;
         };
+        // the first entries of the gathered cells r .. r + K - 1, where look_at finds them too full; at_start becomes g of what
+        // lies behind them.  The cells are in order: a thread walks along a quarter of them in a row, from line to line.
+        auto look_at_first = [&](u32 r, u32 K) {
+            constexpr u32 QUARTERS = 4;
+            for (u32 c = tid; c < K; c += NT) { sm.at_start[c] = may_win(sm.cell[r + c]) ? 0 : U64_MAX; sm.first[c] = U64_MAX; }
+            __syncthreads();
+#pragma unroll 1
+            for (int pass = 0; pass < 2; ++pass) {
+#pragma unroll 1
+                for (u64 q = tid; q < (u64)P * QUARTERS; q += NT) {
+                    const int p = (int)(q / QUARTERS);
+                    const u32 part = (u32)q % QUARTERS, from = part * K / QUARTERS, to = (part + 1) * K / QUARTERS;
+                    const i64* row = inst + (size_t)p * R;
+                    u32 i = 0;
+                    u64 x = first_in(p), nx = (u64)row[R > 1 ? 1 : 0] - base;      // the row's entry at i and the next (the last one: again)
+                    for (u32 ci = from; ci < to; ++ci) {
+                        const u64 lo = first_of(sm.cell[r + ci]), g = sm.at_start[ci], f = sm.first[ci];
+                        if (g == U64_MAX) continue;        // (cannot win)
+                        if (x < lo) {
+                            if (nx >= lo) { ++i; x = nx; }
+                            else { i = row_seek(row, (u32)R, base, i, lo); x = (u64)row[i] - base; }
+                            nx = (u64)row[i + 1 < (u32)R ? i + 1 : i] - base;
+                        }
+                        if (pass == 0) {
+                            if (x > g) atomicMax(&sm.at_start[ci], x);
+                            if (x < f && x >= lo && x <= last_of(sm.cell[r + ci])) atomicMin(&sm.first[ci], x);
+                        } else if (x == f && nx > g)
+                            atomicMax(&sm.at_start[ci], nx);
+                    }
+                }
+                __syncthreads();
+                if (pass == 0) {
+                    Best got{U64_MAX, U64_MAX};
+                    for (u32 ci = tid; ci < K; ci += NT)
+                        if (sm.first[ci] != U64_MAX) {
+                            const Best one{sm.at_start[ci] - sm.first[ci], sm.first[ci]};
+                            if (one.before(got)) got = one;
+                        }
+                    got = block_first_min<NT>(got, sm.red);
+                    if (got.before(best)) best = got;
+                    top = best.d < top ? best.d : top;
+                }
+            }
+        };
+        const u32 level0 = sm.waiting;
+        bool too_full = false, in_pieces = false;          // the latter: the interval leaves too much
         u32 K = (u32)(4 * NT) / (u32)P;
         K = K < 1u ? 1u : (K > (u32)RANGE_ROUND_CELLS ? (u32)RANGE_ROUND_CELLS : K);
-        for (int round = 0;; ++round) {
+        for (int round = 0; !in_pieces; ++round) {
             // gathered: first the cell with the smallest lower bound, then what may still win, in most slices nothing (no
             // thread's smallest bound that was not looked at is among it)
-            u32 now_mask = 0;
+            u32 have;
             if (round == 0) {
+                if (low.d == U64_MAX) break;               // (no entries)
                 const u32 c = (u32)low.x - wave * (NB / NW);                  // inside the wave's cells
-                if (low.d != U64_MAX && c < NB / NW && (c & 255u) >> 2 == lane) {
-                    now_mask = 1u << ((c >> 8) * 4 + (c & 3u));
+                if (c < NB / NW && (c & 255u) >> 2 == lane) {
+                    todo &= ~(1u << ((c >> 8) * 4 + (c & 3u)));
                     first_low.d = second;
                 }
-                todo &= ~now_mask;
+                if (tid == 0) sm.cell[0] = (u16)low.x;
+                have = 1;
+                __syncthreads();
             } else {
+                u32 now_mask = 0;
                 if (round == 1 && !__syncthreads_or(first_low.d <= top)) break;
 #pragma unroll 2
                 for (int i = 0; i < STEPS; ++i) {
@@ -960,40 +1051,92 @@ __device__ __forceinline__ void zl_range_slice(SliceSmem<NT, NB>& sm, const i64*
                 }
                 now_mask &= todo;
                 todo = now_mask;
-            }
-            u32 all;
-            u32 at = block_excl_scan<u32, NT>((u32)__popc(now_mask), (u32*)sm.red, all);
-            for (; now_mask; now_mask &= now_mask - 1, ++at)
-                if (at < (u32)sm.LIVE) {
+                // in order, by way of a bit per cell
+                static_assert(NB / 32 <= NT && NB / 32 <= 2 * SliceSmem<NT, NB, DEEP>::LIST, "a thread per word, in place of the list");
+                u32* const bits = (u32*)sm.lx;
+                if (tid < NB / 32) bits[tid] = 0;
+                __syncthreads();
+                for (u32 m = now_mask; m; m &= m - 1) {
+                    const u32 c = cell_of(__ffs(m) - 1);
+                    atomicOr(&bits[c >> 5], 1u << (c & 31u));
+                }
+                __syncthreads();
+                u32 word = tid < NB / 32 ? bits[tid] : 0u, all;
+                u32 at = block_excl_scan<u32, NT>((u32)__popc(word), (u32*)sm.red, all);
+                for (; word && at < (u32)sm.LIVE; word &= word - 1, ++at) sm.cell[at] = (u16)(tid * 32 + __ffs(word) - 1);
+                __syncthreads();
+                if (all == 0) break;
+                have = all < (u32)sm.LIVE ? all : (u32)sm.LIVE;
+                const u32 last = sm.cell[have - 1];
+                for (; now_mask; now_mask &= now_mask - 1) {
                     const int i = __ffs(now_mask) - 1;
-                    sm.cell[at] = (u16)cell_of(i);
-                    todo &= ~(1u << i);
+                    if (cell_of(i) <= last) todo &= ~(1u << i);
                 }
-            __syncthreads();
-            if (all == 0) break;                           // (an interval without entries has no smallest bound)
-            const u32 have = all < (u32)sm.LIVE ? all : (u32)sm.LIVE;
-            u32 step = K;
-            for (u32 r = 0; r < have;) {
-                const u32 now = have - r < step ? have - r : step;
-                if (look_at(r, now)) { r += now; continue; }
-                step = 1;                                  // one at a time then
-                if (now > 1) continue;
-                if (tid == 0) {                            // this one is cut into cells of its own later
-                    const u32 c = sm.cell[r], to = sm.waiting;
-                    if (to < (u32)RANGE_STACK) {
-                        sm.from[to] = first_of(c);
-                        sm.to[to] = last_of(c);
-                        sm.least[to] = low_bound(sm.cells[(int)c - 1], c);
+            }
+            // K cells at once; (DEEP) from where they are too full on their first entries, and the cells not settled one by one
+            if constexpr (!DEEP) {
+                for (u32 r = 0; r < have; r += K)
+                    if (!look_at(r, have - r < K ? have - r : K, 0)) return false;
+                __syncthreads();
+                continue;
+            }
+            u32 r = 0, group = 0, ci = 0;
+            while (r < have && !in_pieces) {
+                u64 x = 0, h = 0, lb = 0;
+                if (too_full && group == 0) {
+                    group = have - r < (u32)RANGE_ROUND_CELLS ? have - r : (u32)RANGE_ROUND_CELLS;
+                    look_at_first(r, group);
+                    ci = 0;
+                }
+                if (group > 0) {
+                    for (; ci < group; ++ci) {
+                        const u32 c = sm.cell[r + ci];
+                        const u64 g = sm.at_start[ci];
+                        x = sm.first[ci];
+                        h = (u64)last_of(c);
+                        lb = g > h ? g - h : 0ull;
+                        if (x < h && may_win(c) && may_be(lb, x + 1)) break;
                     }
-                    sm.waiting = to + 1;
+                    __syncthreads();                       // (the cells' places may be written again)
+                    if (ci == group) { r += group; group = ci = 0; continue; }
                 }
-                ++r;
+                const u32 now = group > 0 ? 1u : have - r < K ? have - r : K;
+                const bool seen = look_at(r + ci, now, ci);
+                if (group == 0) {
+                    if (seen) r += now;
+                    too_full = !seen;
+                    continue;
+                }
+                if (!seen) {                               // cut into cells of its own later
+                    const u32 to = sm.waiting;
+                    __syncthreads();
+                    in_pieces = to - level0 >= (u32)RANGE_LEVEL;
+                    if (tid == 0 && !in_pieces) {
+                        if (to < (u32)RANGE_STACK) { sm.from[to] = x + 1; sm.to[to] = h; sm.least[to] = lb; }
+                        sm.waiting = to + 1;
+                    }
+                }
+                ++ci;
             }
             __syncthreads();
         }
+        if constexpr (!DEEP) break;
+        if (in_pieces) {
+            const u32 n_cells = (u32)((E - A) >> sh) + 1u, per = (n_cells + RANGE_LEVEL - 1) / RANGE_LEVEL;
+            const u32 at = level0 + (u32)tid, c = per * (u32)(RANGE_LEVEL - 1 - tid);        // (the first piece on top)
+            if (tid < RANGE_LEVEL && at < (u32)RANGE_STACK) {
+                const u32 z = c + per - 1 < n_cells ? c + per - 1 : n_cells - 1u;
+                // (behind the interval's end: one that cannot win)
+                sm.from[at] = c < n_cells ? (u64)first_of(c) : U64_MAX;
+                sm.to[at] = c < n_cells ? (u64)last_of(z) : U64_MAX;
+                const u64 g = c < n_cells ? (u64)((V)(sm.cells[(int)c - 1] - 1u) << ms) : 0ull;
+                sm.least[at] = c >= n_cells ? U64_MAX : g > sm.to[at] ? g - sm.to[at] : 0ull;
+            }
+            if (tid == 0) sm.waiting = level0 + RANGE_LEVEL;
+        }
         __syncthreads();
         u32 waiting = sm.waiting;
-        if (waiting > (u32)RANGE_STACK) { out.left = 1; return; }
+        if (waiting > (u32)RANGE_STACK) { out.left = 1; return true; }
         while (waiting > 0 && !may_be(sm.least[waiting - 1], sm.from[waiting - 1])) --waiting;
         if (waiting == 0) break;
         A = sm.from[waiting - 1];
@@ -1005,6 +1148,7 @@ __device__ __forceinline__ void zl_range_slice(SliceSmem<NT, NB>& sm, const i64*
     }
     out.d = best.d;
     out.g = best.x + best.d;
+    return true;
 }
 
 // With one slice per instance the results go straight to the caller's arrays (dmin: DEFERRED where the slice gave up).
@@ -1013,7 +1157,7 @@ __global__ __launch_bounds__(NT, (NB == 8192 ? 3 : 4)) void zl_range_fast_kernel
     const i64* __restrict__ ts, int P, int R, u32 slices, int lanes_log, RangePart* __restrict__ part,
     i64* __restrict__ barrier, int* __restrict__ iters, i64* __restrict__ dmin, int* __restrict__ status)
 {
-    __shared__ __align__(16) SliceSmem<NT, NB> sm;
+    __shared__ __align__(16) SliceSmem<NT, NB, false> sm;
     const int tid = threadIdx.x;
     const i64 b = blockIdx.x / slices;
     const u32 k = blockIdx.x % slices;
@@ -1023,10 +1167,15 @@ __global__ __launch_bounds__(NT, (NB == 8192 ? 3 : 4)) void zl_range_fast_kernel
     const RowEnds ends = row_ends<NT>(inst, P, R, sm.red, own_first, own_last);
     const u64 base = (u64)ends.base;
     RangePart r;
-    if (ends.range >> 31) zl_range_slice<NT, NB, true>(sm, inst, P, R, slices, k, lanes_log, ends, own_first, own_last, r);
-    else zl_range_slice<NT, NB, false>(sm, inst, P, R, slices, k, lanes_log, ends, own_first, own_last, r);
+    const bool done = ends.range >> 31
+        ? zl_range_slice<NT, NB, true, false>(sm, inst, P, R, slices, k, lanes_log, ends, own_first, own_last, r)
+        : zl_range_slice<NT, NB, false, false>(sm, inst, P, R, slices, k, lanes_log, ends, own_first, own_last, r);
+    r.left = !done;
     if (slices > 1) {
-        if (tid == 0) part[blockIdx.x] = r;
+        if (tid == 0) {
+            part[blockIdx.x] = r;
+            if (k == 0) range_rest(part, gridDim.x).ended[b] = 0;
+        }
         return;
     }
     if (r.d == U64_MAX) r.d = r.g = 0;                     // (unsorted rows only, or nothing found out)
@@ -1038,16 +1187,19 @@ __global__ __launch_bounds__(NT, (NB == 8192 ? 3 : 4)) void zl_range_fast_kernel
     store_iters<NT>(inst, P, R, base, r.g, own_first, own_last, iters + b * (i64)P);
 }
 
-// The instances the kernels above gave up (values clustered beyond what their cells resolve): the sort-based search over
-// whole rows; and, for instances in slices, the best of the slices and the iteration counts.  A fixed grid; every
-// workgroup looks through its share of the instances.
-template <int NT, int ITEMS>
-__global__ __launch_bounds__(NT) void zl_range_window_kernel(
-    const i64* __restrict__ ts, i64 B, int P, int R, u32 slices, const RangePart* __restrict__ part,
+// What the kernels above gave up, and, for instances in slices, the best of the slices and the iteration counts.  DEEP: the
+// slices are searched again, too full cells gone into, a workgroup each (without slices: a fixed grid, every workgroup looks
+// through its share of the instances).  The last of an instance's to end takes the best of them.  What that gives up as well,
+// and small instances (not DEEP), go to the sort-based search over whole rows.
+template <int NT, int ITEMS, int NB, bool DEEP>
+__global__ __launch_bounds__(NT, DEEP ? 4 : 1) void zl_range_window_kernel(
+    const i64* __restrict__ ts, i64 B, int P, int R, u32 slices, int lanes_log, RangePart* part,
     i64* __restrict__ barrier, int* __restrict__ iters, i64* __restrict__ dmin, int* __restrict__ status)
 {
     using C = WinCfg<NT, ITEMS>;
-    __shared__ __align__(16) unsigned char smem[C::BYTES];
+    using Slice = SliceSmem<NT, NB, true>;
+    constexpr size_t BYTES = DEEP && sizeof(Slice) > C::BYTES ? sizeof(Slice) : C::BYTES;
+    __shared__ __align__(16) unsigned char smem[BYTES];
     const Smem sm = carve<NT, ITEMS>(smem);
     const int tid = threadIdx.x;
     auto store = [&](i64 b, i64 base, Best best, int flags) {            // best.x: the barrier, relative to base
@@ -1073,26 +1225,84 @@ __global__ __launch_bounds__(NT) void zl_range_window_kernel(
         else zl_range_window<NT, ITEMS, false>(sm, rw, ends.thr, 0ull, ends.range, d, g, bad);
         store(b, ends.base, Best{d, g}, __syncthreads_or(bad));
     };
-    if (slices > 1) {
-        for (i64 b = blockIdx.x; b < B; b += gridDim.x) {
-            Best best{U64_MAX, U64_MAX};
-            int flags = 0, left = 0;
-            for (u32 k = tid; k < slices; k += NT) {
-                const RangePart r = part[b * slices + k];
+    auto go_into = [&](i64 b, u32 k, i64& base) -> RangePart {
+        Slice& sl = *(Slice*)smem;
+        const i64* __restrict__ inst = ts + (size_t)b * P * R;
+        __syncthreads();
+        for (int c = tid; c < NB / 4; c += NT) ((uint4*)sl.cells)[c] = make_uint4(0u, 0u, 0u, 0u);
+        u64 own_first, own_last;
+        const RowEnds ends = row_ends<NT>(inst, P, R, sl.red, own_first, own_last);
+        base = ends.base;
+        RangePart r;
+        if (ends.range >> 31) zl_range_slice<NT, NB, true, true>(sl, inst, P, R, slices, k, lanes_log, ends, own_first, own_last, r);
+        else zl_range_slice<NT, NB, false, true>(sl, inst, P, R, slices, k, lanes_log, ends, own_first, own_last, r);
+        __syncthreads();
+        return r;
+    };
+    if (DEEP && slices > 1) {
+        // (the instances are shared out by the first workgroups, so that all dies of the chip have some)
+        const RangeRest rest = range_rest(part, gridDim.x);
+        Best best;
+        int flags;
+        u32 left;
+        auto look_through = [&](i64 b) {
+            best = Best{U64_MAX, U64_MAX};
+            flags = 0;
+            left = 0;
+            for (u32 j = tid; j < slices; j += NT) {
+                const RangePart r = part[b * slices + j];
                 const Best got{r.d, r.g};
-                if (got.before(best)) best = got;
+                if (!r.left && got.before(best)) best = got;
                 flags |= (int)r.flags;
-                left |= (int)r.left;
+                left += r.left;
             }
-            // (the slices have seen all neighbours in all rows; the search by pieces may miss a step back between two of them)
-            flags = __syncthreads_or(flags);
-            if (__syncthreads_or(left) && !flags) { search(b); continue; }
+            flags = __syncthreads_or(flags);               // (the slices have seen all neighbours in all rows)
+            left = block_reduce<u32, NT>(left, (u32*)sm.red, OpAdd());
+        };
+        auto finish = [&](i64 b) {
             i64 base = INT64_MAX;
             for (int p = tid; p < P; p += NT) { const i64 f = ts[((size_t)b * P + p) * R]; base = f < base ? f : base; }
             base = block_reduce<i64, NT>(base, (i64*)sm.red, OpMin());
             best = block_first_min<NT>(best, sm.red);
             store(b, base, best, flags);
+        };
+        i64 whose = -1;                                    // the instance to finish
+        if (blockIdx.x < B) {
+            look_through(blockIdx.x);
+            if (left == 0 || flags) whose = blockIdx.x;
         }
+        if (part[blockIdx.x].left) {
+            const i64 b = blockIdx.x / slices;
+            if (whose >= 0) { finish(whose); whose = -1; }
+            look_through(b);
+            if (flags) return;                             // (finished by another workgroup)
+            i64 base;
+            const RangePart r = go_into(b, blockIdx.x % slices, base);
+            if (tid == 0) {
+                u64* const to = (u64*)(rest.part + blockIdx.x);
+                __hip_atomic_store(to, r.d, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                __hip_atomic_store(to + 1, r.g, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                __hip_atomic_store(to + 2, (u64)r.left, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                sm.red[0] = __hip_atomic_fetch_add(&rest.ended[b], 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
+            }
+            __syncthreads();
+            const bool last = sm.red[0] + 1 == left;
+            __syncthreads();
+            if (!last) return;
+            __threadfence();
+            int again = 0;
+            for (u32 j = tid; j < slices; j += NT)
+                if (part[b * slices + j].left) {
+                    u64* const from = (u64*)(rest.part + b * slices + j);
+                    const Best got{__hip_atomic_load(from, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT),
+                                   __hip_atomic_load(from + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)};
+                    if (got.before(best)) best = got;
+                    again |= __hip_atomic_load(from + 2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
+                }
+            if (__syncthreads_or(again)) { search(b); return; }
+            whose = b;
+        }
+        if (whose >= 0) finish(whose);
         return;
     }
     const u32 total = (u32)B;
@@ -1109,7 +1319,15 @@ __global__ __launch_bounds__(NT) void zl_range_window_kernel(
             const u32 b = block_reduce<u32, NT>(mine ? idx : 0xffffffffu, (u32*)sm.red, OpMin());
             if (b == 0xffffffffu) break;
             if (b == idx) mine = false;
-            search((i64)b);
+            bool again = true;
+            if constexpr (DEEP) {
+                i64 base;
+                const RangePart r = go_into((i64)b, 0, base);
+                again = r.left != 0;
+                if (!again) store((i64)b, base, Best{r.d, r.g}, (int)r.flags);
+            }
+            if (again) search((i64)b);
+            __syncthreads();
         }
     }
 }

@@ -279,3 +279,23 @@ def test_rows_out_of_order_where_cells_are_given_up(zl, B, P, R, unit, apart):
         ts[b, p, i] = ts[b, p, i - 1] - back[b % len(back)]
     st = gpu_run(zl, ts)[3]
     assert (st == zl.STATUS_UNSORTED).all(), np.nonzero(st != zl.STATUS_UNSORTED)[0]
+
+
+# workers in step: more entries of a round in one cell than its list holds, which the cell's first entry settles; two
+# iterations in quick succession, where it does not and the cells are cut further, few of them or (more than a level keeps)
+# in pieces; three in a row with a pause of their own, where that repeats.  Several slices and one, workgroups of 256 and 512
+# threads, narrow and wide values
+@pytest.mark.parametrize("unit", [0, 33])
+@pytest.mark.parametrize("B,P,R", [(64, 300, 400), (600, 300, 240), (1100, 300, 60), (4, 1100, 300), (16, 600, 24)])
+def test_workers_in_step(zl, oracle, B, P, R, unit):
+    rng = np.random.default_rng(B + P + R)
+    round_ = np.arange(R, dtype=np.int64) * 100_000
+    pairs = np.arange(R, dtype=np.int64) // 2 * 100_000 + np.arange(R, dtype=np.int64) % 2 * 40
+    triples = np.arange(R, dtype=np.int64) // 3 * 100_000 + np.arange(R, dtype=np.int64) % 3 ** 2 // 3 * 30 + np.arange(R, dtype=np.int64) % 3
+    for steps in (round_, pairs, triples):
+        for apart in (1, 30, 1000):
+            ts = steps + rng.integers(0, apart, size=(B, P, R))
+            ts = np.sort(ts, axis=2) << unit
+            if unit:
+                ts += np.sort(rng.integers(0, 1 << unit, size=(B, P, R)), axis=2)
+            assert_same(zl, oracle, np.sort(ts, axis=2), f"B={B} P={P} R={R} apart={apart}")
