@@ -48,8 +48,8 @@ __device__ __forceinline__ DirectFacts direct_rows(DirectSmem<NT, PM, SPLIT>& sm
     for (int p = threadIdx.x; p < P; p += NT) {
         // (start times may be anything: a difference that does not fit 64 bits would look small wrapped round)
         const i64 s = iv[p];
-        i64 from, first;
-        const bool wraps = __builtin_sub_overflow(le ? le[p] : f.ref, f.ref, &from) | __builtin_add_overflow(from, s, &first);
+        const i64 l = le ? le[p] : f.ref, first = (i64)((u64)l - (u64)f.ref + (u64)s);
+        const bool wraps = __builtin_fabs((double)l - (double)f.ref) > 0x1p61;
         back |= s < 0;
         off |= wraps || s < 0 || s > most_step || first > most || first < -most;
         const double fs = (double)s, ff = (double)first, rcp = direct_rcp(fs);
