@@ -819,10 +819,12 @@ int ebsp_simulate_supersteps(const int64_t* last_end0, const int64_t* interval, 
         }
         if (int rc = launch_direct(K_RUN, (const i64*)last_end0, (const i64*)interval, B, s0 * B, (S - s0) * B, P, R, (i64*)barrier, iters,
                                    (i64*)wait, status, st)) return rc;
-        if (P <= 64) LAUNCH(K_ADVANCE, (zl_direct_starts_kernel<64, 4>), dim3((unsigned)B), dim3(WAVE), (const i64*)last_end0,
-                            (const i64*)interval, (i64)sync_cost, (int)S, B, P, R, (i64*)barrier, iters, (i64*)wait, status);
-        else LAUNCH(K_ADVANCE, (zl_direct_starts_kernel<DIRECT_PMAX, 4>), dim3((unsigned)B), dim3(WAVE), (const i64*)last_end0,
-                    (const i64*)interval, (i64)sync_cost, (int)S, B, P, R, (i64*)barrier, iters, (i64*)wait, status);
+#define LAUNCH_STARTS(NT_, PM_)                                                                              \
+    LAUNCH(K_ADVANCE, (zl_direct_starts_kernel<NT_, PM_, 4>), dim3((unsigned)B), dim3(NT_), (const i64*)last_end0, \
+           (const i64*)interval, (i64)sync_cost, (int)S, B, P, R, (i64*)barrier, iters, (i64*)wait, status)
+        if (P <= 64 && n <= 4096) LAUNCH_STARTS(64, 64);
+        else LAUNCH_STARTS(1024, DIRECT_PMAX);
+#undef LAUNCH_STARTS
         prof_count(S - s0);
         return EBSP_OK;
     }

@@ -165,6 +165,7 @@ __device__ __forceinline__ DirectBest direct_search(DirectSmem<NT, PM, SPLIT>& s
         const bool any = dw < none;
         return direct_first_min<NT>(any ? (u64)(i64)(dw - f.sum) : U64_MAX, any ? (i64)dc : INT64_MAX, sm.red);
     }
+    if (f.flags) return DirectBest{0ull, 0};               // (no results then)
     u64 bw = U64_MAX;
     i64 bc = INT64_MAX;
     const u64 thr = sm.red[2 * NW];
@@ -266,12 +267,13 @@ __global__ __launch_bounds__(NT) void zl_direct_finish_kernel(
 // The supersteps' start times: a running sum of the times to the barrier and the synchronisation, a wave per instance.  A
 // superstep whose search raised a status bit has no barrier: the next one starts where it did.  If that is so from
 // superstep 0 on, the workers keep start times of their own, and those supersteps are searched again here.
-template <int PM, int K>
-__global__ __launch_bounds__(WAVE) void zl_direct_starts_kernel(
+// Those are few, or flagged like the first (and then not searched), but may be large: NT threads.
+template <int NT, int PM, int K>
+__global__ __launch_bounds__(NT) void zl_direct_starts_kernel(
     const i64* __restrict__ le, const i64* __restrict__ iv, i64 sync_cost, int S, i64 B, int P, int R,
     i64* __restrict__ barrier, int* __restrict__ iters, i64* __restrict__ wait, int* __restrict__ status)
 {
-    __shared__ DirectSmem<WAVE, PM> sm;
+    __shared__ DirectSmem<NT, PM> sm;
     const i64 b = blockIdx.x;
     const int lane = threadIdx.x;
     int s = 1;
@@ -283,7 +285,7 @@ __global__ __launch_bounds__(WAVE) void zl_direct_starts_kernel(
         const i64* step = iv + at * (i64)P;
         __syncthreads();
         const DirectFacts f = direct_rows(sm, from, step, P, R);
-        const DirectBest best = direct_search<WAVE, PM, K, false>(sm, f, from, step, P, R, 0, P * R);
+        const DirectBest best = direct_search<NT, PM, K, false>(sm, f, from, step, P, R, 0, P * R);
         const i64 bar = (i64)((u64)f.ref + (u64)best.c);
         if (lane == 0) {
             barrier[at] = bar;
@@ -294,6 +296,7 @@ __global__ __launch_bounds__(WAVE) void zl_direct_starts_kernel(
         flagged = f.flags != 0;
         start = (u64)bar + (u64)sync_cost;
     }
+    if (lane >= WAVE) return;
     for (; s < S; s += WAVE) {
         const int mine = s + lane;
         const i64 at = (i64)mine * B + b;

@@ -309,3 +309,20 @@ def test_supersteps_side_by_side_flag_start_times_2_to_the_64_apart(zl, oracle, 
     le[1, 1:] += np.iinfo(np.int64).max - 80 - 120 * R
     st = gpu_run(zl, le, iv, R, 3)[3]
     assert (st[:, 0] == 0).all() and (st[:, 1] == zl.STATUS_OVERFLOW).all()      # (the workers keep their start times)
+
+
+# start times too far apart flag every superstep, and none of them is searched; workers out of order in the first superstep
+# alone leave large searches to the kernel that adds the start times up
+@pytest.mark.parametrize("P,R", [(60, 70), (200, 100), (40, 600)])
+def test_large_flagged_supersteps_side_by_side(zl, oracle, P, R):
+    rng = np.random.default_rng(P)
+    S = 4
+    iv = rng.integers(80, 120, size=(S, 3, P)).astype(np.int64)
+    le = rng.integers(0, 80, size=(3, P)).astype(np.int64)
+    le[1, 0] -= 1 << 62
+    iv[0, 2, P // 2] = -5
+    bar, it, w, st = gpu_run(zl, le, iv, R, 3)
+    assert (st[:, 0] == 0).all() and (st[:, 1] == zl.STATUS_OVERFLOW).all() and st[0, 2] & zl.STATUS_UNSORTED and (st[1:, 2] == 0).all()
+    for b, s0 in ((0, 0), (2, 1)):                         # (the third one keeps its start times for its second superstep)
+        ob, oi, ow = oracle.simulate(le[b:b + 1], np.ascontiguousarray(iv[s0:, b:b + 1]), R, 3)[:3]
+        assert np.array_equal(bar[s0:, b:b + 1], ob) and np.array_equal(w[s0:, b:b + 1], ow) and np.array_equal(it[s0:, b:b + 1], oi)
