@@ -11,8 +11,9 @@ namespace {
 // comes from P divisions with no order, sums or memory between candidates.  They are done in double precision, whose
 // vector rate is that of 32-bit integers here, and exactly (direct_quotient): four instructions per (candidate, worker), a
 // fused multiply-add, the rounding to a whole number, the minimum with R - 1, and a fused multiply-add into the sum of
-// q * step (whole numbers below 2^53).  Values that do not fit are divided as 64-bit integers instead, which is slow.
-// Bound by these instructions (57 us for 64 supersteps of 256 of 16 x 60, a quarter billion divisions: 28 us of them; 487
+// q * step (whole numbers below 2^53).  Values that do not fit are held as 64-bit integers, their quotient estimated in
+// double precision and put right by the remainder (one of 1000 x 150 45 us and 395, 1000 of 32 x 256 60 and 195).
+// Bound by these instructions (54 us for 64 supersteps of 256 of 16 x 60, a quarter billion divisions: 28 us of them; 487
 // us by the bucket search, a superstep after the other); for few candidates by the launches and one chain of steps.
 constexpr int DIRECT_PMAX = 1024;            // workers whose constants LDS holds
 struct DirectRow {
@@ -21,7 +22,7 @@ struct DirectRow {
 template <int NT, int PM, bool SPLIT = false>
 struct DirectSmem {
     DirectRow row[PM];
-    double step[PM], first[PM];
+    double step[PM], first[PM];              // (of values that do not fit: the bits of whole numbers, first relative to ref)
     u64 red[2 * (NT / WAVE) + 2];
     double part[SPLIT ? NT / WAVE : 1][SPLIT ? NT : 1];
 };
@@ -42,7 +43,9 @@ __device__ __forceinline__ DirectFacts direct_rows(DirectSmem<NT, PM, SPLIT>& sm
 {
     DirectFacts f;
     f.ref = le ? le[0] : 0;
-    const i64 most = ((i64)1 << (DIRECT_BITS - 1)) / P, most_step = most / R;      // (a row ends at twice that at most)
+    // Quotients want values up to 2^DIRECT_BITS (a row ends at twice `most` at most), sums over the workers whole numbers
+    // up to 2^53 (three times `most` each: a candidate and its distance to a first entry).
+    const i64 sums = ((i64)1 << 51) / P, most = sums < (i64)1 << (DIRECT_BITS - 1) ? sums : (i64)1 << (DIRECT_BITS - 1), most_step = most / R;
     double thr = -1e300, sum = 0.0;
     int off = 0, back = 0;
     for (int p = threadIdx.x; p < P; p += NT) {
@@ -78,6 +81,12 @@ __device__ __forceinline__ DirectFacts direct_rows(DirectSmem<NT, PM, SPLIT>& sm
         if (R > 1 && back) f.flags |= EBSP_STATUS_UNSORTED;
         if ((u64)mxl - (u64)mn > (u64)INT64_MAX / (u64)P) f.flags |= EBSP_STATUS_OVERFLOW;
         f.ref = mn;                          // candidates relative to the smallest first entry
+        for (int p = threadIdx.x; p < P; p += NT) {
+            const u64 s = (u64)iv[p], a = (le ? (u64)le[p] : 0ull) + s - (u64)mn;
+            sm.step[p] = __longlong_as_double((i64)s);
+            sm.first[p] = __longlong_as_double((i64)a);
+            sm.row[p].rcp = s ? 1.0 / (double)s : 0.0;
+        }
         f.thr = 0.0;
         f.sum = 0.0;
         if (threadIdx.x == 0) sm.red[2 * (NT / WAVE)] = (u64)mxf - (u64)mn;
@@ -169,19 +178,26 @@ __device__ __forceinline__ DirectBest direct_search(DirectSmem<NT, PM, SPLIT>& s
     u64 bw = U64_MAX;
     i64 bc = INT64_MAX;
     const u64 thr = sm.red[2 * NW];
-    for (int e = e0 + tid; e < e1; e += NT) {
-        const int row = e / R;
-        auto first = [&](int p) -> u64 { return (le ? (u64)le[p] : 0ull) + (u64)iv[p] - (u64)f.ref; };
-        const u64 c = first(row) + (u64)(e - row * R) * (u64)iv[row];
-        if (c < thr) continue;
-        u64 w = 0;
-        for (int p = 0; p < P; ++p) {
-            const u64 a = first(p), s = (u64)iv[p];
-            u64 q = s ? (c - a) / s : 0ull;
-            q = q < (u64)R - 1 ? q : (u64)R - 1;
-            w += c - a - q * s;
+    auto first = [&](int p) -> u64 { return (u64)__double_as_longlong(sm.first[p]); };
+    auto step = [&](int p) -> u64 { return (u64)__double_as_longlong(sm.step[p]); };
+    constexpr int KF = SPLIT ? 1 : K;                      // (a split search has NT candidates a workgroup)
+    for (int base = e0 + tid; base < e1; base += NT * KF) {
+        u64 c[KF], w[KF];
+#pragma unroll
+        for (int j = 0; j < KF; ++j) {
+            const int e = base + j * NT < e1 ? base + j * NT : e1 - 1, row = e / R;
+            c[j] = first(row) + (u64)(e - row * R) * step(row);
+            w[j] = 0;
         }
-        if (w < bw || (w == bw && (i64)c < bc)) { bw = w; bc = (i64)c; }
+        for (int p = 0; p < P; ++p) {
+            const u64 a = first(p), s = step(p);
+            const double rcp = sm.row[p].rcp;
+#pragma unroll
+            for (int j = 0; j < KF; ++j) w[j] += direct_remainder(c[j] - a, s, rcp, (u32)(R - 1));
+        }
+#pragma unroll
+        for (int j = 0; j < KF; ++j)
+            if (c[j] >= thr && (w[j] < bw || (w[j] == bw && (i64)c[j] < bc))) { bw = w[j]; bc = (i64)c[j]; }
     }
     return direct_first_min<NT>(bw, bc, sm.red);
 }

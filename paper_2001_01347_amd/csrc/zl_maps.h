@@ -155,6 +155,18 @@ ZL_FN double direct_quotient(double c, double rcp, double shift, double top)
     return __builtin_fmin(__builtin_rint(__builtin_fma(c, rcp, shift)), top);
 }
 
+// What barrier c waits for the row first, first + step, ..., first + top * step, for d = c - first below 2^63 and any step:
+// d - min(d / step, top) * step, with rcp = 1 / step (0 where step is 0: d).  The estimated quotient is off by
+// 2^31 * 2^-51 before it is rounded down, so by one at most after.
+ZL_FN u64 direct_remainder(u64 d, u64 step, double rcp, u32 top)
+{
+    const double est = (double)d * rcp;
+    const u32 q = est < (double)top ? (u32)est : top;
+    const u64 r = d - (u64)q * step;
+    if ((i64)r < 0) return r + step;
+    return r >= step && q < top ? r - step : r;
+}
+
 // Monotone maps of keys onto value buckets [0, NB).
 // LinearMap: bucket = (key * scale) >> 32, equal slices of [0, span]; right when the
 // keys are spread evenly, as inside a window of the multi-window path.

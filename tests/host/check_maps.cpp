@@ -436,8 +436,35 @@ static void check_direct()
     }
 }
 
+// direct_remainder: differences up to 2^63, any step.
+static void check_remainder()
+{
+    for (int t = 0; t < 60000; ++t) {
+        const u32 top = (u32)(rnd() >> (33 + rnd() % 31));
+        u64 step = rnd() >> (1 + rnd() % 63);
+        if (t % 50 == 0) step = 0;
+        if (t % 50 == 1) step = 1;
+        if (t % 50 == 2) step = (u64)1 << (rnd() % 63);
+        const double rcp = step ? 1.0 / (double)step : 0.0;
+        for (int k = 0; k < 60; ++k) {
+            u64 d = rnd() >> (1 + rnd() % 63);
+            const u64 near = (rnd() % ((u64)top + 2)) * step;      // (may wrap round: as good as any)
+            if (k % 3 == 0) d = near + rnd() % 3 - 1;
+            if (k % 3 == 1) d = near + (step ? rnd() % step : 0);
+            if (d >> 63) continue;
+            const u64 q = step ? d / step : 0;
+            ++checks;
+            if (direct_remainder(d, step, rcp, top) != d - (q < top ? q : top) * step) {
+                if (++failures < 20) std::printf("remainder: d %llu step %llu top %u\n", d, step, top);
+            }
+        }
+    }
+}
+
 int main()
 {
+    check_remainder();
+    std::printf("remainders: %lld checks, %lld failures so far\n", checks, failures);
     check_direct();
     std::printf("quotients in double precision: %lld checks, %lld failures so far\n", checks, failures);
     check_cut();

@@ -183,6 +183,30 @@ def test_every_candidate_evaluated_at_the_limits_of_double_precision(zl, oracle,
         assert_same(zl, oracle, -le, iv, R, f"P={P} R={R} first -{first} step {step}")
 
 
+# the same where the sums over the workers set the limit (2^51 / P) or the quotients do (2^47), one step inside and one beyond;
+# and whole numbers of every size up to what P of them may spread over, workers that stand still and that step by 1 among them
+@pytest.mark.parametrize("P,R", [(2, 3), (15, 65), (16, 60), (17, 300), (100, 150), (300, 60), (1000, 150)])
+def test_every_candidate_evaluated_beyond_double_precision(zl, oracle, P, R):
+    rng = np.random.default_rng(P * R)
+    most = min(1 << 47, (1 << 51) // P)
+    for first, step in ((most - most // R, most // R), (most - most // R + 1, most // R), (0, most // R), (0, most // R + 1)):
+        iv = step - rng.integers(0, 1 + step // 1000, size=(2, P)).astype(np.int64)
+        iv[:, P // 2] = step
+        le = first - rng.integers(0, 1 + first // 3, size=(2, P)).astype(np.int64)
+        le[:, 0], le[:, P - 1] = 0, first
+        assert_same(zl, oracle, le, iv, R, f"P={P} R={R} first {first} step {step}")
+        assert_same(zl, oracle, -le, iv, R, f"P={P} R={R} first -{first} step {step}")
+    widest = (1 << 62) // (P * R)
+    iv = (widest * 2.0 ** -rng.uniform(0, 50, size=(6, P))).astype(np.int64)
+    le = (widest * 2.0 ** -rng.uniform(0, 50, size=(6, P))).astype(np.int64)
+    iv[:, 0] = widest
+    iv[2:4, 1::5] = 0
+    iv[4:, 1::3] = 1
+    iv[5, 1::2] = widest - 1
+    assert_same(zl, oracle, le, iv, R, f"P={P} R={R} up to {widest}")
+    assert_same(zl, oracle, le, np.sort(iv, axis=1) // 7 * 7, R, f"P={P} R={R} up to {widest}, sorted")
+
+
 @pytest.mark.parametrize("P,R", [(16, 60), (16, 300), (100, 150)])
 def test_every_candidate_evaluated_flags(zl, oracle, P, R):
     rng = np.random.default_rng(P)
