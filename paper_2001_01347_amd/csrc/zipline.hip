@@ -385,6 +385,12 @@ int launch_run(const i64* ts, const i64* le, const i64* iv, i64 sync_cost, i64 S
 //   few workers    4096 of 16 x 64 34 / 18, of 32 x 32 33 / 25, of 40 x 25 36 / 28, of 48 x 20 35 / 32, of 64 x 16 34 / 41;
 //                  4096 of 24 x 170 149 / 66, 2048 of 32 x 500 255 / 159, 1000 of 48 x 300 103 / 124;
 //                  500 of 16 x 4096 228 / 102, 1000 of 24 x 2000 354 / 197, 100 of 32 x 4096 139 / 91
+//                  (of more than 16384 entries the workers count: where some are through early, most windows are ruled out.
+//                  Configuration 2's steady workers | configuration 5's 20 to 200 ms: 682 of 24 x 4096 440 / 239 | 277 / 234,
+//                  3994 of 28 x 600 538 / 282 | 478 / 281, 585 of 28 x 4096 413 / 268 | 250 / 263, 2097 of 32 x 1000
+//                  429 / 339 | 266 / 338, 2796 of 40 x 600 414 / 371 | 259 / 369, 409 of 40 x 4096 355 / 358 | 205 / 351;
+//                  smaller batches of them 800 of 32 x 1000 224 / 130 | 200 / 133, 100 of 40 x 4096 181 / 110 | 135 / 108,
+//                  200 of 40 x 4096 208 / 192 | 135 / 190)
 //   small batches  one of 100 x 150 28.6 / 14.5, of 1024 x 15 26.7 / 22.6, 64 of 64 x 256 35 / 19, 40 of 200 x 60 26.5 / 25,
 //                  128 of 100 x 150 31 / 41; one of 1000 x 150 60 / 45, 2 of 1000 x 100 101 / 52, 20 of 256 x 120 84 / 38;
 //                  up to 1024 entries one of 100 x 10 10.6 / 10.9, of 128 x 8 11.4 / 12.1 (one launch as well)
@@ -394,7 +400,8 @@ constexpr i64 DIRECT_NMAX = 1 << 18;             // a search has P / 4 workgroup
 bool takes_direct(i64 B, int P, i64 n, bool run)
 {
     if (P > DIRECT_PMAX || n > DIRECT_NMAX) return false;
-    if (P <= (n > 1024 ? 40 : run ? 64 : 48)) return true;
+    if (P <= (n > 16384 ? 28 : n > 1024 ? 40 : run ? 64 : 48)) return true;
+    if (P <= 40 && n > 16384) return B * n * P <= 900000000ll;
     return n > 1024 && B * n * P <= (n > 16384 ? 300000000ll : 100000000ll);
 }
 
