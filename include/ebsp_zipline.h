@@ -171,8 +171,9 @@ int ebsp_predict_zipline_batch(const int64_t* last_end, const int64_t* interval,
  *   workspace      at least ebsp_simulate_workspace_bytes(B, P, R) bytes (never
  *                  0 for a valid shape: it holds the start times), 256-byte
  *                  aligned.
- * The supersteps are enqueued one after the other on `stream`; nothing is
- * copied to the host in between.  S == 0 or B == 0 is a valid no-op.
+ * All work is enqueued on `stream` (of small instances all supersteps are
+ * searched side by side: relative to its start, a superstep does not depend on
+ * the one before); nothing is copied to the host in between.  S == 0 or B == 0 is a valid no-op.
  * Precondition: no start + R * interval overflows int64.  Return codes as above
  * (EBSP_ERR_SHAPE also for S < 0 or sync_cost < 0).
  */

@@ -50,7 +50,7 @@ int ebsp_zipline_tune(int32_t window_cap, int32_t single_max, int32_t window_fil
  *   sweep_min   positive: instances of at least that many entries (P*R) and at
  *               most 1024 workers take the sweep; 0 = the default and negative:
  *               no batch does (every batch takes the kernels that predicted
- *               rows and the range objective use, which are faster today).
+ *               rows use, which are faster today).
  *   slice_keys  entries per slice of an instance's value range (at least 256);
  *               0 = chosen from the batch.
  *   lines       128-byte lines of the input that one window of the sweep may
@@ -68,7 +68,9 @@ int ebsp_zipline_tune_sweep(int32_t sweep_min, int32_t slice_keys, int32_t lines
  * records a pair of HIP events around each kernel it launches, on the call's own
  * stream, without synchronising (events are created up front, for at most
  * max_calls calls; further calls run untimed, and of a kernel whose run of
- * supersteps passes max_calls only the part up to there is counted).
+ * supersteps passes max_calls only the part up to there is counted).  A run's
+ * supersteps searched by one launch count as zl_run_kernel and what advances
+ * their start times as zl_advance_kernel, whichever kernels these are.
  * Do not capture a stream into a HIP graph while a profile is open.
  * ebsp_zipline_profile_end() synchronises the device, writes to kernel_ms
  * (HOST array of ebsp_zipline_kernel_count() floats, may be NULL) the summed

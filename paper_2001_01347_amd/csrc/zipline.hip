@@ -141,7 +141,8 @@ struct Plan {
 };
 
 // single_limit: the most entries one workgroup takes whole on the path the plan is for;
-// list_room: the range objective's scratch, whose size counts windows that leave a quarter or more of a workgroup's records free
+// list_room: the scratch asked for under the range objective, whose size counts windows that leave a quarter or more of a
+// workgroup's records free.  The kernels use range_rest_bytes of it; callers size buffers for several calls by it.
 bool make_plan(i64 B, int P, int R, Plan& pl, int single_limit = SINGLE_MAX, bool list_room = false, bool stored_sum = false)
 {
     if (B < 0 || P < 1 || R < 1) return false;
@@ -814,8 +815,8 @@ int ebsp_simulate_supersteps(const int64_t* last_end0, const int64_t* interval, 
     i64* start = (i64*)((char*)workspace + search_bytes);
     const i64 per = B * (i64)P;
     const i64 n = (i64)P * R;
-    // All supersteps side by side (zl_direct_kernel); of instances of more than 1024 entries the first one, whose workers
-    // have start times of their own, by a bucket search.
+    // All supersteps side by side (zl_direct_kernel, timed as zl_run_kernel like the other launch that takes a run whole); of
+    // instances of more than 1024 entries the first one, whose workers have start times of their own, by a bucket search.
     if (S > 1 && S * B * (P / 4 + 1) <= 0x7fffffffll && takes_direct(B, P, n, true)) {
         if (int rc = check_device()) return rc;
         const i64 s0 = n > 1024 ? 1 : 0;

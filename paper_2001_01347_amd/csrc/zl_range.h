@@ -485,7 +485,7 @@ __device__ __forceinline__ void store_iters(const i64* __restrict__ inst, int P,
 // on the values alone (about one where iteration times vary); RANGE_TRIES of them leave the instance to
 // zl_range_window_kernel where SORT_REST says that it follows.
 // Bound by the chain of one workgroup's steps and by the vector ALU.  4096 of 16 x 64: 77.8 us by a radix sort of
-// every instance, 23.2 so; 16384 of 64 x 30: 607, 160.
+// every instance, 25 so; 16384 of 64 x 30: 607, 160.
 constexpr int RANGE_TRIES = 96;
 
 // Values spread over 2^32 and more (`wide`): keys, cells and bounds from the values shifted down to 32 bits, which widens
