@@ -729,10 +729,12 @@ __device__ __forceinline__ void row_pairs(const i64* __restrict__ row, u32 from,
 // as short as a cell is wide), it is cut into RANGE_LEVEL pieces instead.
 // `cells` words hold (y >> ms) + 1, 0 where no predecessor falls in the cell.
 // Workers in step, a round within 20 us of 100 ms, us, with every such cell on the stack and whole instances left to one
-// workgroup's sort / so: 64 of 1024 x 4096 800 000 / 12 900, 300 of 600 x 100 13 900 / 500, 1100 of 300 x 300 41 800 / 2640,
-// 2000 of 300 x 60 9870 / 1120, 64 of 520 x 150 1320 / 290 (within 1000 us 2080 / 530), one of 1000 x 150 235 / 131.
+// workgroup's sort / so: 64 of 1024 x 4096 800 000 / 7800 (13 400 with 16 cells a walk), 300 of 600 x 100 13 900 / 490,
+// 1100 of 300 x 300 41 800 / 2340, 2000 of 300 x 60 9870 / 830, 64 of 520 x 150 1320 / 277 (within 1000 us 2080 / 437), one
+// of 1000 x 150 235 / 95.
 constexpr int RANGE_ROUND_CELLS = 64;                     // cells looked at together
 constexpr int RANGE_LEVEL = 16;                           // intervals that one interval leaves at most
+constexpr int RANGE_WALK = 8;                             // cells that a thread walks along
 constexpr int RANGE_STACK = 96;                           // intervals that wait
 template <int NT, int NB, bool DEEP>
 struct SliceSmem {
@@ -975,17 +977,17 @@ __device__ __forceinline__ bool zl_range_slice(SliceSmem<NT, NB, DEEP>& sm, cons
             return true;
         };
         // the first entries of the gathered cells r .. r + K - 1, where look_at finds them too full; at_start becomes g of what
-        // lies behind them.  The cells are in order: a thread walks along a quarter of them in a row, from line to line.
+        // lies behind them.  The cells are in order: a thread walks along a few of them in a row, from line to line.
         auto look_at_first = [&](u32 r, u32 K) {
-            constexpr u32 QUARTERS = 4;
+            const u32 parts = (K + RANGE_WALK - 1) / RANGE_WALK;
             for (u32 c = tid; c < K; c += NT) { sm.at_start[c] = may_win(sm.cell[r + c]) ? 0 : U64_MAX; sm.first[c] = U64_MAX; }
             __syncthreads();
 #pragma unroll 1
             for (int pass = 0; pass < 2; ++pass) {
 #pragma unroll 1
-                for (u64 q = tid; q < (u64)P * QUARTERS; q += NT) {
-                    const int p = (int)(q / QUARTERS);
-                    const u32 part = (u32)q % QUARTERS, from = part * K / QUARTERS, to = (part + 1) * K / QUARTERS;
+                for (u64 q = tid; q < (u64)P * parts; q += NT) {
+                    const int p = (int)(q / parts);
+                    const u32 part = (u32)(q % parts), from = part * K / parts, to = (part + 1) * K / parts;
                     const i64* row = inst + (size_t)p * R;
                     u32 i = 0;
                     u64 x = first_in(p), nx = (u64)row[R > 1 ? 1 : 0] - base;      // the row's entry at i and the next (the last one: again)
@@ -1019,7 +1021,7 @@ __device__ __forceinline__ bool zl_range_slice(SliceSmem<NT, NB, DEEP>& sm, cons
             }
         };
         const u32 level0 = sm.waiting;
-        bool too_full = false, in_pieces = false;          // the latter: the interval leaves too much
+        bool in_pieces = false;                            // the interval leaves too much
         u32 K = (u32)(4 * NT) / (u32)P;
         K = K < 1u ? 1u : (K > (u32)RANGE_ROUND_CELLS ? (u32)RANGE_ROUND_CELLS : K);
         for (int round = 0; !in_pieces; ++round) {
@@ -1073,40 +1075,32 @@ __device__ __forceinline__ bool zl_range_slice(SliceSmem<NT, NB, DEEP>& sm, cons
                     if (cell_of(i) <= last) todo &= ~(1u << i);
                 }
             }
-            // K cells at once; (DEEP) from where they are too full on their first entries, and the cells not settled one by one
             if constexpr (!DEEP) {
                 for (u32 r = 0; r < have; r += K)
                     if (!look_at(r, have - r < K ? have - r : K, 0)) return false;
                 __syncthreads();
                 continue;
             }
+            // the cells' first entries, then those not settled one by one
             u32 r = 0, group = 0, ci = 0;
             while (r < have && !in_pieces) {
-                u64 x = 0, h = 0, lb = 0;
-                if (too_full && group == 0) {
+                if (group == 0) {
                     group = have - r < (u32)RANGE_ROUND_CELLS ? have - r : (u32)RANGE_ROUND_CELLS;
                     look_at_first(r, group);
                     ci = 0;
                 }
-                if (group > 0) {
-                    for (; ci < group; ++ci) {
-                        const u32 c = sm.cell[r + ci];
-                        const u64 g = sm.at_start[ci];
-                        x = sm.first[ci];
-                        h = (u64)last_of(c);
-                        lb = g > h ? g - h : 0ull;
-                        if (x < h && may_win(c) && may_be(lb, x + 1)) break;
-                    }
-                    __syncthreads();                       // (the cells' places may be written again)
-                    if (ci == group) { r += group; group = ci = 0; continue; }
+                u64 x = 0, h = 0, lb = 0;
+                for (; ci < group; ++ci) {
+                    const u32 c = sm.cell[r + ci];
+                    const u64 g = sm.at_start[ci];
+                    x = sm.first[ci];
+                    h = (u64)last_of(c);
+                    lb = g > h ? g - h : 0ull;
+                    if (x < h && may_win(c) && may_be(lb, x + 1)) break;
                 }
-                const u32 now = group > 0 ? 1u : have - r < K ? have - r : K;
-                const bool seen = look_at(r + ci, now, ci);
-                if (group == 0) {
-                    if (seen) r += now;
-                    too_full = !seen;
-                    continue;
-                }
+                __syncthreads();                           // (the cells' places may be written again)
+                if (ci == group) { r += group; group = 0; continue; }
+                const bool seen = look_at(r + ci, 1, ci);
                 if (!seen) {                               // cut into cells of its own later
                     const u32 to = sm.waiting;
                     __syncthreads();
