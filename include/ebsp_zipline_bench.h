@@ -70,7 +70,11 @@ int ebsp_zipline_tune_sweep(int32_t sweep_min, int32_t slice_keys, int32_t lines
  * max_calls calls; further calls run untimed, and of a kernel whose run of
  * supersteps passes max_calls only the part up to there is counted).  A run's
  * supersteps searched by one launch count as zl_run_kernel and what advances
- * their start times as zl_advance_kernel, whichever kernels these are.
+ * their start times as zl_advance_kernel, whichever kernels these are; the
+ * kernels of the search over value cells in slices count as the window
+ * kernels in whose place they stand (zl_window_kernel the slices,
+ * zl_plan_kernel and zl_finish_kernel the cells they leave,
+ * zl_window_general_kernel the rest).
  * Do not capture a stream into a HIP graph while a profile is open.
  * ebsp_zipline_profile_end() synchronises the device, writes to kernel_ms
  * (HOST array of ebsp_zipline_kernel_count() floats, may be NULL) the summed

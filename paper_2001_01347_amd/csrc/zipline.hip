@@ -38,6 +38,7 @@
 //   zl_finish.h    reduction over windows, zl_iters; the copy yardstick
 //   zl_direct.h    predicted rows, every candidate evaluated; runs of supersteps side by side
 //   zl_cells.h     one workgroup per stored instance of few rows: value cells
+//   zl_slices.h    larger instances: value cells, in slices of an instance's values
 //   zl_sweep.h     the frontier sweep: stored rows searched in one pass, no crossing table
 //   zl_gridscan.h  GridScan and FullGridScan, the paper's comparators
 // This file: the host side (plans, launches, the C entry points).
@@ -464,6 +465,77 @@ bool takes_cells(i64 B, int P, int R)
     return (n > 2048 && n <= 4096) || n > 8192 || (n > 4096 && B <= GENERAL_GRID);
 }
 
+constexpr i64 RANGE_SMALL = 32768;               // entries of a slice that is small
+
+// The search over value cells in slices (zl_slices_kernel), for instances of several windows.  Windows / slices, us, with
+// configuration 2's steady workers | 5's 20 to 200 ms (one number: as named):
+//   predicted rows   64 of 1024 x 4096 775 / 284 | 390 / 141, 1024 of 256 x 1024 764 / 287 | 391 / 173, 2542 of 378 x 239 930 / 424,
+//                    8690 of 246 x 114 1150 / 824, 2000 of 1000 x 17 626 / 302, 1500 of 45 x 400 186 / 116, 500 of 100 x 200 110 / 66,
+//                    100 of 300 x 100 73 / 50, 16 of 1000 x 150 69 / 63, 4 of 1000 x 100 64 / 57
+//   stored rows      64 of 1024 x 4096 1517 / 866 | 933 / 663, 1024 of 256 x 1024 1141 / 854 | 779 / 663 (configuration 4 1158 / 909,
+//                    in nanoseconds 1167 / 960), 512 of 64 x 4096 766 / 410 | 455 / 340, 2000 of 32 x 1024 597 / 479, 100 of 512 x
+//                    1024 345 / 275, 900 of 64 x 1000 243 / 227 (5's)
+//   not those: fewer stored entries (64 of 256 x 1024 127 / 152) or instances (16 of 1024 x 4096 442 / 401 | 292 / 353), whose
+//   slices are short; short rows, whose searches are most of it (273 of 1024 x 240 545 / 700, 8000 of 300 x 60 1622 / 2197); few
+//   workers, whose cells have to be wide (100 of 12 x 4000 137 / 1750).
+// Workers in step, or of one iteration time (predicted, offsets anywhere | within 20 us): 64 of 1024 x 4096 1330 / 2550 | 12800 /
+// 6140, 1024 of 256 x 1024 1330 / 3160 | 8590 / 15700, 1000 of 60 x 1000 499 / 986 | 973 / 1900, 100 of 300 x 100 91 / 105 | 250 / 162;
+// stored within 20 us 64 of 1024 x 1024 3490 / 2350, in nanoseconds 4050 / 7280.
+struct Slices {
+    i64 count;           // per instance; 0: the search by windows
+    u32 room;            // cells listed per slice
+};
+Slices plan_slices(const Plan& pl, i64 B, int P, int R, bool pred)
+{
+    Slices s{0, 0};
+    const Tuning t = tuning();
+    if (t.window_cap || t.single_max || t.window_fill || P < 8 || P > SLICE_PMAX || R < 8) return s;
+    const i64 n = (i64)P * R;
+    if (!pred && (P < 32 || R < 512 || B < 32 || B * n < 50000000)) return s;
+    // Two workgroups on every CU; one where that leaves a slice few entries.  More than 64 slices list more cells than they save time.
+    i64 slices = 2 * GENERAL_GRID / B;
+    if (slices > 1 && n / slices <= RANGE_SMALL) slices = GENERAL_GRID / B;
+    const i64 most = n / 2048 < R / 4 ? n / 2048 : R / 4;
+    if (slices > most) slices = most;
+    if (slices > 64) slices = 64;
+    if (slices < 1) slices = 1;
+    for (;; slices = (slices + 1) / 2) {             // (callers size the workspace by the windows')
+        const size_t fixed = slice_space_fixed(B, slices, pred ? 0 : P);
+        const i64 room = fixed < pl.bytes ? (i64)((pl.bytes - fixed) / SLICE_CELL_BYTES) / (B * slices) : 0;
+        if (room >= 64) { s.count = slices; s.room = (u32)(room < 4096 ? room : 4096); break; }
+        if (slices == 1) break;
+    }
+    if (s.count * B * s.room > 0xfffffffell || s.count * B > 0x7fffffffll) s.count = 0;      // (cells are numbered in 32 bits)
+    return s;
+}
+
+int launch_slices(const Slices& sl, const i64* ts, const i64* le, const i64* iv, i64 B, int P, int R, void* workspace,
+                  i64* barrier, int* iters, i64* wait, int* status, hipStream_t st)
+{
+    const i64 n = (i64)P * R;
+    const dim3 grid((unsigned)(B * sl.count));
+#define LAUNCH_SLICES(NT_, NB_)                                                                              \
+    do {                                                                                                     \
+        if (ts) LAUNCH(K_WINDOW, (zl_slices_kernel<NT_, NB_, false>), grid, dim3(NT_), ts, le, iv, B, P, R, (u32)sl.count, workspace, sl.room); \
+        else LAUNCH(K_WINDOW, (zl_slices_kernel<NT_, NB_, true>), grid, dim3(NT_), ts, le, iv, B, P, R, (u32)sl.count, workspace, sl.room); \
+    } while (0)
+    const bool many = n / sl.count > RANGE_SMALL;
+    if (many) LAUNCH_SLICES(512, 16384);
+    else LAUNCH_SLICES(512, 4096);
+#undef LAUNCH_SLICES
+#define LAUNCH_CELLS_OF(KERNEL_, KID_, NT_, GRID_)                                                           \
+    LAUNCH(KID_, KERNEL_, dim3((unsigned)(GRID_)), dim3(NT_), ts, le, iv, B, P, R, (u32)sl.count, workspace, sl.room, barrier, iters, wait, status)
+    const i64 cells_grid = 4 * GENERAL_GRID, rest_grid = 2 * GENERAL_GRID;
+    if (ts) LAUNCH_CELLS_OF((zl_slices_queue_kernel<256, false>), K_PLAN, 256, B);
+    else LAUNCH_CELLS_OF((zl_slices_queue_kernel<256, true>), K_PLAN, 256, B);
+    if (ts) LAUNCH_CELLS_OF(zl_slices_cells_kernel<false>, K_FINISH, 256, cells_grid);
+    else LAUNCH_CELLS_OF(zl_slices_cells_kernel<true>, K_FINISH, 256, cells_grid);
+    if (ts) LAUNCH_CELLS_OF((zl_slices_rest_kernel<512, 8, false>), K_WINDOW_GENERAL, 512, rest_grid);
+    else LAUNCH_CELLS_OF((zl_slices_rest_kernel<512, 8, true>), K_WINDOW_GENERAL, 512, rest_grid);
+#undef LAUNCH_CELLS_OF
+    return EBSP_OK;
+}
+
 // The rows are either stored (ts != nullptr) or predicted: t[p][i] = le[p] + (i + 1) * iv[p] (ts == nullptr; direct: every
 // candidate may be evaluated).
 int run_batch(const i64* ts, const i64* le, const i64* iv, i64 B, int P, int R,
@@ -574,6 +646,8 @@ int run_batch(const i64* ts, const i64* le, const i64* iv, i64 B, int P, int R,
     if (pblocks * B > 0x7fffffffll) return fail(EBSP_ERR_SHAPE, "batch too large for one call");
     if (int rc = check_device()) return rc;
     if (pred && direct && takes_direct(B, P, n, false)) return launch_direct(K_DIRECT, le, iv, B, 0, B, P, R, barrier, iters, wait, status, st);
+    if (const Slices sl = plan_slices(pl, B, P, R, pred); sl.count)
+        return launch_slices(sl, ts, le, iv, B, P, R, workspace, barrier, iters, wait, status, st);
     if (int rc = plan_windows(pl, ts, le, iv, B, P, R, wsp, status, st)) return rc;
     // Batches whose windows are all on the chip at once (two workgroups per CU; max_win is about twice the windows
     // there are) are as fast as one workgroup: a window each instead of two.
@@ -615,7 +689,6 @@ int run_batch(const i64* ts, const i64* le, const i64* iv, i64 B, int P, int R,
 
 // The search under the paper's formal objective: small instances in registers, others in slices of their values.
 constexpr int RANGE_SINGLE_MAX = WinCfg<LARGE_NT, LARGE_ITEMS>::CAP_WIDE;      // larger ones need a workspace
-constexpr i64 RANGE_SMALL = 32768;               // entries of a slice that is small
 
 int run_range_batch(const i64* ts, i64 B, int P, int R, i64* barrier, int* iters, i64* dmin, int* status,
                     void* workspace, size_t workspace_bytes, hipStream_t st)

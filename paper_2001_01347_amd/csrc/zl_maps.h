@@ -167,6 +167,21 @@ ZL_FN u64 direct_remainder(u64 d, u64 step, double rcp, u32 top)
     return r >= step && q < top ? r - step : r;
 }
 
+// How many entries of the row first, first + step, ... (R of them) lie below v, for values below 2^63, with rcp = 1 / step (0
+// where step is 0).  The estimated quotient is off by one at most (direct_remainder).
+ZL_FN u32 predicted_below(u64 first, u64 step, double rcp, u32 R, u64 v)
+{
+    if (v <= first) return 0;
+    if (step == 0) return R;
+    const u64 d = v - first - 1;
+    const double est = (double)d * rcp;
+    u32 q = est < (double)R ? (u32)est : R;
+    const u64 r = d - (u64)q * step;
+    if ((i64)r < 0) --q;
+    else if (r >= step && q < R) ++q;
+    return q < R ? q + 1 : R;
+}
+
 // Monotone maps of keys onto value buckets [0, NB).
 // LinearMap: bucket = (key * scale) >> 32, equal slices of [0, span]; right when the
 // keys are spread evenly, as inside a window of the multi-window path.

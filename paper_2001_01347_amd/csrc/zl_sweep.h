@@ -1,7 +1,7 @@
 // The frontier sweep: the summed-wait search of stored rows in one pass over the input.
 // Part of the ZipLine library (see zipline.hip); device code for gfx950.
 #pragma once
-#include "zl_cells.h"
+#include "zl_slices.h"
 
 namespace {
 

@@ -461,8 +461,36 @@ static void check_remainder()
     }
 }
 
+// predicted_below: rows of any first entry and step, values up to 2^63, near and far from where the index changes.
+static void check_below()
+{
+    for (int t = 0; t < 60000; ++t) {
+        const u32 R = 1 + (u32)(rnd() >> (33 + rnd() % 31));
+        u64 step = rnd() >> (2 + rnd() % 62);
+        if (t % 50 == 0) step = 0;
+        if (t % 50 == 1) step = 1;
+        if (t % 50 == 2) step = (u64)1 << (rnd() % 62);
+        const u64 first = rnd() >> (2 + rnd() % 62);
+        const double rcp = step ? 1.0 / (double)step : 0.0;
+        for (int k = 0; k < 60; ++k) {
+            u64 v = rnd() >> (1 + rnd() % 63);
+            if (k % 3) {
+                const u128 near = (u128)first + (u128)(rnd() % ((u64)R + 2)) * step + rnd() % 3;
+                if (near >> 63) continue;
+                v = (u64)near ? (u64)near - 1 : 0;
+            }
+            u64 below = v > first ? (step ? (v - first - 1) / step + 1 : R) : 0;
+            below = below < R ? below : R;
+            ++checks;
+            if (predicted_below(first, step, rcp, R, v) != below) FAIL("predicted_below: first %llu step %llu R %u v %llu", first, step, R, v);
+        }
+    }
+}
+
 int main()
 {
+    check_below();
+    std::printf("indices of predicted rows: %lld checks, %lld failures so far\n", checks, failures);
     check_remainder();
     std::printf("remainders: %lld checks, %lld failures so far\n", checks, failures);
     check_direct();

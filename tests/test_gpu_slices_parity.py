@@ -1,0 +1,105 @@
+"""The summed-wait search over value cells in slices (``zl_slices_kernel`` and what follows it) against the CPU oracle, bit
+for bit: the shapes at the edges of its rule, and the inputs that leave its common path (needs an MI355X)."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+EPOCH = 1_700_000_000_000_000
+
+
+@pytest.fixture(scope="module")
+def zl():
+    assert torch.cuda.is_available(), "these tests need a GPU"
+    from paper_2001_01347_amd import zipline
+    zipline.load()
+    return zipline
+
+
+def sliced(zl, call):
+    """The call's outputs, and whether it went by slices (which need no zl_bounds_kernel)."""
+    zl.ebsp_zipline_profile_begin(1)
+    out = call()
+    ms, _ = zl.ebsp_zipline_profile_end()
+    return [x.cpu().numpy() for x in out], ms["zl_window_kernel"] > 0 and ms["zl_bounds_kernel"] == 0
+
+
+def same_as(got, want, label):
+    bar, it, w, st = got
+    ob, oi, ow, rc, _ = want
+    assert (rc == 0).all() and (st == 0).all(), f"{label}: status {np.unique(st)}"
+    assert np.array_equal(w, ow), f"{label}: wait differs at {np.nonzero(w != ow)[0][:5]}"
+    assert np.array_equal(bar, ob), f"{label}: barrier differs at {np.nonzero(bar != ob)[0][:5]}"
+    assert np.array_equal(it, oi), f"{label}: iters differ at {np.nonzero((it != oi).any(axis=1))[0][:5]}"
+
+
+# rows either side of a wave and of a workgroup's threads, one entry more than a chunk, the fewest and the most rows, short rows
+@pytest.mark.parametrize("B,P,R", [(3, 8, 32769), (2, 63, 4200), (2, 64, 4097), (2, 65, 4099), (3, 511, 520), (40, 1024, 17), (24, 1023, 241),
+                                   (30, 1000, 33), (300, 129, 128)])
+def test_predicted_rows(zl, oracle, B, P, R):
+    rng = np.random.default_rng(P * R)
+    mean = rng.integers(20_000, 200_000, size=(B, P)).astype(np.int64)
+    off = (rng.random((B, P)) * mean).astype(np.int64)
+    some = rng.random((B, P)) < 0.1
+    cases = {"spread": (off, mean),
+             "ties": (off // 1000 * 1000, mean // 1000 * 1000),
+             "nanoseconds": (off * 1000 + 7, mean * 1000 + rng.integers(0, 1000, size=(B, P))),
+             "one iteration time": (off, np.full_like(mean, 100_000)),
+             "in step": (off % 20, np.full_like(mean, 100_000)),
+             "in step, nanoseconds": (off % 20_000, np.full_like(mean, 100_000_000)),
+             "identical": (np.zeros_like(off), np.full_like(mean, 777)),
+             "some stand still": (off, np.where(some, 0, mean)),
+             "one late": (np.where(np.arange(P) == P // 2, off + 30 * mean.max(), off), mean),
+             "one slow": (off, np.where(np.arange(P) == P // 3, mean * 10_000, mean)),
+             "spreads of 2^45": (off << 24, mean << 24)}
+    for label, (le, iv) in cases.items():
+        for epoch in (0, EPOCH):
+            le_, iv_ = torch.from_numpy(le + epoch).cuda(), torch.from_numpy(iv).cuda()
+            got, is_sliced = sliced(zl, lambda: zl.ebsp_predict_zipline_batch(le_, iv_, R))
+            assert is_sliced
+        same_as(got, oracle.zipline(oracle.predicted_rows(le + EPOCH, iv, R), "sweep", threads=16), f"{B} x {P} x {R} {label}")
+
+
+def stored_rows(B, P, R, kind, seed):
+    rng = np.random.default_rng(seed)
+    mean = rng.integers(20_000, 200_000, size=(B, P, 1)) if kind != "alike" else rng.integers(95_000, 105_000, size=(B, P, 1))
+    d = rng.integers(90, 111, size=(B, P, R), dtype=np.int64)
+    if kind == "in step":
+        return np.arange(1, R + 1) * 100_000 + rng.integers(0, 20, size=(B, P, R), dtype=np.int64)
+    d *= mean // 100
+    t = np.cumsum(d, axis=2) + (rng.random((B, P, 1)) * mean).astype(np.int64)
+    if kind == "ties":
+        t = t // 1000 * 1000
+    if kind == "nanoseconds":
+        t = t * 1000 + 321
+    if kind == "pauses":
+        t[:, :, R // 3:] += 3_000_000_000 * (rng.random((B, P, 1)) < 0.2)
+    return t
+
+
+# the fewest entries that go by slices: few instances of many rows (several slices each), and one workgroup per instance
+@pytest.mark.parametrize("kind", ["spread", "alike", "ties", "nanoseconds", "pauses", "in step"])
+@pytest.mark.parametrize("B,P,R", [(48, 1021, 1031), (640, 150, 523)])
+def test_stored_rows(zl, oracle, B, P, R, kind):
+    ts = stored_rows(B, P, R, kind, P + R) + EPOCH
+    dev = torch.from_numpy(ts).cuda()
+    got, is_sliced = sliced(zl, lambda: zl.ebsp_zipline_batch(dev))
+    assert is_sliced
+    same_as(got, oracle.zipline(ts, "sweep", threads=16), f"{B} x {P} x {R} {kind}")
+
+
+def test_stored_rows_out_of_order_are_flagged_wherever_they_are(zl, oracle):
+    B, P, R = 48, 1021, 1031
+    ts = stored_rows(B, P, R, "spread", 5) + EPOCH
+    where = [1, 2, 3, 60, R // 8, R // 4, R // 2, R - 200, R - 2, R - 1]      # before the first barrier, in the slices, behind the last value that can win
+    for b, i in enumerate(where):
+        for p in (int(ts[b, :, -1].argmin()), int(ts[b, :, -1].argmax())):
+            ts[b, p, i] = ts[b, p, i - 1] - 1
+    big = len(where)
+    ts[big, 3, R // 2:] += 1 << 60                                           # P waits of that size do not fit
+    bar, it, w, st = [x.cpu().numpy() for x in zl.ebsp_zipline_batch(torch.from_numpy(ts).cuda())]
+    assert (st[:big] == 1).all() and st[big] == 2 and (st[big + 1:] == 0).all(), st
+    rest = ts[big + 1:]
+    same_as([x[big + 1:] for x in (bar, it, w, st)], oracle.zipline(rest, "sweep", threads=16), "the others")
