@@ -685,18 +685,46 @@ struct RangeRest {
 __device__ __forceinline__ RangeRest range_rest(RangePart* part, i64 all) { return RangeRest{part + all, (u32*)(part + 2 * all)}; }
 ZL_FN size_t range_rest_bytes(i64 B, i64 slices) { return (size_t)B * ((size_t)slices * 2 * sizeof(RangePart) + sizeof(u32)); }
 
-// The pairs of neighbouring entries (i - 1, i), from < i <= to, of a row, by LANES = 2^lanes_log lanes: f(before, entry).
-// Whole waves walk 64 entries a step, four steps asked for ahead, the entry before from the neighbouring lane; fewer
-// lanes (short stretches) load both.
-constexpr int ROW_AHEAD = 4;
-template <class F>
+// The pairs of neighbouring entries (i - 1, i), from < i <= to, of a row: f(before, entry).  A whole wave, 128 entries a step, two
+// neighbouring ones to a lane, U steps asked for ahead, the entry before a lane's from the neighbouring lane.
+template <int U, class F>
+__device__ __forceinline__ void row_pairs_ahead(const i64* __restrict__ row, u32 from, u32 to, const F& f)
+{
+    const u32 lane = threadIdx.x & (WAVE - 1);
+    i64 carry = 0;
+    for (u64 s = from; s <= to; s += U * 2 * WAVE) {       // (64 bits: to may be near 2^31)
+        i64 v[U][2];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const u64 i = s + (u64)(u * 2 * WAVE) + 2 * lane;
+            const i64* e = row + (i < to ? i : (u64)to - 1);
+            v[u][0] = e[0];
+            v[u][1] = e[1];
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const u64 i = s + (u64)(u * 2 * WAVE) + 2 * lane;
+            i64 p = dpp_take<DPP_WAVE_SHR1, 0xf>((i64)0, v[u][1]);
+            if (lane == 0) p = carry;
+            carry = (i64)last_lane((u64)v[u][1]);
+            if (i > from && i <= to) f(p, i < to ? v[u][0] : v[u][1]);
+            if (i < to) f(v[u][0], v[u][1]);
+        }
+    }
+}
+// The same by LANES = 2^lanes_log lanes: fewer than a wave (short stretches) load both.  Whole waves ask for as much ahead as the
+// stretch has.  us, an entry a lane and 256 ahead / two, 256 ahead / 512 / 1024 / by the stretch: 1024 of 256 x 1024 531 / 529 / 507 /
+// 477 / 479, 64 of 1024 x 4096 595 / 583 / 581 / 620 / 569, 8192 of 64 x 128 236 / 224 / 239 / 320 / 230.
+// MOST: the most steps; workgroups of small slices have no long stretches.  0: an entry a lane, 256 ahead, where registers are
+// short (zl_range_window_kernel, which has nothing to do as a rule, 9.5 us for one of 1000 x 150 and 10.6 with two a lane).
+template <int MOST = 8, class F>
 __device__ __forceinline__ void row_pairs(const i64* __restrict__ row, u32 from, u32 to, int lanes_log, const F& f)
 {
     const u32 lane = threadIdx.x & (WAVE - 1);
-    if (lanes_log == 6) {
-        constexpr int U = ROW_AHEAD;
+    if (MOST == 0 && lanes_log == 6) {
+        constexpr int U = 4;
         i64 carry = 0;
-        for (u64 s = from; s <= to; s += U * WAVE) {       // (64 bits: to may be near 2^31)
+        for (u64 s = from; s <= to; s += U * WAVE) {
             i64 v[U];
 #pragma unroll
             for (int u = 0; u < U; ++u) {
@@ -712,6 +740,13 @@ __device__ __forceinline__ void row_pairs(const i64* __restrict__ row, u32 from,
                 if (i > from && i <= to) f(p, v[u]);
             }
         }
+    } else if (lanes_log == 6) {
+        from = uniform(from);
+        to = uniform(to);
+        if (from >= to) return;
+        if (MOST == 2 || to - from < 4 * WAVE) row_pairs_ahead<2>(row, from, to, f);
+        else if (to - from < 8 * WAVE) row_pairs_ahead<4>(row, from, to, f);
+        else row_pairs_ahead<8>(row, from, to, f);
     } else {
         const u32 lanes = 1u << lanes_log;
         for (u64 i = (u64)from + 1 + (lane & (lanes - 1)); i <= to; i += lanes) f(row[i - 1], row[i]);
@@ -767,7 +802,7 @@ __device__ __forceinline__ bool zl_range_slice(SliceSmem<NT, NB, DEEP>& sm, cons
                                                int lanes_log, const RowEnds& ends, u64 own_first, u64 own_last, RangePart& out)
 {
     using V = typename SliceWord<WIDE>::type;
-    constexpr int LOG = __builtin_ctz((unsigned)NB), NW = NT / WAVE, STEPS = NB / NT / 4;
+    constexpr int LOG = __builtin_ctz((unsigned)NB), NW = NT / WAVE, STEPS = NB / NT / 4, MOST = DEEP ? 0 : NB >= 16384 ? 8 : 2;
     static_assert(NB % (4 * NT) == 0 && 4 * STEPS <= 32, "whole steps; a thread's cells are bits of a word");
     const int tid = threadIdx.x;
     const u64 base = (u64)ends.base;
@@ -809,7 +844,7 @@ __device__ __forceinline__ bool zl_range_slice(SliceSmem<NT, NB, DEEP>& sm, cons
             if (t0 + 1 >= (u32)R) continue;
             const u64 len = (u64)R - 1 - t0;
             const u32 from = t0 + (u32)(len * q / pieces), to = t0 + (u32)(len * (q + 1) / pieces);
-            row_pairs(row, from, to, lanes_log, [&](i64 p, i64 y) { bad |= y < p; });
+            row_pairs<MOST>(row, from, to, lanes_log, [&](i64 p, i64 y) { bad |= y < p; });
         }
     }
     if (tid == 0) { sm.listed = 0; sm.waiting = 0; }
@@ -836,7 +871,7 @@ __device__ __forceinline__ bool zl_range_slice(SliceSmem<NT, NB, DEEP>& sm, cons
                 for (int r = group; r < rows; r += groups) {
                     const u32 i0 = whole ? 0u : sm.lo[r], i1 = whole ? (u32)R : sm.hi[r];
                     const u32 to = i1 < (u32)R ? i1 : (u32)R - 1u;
-                    if (i0 < to) row_pairs(inst + (size_t)(p0 + r) * R, i0, to, lanes_log, pair);
+                    if (i0 < to) row_pairs<MOST>(inst + (size_t)(p0 + r) * R, i0, to, lanes_log, pair);
                 }
             }
             start = block_reduce_any<u64, NT>(far, sm.red, OpMax());
