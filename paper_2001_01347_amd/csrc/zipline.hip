@@ -980,7 +980,10 @@ int ebsp_gridscan_batch(const int64_t* ts, int64_t B, int32_t P, int32_t R, int3
 #define LAUNCH_GRIDSCAN(NT_, PER_)                                                                                        \
     LAUNCH(K_GRIDSCAN, (zl_gridscan_kernel<NT_, PER_>), dim3((unsigned)(B * pieces)), dim3(NT_), (const i64*)ts, P, R,   \
            full ? 1 : 0, (int)pieces, pthreads, best, status)
-        if (per_thread == 1) LAUNCH_GRIDSCAN(1024, 1);
+        if (full && per_thread == 4 && !small && R <= GRID_FULL_RMAX && P >= GRID_FULL_PMIN)
+            LAUNCH(K_GRIDSCAN, (zl_fullgridscan_kernel<1024, 4>), dim3((unsigned)(B * pieces)), dim3(1024), (const i64*)ts, P, R, (int)pieces,
+                   pthreads, best, status);
+        else if (per_thread == 1) LAUNCH_GRIDSCAN(1024, 1);
         else if (small && pthreads <= 256) LAUNCH_GRIDSCAN(256, 4);
         else if (small && pthreads <= 512) LAUNCH_GRIDSCAN(512, 4);
         else LAUNCH_GRIDSCAN(1024, 4);

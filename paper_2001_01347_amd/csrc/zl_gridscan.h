@@ -323,6 +323,225 @@ __global__ __launch_bounds__(NT, 8) void zl_gridscan_kernel(
     }
 }
 
+// FullGridScan of many rows: most points need few of them.  max(Z) - min(Z) only grows from row to row, so a point whose set has
+// spread beyond the best found is out.  The rows that spread it are those with the longest iterations (a point's nearest
+// entry is half an iteration away at most), and FIRST of them are searched for all points; each wave's narrowest set is
+// then evaluated over all rows, and so are the points whose sets are no wider than the best of those, a thread per row.  Where that
+// leaves more than LEFT points (rows all alike), every row is searched for every point as above.
+// FullGridScan of 64 of 100 x 150: 302 us with all rows searched for all points, 149 so (with
+// configuration 5's workers 306 and 192); 64 of 50 x 240 105 and 126, so not fewer rows than GRID_FULL_PMIN.
+constexpr int GRID_FIRST = 16, GRID_LEFT = 256, GRID_FULL_RMAX = 512, GRID_FULL_PMIN = 96;
+template <int NT, int PER, class VT>
+__device__ __forceinline__ bool grid_scan_pruned(const i64* __restrict__ inst, u64 base, u64 longest, int P, int R, u32 first, u32 points, int slice,
+                                                 int slices, int pthreads, int pt, unsigned char* stage, u64& bd, u32& bj)
+{
+    constexpr int BINS = 64;
+    static_assert(NT >= 1024 && GRID_LEFT <= NT, "a thread per point of the list");
+    __shared__ u32 bins[BINS], rows[GRID_FIRST], taken, left, list[GRID_LEFT];
+    __shared__ u64 top[16], bot[16], ub, early, late;
+    VT* const staged = (VT*)stage;
+    const int tid = threadIdx.x;
+    // the rows with the longest iterations, roughly
+    for (int q = tid; q < BINS; q += NT) bins[q] = 0;
+    if (tid == 0) { taken = 2; left = 0; ub = U64_MAX; early = U64_MAX; late = 0; rows[0] = rows[1] = 0; }
+    __syncthreads();
+    const float scale = (float)(BINS - 1) / ((float)longest + 1.0f);
+    auto bin_of = [&](int p) -> u32 {
+        const i64* row = inst + (size_t)p * R;
+        const float q = (float)((u64)row[R - 1] - (u64)row[0]) * scale;
+        return q < (float)(BINS - 1) ? (u32)q : (u32)BINS - 1;      // (beyond in unsorted rows only)
+    };
+    u64 mine_early = U64_MAX, mine_late = 0;
+    for (int p = tid; p < P; p += NT) {
+        atomicAdd(&bins[bin_of(p)], 1u);
+        const u64 f = (u64)inst[(size_t)p * R] - base, l = (u64)inst[(size_t)p * R + R - 1] - base;
+        mine_early = l < mine_early ? l : mine_early;
+        mine_late = f > mine_late ? f : mine_late;
+    }
+    if (mine_early != U64_MAX) { atomicMin(&early, mine_early); atomicMax(&late, mine_late); }
+    __syncthreads();
+    // and the first to end and the last to begin, far from every point behind or ahead of them
+    for (int p = tid; p < P; p += NT) {
+        if ((u64)inst[(size_t)p * R + R - 1] - base == early) rows[0] = (u32)p;
+        if ((u64)inst[(size_t)p * R] - base == late) rows[1] = (u32)p;
+    }
+    const int want = GRID_FIRST * R * (int)sizeof(VT) <= NT * GRID_STAGE_PER_THREAD ? GRID_FIRST : GRID_FIRST / 2;
+    int cut = BINS - 1;                                    // its rows and those of the bins above are `want` or more
+    for (u32 sum = bins[cut]; cut > 0 && sum < (u32)want;) sum += bins[--cut];
+    for (int pass = 0; pass < 2; ++pass) {
+        for (int p = tid; p < P; p += NT) {
+            const int q = (int)bin_of(p);
+            if (pass == 0 ? q > cut : q == cut) {
+                const u32 at = atomicAdd(&taken, 1u);
+                if (at < (u32)want) rows[at] = (u32)p;
+            }
+        }
+        __syncthreads();
+    }
+    const int count = (int)taken < want ? (int)taken : want;
+    for (int i = tid; i < count * R; i += NT) {
+        const int r = i / R;
+        staged[i] = (VT)((u64)inst[(size_t)rows[r] * R + (i - r * R)] - base);
+    }
+    __syncthreads();
+    VT e[PER], mx[PER], mn[PER];
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+        const u32 j = first + (u32)k < points ? first + (u32)k : points - 1;      // (beyond the end: the last point again)
+        e[k] = mx[k] = mn[k] = (VT)((u64)inst[j] - base);
+    }
+    if (slice < slices)
+        for (int r = slice; r < count; r += slices) {
+            const VT* row = staged + r * R;
+            u32 pos = grid_seek<VT>(row, (u32)R, e[0], (u32)R / 2);
+#pragma unroll
+            for (int k = 0; k < PER; ++k) {
+                if (k > 0) pos = grid_seek<VT>(row, (u32)R, e[k], pos);
+                const VT below = row[pos > 0 ? pos - 1 : 0], above = row[pos < (u32)R ? pos : (u32)R - 1];
+                const VT v = (VT)(e[k] - below) <= (VT)(above - e[k]) ? below : above;
+                mx[k] = v > mx[k] ? v : mx[k];
+                mn[k] = v < mn[k] ? v : mn[k];
+            }
+        }
+    __syncthreads();
+    if (slices > 1) {                                      // the slices' max(Z) and min(Z) per point
+        VT* const hi = staged;
+        VT* const lo = staged + pthreads * PER;
+        if (slice == 0)
+            for (int k = 0; k < PER; ++k) { hi[k * pthreads + pt] = mx[k]; lo[k * pthreads + pt] = mn[k]; }
+        __syncthreads();
+        if (slice > 0 && slice < slices)
+            for (int k = 0; k < PER; ++k) { atomicMax(&hi[k * pthreads + pt], mx[k]); atomicMin(&lo[k * pthreads + pt], mn[k]); }
+        __syncthreads();
+        if (slice == 0)
+            for (int k = 0; k < PER; ++k) { mx[k] = hi[k * pthreads + pt]; mn[k] = lo[k * pthreads + pt]; }
+    }
+    // the narrowest set of every 16 threads so far
+    u64 d = U64_MAX;
+    u32 j = 0xffffffffu;
+    if (slice == 0)
+#pragma unroll
+        for (int k = 0; k < PER; ++k) {
+            const u64 w = (u64)(VT)(mx[k] - mn[k]);
+            if (first + (u32)k < points && w < d) { d = w; j = first + (u32)k; }
+        }
+    for (int m = 1; m < 16; m *= 2) {
+        const u64 od = (u64)__shfl_xor((i64)d, m);
+        const u32 oj = (u32)__shfl_xor((int)j, m);
+        if (od < d || (od == d && oj < j)) { d = od; j = oj; }
+    }
+    if ((tid & 15) == 0 && j != 0xffffffffu) {
+        const u32 at = atomicAdd(&left, 1u);
+        if (at < (u32)GRID_LEFT) list[at] = j;
+    }
+    __syncthreads();
+    // the listed points over all rows, G at a time: ub becomes the best; (bd, bj) the thread's own
+    auto evaluate = [&](u32 n) {
+        const int per = P < NT ? (P + WAVE - 1) / WAVE * WAVE : NT;
+        const int G = NT / per < 16 ? NT / per : 16, g = tid / per;
+        for (u32 q0 = 0; q0 < n; q0 += (u32)G) {
+            if (tid < G) { top[tid] = 0; bot[tid] = U64_MAX; }
+            __syncthreads();
+            if (g < G && q0 + g < n) {
+                const u32 point = list[q0 + g];
+                const i64 at = inst[point];
+                u64 hi = 0, lo = U64_MAX;
+                for (int p = tid - g * per; p < P; p += per) {
+                    const u64 v = (u64)((u32)p == point / (u32)R ? at : grid_nearest(inst + (size_t)p * R, (u32)R, at)) - base;
+                    hi = v > hi ? v : hi;
+                    lo = v < lo ? v : lo;
+                }
+                hi = wave_scan(hi, OpMax());
+                lo = wave_scan(lo, OpMin());
+                if ((tid & (WAVE - 1)) == WAVE - 1) { atomicMax(&top[g], hi); atomicMin(&bot[g], lo); }
+            }
+            __syncthreads();
+            if (tid < G && q0 + tid < n) {
+                const u64 w = top[tid] - bot[tid];
+                const u32 point = list[q0 + tid];
+                if (w < bd || (w == bd && point < bj)) { bd = w; bj = point; }
+                atomicMin(&ub, w);
+            }
+            __syncthreads();
+        }
+    };
+    evaluate(left);
+    const u64 best = ub;
+    __syncthreads();
+    if (tid == 0) left = 0;
+    __syncthreads();
+    if (slice == 0)
+#pragma unroll
+        for (int k = 0; k < PER; ++k)
+            if (first + (u32)k < points && (u64)(VT)(mx[k] - mn[k]) <= best) {
+                const u32 at = atomicAdd(&left, 1u);
+                if (at < (u32)GRID_LEFT) list[at] = first + (u32)k;
+            }
+    __syncthreads();
+    const u32 n = left;
+    if (n > (u32)GRID_LEFT) return false;
+    evaluate(n);
+    return true;
+}
+
+template <int NT, int PER>
+__global__ __launch_bounds__(NT, 8) void zl_fullgridscan_kernel(
+    const i64* __restrict__ ts, int P, int R, int pieces, int pthreads, GridBest* __restrict__ best, int* __restrict__ status)
+{
+    __shared__ __align__(16) unsigned char stage[NT * GRID_STAGE_PER_THREAD];
+    constexpr int NW = NT / WAVE;
+    __shared__ u64 red[3 * NW];
+    const int tid = threadIdx.x, lane = tid & (WAVE - 1), wave = tid >> 6;
+    const i64 b = blockIdx.x / (u32)pieces;
+    const int piece = (int)(blockIdx.x % (u32)pieces);
+    const i64* __restrict__ inst = ts + b * (i64)P * R;
+    i64 mn = INT64_MAX, mxl = INT64_MIN, longest = 0;
+    for (int p = tid; p < P; p += NT) {
+        const i64 f = inst[(size_t)p * R], l = inst[(size_t)p * R + (R - 1)], s = (i64)((u64)l - (u64)f);
+        mn = f < mn ? f : mn;
+        mxl = l > mxl ? l : mxl;
+        longest = s > longest ? s : longest;
+    }
+    i64 base, top;
+    block_bounds<NT>(mn, mxl, longest, (i64*)red, base, top, longest);
+    int bad = 0;
+    if (status != nullptr && piece == 0)                       // one workgroup per instance checks the rows' order
+        for (int i = tid; i < P * R; i += NT)
+            if (i % R != 0) bad |= inst[i] < inst[i - 1];
+    const u32 points = (u32)(P * R);
+    const int slices = NT / pthreads;
+    const int slice = tid / pthreads, pt = tid - slice * pthreads;
+    const u32 first = (u32)piece * (u32)(pthreads * PER) + (u32)(pt * PER);
+    u64 bd = U64_MAX;
+    u32 bj = 0xffffffffu;
+    const bool narrow = (((u64)top - (u64)base) >> 32) == 0;
+    bool found;
+    if (narrow) found = grid_scan_pruned<NT, PER, u32>(inst, (u64)base, (u64)longest, P, R, first, points, slice, slices, pthreads, pt, stage, bd, bj);
+    else found = grid_scan_pruned<NT, PER, u64>(inst, (u64)base, (u64)longest, P, R, first, points, slice, slices, pthreads, pt, stage, bd, bj);
+    if (!found) {
+        bd = U64_MAX;
+        bj = 0xffffffffu;
+        int seen = 0;
+        if (narrow) grid_scan_points<NT, PER, u32>(inst, inst, (u64)base, P, R, first, points, slice, slices, pthreads, pt, stage, false, seen, bd, bj);
+        else grid_scan_points<NT, PER, u64>(inst, inst, (u64)base, P, R, first, points, slice, slices, pthreads, pt, stage, false, seen, bd, bj);
+    }
+    wave_argmin(bd, bj);
+    __syncthreads();
+    if (lane == WAVE - 1) { red[wave] = bd; red[NW + wave] = bj; }
+    bad = __syncthreads_or(bad);
+    if (tid == 0) {
+        u64 w = red[0];
+        u32 j = (u32)red[NW];
+        for (int k = 1; k < NW; ++k) {
+            const u64 ow = red[k];
+            const u32 oj = (u32)red[NW + k];
+            if (ow < w || (ow == w && oj < j)) { w = ow; j = oj; }
+        }
+        best[blockIdx.x] = GridBest{w, j / (u32)R, j % (u32)R};
+        if (status != nullptr && piece == 0) status[b] = bad ? (int)EBSP_STATUS_UNSORTED : 0;
+    }
+}
+
 __global__ __launch_bounds__(GRID_NT) void zl_gridscan_finish_kernel(
     const i64* __restrict__ ts, int P, int R, int pieces, const GridBest* __restrict__ best,
     i64* __restrict__ barrier, int* __restrict__ iters, i64* __restrict__ dz)

@@ -151,3 +151,24 @@ def test_batches_of_more_workgroups_than_the_chip_takes(zl, oracle, P, R, scale)
     rng = np.random.default_rng(91 * P + R)
     ts = np.cumsum(rng.integers(0, 2000, size=(513, P, R)), axis=2) + rng.integers(0, 2000, size=(513, P, 1))
     assert_same(zl, oracle, ts * scale + EPOCH, f"P={P} R={R} scale={scale}")
+
+
+# FullGridScan of many rows, most points ruled out by a few of them (512 workgroups of 1024 points or more): rows that all
+# continue, that end and begin at very different times, that are alike (too many points left), values beyond 32 bits
+@pytest.mark.parametrize("B,P,R", [(64, 96, 90), (60, 100, 151), (37, 129, 130), (40, 97, 512), (200, 96, 33)])
+def test_full_scan_of_many_rows(zl, oracle, B, P, R):
+    rng = np.random.default_rng(P * R)
+    mean = rng.integers(20_000, 200_000, size=(B, P, 1))
+    d = rng.integers(80, 121, size=(B, P, R)) * (mean // 100)
+    spread = np.cumsum(d, axis=2) + (rng.random((B, P, 1)) * mean).astype(np.int64)
+    alike = np.arange(R) * 1000 + rng.integers(0, 900, size=(B, P, R))
+    late = spread + (rng.random((B, P, 1)) < 0.05) * int(spread.max() // 2)
+    for label, ts in (("spread", spread), ("ties", spread // 5000 * 5000), ("alike", alike), ("late", late), ("wide", spread * 100_003),
+                      ("one value", np.zeros_like(spread))):
+        ts = np.ascontiguousarray(ts + EPOCH)
+        bar, it, dz, st = gpu_run(zl, ts, True)
+        ob, oi, od, rc, _ = oracle.gridscan(ts, True, "bisect", threads=16)
+        assert (rc == 0).all() and (st == 0).all(), label
+        assert np.array_equal(dz, od) and np.array_equal(bar, ob) and np.array_equal(it, oi), label
+    spread[5, 7, R - 1] = spread[5, 7, R - 2] - 1
+    assert gpu_run(zl, spread, True)[3].tolist() == [1 if b == 5 else 0 for b in range(B)]
