@@ -971,7 +971,8 @@ __global__ __launch_bounds__(NT, 4) void zl_slices_queue_kernel(
     });
 }
 
-// A wave per cell, from the queue until it is empty: no barriers.  Up to 64 entries, a lane each.
+// A wave per cell, from the queue until it is empty, or, where the queue leaves most waves without one, a workgroup's four
+// waves together (64 of 1024 x 4096, predicted, 1400 cells: 28 us by waves, 23 together; stored, with more cells, 122 and 163).  Up to 64 entries, a lane each.
 template <bool PRED>
 __global__ __launch_bounds__(256, 4) void zl_slices_cells_kernel(
     const i64* __restrict__ ts, const i64* __restrict__ le, const i64* __restrict__ iv, i64 B, int P, int R, u32 slices,
@@ -980,33 +981,46 @@ __global__ __launch_bounds__(256, 4) void zl_slices_cells_kernel(
     constexpr int NW = 4;
     __shared__ u64 lx[NW][WAVE], ld[NW][WAVE];
     __shared__ u32 listed[NW];
+    __shared__ u64 shares[NW];
     const int lane = threadIdx.x & (WAVE - 1);
     const u32 wave = uniform((u32)threadIdx.x >> 6);
     const SliceSpace space = slice_space(workspace, B, slices, PRED ? 0 : P, room);
     const SliceRows<PRED> all{ts, le, iv, P, R};
     const u32 total = space.queue->cells;
-    for (u32 i = blockIdx.x * NW + wave; i < total; i += gridDim.x * NW) {
+    const bool together = total <= gridDim.x * NW / 2;      // (the same in every workgroup)
+    const u32 list_of = together ? 0u : wave;
+    for (u32 i = together ? blockIdx.x : blockIdx.x * NW + wave; i < total; i += together ? gridDim.x : gridDim.x * NW) {
         const u32 number = uniform(space.order[i]);
         const u32 slice = number / room, b = slice / slices;
         if (space.queued[b].many) continue;
         const SlicePart& s = space.part[slice];
         const LiveCell c = live_cell(s, space.cell[number], slice - b * slices);
         u64 w = U64_MAX, x = U64_MAX;
-        if (c.least <= (i64)published(&space.queued[b].best)) {
+        bool look = c.least <= (i64)published(&space.queued[b].best);
+        if (together) look = __syncthreads_or(look);       // (the answer may change; also: the list is free)
+        if (look) {
             const CellRows<PRED> rows = all.of(b, (u64)s.base);
-            if (lane == 0) listed[wave] = 0;
+            if (lane == 0 && (!together || wave == 0)) listed[list_of] = 0;
+            if (together) __syncthreads();
             __builtin_amdgcn_wave_barrier();
             auto list = [&](u64 y, u64 prev) {
-                const u32 at = atomicAdd(&listed[wave], 1u);
-                if (at < (u32)WAVE) { lx[wave][at] = y; ld[wave][at] = y - prev; }
+                const u32 at = atomicAdd(&listed[list_of], 1u);
+                if (at < (u32)WAVE) { lx[list_of][at] = y; ld[list_of][at] = y - prev; }
             };
             u64 before = 0;
             const bool exact = s.exact != 0;
-            cell_entries<PRED>(space, all, rows, slices, b, c, !exact, 0, 1, before, list, &listed[wave], WAVE);
+            cell_entries<PRED>(space, all, rows, slices, b, c, !exact, together ? (int)wave : 0, together ? NW : 1, before, list, &listed[list_of], WAVE);
             if (!exact) before = last_lane(wave_incl_scan(before));
+            if (together) {
+                if (lane == 0) shares[wave] = before;
+                __syncthreads();
+                before = 0;
+                for (int q = 0; q < NW; ++q) before += shares[q];
+                if (wave != 0) continue;                   // (the first wave goes on alone)
+            }
             __builtin_amdgcn_wave_barrier();
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-            const u32 n = uniform(listed[wave]);
+            const u32 n = uniform(listed[list_of]);
             if (n > (u32)WAVE) {                           // left to zl_slices_rest_kernel
                 if (lane == 0) {
                     if (exact && s.shift <= (u32)SLICE_FINE_LOG) space.crowded[atomicAdd(&space.queue->crowded, 1u)] = number;
@@ -1015,11 +1029,11 @@ __global__ __launch_bounds__(256, 4) void zl_slices_cells_kernel(
                 continue;
             }
             if (lane < (int)n) {
-                x = lx[wave][lane];
+                x = lx[list_of][lane];
                 u64 behind = 0, upto = before;
                 for (u32 o = 0; o < n; ++o) {
-                    const u64 d = ld[wave][o];
-                    if (lx[wave][o] > x) behind += d; else upto += d;
+                    const u64 d = ld[list_of][o];
+                    if (lx[list_of][o] > x) behind += d; else upto += d;
                 }
                 w = exact ? (u64)c.least + (u64)P * (x - c.first) + behind : (u64)P * x - upto;
                 if (x < s.thr) w = x = U64_MAX;
@@ -1028,6 +1042,7 @@ __global__ __launch_bounds__(256, 4) void zl_slices_cells_kernel(
             w = last_lane(w);
             x = last_lane(x);
         }
+        if (together && wave != 0) continue;
         int last = 0;
         if (lane == 0) last = cell_done(space, b, number, w, x);
         if (__builtin_amdgcn_readfirstlane(last)) instance_done<PRED>(space, all, b, slices, room, barrier, iters, wait, status);
