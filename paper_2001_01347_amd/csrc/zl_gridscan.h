@@ -505,9 +505,14 @@ __global__ __launch_bounds__(NT, 8) void zl_fullgridscan_kernel(
     i64 base, top;
     block_bounds<NT>(mn, mxl, longest, (i64*)red, base, top, longest);
     int bad = 0;
-    if (status != nullptr && piece == 0)                       // one workgroup per instance checks the rows' order
-        for (int i = tid; i < P * R; i += NT)
-            if (i % R != 0) bad |= inst[i] < inst[i - 1];
+    if (status != nullptr && piece == 0) {                     // one workgroup per instance checks the rows' order
+        const u32 all = (u32)P * (u32)R;
+#pragma unroll 4
+        for (u32 i = (u32)tid; i < all; i += NT) {             // (a row's first entry: against itself)
+            const u32 before = i % (u32)R ? i - 1 : i;
+            bad |= inst[i] < inst[before];
+        }
+    }
     const u32 points = (u32)(P * R);
     const int slices = NT / pthreads;
     const int slice = tid / pthreads, pt = tid - slice * pthreads;
