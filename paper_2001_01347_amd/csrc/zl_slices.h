@@ -526,10 +526,14 @@ __global__ __launch_bounds__(NT, 4) void zl_slices_kernel(
         A = E + 1;
         before = after;
     }
-    if (!PRED && slices == 1 && !bad && !out.left) {       // the order of what lies behind C
+    if (!PRED && !bad && (slices == 1 || out.left)) {
+        // the order of what has not been walked: the rest of a slice that was left, and behind C where nobody else reads that
         for (int p = wave; p < P; p += NW) {
-            const u32 t0 = sm.hi[p] ? sm.hi[p] - 1 : 0u;
-            if (t0 + 1 < (u32)R) row_pairs(inst + (size_t)p * R, t0, (u32)R - 1, 6, [&](i64 a, i64 y) { bad |= y < a; });
+            const i64* r = inst + (size_t)p * R;
+            const u32 hi = sm.hi[p], from = hi ? hi - 1 : 0u;
+            const u32 end = slices == 1 ? (u32)R : row_first_at_least(r, (u32)R, base, (u64)(last_key + 1) << ms);
+            bad |= end < hi;
+            if (from + 1 < end) row_pairs(r, from, end - 1, 6, [&](i64 a, i64 y) { bad |= y < a; });
         }
     }
     if (!PRED) bad = __syncthreads_or(bad);

@@ -103,3 +103,26 @@ def test_stored_rows_out_of_order_are_flagged_wherever_they_are(zl, oracle):
     assert (st[:big] == 1).all() and st[big] == 2 and (st[big + 1:] == 0).all(), st
     rest = ts[big + 1:]
     same_as([x[big + 1:] for x in (bar, it, w, st)], oracle.zipline(rest, "sweep", threads=16), "the others")
+
+
+# One common pause: with all workers in step after it, their steps over it fall into one or two cells, whose sums pass 2^32, and
+# the slices there are left to the search by windows.  A quarter of the workers end early: values behind those that can win.
+@pytest.mark.parametrize("B,P,R", [(512, 256, 768), (64, 1021, 1031)])       # one slice per instance, and several
+def test_stored_rows_of_a_slice_that_is_left(zl, oracle, B, P, R):
+    rng = np.random.default_rng(P)
+    T, pause, early = 100_000, 100_000_000, np.arange(P) % 4 == 0
+    assert (P - early.sum()) * pause // 2 > 1 << 32 and 0.7 * 0.6 * T / np.sqrt(12 * P) > 20      # wider than the workers are apart
+    ts = np.where(early, 6 * T // 10, T)[:, None] * np.arange(1, R + 1) + rng.integers(0, 20, size=(B, P, R), dtype=np.int64)
+    ts += np.where(ts > T * R // 5, pause, 0) + EPOCH
+    dev = torch.from_numpy(ts).cuda()
+    got, is_sliced = sliced(zl, lambda: zl.ebsp_zipline_batch(dev))
+    assert is_sliced
+    same_as(got, oracle.zipline(ts, "sweep", threads=16), f"{B} x {P} x {R} sorted")
+    where = [R // 10, R // 5 + 3, R // 4, R // 3, 2 * R // 5, R // 2, 2 * R // 3, R - 2, R - 1]      # before the pause, after it, behind
+    for b, i in enumerate(where):
+        p = 1 + 4 * b                                                        # (a worker that ends late)
+        ts[b, p, i] = ts[b, p, i - 1] - 1
+    bar, it, w, st = [x.cpu().numpy() for x in zl.ebsp_zipline_batch(torch.from_numpy(ts).cuda())]
+    n = len(where)
+    assert (st[:n] == 1).all() and (st[n:] == 0).all(), st
+    same_as([x[n:] for x in (bar, it, w, st)], oracle.zipline(ts[n:], "sweep", threads=16), "the others")
