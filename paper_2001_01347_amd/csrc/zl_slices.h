@@ -327,6 +327,11 @@ __global__ __launch_bounds__(NT, 4) void zl_slices_kernel(
     out.flags = back ? (u32)EBSP_STATUS_UNSORTED : 0u;
     if ((!back && wrapped) || range > (u64)INT64_MAX / (u64)P) out.flags |= EBSP_STATUS_OVERFLOW;
     if (out.flags) {                                       // (the same in every slice: nothing below may rely on such rows)
+        if (!PRED && !back) {                              // values too far apart: rows out of order are flagged as well
+            for (int p = (int)k * NW + wave; p < P; p += (int)slices * NW)
+                row_pairs(inst + (size_t)p * R, 0u, (u32)R - 1, 6, [&](i64 a, i64 y) { back |= y < a; });
+            if (__syncthreads_or(back)) out.flags |= EBSP_STATUS_UNSORTED;
+        }
         if (tid == 0) space.part[blockIdx.x] = out;
         return;
     }

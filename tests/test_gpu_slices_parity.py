@@ -126,3 +126,14 @@ def test_stored_rows_of_a_slice_that_is_left(zl, oracle, B, P, R):
     n = len(where)
     assert (st[:n] == 1).all() and (st[n:] == 0).all(), st
     same_as([x[n:] for x in (bar, it, w, st)], oracle.zipline(ts[n:], "sweep", threads=16), "the others")
+
+
+def test_rows_out_of_order_are_flagged_where_values_are_too_far_apart_too(zl):
+    B, P, R = 64, 1021, 1031
+    ts = stored_rows(B, P, R, "spread", 7) + EPOCH
+    ts[::2, 3, R // 2:] += 1 << 60                                           # P waits of that size do not fit
+    where = [(b, (37 * b + 5) % P, 1 + (97 * b) % (R - 1)) for b in range(0, B, 4)]
+    for b, p, i in where:
+        ts[b, p, i] = ts[b, p, i - 1] - 1
+    st = zl.ebsp_zipline_batch(torch.from_numpy(ts).cuda())[3].cpu().numpy()
+    assert st.tolist() == [3 if b % 4 == 0 else 2 if b % 2 == 0 else 0 for b in range(B)]
