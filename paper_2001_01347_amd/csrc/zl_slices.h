@@ -271,6 +271,8 @@ __global__ __launch_bounds__(NT, 4) void zl_slices_kernel(
     i64 mn = INT64_MAX, mxf = INT64_MIN, mxl = INT64_MIN, mnl = INT64_MAX;
     u64 spans = 0;
     int back = 0, wrapped = 0;
+    const u64 interval = PRED ? (u64)iv[0] : 0ull;
+    u64 differ = 0;                                        // 1: not all intervals are this one
 #pragma unroll
     for (int r = 0; r < RPT; ++r) {
         const int p = tid + r * NT;
@@ -284,6 +286,7 @@ __global__ __launch_bounds__(NT, 4) void zl_slices_kernel(
                 l = (i64)(from + (u64)R * s);
                 back |= R > 1 && (i64)s < 0;
                 wrapped |= l < f;
+                differ |= s != interval ? 1ull : 0ull;
                 row[r].step = s;
             } else {
                 row[r].row = inst + (size_t)p * R;
@@ -310,12 +313,14 @@ __global__ __launch_bounds__(NT, 4) void zl_slices_kernel(
         block_reduce_to<NT>(sm.red, 2, v2, OpMax());
         block_reduce_to<NT>(sm.red, 3, v3, OpMin());
         block_reduce_to<NT>(sm.red, 4, spans, OpAdd());
+        if constexpr (PRED) block_reduce_to<NT>(sm.red, 5, differ, OpMax());
         back = __syncthreads_or(back);
         v0 = block_reduced<NT>(sm.red, 0, OpMin());
         v1 = block_reduced<NT>(sm.red, 1, OpMax());
         v2 = block_reduced<NT>(sm.red, 2, OpMax());
         v3 = block_reduced<NT>(sm.red, 3, OpMin());
         spans = uniform(block_reduced<NT>(sm.red, 4, OpAdd()));
+        if constexpr (PRED) differ = block_reduced<NT>(sm.red, 5, OpMax());
         wrapped = __syncthreads_or(wrapped);
         mn = (i64)uniform(v0 ^ SIGN); mxf = (i64)uniform(v1 ^ SIGN); mxl = (i64)uniform(v2 ^ SIGN); mnl = (i64)uniform(v3 ^ SIGN);
     }
@@ -375,6 +380,10 @@ __global__ __launch_bounds__(NT, 4) void zl_slices_kernel(
             const u64 was = C;
             if (!cut_step(C, lb, n, ub) || was - C < C >> 9) break;       // (the same in every thread)
         }
+        // One interval for all workers: every candidate x from thr + interval on has one an interval before it, and there no
+        // worker waits longer (one that is not through by x waits as long, one that is waits longer at x).
+        if constexpr (PRED)
+            if (!differ && interval && C - thr >= interval) C = thr + interval - 1;
         C = uniform(C);
     }
 

@@ -47,6 +47,8 @@ def test_predicted_rows(zl, oracle, B, P, R):
              "ties": (off // 1000 * 1000, mean // 1000 * 1000),
              "nanoseconds": (off * 1000 + 7, mean * 1000 + rng.integers(0, 1000, size=(B, P))),
              "one iteration time": (off, np.full_like(mean, 100_000)),
+             "one iteration time, starts far apart": ((rng.random((B, P)) ** 3 * 1.2 * R * 100_000).astype(np.int64), np.full_like(mean, 100_000)),
+             "one iteration time, others in one": (off, np.where(np.arange(B)[:, None] % 2 == 0, 1, mean)),
              "in step": (off % 20, np.full_like(mean, 100_000)),
              "in step, nanoseconds": (off % 20_000, np.full_like(mean, 100_000_000)),
              "identical": (np.zeros_like(off), np.full_like(mean, 777)),
@@ -59,7 +61,7 @@ def test_predicted_rows(zl, oracle, B, P, R):
             le_, iv_ = torch.from_numpy(le + epoch).cuda(), torch.from_numpy(iv).cuda()
             got, is_sliced = sliced(zl, lambda: zl.ebsp_predict_zipline_batch(le_, iv_, R))
             assert is_sliced
-        same_as(got, oracle.zipline(oracle.predicted_rows(le + EPOCH, iv, R), "sweep", threads=16), f"{B} x {P} x {R} {label}")
+            same_as(got, oracle.zipline(oracle.predicted_rows(le + epoch, iv, R), "sweep", threads=16), f"{B} x {P} x {R} {label} from {epoch}")
 
 
 def stored_rows(B, P, R, kind, seed):
