@@ -882,13 +882,13 @@ __global__ __launch_bounds__(NT, 4) void zl_slices_queue_kernel(
         return;
     }
     top = (i64)uniform((u64)block_reduce<i64, NT>(top, (i64*)red, OpMin()));
-    if (left) {
+    auto by_windows = [&] {
         if (tid == 0) {
             space.queued[b] = SliceQueued{(u64)top, 0, 0, 0, NO_CELL, 0, 0};
             space.rest[atomicAdd(&space.queue->rest, 1u)] = (u32)b;
         }
-        return;
-    }
+    };
+    if (left) { by_windows(); return; }
     cells = uniform(block_reduce<u32, NT>(cells, (u32*)red, OpMax()));               // the most of a slice
     // the cells of all slices: a thread per cell, as many slices at once as that makes
     const u32 chunk = cells < (u32)NT ? cells : (u32)NT, at_once = (u32)NT / (chunk ? chunk : 1u);
@@ -908,11 +908,8 @@ __global__ __launch_bounds__(NT, 4) void zl_slices_queue_kernel(
         if (l < low || (l == low && number < where)) { low = l; where = number; }
     });
     if (tid == 0) listed = 0;
-    const u32 lowest = (u32)block_first_min<NT>(Best{low, where}, red).x;      // (a slice's smallest upper bound is above some cell's lower one)
-    if (lowest == NO_CELL) {                               // (never)
-        if (tid == 0) space.queued[b] = SliceQueued{(u64)top, 0, 0, 0, NO_CELL, 0, 0};
-        return;
-    }
+    const u32 lowest = (u32)block_first_min<NT>(Best{low, where}, red).x;
+    if (lowest == NO_CELL) { by_windows(); return; }       // (never: a slice's smallest upper bound is above some cell's lower one)
     const u32 slice = lowest / room;
     const SlicePart& s = space.part[slice];
     const LiveCell c = live_cell(s, space.cell[lowest], slice - (u32)(b * slices));
@@ -946,13 +943,7 @@ __global__ __launch_bounds__(NT, 4) void zl_slices_queue_kernel(
     // Many cells: workers with one and the same iteration time, whose waits repeat, are searched by windows; workers in step, whose
     // cells hold more entries than a window's bucket may, by cells, but not by a wave's list.
     const bool many = count > (u32)R / 4 + WAVE;
-    if (many && n <= BUCKET_LIMIT) {
-        if (tid == 0) {
-            space.queued[b] = SliceQueued{(u64)top, 0, 0, 0, NO_CELL, 0, 0};
-            space.rest[atomicAdd(&space.queue->rest, 1u)] = (u32)b;
-        }
-        return;
-    }
+    if (many && n <= BUCKET_LIMIT) { by_windows(); return; }
     const bool crowd = many && exact && s.shift <= (u32)SLICE_FINE_LOG;
     if (tid == 0) {
         at = atomicAdd(&space.queue->cells, count);
