@@ -1313,7 +1313,8 @@ struct RestSearch {
 };
 
 // A slice by windows (see zl_window.h) without a crossing table: the rows are searched for each window's end, and windows are
-// as wide as the ones before have shown to fit.  Those that the fast search gives up are left to the general one.
+// as wide as the ones before have shown to fit.  Behind one of few entries the next begins where an entry is, so that there are no
+// more windows than entries, however far apart those are.  Windows that the fast search gives up are left to the general one.
 template <int NT, bool PRED>
 struct SliceWindowsSmem {
     __align__(16) unsigned char hot[WinHot<NT, 16, PRED>::BYTES];
@@ -1353,7 +1354,7 @@ __device__ __forceinline__ void slice_windows(unsigned char* smem, RestSearch<NT
     InstInfo ii{};
     ii.base = s.base;
     ii.thr = s.thr;
-    const bool fits = (!s.far || !PRED) && (u64)P * (u64)R < HOT_MAX_ENTRIES;
+    const bool fits = (u64)P * (u64)R < HOT_MAX_ENTRIES;
     u64 a = s.from, width = (s.to - s.from) / 16 + 1;
     u32 lo[RPT], hi[RPT];
 #pragma unroll
@@ -1366,7 +1367,7 @@ __device__ __forceinline__ void slice_windows(unsigned char* smem, RestSearch<NT
         if (width > 0xffffffffull) width = 0xffffffffull;
         const u64 el = s.to - a < width ? s.to : a + width - 1;
         u32 mine = 0;
-        int far = 0;
+        int far = 0;                                       // distances that do not fit 32 bits
         if constexpr (PRED) rw.par = sm.par;
 #pragma unroll
         for (int c = 0; c < RPT; ++c) {
@@ -1376,7 +1377,8 @@ __device__ __forceinline__ void slice_windows(unsigned char* smem, RestSearch<NT
                 hi[c] = r.below(el + 1);
                 hi[c] = hi[c] < lo[c] ? lo[c] : hi[c];
                 mine += hi[c] - lo[c];
-                if (s.far && hi[c] > lo[c]) far |= ((r.at(lo[c]) - (lo[c] ? r.at(lo[c] - 1) : a)) >> 32) != 0;
+                if (s.far && (PRED || hi[c] > lo[c]))      // (of stored rows without an entry zl_place_rows takes the whole values)
+                    far |= (((hi[c] > lo[c] ? r.at(lo[c]) : a) - (lo[c] ? r.at(lo[c] - 1) : a)) >> 32) != 0;
                 if constexpr (PRED) sm.par[p] = make_uint2((u32)((u64)r.f + base), (u32)r.step);
             }
         }
@@ -1401,10 +1403,23 @@ __device__ __forceinline__ void slice_windows(unsigned char* smem, RestSearch<NT
             if (f.wait == U64_MAX && f.brel == DEFERRED_WINDOW) search.general(a, el);
             else if (f.wait != U64_MAX) search.take(Best{f.wait, f.brel});
         }
+        u64 next = el + 1;
+        if (count < (u32)H::CAP / 4) {
+            next = U64_MAX;
+#pragma unroll
+            for (int c = 0; c < RPT; ++c) {
+                const int p = tid + c * NT;
+                if (p < P && hi[c] < (u32)R) {
+                    const u64 x = row_of(p).at(hi[c]);
+                    next = x < next ? x : next;
+                }
+            }
+            next = block_reduce<u64, NT>(next, hot.red, OpMin());
+        }
 #pragma unroll
         for (int c = 0; c < RPT; ++c) lo[c] = hi[c];
         if (el == s.to) break;
-        a = el + 1;
+        a = next;
         if (count < (u32)H::CAP / 2) width *= 2;
     }
 }

@@ -139,3 +139,41 @@ def test_rows_out_of_order_are_flagged_where_values_are_too_far_apart_too(zl):
         ts[b, p, i] = ts[b, p, i - 1] - 1
     st = zl.ebsp_zipline_batch(torch.from_numpy(ts).cuda())[3].cpu().numpy()
     assert st.tolist() == [3 if b % 4 == 0 else 2 if b % 2 == 0 else 0 for b in range(B)]
+
+
+# Workers whose waits repeat: every cell of one kind may win, and the instances are searched by windows.  In nanoseconds, and with
+# the entries so far apart that almost every window of 2^32 values is empty.
+def intervals_of(kind, rng, B, P):
+    return {"one": np.full((B, P), 100_000), "two": np.where(rng.random((B, P)) < 0.3, 200_000, 100_000),
+            "almost one": 100_000 + rng.integers(0, 3, size=(B, P))}[kind].astype(np.int64)
+
+
+@pytest.mark.parametrize("unit", [1, 1000, 1 << 27])
+@pytest.mark.parametrize("B,P,R", [(3, 8, 32769), (150, 64, 500), (24, 1023, 241)])
+def test_predicted_rows_whose_waits_repeat(zl, oracle, B, P, R, unit):
+    rng = np.random.default_rng(P + R)
+    for kind in ("two", "almost one"):
+        iv = intervals_of(kind, rng, B, P) * unit
+        for label, off in (("anywhere", (rng.random((B, P)) * 100_000).astype(np.int64) * unit), ("in step", rng.integers(0, 20 * unit, size=(B, P)))):
+            le = off + EPOCH
+            got, is_sliced = sliced(zl, lambda: zl.ebsp_predict_zipline_batch(torch.from_numpy(le).cuda(), torch.from_numpy(iv).cuda(), R))
+            assert is_sliced
+            same_as(got, oracle.zipline(oracle.predicted_rows(le, iv, R), "sweep", threads=16), f"{B} x {P} x {R} {kind}, {label}, {unit}")
+
+
+@pytest.mark.parametrize("unit", [1, 1000])
+@pytest.mark.parametrize("kind", ["one", "two", "almost one"])
+@pytest.mark.parametrize("B,P,R", [(48, 1021, 1031), (640, 150, 523)])
+def test_stored_rows_whose_waits_repeat(zl, oracle, B, P, R, kind, unit):
+    rng = np.random.default_rng(P + R)
+    iv = intervals_of(kind, rng, B, P) * unit
+    off = (rng.random((B, P)) * 100_000).astype(np.int64) * unit
+    ts = off[:, :, None] + np.arange(R) * iv[:, :, None] + EPOCH
+    got, is_sliced = sliced(zl, lambda: zl.ebsp_zipline_batch(torch.from_numpy(ts).cuda()))
+    assert is_sliced
+    same_as(got, oracle.zipline(ts, "sweep", threads=16), f"{B} x {P} x {R} {kind}, {unit}")
+    where = [1, 2, R // 8, R // 4, R // 2, R - 200, R - 2]                   # (the last entry stays: all rows of one length)
+    for b, i in enumerate(where):
+        ts[b, 7 * b, i] = ts[b, 7 * b, i - 1] - 1
+    st = zl.ebsp_zipline_batch(torch.from_numpy(ts).cuda())[3].cpu().numpy()
+    assert (st[:len(where)] == 1).all() and (st[len(where):] == 0).all(), st
