@@ -475,6 +475,13 @@ constexpr i64 RANGE_SMALL = 32768;               // entries of a slice that is s
 //   stored rows      64 of 1024 x 4096 1517 / 866 | 933 / 663, 1024 of 256 x 1024 1141 / 854 | 779 / 663 (configuration 4 1158 / 909,
 //                    in nanoseconds 1167 / 960), 512 of 64 x 4096 766 / 410 | 455 / 340, 2000 of 32 x 1024 597 / 479, 100 of 512 x
 //                    1024 345 / 275, 900 of 64 x 1000 243 / 227 (5's)
+//   windows with a cut (CUT_MIN_WINDOWS) leave out what lies behind the last value that can win, which for 5's workers is most, while
+//                    every slice searches every row for its ends: of short rows, up to 100 million entries, 64 of 1024 x 1024 491 / 454 |
+//                    285 / 328, 120 of 900 x 620 474 / 455 | 284 / 457, 100 of 768 x 1000 511 / 484 | 304 / 382, 200 of 600 x 600
+//                    465 / 511 | 296 / 406, 300 of 400 x 600 442 / 537 | 287 / 317, 600 of 300 x 520 541 / 554 | 363 / 409; beyond
+//                    (not short) 128 of 512 x 1024 415 / 376 | 252 / 265, 160 of 448 x 1000 430 / 340 | 262 / 272, 36 of 1024 x 2048
+//                    574 / 401 | 328 / 321, (more) 400 of 600 x 520 780 / 700 | 511 / 512, 128 of 1024 x 1024 901 / 662 | 502 / 465,
+//                    (no cut) 48 of 1021 x 1031 377 / 340 | 382 / 280, 100 of 1024 x 600 466 / 466 | 462 / 358
 //   not those: fewer stored entries (64 of 256 x 1024 127 / 152) or instances (16 of 1024 x 4096 442 / 401 | 292 / 353), whose
 //   slices are short; short rows, whose searches are most of it (273 of 1024 x 240 545 / 700, 8000 of 300 x 60 1622 / 2197); few
 //   workers, whose cells have to be wide (100 of 12 x 4000 137 / 1750).
@@ -492,6 +499,7 @@ Slices plan_slices(const Plan& pl, i64 B, int P, int R, bool pred)
     if (t.window_cap || t.single_max || t.window_fill || P < 8 || P > SLICE_PMAX || R < 8) return s;
     const i64 n = (i64)P * R;
     if (!pred && (P < 32 || R < 512 || B < 32 || B * n < 50000000)) return s;
+    if (!pred && R < 2 * P && B * n < 100000000 && B * (i64)pl.max_win > CUT_MIN_WINDOWS) return s;
     // Two workgroups on every CU; one where that leaves a slice few entries.  More than 64 slices list more cells than they save time.
     i64 slices = 2 * GENERAL_GRID / B;
     if (slices > 1 && n / slices <= RANGE_SMALL) slices = GENERAL_GRID / B;
