@@ -988,7 +988,8 @@ int ebsp_gridscan_batch(const int64_t* ts, int64_t B, int32_t P, int32_t R, int3
 #define LAUNCH_GRIDSCAN(NT_, PER_)                                                                                        \
     LAUNCH(K_GRIDSCAN, (zl_gridscan_kernel<NT_, PER_>), dim3((unsigned)(B * pieces)), dim3(NT_), (const i64*)ts, P, R,   \
            full ? 1 : 0, (int)pieces, pthreads, best, status)
-        if (full && per_thread == 4 && !small && R <= GRID_FULL_RMAX && P >= GRID_FULL_PMIN)
+        if (full && per_thread == 4 && !small && R <= GRID_FULL_RMAX && P >= GRID_FULL_PMIN && P <= GRID_FULL_PMAX &&
+            (P >= 128 || B * pieces > 3 * GENERAL_GRID))
             LAUNCH(K_GRIDSCAN, (zl_fullgridscan_kernel<1024, 4>), dim3((unsigned)(B * pieces)), dim3(1024), (const i64*)ts, P, R, (int)pieces,
                    pthreads, best, status);
         else if (per_thread == 1) LAUNCH_GRIDSCAN(1024, 1);

@@ -325,12 +325,20 @@ __global__ __launch_bounds__(NT, 8) void zl_gridscan_kernel(
 
 // FullGridScan of many rows: most points need few of them.  max(Z) - min(Z) only grows from row to row, so a point whose set has
 // spread beyond the best found is out.  The rows that spread it are those with the longest iterations (a point's nearest
-// entry is half an iteration away at most), and FIRST of them are searched for all points; each wave's narrowest set is
-// then evaluated over all rows, and so are the points whose sets are no wider than the best of those, a thread per row.  Where that
-// leaves more than LEFT points (rows all alike), every row is searched for every point as above.
-// FullGridScan of 64 of 100 x 150: 302 us with all rows searched for all points, 149 so (with
-// configuration 5's workers 306 and 192); 64 of 50 x 240 105 and 126, so not fewer rows than GRID_FULL_PMIN.
-constexpr int GRID_FIRST = 16, GRID_LEFT = 256, GRID_FULL_RMAX = 512, GRID_FULL_PMIN = 96;
+// entry is half an iteration away at most), and FIRST of them are searched for all points; the narrowest set of every 16
+// threads is then evaluated over all rows, and so are the points whose sets are no wider than the best of those, a thread per row.
+// Where that leaves more than LEFT points, every row is searched for every point as above, and so it is from the start where more
+// than LONG rows are three quarters as long as the longest or more: then a few of them rule out little.
+// us, all rows searched for all points / so, with configuration 2's workers of whom one in twenty is 1.5 to 3 times slower | 5's |
+// alike: 64 of 100 x 150 302 / 284 | 300 / 203 | 294 / 298, 64 of 128 x 150 456 / 363 | 454 / 276 | 446 / 454, 64 of 200 x 100
+// 502 / 295 | 499 / 537 | 471 / 478, 30 of 300 x 150 1210 / 415 | 1201 / 1209 | 1189 / 1199, 20 of 500 x 100 984 / 730 | 972 / 983 |
+// 923 / 932.  Without LONG and with 256 points left, 64 of 100 x 150 of workers alike took 400, 64 of 200 x 100 644, 20 of 500 x
+// 100 of 5's 2606 (where a point at a time is evaluated).
+// Beyond PMAX a round of evaluation takes one point: 10 of 1000 x 150 4017 / 4518, 64 of 1000 x 60 6471 / 8194; below PMIN there
+// are too few rows to save: 64 of 50 x 240 105 / 126.  R up to RMAX: the first rows fit the stage, and longer ones are searched in
+// pieces of a row or more by chips that are not full, 16 of 96 x 512 188 / 349 (256 points left).  Fewer than 128 rows in small
+// batches (ebsp_gridscan_batch): 40 of 100 x 180 178 / 208 | 179 / 177, 32 of 100 x 240 189 / 228 | 188 / 203.
+constexpr int GRID_FIRST = 16, GRID_LEFT = 128, GRID_LONG = 52, GRID_FULL_RMAX = 256, GRID_FULL_PMIN = 96, GRID_FULL_PMAX = 512;
 template <int NT, int PER, class VT>
 __device__ __forceinline__ bool grid_scan_pruned(const i64* __restrict__ inst, u64 base, u64 longest, int P, int R, u32 first, u32 points, int slice,
                                                  int slices, int pthreads, int pt, unsigned char* stage, u64& bd, u32& bj)
@@ -365,7 +373,8 @@ __device__ __forceinline__ bool grid_scan_pruned(const i64* __restrict__ inst, u
         if ((u64)inst[(size_t)p * R + R - 1] - base == early) rows[0] = (u32)p;
         if ((u64)inst[(size_t)p * R] - base == late) rows[1] = (u32)p;
     }
-    const int want = GRID_FIRST * R * (int)sizeof(VT) <= NT * GRID_STAGE_PER_THREAD ? GRID_FIRST : GRID_FIRST / 2;
+    constexpr int want = GRID_FIRST;
+    static_assert((size_t)GRID_FIRST * GRID_FULL_RMAX * sizeof(u64) <= (size_t)NT * GRID_STAGE_PER_THREAD, "the first rows are staged together");
     int cut = BINS - 1;                                    // its rows and those of the bins above are `want` or more
     for (u32 sum = bins[cut]; cut > 0 && sum < (u32)want;) sum += bins[--cut];
     for (int pass = 0; pass < 2; ++pass) {
@@ -495,15 +504,16 @@ __global__ __launch_bounds__(NT, 8) void zl_fullgridscan_kernel(
     const i64 b = blockIdx.x / (u32)pieces;
     const int piece = (int)(blockIdx.x % (u32)pieces);
     const i64* __restrict__ inst = ts + b * (i64)P * R;
-    i64 mn = INT64_MAX, mxl = INT64_MIN, longest = 0;
-    for (int p = tid; p < P; p += NT) {
-        const i64 f = inst[(size_t)p * R], l = inst[(size_t)p * R + (R - 1)], s = (i64)((u64)l - (u64)f);
-        mn = f < mn ? f : mn;
-        mxl = l > mxl ? l : mxl;
-        longest = s > longest ? s : longest;
+    static_assert(GRID_FULL_PMAX <= NT, "a row to a thread");
+    i64 mn = INT64_MAX, mxl = INT64_MIN, mine = 0, longest;
+    if (tid < P) {
+        mn = inst[(size_t)tid * R];
+        mxl = inst[(size_t)tid * R + (R - 1)];
+        mine = (i64)((u64)mxl - (u64)mn);
     }
     i64 base, top;
-    block_bounds<NT>(mn, mxl, longest, (i64*)red, base, top, longest);
+    block_bounds<NT>(mn, mxl, mine, (i64*)red, base, top, longest);
+    const bool few = __syncthreads_count(tid < P && mine >= longest - longest / 4) <= GRID_LONG;      // rows that may rule points out
     int bad = 0;
     if (status != nullptr && piece == 0) {                     // one workgroup per instance checks the rows' order
         const u32 all = (u32)P * (u32)R;
@@ -520,9 +530,9 @@ __global__ __launch_bounds__(NT, 8) void zl_fullgridscan_kernel(
     u64 bd = U64_MAX;
     u32 bj = 0xffffffffu;
     const bool narrow = (((u64)top - (u64)base) >> 32) == 0;
-    bool found;
-    if (narrow) found = grid_scan_pruned<NT, PER, u32>(inst, (u64)base, (u64)longest, P, R, first, points, slice, slices, pthreads, pt, stage, bd, bj);
-    else found = grid_scan_pruned<NT, PER, u64>(inst, (u64)base, (u64)longest, P, R, first, points, slice, slices, pthreads, pt, stage, bd, bj);
+    bool found = false;
+    if (few && narrow) found = grid_scan_pruned<NT, PER, u32>(inst, (u64)base, (u64)longest, P, R, first, points, slice, slices, pthreads, pt, stage, bd, bj);
+    if (few && !narrow) found = grid_scan_pruned<NT, PER, u64>(inst, (u64)base, (u64)longest, P, R, first, points, slice, slices, pthreads, pt, stage, bd, bj);
     if (!found) {
         bd = U64_MAX;
         bj = 0xffffffffu;

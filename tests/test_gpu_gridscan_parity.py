@@ -172,3 +172,20 @@ def test_full_scan_of_many_rows(zl, oracle, B, P, R):
         assert np.array_equal(dz, od) and np.array_equal(bar, ob) and np.array_equal(it, oi), label
     spread[5, 7, R - 1] = spread[5, 7, R - 2] - 1
     assert gpu_run(zl, spread, True)[3].tolist() == [1 if b == 5 else 0 for b in range(B)]
+
+
+# the edges of its rule: the fewest rows, the longest ones, the most, small batches that do not take it, and of all of them a few rows
+# much longer than the others, which rule points out, and as many as still do
+@pytest.mark.parametrize("B,P,R", [(100, 96, 90), (60, 100, 151), (34, 127, 256), (20, 128, 255), (12, 511, 100), (13, 512, 97), (30, 100, 180), (12, 513, 100)])
+@pytest.mark.parametrize("slow", [5, 51, 60])
+def test_full_scan_of_rows_a_few_of_which_are_long(zl, oracle, B, P, R, slow):
+    rng = np.random.default_rng(P * R + slow)
+    mean = rng.integers(90_000, 110_000, size=(B, P, 1))
+    mean[np.argsort(rng.random((B, P)), axis=1) < slow] *= 2
+    ts = np.cumsum(rng.integers(90, 111, size=(B, P, R)) * (mean // 100), axis=2) + (rng.random((B, P, 1)) * mean).astype(np.int64)
+    ts[B // 2:] *= 50_021                                                    # values beyond 32 bits
+    ts = np.ascontiguousarray(ts + EPOCH)
+    bar, it, dz, st = gpu_run(zl, ts, True)
+    ob, oi, od, rc, _ = oracle.gridscan(ts, True, "bisect", threads=16)
+    assert (rc == 0).all() and (st == 0).all()
+    assert np.array_equal(dz, od) and np.array_equal(bar, ob) and np.array_equal(it, oi)
