@@ -940,11 +940,14 @@ __global__ __launch_bounds__(NT, 4) void zl_slices_queue_kernel(
     u32 count = 0;
     each([&](bool is, u32 number, i64 least) { count += is && least <= top && !(seen && number == lowest) ? 1u : 0u; });
     count = block_reduce<u32, NT>(count, (u32*)red, OpAdd());
-    // Many cells: workers with one and the same iteration time, whose waits repeat, are searched by windows; workers in step, whose
-    // cells hold more entries than a window's bucket may, by cells, but not by a wave's list.
+    // Many cells: workers whose waits repeat, searched by windows.  Those in step fill cells with more entries than a window's bucket may
+    // hold, and take the general search there, or are searched by cells, but not by a wave's list: cell by cell they are read
+    // eight entries to a row, and keys that are shifted three times.  us, by windows / by cells, within 20 us: stored 256 of 256 x
+    // 1024 3237 / 4658, 1024 of 256 x 1024 11795 / 18377, 200 of 300 x 1024 4224 / 4225, 60 of 1021 x 1031 5018 / 2246; in
+    // nanoseconds 256 of 256 x 1024 3578 / 16433, 60 of 1021 x 1031 5010 / 7113; predicted 1024 of 256 x 1024 11340 / 8102.
     const bool many = count > (u32)R / 4 + WAVE;
-    if (many && n <= BUCKET_LIMIT) { by_windows(); return; }
-    const bool crowd = many && exact && s.shift <= (u32)SLICE_FINE_LOG;
+    const bool crowd = many && n > (PRED ? 1u : 2u) * BUCKET_LIMIT && exact && s.shift <= (u32)SLICE_FINE_LOG;
+    if (many && !crowd) { by_windows(); return; }
     if (tid == 0) {
         at = atomicAdd(&space.queue->cells, count);
         if (crowd) crowded_at = atomicAdd(&space.queue->crowded, count);
@@ -1156,13 +1159,16 @@ __device__ __forceinline__ void slices_crowded(unsigned char* smem, const SliceS
     __syncthreads();
 }
 
-struct RowsBetween : Rows {                      // whole rows, the entries in [from, to] alone
-    u64 from, to;
-    __device__ __forceinline__ void range(int p, u32& lo, u32& hi) const
+template <int NT>
+struct RowsBetween : Rows {                      // of whole rows a part, which the thread that asks for a row knows: row tid + c * NT
+    u32 lo[ROWS_PER_THREAD<NT>], hi[ROWS_PER_THREAD<NT>];
+    __device__ __forceinline__ void range(int p, u32& first, u32& end) const
     {
-        const Rows& all = *this;
-        lo = row_lower_bound(all, p, 0u, (u32)R, from);
-        hi = row_lower_bound(all, p, lo, (u32)R, to + 1);
+        first = lo[0];
+        end = hi[0];
+#pragma unroll
+        for (int c = 1; c < ROWS_PER_THREAD<NT>; ++c)
+            if (p >= c * NT) { first = lo[c]; end = hi[c]; }
     }
 };
 template <int NT>
@@ -1193,21 +1199,40 @@ struct RestSearch {
         if (got.before(best)) best = got;
         if (best.d < (u64)top) top = (i64)best.d;
     }
-    // the general search (takes the whole of LDS)
-    __device__ __forceinline__ void general(u64 first, u64 last)
+    // the general search of the entries lo[p] up to hi[p] (not itself) of every row, all those in [first, last] (takes the whole of LDS)
+    __device__ __forceinline__ void general(u64 first, u64 last, const u32 (&lo)[ROWS_PER_THREAD<NT>], const u32 (&hi)[ROWS_PER_THREAD<NT>])
     {
         __syncthreads();
         const Smem gm = carve<NT, ITEMS>(smem);
-        const CellRows<PRED> rows = all.of(b, base);
-        RowsBetween rw;
-        rw.inst = rows.inst; rw.le = rows.le; rw.iv = rows.iv;
-        rw.par = nullptr; rw.cr = nullptr; rw.narrow = false; rw.wide = false; rw.stride = 0; rw.k0 = rw.k1 = 0;
-        rw.P = all.P; rw.R = all.R; rw.base = base; rw.from = first; rw.to = last;
+        RowsBetween<NT> rw = rows_of();
+#pragma unroll
+        for (int c = 0; c < ROWS_PER_THREAD<NT>; ++c) { rw.lo[c] = lo[c]; rw.hi[c] = hi[c]; }
         int none = 0;
         u64 w = U64_MAX, x = 0;
-        zl_window<NT, ITEMS, true, false, RowsBetween>(gm, rw, thr, first, last, w, x, none);
+        zl_window<NT, ITEMS, true, false, RowsBetween<NT>>(gm, rw, thr, first, last, w, x, none);
         __syncthreads();
         if (w != U64_MAX) take(Best{w, x});
+    }
+    __device__ __forceinline__ void general(u64 first, u64 last)
+    {
+        const Rows rw = rows_of();
+        u32 lo[ROWS_PER_THREAD<NT>], hi[ROWS_PER_THREAD<NT>];
+#pragma unroll
+        for (int c = 0; c < ROWS_PER_THREAD<NT>; ++c) {
+            const int p = (int)threadIdx.x + c * NT;
+            lo[c] = p < all.P ? row_lower_bound(rw, p, 0u, (u32)all.R, first) : 0u;
+            hi[c] = p < all.P ? row_lower_bound(rw, p, lo[c], (u32)all.R, last + 1) : 0u;
+        }
+        general(first, last, lo, hi);
+    }
+    __device__ __forceinline__ RowsBetween<NT> rows_of() const
+    {
+        const CellRows<PRED> rows = all.of(b, base);
+        RowsBetween<NT> rw;
+        rw.inst = rows.inst; rw.le = rows.le; rw.iv = rows.iv;
+        rw.par = nullptr; rw.cr = nullptr; rw.narrow = false; rw.wide = false; rw.stride = 0; rw.k0 = rw.k1 = 0;
+        rw.P = all.P; rw.R = all.R; rw.base = base;
+        return rw;
     }
     // a cell's entries from a list; false: it does not hold them
     __device__ __forceinline__ bool listed(const LiveCell& c)
@@ -1356,6 +1381,8 @@ __device__ __forceinline__ void slice_windows(unsigned char* smem, RestSearch<NT
     ii.thr = s.thr;
     const bool fits = (u64)P * (u64)R < HOT_MAX_ENTRIES;
     u64 a = s.from, width = (s.to - s.from) / 16 + 1;
+    constexpr u32 GENERAL = WinCfg<NT, ITEMS>::CAP_WIDE;
+    u32 limit = H::CAP;                                    // entries of a window
     u32 lo[RPT], hi[RPT];
 #pragma unroll
     for (int c = 0; c < RPT; ++c) {
@@ -1384,11 +1411,11 @@ __device__ __forceinline__ void slice_windows(unsigned char* smem, RestSearch<NT
         }
         const u32 count = block_reduce<u32, NT>(mine, (u32*)hot.red, OpAdd());
         far = __syncthreads_or(far);
-        if (count > (u32)H::CAP && el > a) {
-            width = (u64)((double)(el - a + 1) * (0.75 * H::CAP) / (double)count);
+        auto narrower = [&] {
+            width = (u64)((double)(el - a + 1) * (0.75 * limit) / (double)count);
             width = width ? width : 1;
-            continue;
-        }
+        };
+        if (count > limit && el > a) { narrower(); continue; }
         if (count > 0) {
             WinVal wv;
             wv.A = a;
@@ -1400,8 +1427,14 @@ __device__ __forceinline__ void slice_windows(unsigned char* smem, RestSearch<NT
             __syncthreads();
             const Partial f = sm.found;
             __syncthreads();
-            if (f.wait == U64_MAX && f.brel == DEFERRED_WINDOW) search.general(a, el);
-            else if (f.wait != U64_MAX) search.take(Best{f.wait, f.brel});
+            if (f.wait == U64_MAX && f.brel == DEFERRED_WINDOW) {
+                // (workers in step: as many entries as the general search takes at once, which otherwise looks for where to cut)
+                if (count > GENERAL && el > a) { limit = GENERAL; narrower(); continue; }
+                search.general(a, el, lo, hi);
+            } else {
+                if (f.wait != U64_MAX) search.take(Best{f.wait, f.brel});
+                limit = limit < (u32)H::CAP / 2 ? 2 * limit : (u32)H::CAP;
+            }
         }
         u64 next = el + 1;
         if (count < (u32)H::CAP / 4) {
@@ -1420,7 +1453,7 @@ __device__ __forceinline__ void slice_windows(unsigned char* smem, RestSearch<NT
         for (int c = 0; c < RPT; ++c) lo[c] = hi[c];
         if (el == s.to) break;
         a = next;
-        if (count < (u32)H::CAP / 2) width *= 2;
+        if (count < limit / 2) width *= 2;
     }
 }
 

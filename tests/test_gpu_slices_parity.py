@@ -163,13 +163,16 @@ def test_predicted_rows_whose_waits_repeat(zl, oracle, B, P, R, unit):
 
 
 @pytest.mark.parametrize("unit", [1, 1000])
-@pytest.mark.parametrize("kind", ["one", "two", "almost one"])
-@pytest.mark.parametrize("B,P,R", [(48, 1021, 1031), (640, 150, 523)])
+@pytest.mark.parametrize("kind", ["one", "two", "almost one", "in step"])
+@pytest.mark.parametrize("B,P,R", [(48, 1021, 1031), (640, 150, 523), (190, 257, 1024)])
 def test_stored_rows_whose_waits_repeat(zl, oracle, B, P, R, kind, unit):
     rng = np.random.default_rng(P + R)
-    iv = intervals_of(kind, rng, B, P) * unit
-    off = (rng.random((B, P)) * 100_000).astype(np.int64) * unit
-    ts = off[:, :, None] + np.arange(R) * iv[:, :, None] + EPOCH
+    if kind == "in step":
+        ts = np.arange(R) * (100_000 * unit) + rng.integers(0, 20 * unit, size=(B, P, R)) + EPOCH
+    else:
+        iv = intervals_of(kind, rng, B, P) * unit
+        off = (rng.random((B, P)) * 100_000).astype(np.int64) * unit
+        ts = off[:, :, None] + np.arange(R) * iv[:, :, None] + EPOCH
     got, is_sliced = sliced(zl, lambda: zl.ebsp_zipline_batch(torch.from_numpy(ts).cuda()))
     assert is_sliced
     same_as(got, oracle.zipline(ts, "sweep", threads=16), f"{B} x {P} x {R} {kind}, {unit}")
