@@ -117,10 +117,9 @@ def searched_entries(rows, summed: bool) -> float:
 
 
 def algorithmic_bytes(kernel: str, B: int, P: int, R: int, bins: float, windows: float, predicted: bool = False,
-                      supersteps: int = 0, searched: float = 0.0, sliced: bool = False) -> float:
+                      supersteps: int = 0, searched: float = 0.0) -> float:
     """Bytes a kernel must move per search (inputs it has to read once + what it has to write).  bins (per instance) and
-    windows (of the batch) are those searched, `searched` the entries in them (0: all, no value is left out).  sliced: the
-    search over value cells in slices, whose kernels are timed under the windows' names."""
+    windows (of the batch) are those searched, `searched` the entries in them (0: all, no value is left out)."""
     n = float(B) * P * R
     cut, entries = searched > 0.0, searched or n
     cw = 2.0 if R < 65536 else 4.0          # bytes of one crossing index
@@ -136,9 +135,9 @@ def algorithmic_bytes(kernel: str, B: int, P: int, R: int, bins: float, windows:
         return 16.0 * B * P + B * (16.0 + 8.0 * P)
     if kernel == "zl_advance_kernel":       # the barriers, every worker's next start time
         return 8.0 * B + 8.0 * B * P
-    if sliced and kernel == "zl_window_kernel":     # every timestamp once; predicted rows: 16 bytes per worker
+    if kernel == "zl_slices_kernel":        # every timestamp once; predicted rows: 16 bytes per worker
         return rows
-    if sliced and kernel in ("zl_plan_kernel", "zl_finish_kernel"):     # the cells that are left; all three outputs
+    if kernel in ("zl_slices_queue_kernel", "zl_slices_cells_kernel"):      # the cells that are left; all three outputs
         return B * (16.0 + 4.0 * P)
     if kernel == "zl_window_kernel":        # every searched timestamp once, two crossing rows per window, one result
         return inside + windows * (2.0 * cw * P + 16.0)
@@ -166,9 +165,21 @@ def algorithmic_bytes(kernel: str, B: int, P: int, R: int, bins: float, windows:
     if kernel == "zl_finish_kernel":        # window results; per row its crossing indices at the barrier's bin and two probes
         probes = 0.0 if predicted else 64.0 * 3.0       # (predicted rows: nothing is probed), outputs
         return 16.0 * windows + B * P * (probes + 4.0) + 16.0 * B
-    if kernel in ("zl_window_general_kernel", "zl_instance_general_kernel"):    # next to nothing where nothing is left to them
+    if kernel in ("zl_window_general_kernel", "zl_instance_general_kernel", "zl_slices_rest_kernel"):    # next to nothing where nothing is left to them
         return 0.0
     raise ValueError(f"no byte model for {kernel}")
+
+
+# The kernels of the search over value cells in slices, which a profile counts as those of the windows (the header of
+# ebsp_zipline_profile_begin says which); windows are never searched without zl_bounds_kernel ahead of them.
+OF_SLICES = {"zl_window_kernel": "zl_slices_kernel", "zl_plan_kernel": "zl_slices_queue_kernel",
+             "zl_finish_kernel": "zl_slices_cells_kernel", "zl_window_general_kernel": "zl_slices_rest_kernel"}
+
+
+def named_by_what_ran(per_kernel: dict) -> dict:
+    if "zl_window_kernel" not in per_kernel or "zl_bounds_kernel" in per_kernel:
+        return per_kernel
+    return {OF_SLICES.get(k, k): v for k, v in per_kernel.items()}
 
 
 # Table II of the paper (run time in microseconds on its 24-core Xeon server, mean of 10 trials): context only.
@@ -426,16 +437,16 @@ def main() -> int:
     windows = (searched or float(B) * P * R) / fill if shape["multi"] else 0.0
     if "zl_sweep_kernel" in per_kernel:     # the frontier sweep: one partial result per slice, no windows
         windows = B * shape["slices"]
-    sliced = "zl_window_kernel" in per_kernel and "zl_bounds_kernel" not in per_kernel
+    per_kernel = named_by_what_ran(per_kernel)
     dom = max(per_kernel, key=per_kernel.get)
-    dom_bytes = algorithmic_bytes(dom, B, P, R, bins, windows, args.predicted, S, searched, sliced)
+    dom_bytes = algorithmic_bytes(dom, B, P, R, bins, windows, args.predicted, S, searched)
     achieved = dom_bytes / (per_kernel[dom] * 1e-3) / 1e9
     counted = COUNTED_TRAFFIC.get((args.objective, bool(args.predicted), args.config))
     tuned = bool(args.window_cap or args.single_max or args.window_fill or args.sweep_min or args.slice_keys or args.sweep_lines)
     traffic = call_traffic = None
     if counted and counted[0] == dom and not tuned and not S and kernel_sources_sha256() == COUNTED_SOURCES_SHA256:
         traffic, call_traffic = float(counted[1]), float(counted[2])
-    total_bytes = searches * sum(algorithmic_bytes(k, B, P, R, bins, windows, args.predicted, S, searched, sliced) for k in per_kernel)
+    total_bytes = searches * sum(algorithmic_bytes(k, B, P, R, bins, windows, args.predicted, S, searched) for k in per_kernel)
 
     # CPU oracle on a bounded sample of the same workload (baseline, not a target)
     import oracle

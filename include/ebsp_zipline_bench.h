@@ -26,7 +26,9 @@ extern "C" {
  * info[3] = upper bound of windows per instance, info[4] = entries a window
  * holds at most (all 0 when info[0] is 0); info[5] = slices per instance if
  * ebsp_zipline_batch searches stored rows of this shape with the frontier
- * sweep (0: it takes the path that info[0..4] describe).
+ * sweep (0: it takes the path that info[0..4] describe, or, for many shapes of
+ * several windows, the search over value cells in slices, which takes the
+ * workspace that those windows would need and none of them).
  */
 int ebsp_zipline_shape_info(int64_t B, int32_t P, int32_t R, int64_t* info);
 
@@ -74,7 +76,8 @@ int ebsp_zipline_tune_sweep(int32_t sweep_min, int32_t slice_keys, int32_t lines
  * kernels of the search over value cells in slices count as the window
  * kernels in whose place they stand (zl_window_kernel the slices,
  * zl_plan_kernel and zl_finish_kernel the cells they leave,
- * zl_window_general_kernel the rest).
+ * zl_window_general_kernel the rest), and zl_gridscan_kernel stands for
+ * either kernel of a scan.
  * Do not capture a stream into a HIP graph while a profile is open.
  * ebsp_zipline_profile_end() synchronises the device, writes to kernel_ms
  * (HOST array of ebsp_zipline_kernel_count() floats, may be NULL) the summed

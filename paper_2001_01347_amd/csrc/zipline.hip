@@ -485,9 +485,14 @@ constexpr i64 RANGE_SMALL = 32768;               // entries of a slice that is s
 //   not those: fewer stored entries (64 of 256 x 1024 127 / 152) or instances (16 of 1024 x 4096 442 / 401 | 292 / 353), whose
 //   slices are short; short rows, whose searches are most of it (273 of 1024 x 240 545 / 700, 8000 of 300 x 60 1622 / 2197); few
 //   workers, whose cells have to be wide (100 of 12 x 4000 137 / 1750).
-// Workers in step, or of one iteration time (predicted, offsets anywhere | within 20 us): 64 of 1024 x 4096 1330 / 2550 | 12800 /
-// 6140, 1024 of 256 x 1024 1330 / 3160 | 8590 / 15700, 1000 of 60 x 1000 499 / 986 | 973 / 1900, 100 of 300 x 100 91 / 105 | 250 / 162;
-// stored within 20 us 64 of 1024 x 1024 3490 / 2350, in nanoseconds 4050 / 7280.
+// Slower where waits repeat and all cells are alike, whose instances are searched again by windows without a table.  Workers of two
+// intervals | of almost one: predicted 64 of 1024 x 4096 1135 / 2224 | 1241 / 2406, 1024 of 256 x 1024 1146 / 2504 | 1331 / 3100, 1000
+// of 60 x 1000 438 / 909 | 493 / 987, 300 of 48 x 4000 415 / 1429 | 467 / 1617, 100 of 300 x 100 87 / 105 | 82 / 100 (nanoseconds: 14331 /
+// 2298 | 14522 / 2401, 9130 / 2544 | 10482 / 3145, 2555 / 1146 | 2634 / 1240, 3102 / 2169 | 2815 / 2221, 289 / 107 | 285 / 102);
+// stored rows without any jitter 256 of 256 x 1024 400 / 926 | 444 / 1245, 512 of 64 x 4096 1032 / 2080 | 1148 / 2485, 900 of 64 x 1000
+// 481 / 999 | 515 / 1091.  One interval, predicted, is searched over one interval alone: 1296 / 57, 1351 / 91, 496 / 73, 470 / 44,
+// 83 / 38.  Stored rows in step within 20 us | in nanoseconds: 256 of 256 x 1024 4470 / 3247 | 5245 / 3596, 1024 of 256 x 1024 9439
+// / 11794 | 10907 / 13179, 60 of 1021 x 1031 3262 / 2246 | 3832 / 5003, 512 of 64 x 4096 2591 / 3800 | 2370 / 3970.
 struct Slices {
     i64 count;           // per instance; 0: the search by windows
     u32 room;            // cells listed per slice

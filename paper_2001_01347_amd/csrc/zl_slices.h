@@ -11,8 +11,8 @@ namespace {
 //     P * last - S(last)   >=  the wait of the last entry up to `last`, a candidate from thr on.
 // S at the end of every cell is a prefix sum of what the entries add to it, x less the entry before it in its row, one LDS
 // word per cell: no order, no counts, nothing kept per entry.  Cells whose lower bound exceeds the smallest upper bound hold
-// no minimum; the rest, a handful per instance, are listed with their lower bounds for zl_slices_finish_kernel, which
-// evaluates their entries in 64 bits.
+// no minimum; the rest, a handful per instance, are listed with their lower bounds for the kernels that follow (zl_slices_queue_kernel),
+// which evaluate their entries in 64 bits.
 //
 // zl_slices_kernel: one workgroup per slice of the values from thr to C, the last value that can win (cut_step).  Rows are
 // read once, from where a probe finds the slice's first entry in them, and what lies behind C only for its order.
@@ -246,7 +246,8 @@ __device__ __forceinline__ void slice_entries(SlicesSmem<NT, NB>& sm, const i64*
 
 // Bound by the one reading of stored rows (64 of 1024 x 4096: 515 us for 2.15 GB, 270 of them for what lies behind C at 5.7 TB/s and
 // 130 for the cells, the rest the probes and reductions ahead of them; by windows a partition pass of 485 and a search of 386),
-// by the vector ALU and LDS where they are predicted (99 us, 283 by windows).
+// by the vector ALU and LDS where they are predicted (99 us, 283 by windows).  At two workgroups of a CU the compiler keeps 15
+// (predicted: 7) of a thread's registers in memory: mostly the sums of its cells, walked by index where some are listed.
 template <int NT, int NB, bool PRED>
 __global__ __launch_bounds__(NT, 4) void zl_slices_kernel(
     const i64* __restrict__ ts, const i64* __restrict__ le, const i64* __restrict__ iv, i64 B, int P, int R, u32 slices,
@@ -640,7 +641,6 @@ struct CellRows {
             }
             return prev;
         } else {
-            const i64* row = inst + (size_t)p * R;
             u32 b0 = 0, b1 = 0;
             u64 prev = 0;
 #pragma unroll
@@ -786,62 +786,62 @@ __device__ __forceinline__ void cell_entries(const SliceSpace& space, const Slic
 {
     constexpr int U = 2;
     const int lane = threadIdx.x & (WAVE - 1), P = all.P, R = all.R;
-                if constexpr (PRED) {
-                    for (int p = wave * WAVE + lane; p - lane < P; p += waves * WAVE) {
+    if constexpr (PRED) {
+        for (int p = wave * WAVE + lane; p - lane < P; p += waves * WAVE) {
             if (listed && uniform(*(volatile const u32*)listed) > most) return;
             if (p < P) before += rows.entries(p, typename CellRows<PRED>::Window{}, c.first, c.last, list);
         }
-                } else {
-                    // Eight lanes to a row, an entry each, 64 U rows in flight: a lane's loads of eight entries of a row of its own would
-                    // ask the cache for 64 lines eight times over.
-                    constexpr u32 W = CellRows<PRED>::W;
-                    const u32 k = (u32)lane & (W - 1);
-                    for (int p0 = wave * WAVE * U; p0 < P; p0 += waves * WAVE * U) {
-                        if (listed && uniform(*(volatile const u32*)listed) > most) return;
+    } else {
+        // Eight lanes to a row, an entry each, 64 U rows in flight: a lane's loads of eight entries of a row of its own would
+        // ask the cache for 64 lines eight times over.
+        constexpr u32 W = CellRows<PRED>::W;
+        const u32 k = (u32)lane & (W - 1);
+        for (int p0 = wave * WAVE * U; p0 < P; p0 += waves * WAVE * U) {
+            if (listed && uniform(*(volatile const u32*)listed) > most) return;
             u32 from[U], pending = 0;
-    #pragma unroll
-                        for (int u = 0; u < U; ++u) {
-                            const int p = p0 + u * WAVE + lane;
-                            from[u] = rows.start(all.range(space, slices, b, c.slice, p < P ? p : P - 1), c.at);
-                        }
-                        i64 v[U][W];
-    #pragma unroll
-                        for (int u = 0; u < U; ++u)
-    #pragma unroll
-                            for (u32 j = 0; j < W; ++j) {
-                                const int r = (int)(j * W) + (lane >> 3), p = p0 + u * WAVE + r;
-                                const u32 i = (u32)__shfl((int)from[u], r) + k;
-                                v[u][j] = rows.inst[(size_t)(p < P ? p : P - 1) * R + (i < (u32)R ? i : (u32)R - 1)];
-                            }
-    #pragma unroll
-                        for (int u = 0; u < U; ++u)
-    #pragma unroll
-                            for (u32 j = 0; j < W; ++j) {
-                                const u64 y = (u64)v[u][j] - rows.base;
-                                const bool in = y >= c.first && y <= c.last;
-                                const bool open = k == 0 ? y >= c.first : k == W - 1 && y <= c.last;      // the row goes on to that side
-                                const u64 seen = __ballot(in || open);
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int p = p0 + u * WAVE + lane;
+                from[u] = rows.start(all.range(space, slices, b, c.slice, p < P ? p : P - 1), c.at);
+            }
+            i64 v[U][W];
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+#pragma unroll
+                for (u32 j = 0; j < W; ++j) {
+                    const int r = (int)(j * W) + (lane >> 3), p = p0 + u * WAVE + r;
+                    const u32 i = (u32)__shfl((int)from[u], r) + k;
+                    v[u][j] = rows.inst[(size_t)(p < P ? p : P - 1) * R + (i < (u32)R ? i : (u32)R - 1)];
+                }
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+#pragma unroll
+                for (u32 j = 0; j < W; ++j) {
+                    const u64 y = (u64)v[u][j] - rows.base;
+                    const bool in = y >= c.first && y <= c.last;
+                    const bool open = k == 0 ? y >= c.first : k == W - 1 && y <= c.last;      // the row goes on to that side
+                    const u64 seen = __ballot(in || open);
                     if (seen == 0 && !sums) continue;      // (half of the times)
-                                const int r = (int)(j * W) + (lane >> 3), p = p0 + u * WAVE + r;
-                                const u32 s = (u32)__shfl((int)from[u], r);
-                                const u64 ahead = dpp_take<DPP_WAVE_SHR1, 0xf>(0ull, y);
-                                const u64 opens = __ballot(open && (k == 0 ? s > 0 : s + W < (u32)R)) >> (lane & ~7) & 0xff;
-                                if (p < P && opens == 0 && in && s + k < (u32)R) list(y, k == 0 ? 0ull : ahead);
-                                if (sums) {                            // the last entry before the cell
+                    const int r = (int)(j * W) + (lane >> 3), p = p0 + u * WAVE + r;
+                    const u32 s = (u32)__shfl((int)from[u], r);
+                    const u64 ahead = dpp_take<DPP_WAVE_SHR1, 0xf>(0ull, y);
+                    const u64 opens = __ballot(open && (k == 0 ? s > 0 : s + W < (u32)R)) >> (lane & ~7) & 0xff;
+                    if (p < P && opens == 0 && in && s + k < (u32)R) list(y, k == 0 ? 0ull : ahead);
+                    if (sums) {                            // the last entry before the cell
                         const u64 below = __ballot(y < c.first) >> (lane & ~7) & 0xff;
                         if (p < P && opens == 0 && below && k == (u32)__popcll(below) - 1) before += y;
                     }
                     if (p < P && opens != 0 && k == 0) pending |= 1u << (u * W + j);
-                            }
-                        while (pending) {                      // rows whose entries lie elsewhere
-                            const u32 q = (u32)__builtin_ctz(pending);
-                            pending &= pending - 1;
-                            const int p = p0 + (int)(q * W) + (lane >> 3);
-                            const uint2 range = all.range(space, slices, b, c.slice, p);
-                            before += rows.entries(p, rows.window(p, range, c.at), c.first, c.last, list);
-                        }
-                    }
                 }
+            while (pending) {                      // rows whose entries lie elsewhere
+                const u32 q = (u32)__builtin_ctz(pending);
+                pending &= pending - 1;
+                const int p = p0 + (int)(q * W) + (lane >> 3);
+                const uint2 range = all.range(space, slices, b, c.slice, p);
+                before += rows.entries(p, rows.window(p, range, c.at), c.first, c.last, list);
+            }
+        }
+    }
 }
 
 // A workgroup per instance: looks at its lowest cell, which rules out most of the others, and queues the rest.
@@ -1340,6 +1340,13 @@ struct RestSearch {
 // A slice by windows (see zl_window.h) without a crossing table: the rows are searched for each window's end, and windows are
 // as wide as the ones before have shown to fit.  Behind one of few entries the next begins where an entry is, so that there are no
 // more windows than entries, however far apart those are.  Windows that the fast search gives up are left to the general one.
+// In step, they are then as narrow as that takes at once: cut by bisection, stored rows in step within 20 us, in nanoseconds, 60 of
+// 1021 x 1031 took 224 ms, 5.0 so.
+// What a window costs is a search of every row ahead of it (64 of 1024 x 4096, predicted, two intervals: 26 us a window, by windows
+// with a table 14).  Measured and not kept: a kernel of its own, which no longer keeps 168 registers of a thread in memory beside
+// the general search (2224 -> 1764 us, stored 48 of 1021 x 1031 1260 -> 1071, but a launch more in every call); the rows' ends in
+// registers (3474); all cells added up again and the entries of those that may win listed by a second walk (1860, stored 1303),
+// the same right behind the first walk (the kernel of all other inputs 1.3 times slower).
 template <int NT, bool PRED>
 struct SliceWindowsSmem {
     __align__(16) unsigned char hot[WinHot<NT, 16, PRED>::BYTES];
@@ -1458,7 +1465,7 @@ __device__ __forceinline__ void slice_windows(unsigned char* smem, RestSearch<NT
 }
 
 template <int NT, int ITEMS, bool PRED>
-__global__ __launch_bounds__(NT, 4) void zl_slices_rest_kernel(
+__global__ __launch_bounds__(NT, (PRED ? 2 : 4)) void zl_slices_rest_kernel(
     const i64* __restrict__ ts, const i64* __restrict__ le, const i64* __restrict__ iv, i64 B, int P, int R, u32 slices,
     void* __restrict__ workspace, u32 room, i64* __restrict__ barrier, int* __restrict__ iters, i64* __restrict__ wait, int* __restrict__ status)
 {

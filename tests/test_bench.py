@@ -23,6 +23,16 @@ def test_every_kernel_of_a_search_is_priced():
         bench.algorithmic_bytes("zl_unheard_of_kernel", 2, 100, 50, 20, 8)
 
 
+def test_kernels_of_slices_are_named_and_priced():
+    assert bench.named_by_what_ran({"zl_bounds_kernel": 1.0, "zl_window_kernel": 2.0}) == {"zl_bounds_kernel": 1.0, "zl_window_kernel": 2.0}
+    assert bench.named_by_what_ran({"zl_cells_kernel": 1.0}) == {"zl_cells_kernel": 1.0}
+    got = bench.named_by_what_ran({k: 1.0 for k in bench.OF_SLICES})
+    assert set(got) == set(bench.OF_SLICES.values())
+    for predicted, rows in ((False, 8.0 * 2 * 100 * 50), (True, 16.0 * 2 * 100)):
+        assert bench.algorithmic_bytes("zl_slices_kernel", 2, 100, 50, 20, 8, predicted) == rows
+        assert all(bench.algorithmic_bytes(k, 2, 100, 50, 20, 8, predicted) >= 0.0 for k in got)
+
+
 def test_bytes_of_the_searches_in_one_launch():
     # 3 instances of 16 x 60; outputs: barrier, wait and an iteration count per worker
     out = 3 * (16 + 4 * 16)
