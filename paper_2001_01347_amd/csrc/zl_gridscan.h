@@ -327,18 +327,21 @@ __global__ __launch_bounds__(NT, 8) void zl_gridscan_kernel(
 // spread beyond the best found is out.  The rows that spread it are those with the longest iterations (a point's nearest
 // entry is half an iteration away at most), and FIRST of them are searched for all points; the narrowest set of every 16
 // threads is then evaluated over all rows, and so are the points whose sets are no wider than the best of those, a thread per row.
-// Where that leaves more than LEFT points, every row is searched for every point as above, and so it is from the start where more
-// than LONG rows are three quarters as long as the longest or more: then a few of them rule out little.
-// us, all rows searched for all points / so, with configuration 2's workers of whom one in twenty is 1.5 to 3 times slower | 5's |
-// alike: 64 of 100 x 150 302 / 284 | 300 / 203 | 294 / 298, 64 of 128 x 150 456 / 363 | 454 / 276 | 446 / 454, 64 of 200 x 100
-// 502 / 295 | 499 / 537 | 471 / 478, 30 of 300 x 150 1210 / 415 | 1201 / 1209 | 1189 / 1199, 20 of 500 x 100 984 / 730 | 972 / 983 |
-// 923 / 932.  Without LONG and with 256 points left, 64 of 100 x 150 of workers alike took 400, 64 of 200 x 100 644, 20 of 500 x
-// 100 of 5's 2606 (where a point at a time is evaluated).
+// Where that leaves more than LEFT points, or more than ROUNDS rounds of as many as the workgroup takes at once, every row is searched
+// for every point as above, and so it is from the start where more than LONG rows are three quarters as long as the longest or more:
+// then a few of them rule out little.
+// us, all rows searched for all points / so, with configuration 2's workers | 5's | 4's, of three seeds: 64 of 100 x 150 300 / 145 to
+// 155 | 203 to 214 | 188 to 211, 64 of 128 x 150 455 / 191 to 201 | 278 to 299 | 304 to 362, 64 of 200 x 100 500 / 305 to 345 | 515 to
+// 534 | 623 to 631, 30 of 300 x 150 1205 / 730 to 770 | 1207 to 1211 | 1294 to 1325, 20 of 500 x 100 975 / 1109 to 1129 | 990 to 1005 |
+// 1031 to 1038; with 3's 165 to 175, 216 to 227, 253 to 302, 430 to 614, 798 to 975; workers alike 1.01 to 1.04 of all rows.
+// 256 points whatever the rows: 64 of 200 x 100 of 4's 792 to 836, 20 of 500 x 100 of 2's 1493 to 1727; 128: 64 of 100 x 150 of 5's 206 to
+// 255, 20 of 500 x 100 of 2's 1380 to 1409; 40 rounds: 64 of 200 x 100 of 4's 673 to 691, 24 of 400 x 120 of 3's 635 to 774 instead of
+// 645 to 807.  Without LONG 64 of 200 x 100 of 5's took 463 to 496, but of workers alike 644, 20 of 500 x 100 of 5's 2606.
 // Beyond PMAX a round of evaluation takes one point: 10 of 1000 x 150 4017 / 4518, 64 of 1000 x 60 6471 / 8194; below PMIN there
 // are too few rows to save: 64 of 50 x 240 105 / 126.  R up to RMAX: the first rows fit the stage, and longer ones are searched in
 // pieces of a row or more by chips that are not full, 16 of 96 x 512 188 / 349 (256 points left).  Fewer than 128 rows in small
-// batches (ebsp_gridscan_batch): 40 of 100 x 180 178 / 208 | 179 / 177, 32 of 100 x 240 189 / 228 | 188 / 203.
-constexpr int GRID_FIRST = 16, GRID_LEFT = 128, GRID_LONG = 52, GRID_FULL_RMAX = 256, GRID_FULL_PMIN = 96, GRID_FULL_PMAX = 512;
+// batches (ebsp_gridscan_batch): 40 of 100 x 180 178 / 208 | 179 / 177, 32 of 100 x 240 189 / 228 | 188 / 203 (2's with one straggler in twenty | 5's).
+constexpr int GRID_FIRST = 16, GRID_LEFT = 256, GRID_ROUNDS = 32, GRID_LONG = 52, GRID_FULL_RMAX = 256, GRID_FULL_PMIN = 96, GRID_FULL_PMAX = 512;
 template <int NT, int PER, class VT>
 __device__ __forceinline__ bool grid_scan_pruned(const i64* __restrict__ inst, u64 base, u64 longest, int P, int R, u32 first, u32 points, int slice,
                                                  int slices, int pthreads, int pt, unsigned char* stage, u64& bd, u32& bj)
@@ -445,9 +448,9 @@ __device__ __forceinline__ bool grid_scan_pruned(const i64* __restrict__ inst, u
     }
     __syncthreads();
     // the listed points over all rows, G at a time: ub becomes the best; (bd, bj) the thread's own
+    const int per = P < NT ? (P + WAVE - 1) / WAVE * WAVE : NT;
+    const int G = NT / per < 16 ? NT / per : 16, g = tid / per;
     auto evaluate = [&](u32 n) {
-        const int per = P < NT ? (P + WAVE - 1) / WAVE * WAVE : NT;
-        const int G = NT / per < 16 ? NT / per : 16, g = tid / per;
         for (u32 q0 = 0; q0 < n; q0 += (u32)G) {
             if (tid < G) { top[tid] = 0; bot[tid] = U64_MAX; }
             __syncthreads();
@@ -488,7 +491,7 @@ __device__ __forceinline__ bool grid_scan_pruned(const i64* __restrict__ inst, u
             }
     __syncthreads();
     const u32 n = left;
-    if (n > (u32)GRID_LEFT) return false;
+    if (n > (u32)GRID_LEFT || n > (u32)(GRID_ROUNDS * G)) return false;
     evaluate(n);
     return true;
 }
@@ -513,7 +516,13 @@ __global__ __launch_bounds__(NT, 8) void zl_fullgridscan_kernel(
     }
     i64 base, top;
     block_bounds<NT>(mn, mxl, mine, (i64*)red, base, top, longest);
-    const bool few = __syncthreads_count(tid < P && mine >= longest - longest / 4) <= GRID_LONG;      // rows that may rule points out
+    const u64 long_rows = __ballot(tid < P && mine >= longest - longest / 4);
+    if (lane == 0) red[wave] = (u64)__popcll(long_rows);
+    __syncthreads();
+    u32 longs = 0;
+#pragma unroll
+    for (int w = 0; w < GRID_FULL_PMAX / WAVE; ++w) longs += (u32)red[w];
+    const bool few = uniform(longs) <= (u32)GRID_LONG;         // rows that may rule points out
     int bad = 0;
     if (status != nullptr && piece == 0) {                     // one workgroup per instance checks the rows' order
         const u32 all = (u32)P * (u32)R;
