@@ -246,7 +246,7 @@ __device__ __forceinline__ void slice_entries(SlicesSmem<NT, NB>& sm, const i64*
 
 // Bound by the one reading of stored rows (64 of 1024 x 4096: 515 us for 2.15 GB, 270 of them for what lies behind C at 5.7 TB/s and
 // 130 for the cells, the rest the probes and reductions ahead of them; by windows a partition pass of 485 and a search of 386),
-// by the vector ALU and LDS where they are predicted (99 us, 283 by windows).  At two workgroups of a CU the compiler keeps 15
+// by the vector ALU and LDS where they are predicted (99 us, 283 by windows).  At two workgroups of a CU the compiler keeps 13
 // (predicted: 7) of a thread's registers in memory: mostly the sums of its cells, walked by index where some are listed.
 template <int NT, int NB, bool PRED>
 __global__ __launch_bounds__(NT, 4) void zl_slices_kernel(
@@ -273,7 +273,7 @@ __global__ __launch_bounds__(NT, 4) void zl_slices_kernel(
     u64 spans = 0;
     int back = 0, wrapped = 0;
     const u64 interval = PRED ? (u64)iv[0] : 0ull;
-    u64 differ = 0;                                        // 1: not all intervals are this one
+    int differ = 0;                                        // 1: not all intervals are this one
 #pragma unroll
     for (int r = 0; r < RPT; ++r) {
         const int p = tid + r * NT;
@@ -287,7 +287,7 @@ __global__ __launch_bounds__(NT, 4) void zl_slices_kernel(
                 l = (i64)(from + (u64)R * s);
                 back |= R > 1 && (i64)s < 0;
                 wrapped |= l < f;
-                differ |= s != interval ? 1ull : 0ull;
+                differ |= s != interval;
                 row[r].step = s;
             } else {
                 row[r].row = inst + (size_t)p * R;
@@ -314,15 +314,22 @@ __global__ __launch_bounds__(NT, 4) void zl_slices_kernel(
         block_reduce_to<NT>(sm.red, 2, v2, OpMax());
         block_reduce_to<NT>(sm.red, 3, v3, OpMin());
         block_reduce_to<NT>(sm.red, 4, spans, OpAdd());
-        if constexpr (PRED) block_reduce_to<NT>(sm.red, 5, differ, OpMax());
-        back = __syncthreads_or(back);
+        const u64 any = (__ballot(back) ? 1ull : 0ull) | (__ballot(wrapped) ? 2ull : 0ull) | (__ballot(differ) ? 4ull : 0ull);
+        if (lane == 0) sm.red[5 * NW + wave] = any;
+        __syncthreads();
         v0 = block_reduced<NT>(sm.red, 0, OpMin());
         v1 = block_reduced<NT>(sm.red, 1, OpMax());
         v2 = block_reduced<NT>(sm.red, 2, OpMax());
         v3 = block_reduced<NT>(sm.red, 3, OpMin());
         spans = uniform(block_reduced<NT>(sm.red, 4, OpAdd()));
-        if constexpr (PRED) differ = block_reduced<NT>(sm.red, 5, OpMax());
-        wrapped = __syncthreads_or(wrapped);
+        u64 flags = 0;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) flags |= sm.red[5 * NW + w];
+        flags = uniform(flags);
+        back = (flags & 1) != 0;
+        wrapped = (flags & 2) != 0;
+        differ = (flags & 4) != 0;
+        __syncthreads();                                   // (they are written again)
         mn = (i64)uniform(v0 ^ SIGN); mxf = (i64)uniform(v1 ^ SIGN); mxl = (i64)uniform(v2 ^ SIGN); mnl = (i64)uniform(v3 ^ SIGN);
     }
     const u64 base = (u64)mn, thr = (u64)mxf - base, range = (u64)mxl - base;
