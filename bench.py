@@ -42,22 +42,19 @@ HBM_PEAK_GBS = 8000.0          # MI355X HBM3E, published peak
 # reads for the plain copy kernel of known size (FETCH_SIZE x 2048 B, WRITE_SIZE x 1024 B per count).  The
 # figures below are the counters' per-dispatch averages, kernel by kernel in launch order.  They hold only for
 # the kernel sources they were taken from: `traffic` is null once those have changed.
-COUNTED_SOURCES_SHA256 = "e6f29f88c429095193295be0ece0fe4a1bc2e1b2e0b80fea609c7dbc4426f7a9"
-FETCH_UNIT, WRITE_UNIT = 2048, 1024      # bytes per count: what the copy kernel's 2 GiB in, 2 GiB out read as (1 048 607 and 2 097 152)
+COUNTED_SOURCES_SHA256 = "29e14c5f5e81cd42744d7d46e4ff6f965af37692dc150fee85815085265f2219"
+FETCH_UNIT, WRITE_UNIT = 2048, 1024      # bytes per count: what the copy kernel's 2 GiB in, 2 GiB out read as (1 048 606 and 2 097 152)
 COUNTED_TRAFFIC = {     # (objective, predicted, config) -> (dominant kernel, its bytes, bytes of all kernels of a call)
-    ("sum", False, 5): ("zl_partition_kernel", 1048998 * FETCH_UNIT + 164728 * WRITE_UNIT,
-                        (29472 + 1048998 + 9705 + 258 + 639084 + 130 + 7711) * FETCH_UNIT
-                        + (70 + 164728 + 272 + 352 + 361 + 8192 + 258) * WRITE_UNIT),
-    ("sum", False, 3): ("zl_cells_kernel", 1204659 * FETCH_UNIT + 71294 * WRITE_UNIT,
-                        (1204659 + 88) * FETCH_UNIT + 71294 * WRITE_UNIT),
-    ("sum", True, 5): ("zl_window_kernel", 73979 * FETCH_UNIT + 276 * WRITE_UNIT,
-                       (617 + 4769 + 2445 + 257 + 73979 + 129 + 881) * FETCH_UNIT
-                       + (582 + 149532 + 271 + 352 + 276 + 8192 + 258) * WRITE_UNIT),
-    ("sum", False, 4): ("zl_window_kernel", 1761470 * FETCH_UNIT + 2180 * WRITE_UNIT,
-                        (123891 + 1053098 + 14177 + 1630 + 1761470 + 558 + 36257) * FETCH_UNIT
-                        + (1122 + 232409 + 1554 + 2065 + 2180 + 0 + 1088) * WRITE_UNIT),
-    ("range", False, 5): ("zl_range_fast_kernel", 1425147 * FETCH_UNIT + 24 * WRITE_UNIT,
-                          (1425147 + 18178) * FETCH_UNIT + (24 + 262) * WRITE_UNIT),
+    ("sum", False, 5): ("zl_slices_kernel", 1378707 * FETCH_UNIT + 18613 * WRITE_UNIT,
+                        (1378707 + 6516 + 121318 + 33) * FETCH_UNIT + (18613 + 20 + 584 + 2048) * WRITE_UNIT),
+    ("sum", False, 3): ("zl_cells_kernel", 1205296 * FETCH_UNIT + 71294 * WRITE_UNIT,
+                        (1205296 + 86) * FETCH_UNIT + 71294 * WRITE_UNIT),
+    ("sum", True, 5): ("zl_slices_kernel", 5156 * FETCH_UNIT + 7402 * WRITE_UNIT,
+                       (5156 + 729 + 3828 + 32) * FETCH_UNIT + (7402 + 13 + 385 + 0) * WRITE_UNIT),
+    ("sum", False, 4): ("zl_slices_kernel", 1377892 * FETCH_UNIT + 31310 * WRITE_UNIT,
+                        (1377892 + 30514 + 108496 + 33) * FETCH_UNIT + (31310 + 325 + 1611 + 2048) * WRITE_UNIT),
+    ("range", False, 5): ("zl_range_fast_kernel", 1429808 * FETCH_UNIT + 24 * WRITE_UNIT,
+                          (1429808 + 18188) * FETCH_UNIT + (24 + 262) * WRITE_UNIT),
 }
 
 
